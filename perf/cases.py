@@ -233,5 +233,5 @@ def tolerance(case: Dict):
     # bags, 0.10 under the causal mask (its first rows see one or two keys), 0.48 with peaky keys (a near one-hot
     # row's dq is a small difference of large terms).
     if case.get("peaky"):
-        return {"rel": 1e-2, "max": 1.0}
+        return {"rel": 1e-2, "max": 0.95}
     return {"rel": 1e-2, "max": 0.4 if case["causal"] else 0.12}
