@@ -199,6 +199,8 @@ __global__ __launch_bounds__(Bwd2Cfg<D>::THREADS, 2) void attn_bwd_dkdv64_kernel
     // that workgroups on different key tiles of one (sequence, head) read the same query tiles at the same
     // time, as they do without the mask
 
+    __syncthreads();
+
     bf16x8 kvf[C::KB][C::KC];
     {
       const uint32_t kv_bytes = (uint32_t)min(L - kv0, C::BN) * row_bytes;
@@ -284,7 +286,7 @@ __global__ __launch_bounds__(Bwd2Cfg<D>::THREADS, 2) void attn_bwd_dkdv64_kernel
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) {
 #pragma unroll
-        for (int kb = 0; kb < C::KB; ++kb) acc[kb][nb] = mfma32(bf[nb], op[kb], acc[kb][nb]);
+        for (int kb = 0; kb < C::KB; ++kb) acc[kb][nb] = mfma32(op[kb], bf[nb], acc[kb][nb]);
         if (nb + AH2 < C::NB) bf[nb + AH2] = cols.get(tB, cb, 16 * cq, nb + AH2);
         between(nb);
         KNAP_SCHED_FENCE();
@@ -432,15 +434,18 @@ __global__ __launch_bounds__(Bwd2Cfg<D>::THREADS, 2) void attn_bwd_dkdv64_kernel
 #undef KNAP_STEP
     wait_vm_loads<0>();
 
-    const auto rd = make_rsrc((role == 0 ? dv : dk) + (size_t)(it.row0 + kv0) * row_stride + head_off,
-                              (uint32_t)min(L - kv0, C::BN) * row_bytes);
+    __bf16* dst = role == 0 ? dv : dk;
     const float out_scale = role == 0 ? 1.0f : scale;
 #pragma unroll
-    for (int kb = 0; kb < C::KB; ++kb) {
-      const uint32_t off = (uint32_t)(64 * pair + 32 * kb + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+    for (int kb = 0; kb < C::KB; ++kb)
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb) store_block(rd, off + 64u * nb, acc[kb][nb], out_scale);
-    }
+      for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int kv = kv0 + 64 * pair + 32 * kb + 8 * (r >> 2) + 4 * hh + (r & 3);
+          if (kv < L)
+            dst[(size_t)(it.row0 + kv) * row_stride + head_off + 32 * nb + l32] = (__bf16)(acc[kb][nb][r] * out_scale);
+        }
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != kv_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;
@@ -627,6 +632,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
       __syncthreads();     // next tile visible; this tile no longer read
     };
 
+    __syncthreads();       // the previous item (or the schedule build) is done with both buffers
     load_tile(0, sK0, sV0);
     wait_async_loads();
     if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
@@ -657,12 +663,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
       if (n_below + 1 < n_tiles) process_tile(diagonal, n_below + 1, sK1, sV1, sK0, sV0);
     }
 
-    {
-      const auto rg = make_rsrc(dq + (size_t)(it.row0 + q0) * row_stride + head_off,
-                                (uint32_t)min(L - q0, C::BM) * row_bytes);
-      const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+    if (q_valid) {
+      __bf16* o_ptr = dq + (size_t)(it.row0 + q_row) * row_stride + head_off;
 #pragma unroll
-      for (int db = 0; db < C::DB; ++db) store_block(rg, off + 64u * db, acc[db], scale);
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const bf16x4 pk = pack4(acc[db][4 * g] * scale, acc[db][4 * g + 1] * scale,
+                                  acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
+          *reinterpret_cast<bf16x4*>(o_ptr + 32 * db + 8 * g + 4 * hh) = pk;
+        }
     }
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != q_tiles - 1 - it.tile) {   // not the middle tile of an odd count
@@ -671,7 +681,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
       }
     }
     if (tid == 0) s_ticket = (int)next_ticket;   // every wave took its copy of the old ticket many barriers ago
-    lds_barrier();
+    __syncthreads();
   }
 }
 

@@ -103,9 +103,6 @@ __device__ __forceinline__ void tile_load_async(__bf16* tile, __amdgpu_buffer_rs
   }
 }
 
-// waits until at most N of this wave's vector-memory operations (loads and stores, in issue order) are in flight
-template <int N>
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_async_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // The swizzle only looks at the low four bits of the row, so a read at (row_base + r, col)
@@ -165,37 +162,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 
 __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t byte_offset) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_offset, 0, 0);
-}
-
-// Stores a 32 x 32 MFMA result block (one output row per lane, registers running along it: element r of a
-// lane is column 8 (r / 4) + 4 hh + r % 4), times `mul`, as bf16.  `off` is the byte offset of this lane's
-// row, plus 16 hh; rows past the descriptor are dropped.  The lanes of a row (l and l ^ 32) trade four
-// columns, so that each stores 8 consecutive ones: two 16-byte stores per block and lane, no predicate.
-__device__ __forceinline__ void store_block(__amdgpu_buffer_rsrc_t r, uint32_t off, const f32x16& x, float mul) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    uint32_t w[2][2];
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        bf16x2 p;
-        p[0] = (__bf16)(x[8 * j + 4 * g + 2 * i] * mul);
-        p[1] = (__bf16)(x[8 * j + 4 * g + 2 * i + 1] * mul);
-        w[g][i] = __builtin_bit_cast(uint32_t, p);
-      }
-    const auto a = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-    const u32x4 v = {a[0], b[0], a[1], b[1]};
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(off + 32u * j), 0, 0);
-  }
-}
-
-// Workgroup barrier for LDS traffic alone: __syncthreads() also waits for every global store in flight.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
 }
 
 // Scheduling helpers.  A fence keeps the scheduler from moving anything across it; the
@@ -395,10 +361,6 @@ struct ItemQueue {
     chunk = max(1, (int)gridDim.x / n_q);
     ctr = counters + q;
   }
-  // a workgroup's first item needs no draw: the first `chunk` tickets go to the queue's workgroups in order,
-  // and the counter deals out the ones after them
-  __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
-  __device__ __forceinline__ int later_ticket(unsigned drawn) const { return chunk + (int)drawn; }
   __device__ __forceinline__ int item(int ticket) const {
     return ((ticket / chunk) * n_q + q) * chunk + ticket % chunk;
   }
