@@ -504,7 +504,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
   // when the item is done, so the counter's latency is never waited for.
   __shared__ int s_ticket;
   ItemQueue queue;
-  queue.init(counters);
+  queue.init(counters, s_start, n_seq);
   if (tid == 0) s_ticket = (int)atomicAdd(queue.ctr, 1u);
   __syncthreads();
   for (;;) {

@@ -17,18 +17,23 @@
 // and P^T in that layout is, unchanged, the B operand of O^T += V^T P^T.  V^T
 // fragments come from the row-major V tile through transposing LDS reads.
 //
-// Softmax bookkeeping: the exponent reference m_ref of a query only moves when
-// a tile's maximum exceeds it by more than 2^8 in base-2 units (the first tile
-// always does).  Otherwise P is formed against the old reference, so P <= 256
-// and the accumulated output needs no rescaling; the final division by the row
-// sum removes the reference exactly as in the textbook recurrence.  The row sum
-// is taken over the bf16-rounded P that the MFMA multiplies, so the effective
-// weights of a row sum to one exactly (a one-hot row returns its v bit for bit);
-// the stored log-sum-exp inherits at most a 2^-9 relative change of that sum.
+// Softmax bookkeeping: P of a half tile (32 keys) is formed against the exponent reference m_ref as it
+// stands, and the row sums that come out of it decide whether the reference has to move: only when a
+// lane's 16 probabilities sum to more than 2^8 (the first half always does: the reference starts at
+// -inf), in which case the maximum is taken, the accumulators are rescaled and P is formed again.  So no
+// maximum is taken per tile (a third of the loop's simple vector instructions: 5.1 -> 3.4 per MFMA);
+// P <= 256 all the same, and the final division by the row sum removes the reference exactly as in
+// the textbook recurrence.  The row sum is taken over the bf16-rounded P that the MFMA multiplies, so the
+// effective weights of a row sum to one exactly (a one-hot row returns its v bit for bit); the stored
+// log-sum-exp inherits at most a 2^-9 relative change of that sum.
+//
+// What bounds it: MFMA and softmax arithmetic share the issue slots, at the clock the power limit leaves.
+// The arithmetic of a half therefore runs in the slot of the next half's MFMAs, and an item's first loads
+// go out under the previous item's epilogue.  Measured at 24 heads of 128 (before -> now, us): 32 sequences
+// of 256..648 tokens 172 -> 144, one of 4292 tokens 305 -> 283, 17 of 328..4533 tokens 1104 -> 1040, one of
+// 65536 and 200 short ones 47500 -> 46600.
 #include "knap_device.h"
 #include "knap_kernels.h"
-
-#include <type_traits>
 
 namespace knap {
 
@@ -41,7 +46,7 @@ struct FwdCfg {
   static constexpr int TILE_ELEMS = BN * Tile<D>::LD;
 };
 
-constexpr float kRescaleThreshold = 8.0f;   // base-2 units
+constexpr float kMaxHalfSum = 256.f;        // of a lane's 16 probabilities against the present reference
 constexpr int kFwdQueueSlots = 256;
 
 template <int D, bool CAUSAL>
@@ -85,81 +90,74 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
   // when the item is done, so the counter's latency is never waited for.
   __shared__ int s_ticket;
   ItemQueue queue;
-  queue.init(counters);
-  if (tid == 0) s_ticket = (int)atomicAdd(queue.ctr, 1u);
-  __syncthreads();
+  queue.init(counters, s_start, n_seq);
+  int w = queue.item(queue.first_ticket());
+  if (w >= n_items) return;
+  WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+  unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
+  int sub = 0;               // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
+
+  bf16x8 qf[C::KC];          // this lane's query row as the B operand of S^T = K Q^T
+  auto q_tile_of = [&]() {
+    return !CAUSAL ? it.tile : sub == 0 ? (it.len + C::BM - 1) / C::BM - 1 - it.tile : it.tile;
+  };
+  // asynchronous copy of tile t (keys 64 t ..) of the item; rows at or past kv_end arrive as zeros
+  auto load_tile = [&](int t, int kv_end, __bf16* dK, __bf16* dV) {
+    const int kv0 = t * C::BN;
+    const uint32_t bytes = (uint32_t)max(0, min(kv_end - kv0, C::BN)) * row_bytes;
+    const size_t off = (size_t)(it.row0 + kv0) * row_stride + (size_t)it.head * D;
+    tile_load_async<D>(dK, make_rsrc(k + off, bytes), row_bytes, C::BN, wave, lane);
+    tile_load_async<D>(dV, make_rsrc(v + off, bytes), row_bytes, C::BN, wave, lane);
+  };
+  const uint32_t q_off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+  // what an item needs before its first product: tile 0 and the query rows (rows past the end read as zero)
+  auto load_first = [&]() {
+    const int q0 = q_tile_of() * C::BM;
+    load_tile(0, CAUSAL ? min(it.len, q0 + C::BM) : it.len, sK0, sV0);
+    const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
+                              (uint32_t)min(it.len - q0, C::BM) * row_bytes);
+#pragma unroll
+    for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, q_off + 32u * cc));
+  };
+  load_first();
+  wait_async_loads();
+  lds_barrier();
+
   for (;;) {
-    const int w = queue.item(__builtin_amdgcn_readfirstlane(s_ticket));
-    if (w >= n_items) break;
-    const WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
     const int L = it.len;
-    const size_t head_off = (size_t)it.head * D;
-    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
-    // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
-    const int q_tiles = (L + C::BM - 1) / C::BM;
-    int sub = 0;
-  second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
-    const int q_tile = !CAUSAL ? it.tile : sub == 0 ? q_tiles - 1 - it.tile : it.tile;
+    const int q_tile = q_tile_of();
     const int q0 = q_tile * C::BM;
     const int q_row = q0 + wave * 32 + l32;      // row inside the sequence
-    const bool q_valid = q_row < L;
     // keys this query tile sees at all
     const int kv_end = CAUSAL ? min(L, q0 + C::BM) : L;
-
-    // this lane's query row as the B operand of S^T = K Q^T (rows past the end read as zero)
-    bf16x8 qf[C::KC];
-    {
-      const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + head_off,
-                                (uint32_t)min(L - q0, C::BM) * row_bytes);
-      const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
-    }
+    const int n_tiles = (kv_end + C::BN - 1) / C::BN;
+    if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
 
     f32x16 o[C::DB];
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) o[db] = zero16();
     float m_ref = -INFINITY;   // exponent reference (raw score units)
+    float mc = -INFINITY;      // m_ref * c
     float l_run = 0.f;         // this lane's share of the row sum (its 32 of the 64 keys per tile)
 
-    const __bf16* k_base = k + (size_t)it.row0 * row_stride + head_off;
-    const __bf16* v_base = v + (size_t)it.row0 * row_stride + head_off;
-    const int n_tiles = (kv_end + C::BN - 1) / C::BN;
+    // the first tile in which some key of this item's queries is masked: past the end of the sequence, or (CAUSAL)
+    // after a query (which covers the ragged end for the rows of the sequence)
+    const int first_masked = CAUSAL ? 2 * q_tile : L / C::BN;
+    const int kv_lim = CAUSAL ? q_row + 1 : L;
 
-    auto load_tile = [&](int t, __bf16* dK, __bf16* dV) {   // asynchronous; a tile past the end arrives as zeros
-      const int kv0 = t * C::BN;
-      const uint32_t bytes = (uint32_t)max(0, min(kv_end - kv0, C::BN)) * row_bytes;
-      tile_load_async<D>(dK, make_rsrc(k_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
-      tile_load_async<D>(dV, make_rsrc(v_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
-    };
-
-    // One tile: 64 keys as two halves of 32.  MODE 1 is the ragged last tile, MODE 2 a tile that
-    // crosses the causal diagonal (for rows of the sequence that mask covers the ragged end too).
-    // A wave whose 32 queries all precede the tile's first key has nothing to do in it.
-    auto process_tile = [&](int t, auto mode_tag, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
-      constexpr int MODE = decltype(mode_tag)::value;
-      load_tile(t + 1, nK, nV);
-      if (!(MODE == 2 && t * C::BN > q0 + 32 * wave_u + 31)) {
+    // One tile: 64 keys as two halves of 32.  A wave whose 32 queries all precede the tile's first key has
+    // nothing to do in it.
+    auto process_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
+      load_tile(t + 1, kv_end, nK, nV);
+      const bool masked = t >= first_masked;
+      if (!(CAUSAL && t * C::BN > q0 + 32 * wave_u + 31)) {
 
       bf16x8 ak0[C::KC], ak1[C::KC];
 #pragma unroll
       for (int cc = 0; cc < C::KC; ++cc) ak0[cc] = k_rows.get(tK, 0, cc);
       KNAP_SCHED_FENCE();
 
-      f32x16 s0, s1;
-      if constexpr (MODE != 0) {   // keys past the end of the sequence, or after the query, start (and stay) at -inf
-        const int kv0 = t * C::BN;
-        const int kv_lim = MODE == 2 ? q_row + 1 : L;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = kv0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-          s0[r] = kv < kv_lim ? 0.f : -INFINITY;
-          s1[r] = kv + 32 < kv_lim ? 0.f : -INFINITY;
-        }
-      } else {
-        s0 = zero16();
-        s1 = zero16();
-      }
+      f32x16 s0 = zero16(), s1 = zero16();
       // slot 1: S^T of keys 0..31 | K fragments of keys 32..63
 #pragma unroll
       for (int cc = 0; cc < C::KC; ++cc) s0 = mfma32(ak0[cc], qf[cc], s0);
@@ -169,64 +167,78 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); }
       KNAP_SCHED_FENCE();
 
-      // slot 2: S^T of keys 32..63 | max over keys 0..31, V^T fragments of keys 0..31
-      bf16x8 vt0[2][C::DB], vt1[2][C::DB];
+      auto mask = [&](f32x16& s, int half) {
+        const int seen = kv_lim - t * C::BN - 32 * half - 4 * hh;   // keys of the half this lane's query sees
 #pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) s1 = mfma32(ak1[cc], qf[cc], s1);
-      float m_loc = s0[0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) m_loc = fmaxf(m_loc, s0[r]);
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-          vt0[0][db] = v_cols.get(tV, 0, db);
-#pragma unroll
-      for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); KNAP_SGB(KNAP_SG_VALU, 2); }
-      KNAP_SCHED_FENCE();
-
-#pragma unroll
-      for (int r = 0; r < 16; ++r) m_loc = fmaxf(m_loc, s1[r]);
-      m_loc = fmaxf(m_loc, xor32(m_loc));
-      // move the reference only when the tile maximum is far above it (always on the first tile)
-      if (__builtin_amdgcn_ballot_w64((m_loc - m_ref) * c > kRescaleThreshold) != 0) {
-        const float m_new = fmaxf(m_ref, m_loc);
-        const float alpha = fast_exp2((m_ref - m_new) * c);
-        m_ref = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      }
-      const float mc = m_ref * c;
-
-      // P^T of a half, packed: element e of chunk ck is key 16 ck + 8 (e / 4) + 4 hh + e % 4
-      auto exps = [&](const f32x16& s, bf16x8 (&pb)[2]) {
+        for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + (r & 3) < seen ? s[r] : -INFINITY;
+      };
+      // P^T of a half, packed, against the reference as it stands: element e of chunk ck is key
+      // 16 ck + 8 (e / 4) + 4 hh + e % 4; `sum` takes the lane's 16 rounded probabilities
+      auto exps = [&](const f32x16& s, bf16x8 (&pb)[2], float& sum) {
         float p[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mc));
+        sum = 0.f;
 #pragma unroll
         for (int ck = 0; ck < 2; ++ck) {
           const int r0 = 8 * ck;
-          pb[ck] = pack8_sum(p[r0], p[r0 + 1], p[r0 + 2], p[r0 + 3], p[r0 + 4], p[r0 + 5], p[r0 + 6], p[r0 + 7], l_run);
+          pb[ck] = pack8_sum(p[r0], p[r0 + 1], p[r0 + 2], p[r0 + 3], p[r0 + 4], p[r0 + 5], p[r0 + 6], p[r0 + 7], sum);
         }
       };
-      bf16x8 pb0[2], pb1[2];
+      // The reference moves only when the half's probabilities against it are too large (always on the first
+      // half, where it is -inf and the sum inf or NaN): up to the half's maximum, with what is accumulated
+      // rescaled and the half's probabilities formed again.
+      auto settle = [&](const f32x16& s, bf16x8 (&pb)[2], float& sum) {
+        if (__builtin_amdgcn_ballot_w64(!(sum <= kMaxHalfSum)) != 0) {
+          float m_loc = s[0];
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-          vt0[1][db] = v_cols.get(tV, 16, db);
-      exps(s0, pb0);
+          for (int r = 1; r < 16; ++r) m_loc = fmaxf(m_loc, s[r]);
+          const float m_new = fmaxf(m_ref, fmaxf(m_loc, xor32(m_loc)));
+          const float alpha = m_new == m_ref ? 1.f : fast_exp2((m_ref - m_new) * c);
+          m_ref = m_new;
+          mc = m_new == -INFINITY ? 0.f : m_new * c;
+          l_run *= alpha;
+#pragma unroll
+          for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+          exps(s, pb, sum);
+        }
+        l_run += sum;
+      };
+
+      if (masked) mask(s0, 0);
+      KNAP_SCHED_FENCE();
+      // slot 2: S^T of keys 32..63 | P^T of keys 0..31, V^T fragments of keys 0..15
+      bf16x8 vt0[2][C::DB], vt1[2][C::DB];
+      bf16x8 pb0[2], pb1[2];
+      float sum0, sum1;
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) s1 = mfma32(ak1[cc], qf[cc], s1);
+      exps(s0, pb0, sum0);
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) vt0[0][db] = v_cols.get(tV, 0, db);
+#pragma unroll
+      for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); KNAP_SGB(KNAP_SG_VALU, 48 / C::KC); }
+      KNAP_SCHED_FENCE();
+      settle(s0, pb0, sum0);
+      if (masked) mask(s1, 1);
       KNAP_SCHED_FENCE();
 
-      // slot 3: O^T += V^T P^T over keys 0..31 | P^T of keys 32..63, V^T fragments of keys 32..47
+      // slot 3: O^T += V^T P^T over keys 0..31 | P^T of keys 32..63, V^T fragments of keys 16..47
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) vt0[1][db] = v_cols.get(tV, 16, db);
 #pragma unroll
       for (int ck = 0; ck < 2; ++ck)
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) o[db] = mfma32(vt0[ck][db], pb0[ck], o[db]);
-      exps(s1, pb1);
+      exps(s1, pb1, sum1);
 #pragma unroll
       for (int db = 0; db < C::DB; ++db) vt1[0][db] = v_cols.get(tV, 32, db);
 #pragma unroll
-      for (int i = 0; i < 2 * C::DB; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); KNAP_SGB(KNAP_SG_VALU, 8); }
+      for (int i = 0; i < 2 * C::DB; ++i) { KNAP_SGB(KNAP_SG_DS_READ, 2); KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_VALU, 24 / C::DB); }
+      KNAP_SCHED_FENCE();
+      settle(s1, pb1, sum1);
       KNAP_SCHED_FENCE();
 
       // slot 4: O^T += V^T P^T over keys 32..63 | V^T fragments of keys 48..63
@@ -244,61 +256,41 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       __syncthreads();     // next tile visible; this tile no longer read
     };
 
-    __syncthreads();       // the previous item (or the schedule build) is done with both buffers
-    load_tile(0, sK0, sV0);
-    wait_async_loads();
-    if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
-    __syncthreads();
-
-    constexpr std::integral_constant<int, 0> plain{};
-    constexpr std::integral_constant<int, 1> ragged_end{};
-    constexpr std::integral_constant<int, 2> diagonal{};
-    if constexpr (!CAUSAL) {
-      const bool ragged = (L % C::BN) != 0;
-      const int n_full = ragged ? n_tiles - 1 : n_tiles;
-      for (int t = 0; t < n_full; t += 2) {
-        process_tile(t, plain, sK0, sV0, sK1, sV1);
-        if (t + 1 < n_full) process_tile(t + 1, plain, sK1, sV1, sK0, sV0);
-      }
-      if (ragged) {
-        if ((n_tiles - 1) & 1) process_tile(n_tiles - 1, ragged_end, sK1, sV1, sK0, sV0);
-        else process_tile(n_tiles - 1, ragged_end, sK0, sV0, sK1, sV1);
-      }
-    } else {
-      // tiles 0 .. 2 q_tile - 1 lie below the diagonal (an even count: the pair loop ends on buffer 0);
-      // tiles 2 q_tile and, if the sequence reaches it, 2 q_tile + 1 cross it
-      const int n_below = 2 * q_tile;
-      for (int t = 0; t < n_below; t += 2) {
-        process_tile(t, plain, sK0, sV0, sK1, sV1);
-        process_tile(t + 1, plain, sK1, sV1, sK0, sV0);
-      }
-      process_tile(n_below, diagonal, sK0, sV0, sK1, sV1);
-      if (n_below + 1 < n_tiles) process_tile(n_below + 1, diagonal, sK1, sV1, sK0, sV0);
+    for (int t = 0; t < n_tiles; t += 2) {
+      process_tile(t, sK0, sV0, sK1, sV1);
+      if (t + 1 < n_tiles) process_tile(t + 1, sK1, sV1, sK0, sV0);
     }
 
-    // epilogue: normalise, store out (bf16) and lse (natural log)
+    // The next item's first loads go out before this one's results are stored, so that they travel under
+    // the epilogue; both tile buffers are free (the last tile ended with a barrier).
+    const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
+                              (uint32_t)min(L - q0, C::BM) * row_bytes);
+    const auto rl = make_rsrc(lse + (size_t)it.head * T + it.row0 + q0, (uint32_t)min(L - q0, C::BM) * 4u);
+    bool more = true;
+    if (CAUSAL && sub == 0 && it.tile != q_tile) {   // not the middle tile of an odd count
+      sub = 1;
+    } else {
+      if (tid == 0) s_ticket = queue.later_ticket(next_ticket);   // every wave read the old one many barriers ago
+      lds_barrier();
+      w = queue.item(__builtin_amdgcn_readfirstlane(s_ticket));
+      more = w < n_items;
+      if (more) it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+      sub = 0;
+    }
+    if (more) load_first();
+    KNAP_SCHED_FENCE();
+
+    // epilogue: normalise, store lse (natural log) and out (bf16)
     const float l_tot = l_run + xor32(l_run);
     const float inv = 1.0f / l_tot;
-    if (q_valid) {
-      __bf16* o_ptr = out + (size_t)(it.row0 + q_row) * row_stride + head_off;
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, m_ref * scale + __logf(l_tot)), rl,
+                                          hh == 0 ? (wave * 32 + l32) * 4 : 4 * C::BM, 0, 0);
 #pragma unroll
-      for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const bf16x4 pk = pack4(o[db][4 * g] * inv, o[db][4 * g + 1] * inv,
-                                  o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv);
-          *reinterpret_cast<bf16x4*>(o_ptr + 32 * db + 8 * g + 4 * hh) = pk;
-        }
-      if (hh == 0) lse[(size_t)it.head * T + it.row0 + q_row] = m_ref * scale + __logf(l_tot);
-    }
-    if constexpr (CAUSAL) {
-      if (sub == 0 && it.tile != q_tiles - 1 - it.tile) {   // not the middle tile of an odd count
-        sub = 1;
-        goto second_tile_of_pair;
-      }
-    }
-    if (tid == 0) s_ticket = (int)next_ticket;   // every wave took its copy of the old ticket many barriers ago
-    __syncthreads();
+    for (int db = 0; db < C::DB; ++db) store_block(ro, q_off + 64u * db, o[db], inv);
+    if (!more) return;
+    // the loads have landed: all but the 2 DB stores of the output, which are younger (in-order completion)
+    wait_vm<2 * C::DB>();
+    lds_barrier();
   }
 }
 

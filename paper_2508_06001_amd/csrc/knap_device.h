@@ -103,6 +103,9 @@ __device__ __forceinline__ void tile_load_async(__bf16* tile, __amdgpu_buffer_rs
   }
 }
 
+// waits until at most N of this wave's vector-memory operations (loads and stores, in issue order) are in flight
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_async_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // The swizzle only looks at the low four bits of the row, so a read at (row_base + r, col)
@@ -162,6 +165,37 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 
 __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t byte_offset) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_offset, 0, 0);
+}
+
+// Stores a 32 x 32 MFMA result block (one output row per lane, registers running along it: element r of a
+// lane is column 8 (r / 4) + 4 hh + r % 4), times `mul`, as bf16.  `off` is the byte offset of this lane's
+// row, plus 16 hh; rows past the descriptor are dropped.  The lanes of a row (l and l ^ 32) trade four
+// columns, so that each stores 8 consecutive ones: two 16-byte stores per block and lane, no predicate.
+__device__ __forceinline__ void store_block(__amdgpu_buffer_rsrc_t r, uint32_t off, const f32x16& x, float mul) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    uint32_t w[2][2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        bf16x2 p;
+        p[0] = (__bf16)(x[8 * j + 4 * g + 2 * i] * mul);
+        p[1] = (__bf16)(x[8 * j + 4 * g + 2 * i + 1] * mul);
+        w[g][i] = __builtin_bit_cast(uint32_t, p);
+      }
+    const auto a = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+    const u32x4 v = {a[0], b[0], a[1], b[1]};
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(off + 32u * j), 0, 0);
+  }
+}
+
+// Workgroup barrier for LDS traffic alone: __syncthreads() also waits for every global store in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Scheduling helpers.  A fence keeps the scheduler from moving anything across it; the
@@ -345,24 +379,50 @@ __device__ __forceinline__ int serpentine_item(int r, int wg, int G) {
   return r * G + ((r & 1) ? G - 1 - wg : wg);
 }
 
+// Items of the sequences at least half as long as the longest one, or `enough` if there are that many:
+// the band of dear items that has to be spread over the whole GPU.  Items per sequence fall along the order.
+__device__ __forceinline__ int dear_items(const int* s_start, int n_seq, int enough) {
+  const int top = s_start[1];
+  if (top >= enough) return enough;
+  int lo = 0, hi = n_seq - 1;     // largest rank with at least half the items of rank 0
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (2 * (s_start[mid + 1] - s_start[mid]) >= top) lo = mid; else hi = mid - 1;
+  }
+  return min(enough, s_start[lo + 1]);
+}
+
 // Dynamic assignment for kernels that are handed zeroed counters (one unsigned per XCD, 8 in
-// all): the descending-cost item list is cut into chunks of G / 8 consecutive items, chunk j
-// belongs to XCD j % 8 (so that the workgroups of an XCD keep meeting on the same K and V in its
-// L2, and every XCD gets every eighth chunk of every cost band), and the workgroups of an XCD
-// draw that XCD's items in order from its counter: list scheduling, longest first, within the
-// XCD.  A ticket is the value the counter returned; the item of a ticket grows with the ticket,
-// so the first ticket whose item is at or past n_items ends the workgroup.
+// all): the descending-cost item list is cut into chunks of consecutive items, every XCD takes one
+// chunk of each round of 8 (so that the workgroups of an XCD keep meeting on the same K and V in its
+// L2), and the workgroups of an XCD draw that XCD's items in order from its counter: list
+// scheduling, longest first, within the XCD.  A ticket is the value the counter returned; the item of
+// a ticket grows with the ticket, so the first ticket whose item is at or past n_items ends the
+// workgroup.
+//
+// Chunks are G / 8 items (smaller ones cost long sequences up to 7 %: fewer workgroups meet in an L2),
+// except where the dear items are fewer than G: those are then dealt evenly, an eighth to every XCD,
+// instead of filling the first XCDs and leaving the others idle (eight sequences of up to 2101 tokens, two
+// heads of 64: forward 54 -> 41 us, dQ 64 -> 45 us).  Rounds run through the XCDs alternately
+// upwards and downwards: an item costs at most what the one before it costs, and always upwards the first
+// XCD would get the dearest chunk of every round (17 sequences of 328..4533 tokens, 24 heads of 128: forward
+// 1104 -> 1087 us, dQ 1511 -> 1482 us).
 struct ItemQueue {
   unsigned* ctr;
   int q, n_q, chunk;
-  __device__ __forceinline__ void init(unsigned* counters) {
+  __device__ __forceinline__ void init(unsigned* counters, const int* s_start, int n_seq) {
     n_q = (gridDim.x % 8 == 0) ? 8 : 1;
     q = (int)(blockIdx.x % n_q);                  // workgroups go to the XCDs round-robin
-    chunk = max(1, (int)gridDim.x / n_q);
+    chunk = __builtin_amdgcn_readfirstlane(max(1, (dear_items(s_start, n_seq, (int)gridDim.x) + n_q - 1) / n_q));
     ctr = counters + q;
   }
+  // a workgroup's first item needs no draw: the first G / n_q tickets go to the queue's workgroups in order,
+  // and the counter deals out the ones after them
+  __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
+  __device__ __forceinline__ int later_ticket(unsigned drawn) const { return (int)gridDim.x / n_q + (int)drawn; }
   __device__ __forceinline__ int item(int ticket) const {
-    return ((ticket / chunk) * n_q + q) * chunk + ticket % chunk;
+    const int round = ticket / chunk;
+    return (round * n_q + ((round & 1) ? n_q - 1 - q : q)) * chunk + ticket % chunk;
   }
 };
 
