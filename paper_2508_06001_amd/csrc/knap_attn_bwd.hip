@@ -505,10 +505,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
   __shared__ int s_ticket;
   ItemQueue queue;
   queue.init(counters, s_start, n_seq);
-  if (tid == 0) s_ticket = (int)atomicAdd(queue.ctr, 1u);
-  __syncthreads();
-  for (;;) {
-    const int w = queue.item(__builtin_amdgcn_readfirstlane(s_ticket));
+  for (int ticket = queue.first_ticket();;) {
+    const int w = queue.item(ticket);
     if (w >= n_items) break;
     const WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
     const int L = it.len;
@@ -632,8 +630,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
       __syncthreads();     // next tile visible; this tile no longer read
     };
 
-    __syncthreads();       // the previous item (or the schedule build) is done with both buffers
-    load_tile(0, sK0, sV0);
+    load_tile(0, sK0, sV0);    // a barrier stands between the last reads of either buffer (or the schedule build) and this
     wait_async_loads();
     if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
     __syncthreads();
@@ -663,16 +660,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
       if (n_below + 1 < n_tiles) process_tile(diagonal, n_below + 1, sK1, sV1, sK0, sV0);
     }
 
-    if (q_valid) {
-      __bf16* o_ptr = dq + (size_t)(it.row0 + q_row) * row_stride + head_off;
+    {
+      const auto rg = make_rsrc(dq + (size_t)(it.row0 + q0) * row_stride + head_off,
+                                (uint32_t)min(L - q0, C::BM) * row_bytes);
+      const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
 #pragma unroll
-      for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const bf16x4 pk = pack4(acc[db][4 * g] * scale, acc[db][4 * g + 1] * scale,
-                                  acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
-          *reinterpret_cast<bf16x4*>(o_ptr + 32 * db + 8 * g + 4 * hh) = pk;
-        }
+      for (int db = 0; db < C::DB; ++db) store_block(rg, off + 64u * db, acc[db], scale);
     }
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != q_tiles - 1 - it.tile) {   // not the middle tile of an odd count
@@ -680,8 +673,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
         goto second_tile_of_pair;
       }
     }
-    if (tid == 0) s_ticket = (int)next_ticket;   // every wave took its copy of the old ticket many barriers ago
-    __syncthreads();
+    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);   // every wave took its copy of the old one many barriers ago
+    lds_barrier();
+    ticket = __builtin_amdgcn_readfirstlane(s_ticket);
   }
 }
 
