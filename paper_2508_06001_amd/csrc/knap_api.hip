@@ -24,7 +24,6 @@ thread_local hipEvent_t g_prof_stop = nullptr;
 struct DeviceInfo {
   int cus = 0;
   int fwd_wg[2] = {0, 0};   // workgroups per CU, index 0: d = 64, 1: d = 128
-  int dkdv_wg[2] = {0, 0};
   int dq_wg[2] = {0, 0};
   unsigned* fwd_queue = nullptr;   // this device's copy of the forward work-queue counters
   unsigned char* scratch = nullptr;   // this device's copy of `scratch`
@@ -46,8 +45,6 @@ void fill_device_info(DeviceInfo& di, int dev) {
   }
   di.fwd_wg[0] = knap::fwd_workgroups_per_cu(64);
   di.fwd_wg[1] = knap::fwd_workgroups_per_cu(128);
-  di.dkdv_wg[0] = knap::bwd_dkdv_workgroups_per_cu(64);
-  di.dkdv_wg[1] = knap::bwd_dkdv_workgroups_per_cu(128);
   di.dq_wg[0] = knap::bwd_dq_workgroups_per_cu(64);
   di.dq_wg[1] = knap::bwd_dq_workgroups_per_cu(128);
   di.fwd_queue = knap::fwd_queue_base();
@@ -116,6 +113,24 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
              int H, int d, float scale, bool causal,
              const void* out, const float* lse, const void* dout, void* dq, void* dk, void* dv,
              int64_t total_tokens, void* workspace, size_t workspace_bytes, bool own_scratch, void* stream);
+
+// Wave pairs per workgroup of the dK/dV kernel (2 or 4, see there), from what the host knows of a bag: its tokens, heads
+// and number of sequences.  Both sides measured as times of that kernel, two pairs against four.
+//  * At most half a 256-key tile per CU: two, which spread the keys over twice as many CUs (3 causal sequences of up to
+//    391 tokens, 6 x 128: 38 against 51 us; 2 of up to 4362, 2 x 64: 104 against 150 us).
+//  * Many short sequences: two, which hide the start and the end of every item (32 of 450 tokens, 24 x 128: 249 against
+//    276 us; 17 causal ones of 328..4533 tokens: 1125 against 1240 us; 10 of 310..6795 tokens, 48 x 64: 2806 against
+//    3057 us).  The causal kernel at d = 64 has little of either to hide and is up to 8 % slower.  The average does not
+//    show one long sequence among many short ones, where two pairs lose (16309 tokens and 54 short, 6 x 128: 1793 against
+//    1692 us), hence the bounds on the whole bag.
+//  * Otherwise four (65536 and 200 short, 24 x 128: 80.3 against 82.4 ms; 30000 tokens, 3 x 128: 2.90 against 3.13 ms).
+int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
+  if (total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
+  const int64_t longest_average = d == 128 && !causal ? 2048 : 4096;
+  const int64_t largest_bag = d == 64 ? (causal ? 0 : 32768) : (causal ? 65536 : 16384);
+  if (total_tokens <= largest_bag && total_tokens < longest_average * n_seq) return 2;
+  return 4;
+}
 
 }  // namespace
 
@@ -205,10 +220,10 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   float* delta = static_cast<float*>(workspace);
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + (need - 256) / 2);
   unsigned* counters = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256);
-  const int grid_dkdv = di->cus * di->dkdv_wg[d == 128];
   const int grid_dq = di->cus * di->dq_wg[d == 128];
   const hipError_t e = knap::launch_bwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, dout,
-                                        dq, dk, dv, delta, lse2, counters, grid_dkdv, grid_dq,
+                                        dq, dk, dv, delta, lse2, counters, dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus),
+                                        di->cus, grid_dq,
                                         static_cast<hipStream_t>(stream), g_prof_start, g_prof_stop);
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
@@ -328,7 +343,7 @@ void knap_bwd_profile_events(void* start, void* stop) {
 int knap_launch_workgroups(int which) {
   DeviceInfo* di = device_info();
   if (!di) return -1;
-  return di->cus * (which == 0 ? di->fwd_wg[1] : which == 1 ? di->dkdv_wg[1] : di->dq_wg[1]);
+  return di->cus * (which == 0 ? di->fwd_wg[1] : which == 1 ? knap::dkdv_workgroups_per_cu(4) : di->dq_wg[1]);
 }
 
 }  // extern "C"

@@ -361,24 +361,6 @@ __device__ __forceinline__ WorkItem decode_item(int w, const int32_t* __restrict
   return it;
 }
 
-// Workgroups are handed to the 8 XCDs round-robin by blockIdx.  Renumber them
-// so that the workgroups of one XCD take neighbouring work items and meet in
-// that XCD's L2 on the same K and V.
-__device__ __forceinline__ int xcd_major_block_id() {
-  const int g = gridDim.x;
-  const int b = blockIdx.x;
-  return (g % 8 == 0) ? (b % 8) * (g / 8) + b / 8 : b;
-}
-
-// Static assignment of the descending-cost item list to G persistent workgroups: in round r
-// workgroup wg takes item r G + wg, in odd rounds r G + (G - 1 - wg).  Dealing the rounds in
-// serpentine order halves the imbalance of plain round-robin (whoever drew the dearest item of
-// one round draws the cheapest of the next) and keeps neighbouring workgroups on neighbouring
-// items.  Items at or past n_items (last round only) do not exist.
-__device__ __forceinline__ int serpentine_item(int r, int wg, int G) {
-  return r * G + ((r & 1) ? G - 1 - wg : wg);
-}
-
 // Items of the sequences at least half as long as the longest one, or `enough` if there are that many:
 // the band of dear items that has to be spread over the whole GPU.  Items per sequence fall along the order.
 __device__ __forceinline__ int dear_items(const int* s_start, int n_seq, int enough) {

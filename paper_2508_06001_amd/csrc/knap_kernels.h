@@ -18,8 +18,23 @@ int fwd_queue_slots();
 hipError_t launch_bwd(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq, int H, int d,
                       float scale, bool causal, const void* out, const float* lse, const void* dout,
                       void* dq, void* dk, void* dv, float* delta, float* lse2, unsigned* counters,
-                      int grid_dkdv, int grid_dq, hipStream_t stream,
+                      int dkdv_pairs, int cus, int grid_dq, hipStream_t stream,
                       hipEvent_t ev_start, hipEvent_t ev_stop);
+
+// dK/dV kernel: `pairs` wave pairs (2 or 4) per workgroup, dkdv_workgroups_per_cu(pairs) workgroups on each CU
+// (two waves per SIMD is what its registers allow).
+struct DkdvArgs {
+  const void *q, *k, *v, *dout;
+  const float *lse2, *delta;
+  const int32_t* cu;
+  int n_seq, H;
+  float scale;
+  void *dk, *dv;
+  unsigned* counters;
+};
+constexpr int dkdv_workgroups_per_cu(int pairs) { return 4 / pairs; }
+hipError_t launch_dkdv(const DkdvArgs& a, int d, int pairs, int cus, hipStream_t stream);
+hipError_t launch_dkdv_causal(const DkdvArgs& a, int d, int pairs, int cus, hipStream_t stream);
 
 // Ulysses layout switch, local data movement; rows of U 16-byte units.
 hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t U, uint32_t g, bool pack,
@@ -32,7 +47,6 @@ hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32
 
 // resident workgroups per compute unit of the persistent kernels
 int fwd_workgroups_per_cu(int d);
-int bwd_dkdv_workgroups_per_cu(int d);
 int bwd_dq_workgroups_per_cu(int d);
 
 }  // namespace knap

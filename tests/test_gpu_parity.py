@@ -492,6 +492,16 @@ def test_causal_repeatable_and_independent_of_other_sequences():
         assert np.array_equal(a[keep], b[5:5 + 1290])
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_four_pair_dkdv_kernel_on_ragged_long_sequences(d, causal):
+    """Sequences long enough (4096 tokens and more on average) and a bag large enough (over 32768 rows of all heads)
+    for the dK/dV kernel's 256-key tiles, which smaller bags no longer reach: one key past a tile, one short of it,
+    32-query step counts of every residue modulo the ring of three buffers."""
+    bag = BagSpec("four_pairs", [5121, 4095, 4385, 4130], H=2, d=d, seed=6100 + d)
+    _full_compare(bag, heads=[1], strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
