@@ -17,8 +17,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libknapattn.so")
 
-HIP_SOURCES = ["knap_attn_fwd.hip", "knap_attn_bwd.hip", "knap_attn_dkdv.hip", "knap_attn_dkdv_causal.hip",
-               "knap_ulysses.hip", "knap_api.hip"]
+HIP_SOURCES = ["knap_attn_fwd.hip", "knap_attn_bwd.hip", "knap_attn_bwd_causal.hip", "knap_ulysses.hip",
+               "knap_api.hip"]
 C_SOURCES = ["knap_host.c"]
 
 HIP_FLAGS = [
@@ -33,9 +33,10 @@ HIP_FLAGS = [
 # flags of single sources
 FILE_FLAGS = {
     # the scheduler's exact register-pressure tracking: without it the causal dK/dV kernel reloads a spilled
-    # register in every step (17 sequences of 328..4533 tokens, 24 x 128: 1302 us against 1202 us); the
-    # bidirectional one has no such reload and is up to 1 % slower with it
-    "knap_attn_dkdv_causal.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
+    # register in every step (17 sequences of 328..4533 tokens, 24 x 128: 1302 us against 1202 us) and the causal dQ
+    # kernel is 5 % slower; the bidirectional kernels have no such reload and are up to 1 % slower with it on
+    # long sequences
+    "knap_attn_bwd_causal.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
 }
 
 

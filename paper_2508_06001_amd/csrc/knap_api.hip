@@ -221,9 +221,9 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + (need - 256) / 2);
   unsigned* counters = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256);
   const int grid_dq = di->cus * di->dq_wg[d == 128];
-  const hipError_t e = knap::launch_bwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, dout,
-                                        dq, dk, dv, delta, lse2, counters, dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus),
-                                        di->cus, grid_dq,
+  const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
+  const hipError_t e = knap::launch_bwd(args, d, causal, dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus), di->cus,
+                                        grid_dq, true,
                                         static_cast<hipStream_t>(stream), g_prof_start, g_prof_stop);
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;

@@ -1,0 +1,15 @@
+// The backward's kernels under the causal mask.
+#include "knap_attn_dkdv.h"
+#include "knap_attn_dq.h"
+
+namespace knap {
+
+hipError_t launch_dq_causal(const BwdArgs& a, int d, int grid, hipStream_t stream) {
+  return launch_dq_m<true>(a, d, grid, stream);
+}
+
+hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream) {
+  return launch_dkdv_m<true>(a, d, pairs, cus, stream);
+}
+
+}  // namespace knap

@@ -1,5 +1,4 @@
-// dK/dV kernel of the backward: one text, compiled for the bidirectional and the causal mask in a translation
-// unit each (the causal one wants another register-pressure heuristic, see build.py).
+// dK/dV kernel of the backward: one text, compiled for either mask in a translation unit of its own (see build.py).
 #pragma once
 
 #include "knap_device.h"
@@ -140,11 +139,10 @@ __global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
   // work items from this XCD's queue, the next one's ticket drawn behind the item's first loads and put down after
   // the barrier that every wave reaches with its copy of the old one
   __shared__ int s_ticket;
-  ItemQueue queue;
-  queue.init(counters, s_start, n_seq);
-  for (int ticket = queue.first_ticket();;) {
+  ItemQueue<0> queue;
+  queue.init(counters, s_start, n_seq, n_items);
+  for (int ticket = queue.first_ticket(); ticket < queue.wide;) {
     const int w = queue.item(ticket);
-    if (w >= n_items) break;
     unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
     WorkItem it = decode_item<C::BN, CAUSAL>(w, cu, n_seq, s_order, s_start);
     // head and tile come out of a division, i.e. of vector instructions: say that they are wave-uniform, so
@@ -389,9 +387,9 @@ __global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
     } while (0)
 
     issue_tile(0, sQ0, sdO0, sLse0, sDelta0);
-    if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
+    if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
     step_sync();      // tile 0 has landed (and the K / V rows requested before it)
-    if (tid == 0 && sub == 0) s_ticket = queue.later_ticket(next_ticket);
+    if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket);
 
     if (role == 0) KNAP_ROLE_LOOP(0);
     else KNAP_ROLE_LOOP(1);
@@ -416,21 +414,22 @@ __global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
         goto second_tile_of_pair;
       }
     }
+    if (!queue.draws) break;
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
   }
 }
 
 template <int D, int PAIRS, bool CAUSAL>
-static hipError_t launch_dkdv_t(const DkdvArgs& a, int cus, hipStream_t stream) {
+static hipError_t launch_dkdv_t(const BwdArgs& a, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
   hipLaunchKernelGGL((attn_bwd_dkdv64_kernel<D, PAIRS, CAUSAL>), dim3(cus * dkdv_workgroups_per_cu(PAIRS)), dim3(128 * PAIRS),
                      dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout,
-                     a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale, (__bf16*)a.dk, (__bf16*)a.dv, a.counters);
+                     a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale, (__bf16*)a.dk, (__bf16*)a.dv, a.counters + 8);
   return hipGetLastError();
 }
 
 template <bool CAUSAL>
-static hipError_t launch_dkdv_m(const DkdvArgs& a, int d, int pairs, int cus, hipStream_t stream) {
+static hipError_t launch_dkdv_m(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream) {
   if (pairs == 2) return d == 64 ? launch_dkdv_t<64, 2, CAUSAL>(a, cus, stream) : launch_dkdv_t<128, 2, CAUSAL>(a, cus, stream);
   return d == 64 ? launch_dkdv_t<64, 4, CAUSAL>(a, cus, stream) : launch_dkdv_t<128, 4, CAUSAL>(a, cus, stream);
 }

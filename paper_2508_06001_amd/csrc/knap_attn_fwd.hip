@@ -50,7 +50,7 @@ constexpr float kMaxHalfSum = 256.f;        // of a lane's 16 probabilities agai
 constexpr int kFwdQueueSlots = 256;
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const int32_t* __restrict__ cu, int n_seq, int H, float scale,
     __bf16* __restrict__ out, float* __restrict__ lse, unsigned* __restrict__ counters) {
@@ -89,11 +89,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
   // before them, the slow counter update would hold up the whole prologue) and only looked at
   // when the item is done, so the counter's latency is never waited for.
   __shared__ int s_ticket;
-  ItemQueue queue;
-  queue.init(counters, s_start, n_seq);
-  int w = queue.item(queue.first_ticket());
-  if (w >= n_items) return;
-  WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+  constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a wide one
+  ItemQueue<SPLIT> queue;
+  queue.init(counters, s_start, n_seq, n_items);
+  int ticket = queue.first_ticket();
+  WorkItem it;
   unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
   int sub = 0;               // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
 
@@ -119,6 +119,48 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
 #pragma unroll
     for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, q_off + 32u * cc));
   };
+  auto mask_half = [&](f32x16& s, int seen) {     // `seen`: keys of the half, from its first, that this lane's query sees
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + (r & 3) < seen - 4 * hh ? s[r] : -INFINITY;
+  };
+
+  // P^T of a half, packed, against the reference as it stands (mc = m_ref c): element e of chunk ck is key
+  // 16 ck + 8 (e / 4) + 4 hh + e % 4; `sum` takes the lane's 16 rounded probabilities
+  auto half_exps = [&](const f32x16& s, float mc, bf16x8 (&pb)[2], float& sum) {
+    float p[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mc));
+    sum = 0.f;
+#pragma unroll
+    for (int ck = 0; ck < 2; ++ck) {
+      const int r0 = 8 * ck;
+      pb[ck] = pack8_sum(p[r0], p[r0 + 1], p[r0 + 2], p[r0 + 3], p[r0 + 4], p[r0 + 5], p[r0 + 6], p[r0 + 7], sum);
+    }
+  };
+  // The reference moves only when the half's probabilities against it are too large (always on the first
+  // half, where it is -inf and the sum inf or NaN): up to the half's maximum, with what is accumulated
+  // rescaled and the half's probabilities formed again.
+  auto half_settle = [&](const f32x16& s, bf16x8 (&pb)[2], float& sum, float& m_ref, float& mc, float& l_run, f32x16 (&o)[C::DB]) {
+    if (__builtin_amdgcn_ballot_w64(!(sum <= kMaxHalfSum)) != 0) {
+      float m_loc = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) m_loc = fmaxf(m_loc, s[r]);
+      const float m_new = fmaxf(m_ref, fmaxf(m_loc, xor32(m_loc)));
+      const float alpha = m_new == m_ref ? 1.f : fast_exp2((m_ref - m_new) * c);
+      m_ref = m_new;
+      mc = m_new == -INFINITY ? 0.f : m_new * c;
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      half_exps(s, mc, pb, sum);
+    }
+    l_run += sum;
+  };
+
+  if (ticket < queue.wide) {
+  it = decode_item<C::BM, CAUSAL>(queue.item(ticket), cu, n_seq, s_order, s_start);
   load_first();
   wait_async_loads();
   lds_barrier();
@@ -131,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
     // keys this query tile sees at all
     const int kv_end = CAUSAL ? min(L, q0 + C::BM) : L;
     const int n_tiles = (kv_end + C::BN - 1) / C::BN;
-    if (tid == 0 && sub == 0) next_ticket = atomicAdd(queue.ctr, 1u);
+    if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
 
     f32x16 o[C::DB];
 #pragma unroll
@@ -155,6 +197,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       bf16x8 ak0[C::KC], ak1[C::KC];
 #pragma unroll
       for (int cc = 0; cc < C::KC; ++cc) ak0[cc] = k_rows.get(tK, 0, cc);
+      if constexpr (D == 128 && !CAUSAL) {   // the reads between the eight copies: all behind them costs three heads of
+        KNAP_SGB(KNAP_SG_DS_READ, 2);        // 131072 keys 1.4 %, all in front of them 1.7 %
+        KNAP_SGB(KNAP_SG_VMEM_READ, 3);
+        KNAP_SGB(KNAP_SG_DS_READ, 1);
+        KNAP_SGB(KNAP_SG_VMEM_READ, 4);
+        KNAP_SGB(KNAP_SG_DS_READ, 1);
+        KNAP_SGB(KNAP_SG_VMEM_READ, 1);
+        KNAP_SGB(KNAP_SG_DS_READ, 4);
+      }
       KNAP_SCHED_FENCE();
 
       f32x16 s0 = zero16(), s1 = zero16();
@@ -167,47 +218,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); }
       KNAP_SCHED_FENCE();
 
-      auto mask = [&](f32x16& s, int half) {
-        const int seen = kv_lim - t * C::BN - 32 * half - 4 * hh;   // keys of the half this lane's query sees
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 8 * (r >> 2) + (r & 3) < seen ? s[r] : -INFINITY;
-      };
-      // P^T of a half, packed, against the reference as it stands: element e of chunk ck is key
-      // 16 ck + 8 (e / 4) + 4 hh + e % 4; `sum` takes the lane's 16 rounded probabilities
-      auto exps = [&](const f32x16& s, bf16x8 (&pb)[2], float& sum) {
-        float p[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mc));
-        sum = 0.f;
-#pragma unroll
-        for (int ck = 0; ck < 2; ++ck) {
-          const int r0 = 8 * ck;
-          pb[ck] = pack8_sum(p[r0], p[r0 + 1], p[r0 + 2], p[r0 + 3], p[r0 + 4], p[r0 + 5], p[r0 + 6], p[r0 + 7], sum);
-        }
-      };
-      // The reference moves only when the half's probabilities against it are too large (always on the first
-      // half, where it is -inf and the sum inf or NaN): up to the half's maximum, with what is accumulated
-      // rescaled and the half's probabilities formed again.
-      auto settle = [&](const f32x16& s, bf16x8 (&pb)[2], float& sum) {
-        if (__builtin_amdgcn_ballot_w64(!(sum <= kMaxHalfSum)) != 0) {
-          float m_loc = s[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) m_loc = fmaxf(m_loc, s[r]);
-          const float m_new = fmaxf(m_ref, fmaxf(m_loc, xor32(m_loc)));
-          const float alpha = m_new == m_ref ? 1.f : fast_exp2((m_ref - m_new) * c);
-          m_ref = m_new;
-          mc = m_new == -INFINITY ? 0.f : m_new * c;
-          l_run *= alpha;
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-          exps(s, pb, sum);
-        }
-        l_run += sum;
-      };
-
-      if (masked) mask(s0, 0);
+      if (masked) mask_half(s0, kv_lim - t * C::BN);
       KNAP_SCHED_FENCE();
       // slot 2: S^T of keys 32..63 | P^T of keys 0..31, V^T fragments of keys 0..15
       bf16x8 vt0[2][C::DB], vt1[2][C::DB];
@@ -215,14 +226,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       float sum0, sum1;
 #pragma unroll
       for (int cc = 0; cc < C::KC; ++cc) s1 = mfma32(ak1[cc], qf[cc], s1);
-      exps(s0, pb0, sum0);
+      half_exps(s0, mc, pb0, sum0);
 #pragma unroll
       for (int db = 0; db < C::DB; ++db) vt0[0][db] = v_cols.get(tV, 0, db);
 #pragma unroll
       for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); KNAP_SGB(KNAP_SG_VALU, 48 / C::KC); }
       KNAP_SCHED_FENCE();
-      settle(s0, pb0, sum0);
-      if (masked) mask(s1, 1);
+      half_settle(s0, pb0, sum0, m_ref, mc, l_run, o);
+      if (masked) mask_half(s1, kv_lim - t * C::BN - 32);
       KNAP_SCHED_FENCE();
 
       // slot 3: O^T += V^T P^T over keys 0..31 | P^T of keys 32..63, V^T fragments of keys 16..47
@@ -232,13 +243,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
       for (int ck = 0; ck < 2; ++ck)
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) o[db] = mfma32(vt0[ck][db], pb0[ck], o[db]);
-      exps(s1, pb1, sum1);
+      half_exps(s1, mc, pb1, sum1);
 #pragma unroll
       for (int db = 0; db < C::DB; ++db) vt1[0][db] = v_cols.get(tV, 32, db);
 #pragma unroll
       for (int i = 0; i < 2 * C::DB; ++i) { KNAP_SGB(KNAP_SG_DS_READ, 2); KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_VALU, 24 / C::DB); }
       KNAP_SCHED_FENCE();
-      settle(s1, pb1, sum1);
+      half_settle(s1, pb1, sum1, m_ref, mc, l_run, o);
       KNAP_SCHED_FENCE();
 
       // slot 4: O^T += V^T P^T over keys 32..63 | V^T fragments of keys 48..63
@@ -269,12 +280,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
     bool more = true;
     if (CAUSAL && sub == 0 && it.tile != q_tile) {   // not the middle tile of an odd count
       sub = 1;
+    } else if (!queue.draws) {
+      more = false;
     } else {
-      if (tid == 0) s_ticket = queue.later_ticket(next_ticket);   // every wave read the old one many barriers ago
+      if (tid == 0) {
+        s_ticket = queue.later_ticket(next_ticket);   // every wave read the old one many barriers ago
+      }
       lds_barrier();
-      w = queue.item(__builtin_amdgcn_readfirstlane(s_ticket));
-      more = w < n_items;
-      if (more) it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+      ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+      more = ticket < queue.wide;
+      if (more) it = decode_item<C::BM, CAUSAL>(queue.item(ticket), cu, n_seq, s_order, s_start);
       sub = 0;
     }
     if (more) load_first();
@@ -287,10 +302,125 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(
                                           hh == 0 ? (wave * 32 + l32) * 4 : 4 * C::BM, 0, 0);
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) store_block(ro, q_off + 64u * db, o[db], inv);
-    if (!more) return;
+    if (!more) break;
     // the loads have landed: all but the 2 DB stores of the output, which are younger (in-order completion)
     wait_vm<2 * C::DB>();
     lds_barrier();
+  }
+  }
+
+  // Narrow items: 64 queries.  A lone workgroup on a CU takes as long for a wide item as one of two (a wave alone on
+  // its SIMD waits out its own latencies), so where the items are few each is cut in two that run side by side.
+  // Waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the second 32; the two
+  // halves of the softmax are merged through LDS at the end.
+  const int rb = wave & 1, kh = wave >> 1;
+  const int kh_u = __builtin_amdgcn_readfirstlane(kh), rb_u = __builtin_amdgcn_readfirstlane(rb);
+  for (int part = ticket - queue.wide; part >= 0 && part < queue.parts;) {
+    const int p = queue.part0 + part;
+    it = decode_item<C::BM, CAUSAL>(queue.n_wide + p / SPLIT, cu, n_seq, s_order, s_start);
+    const int L = it.len;
+    const int q_tiles = (L + C::BM - 1) / C::BM;
+    const int member = (p % SPLIT) >> 1;
+    const int q0 = __builtin_amdgcn_readfirstlane((!CAUSAL ? it.tile : member == 0 ? q_tiles - 1 - it.tile : it.tile) * C::BM + 64 * (p & 1));
+    const bool exists = q0 < L && !(CAUSAL && member == 1 && it.tile == q_tiles - 1 - it.tile);
+    if (exists) {
+      const int q_row = q0 + 32 * rb + l32;
+      const int kv_end = CAUSAL ? min(L, q0 + 64) : L;
+      const int n_tiles = (kv_end + C::BN - 1) / C::BN;
+      const int first_masked = CAUSAL ? q0 / C::BN : L / C::BN;
+      const int kv_lim = CAUSAL ? q_row + 1 : L;
+      const uint32_t off = (uint32_t)(32 * rb + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+      load_tile(0, kv_end, sK0, sV0);
+      const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
+                                (uint32_t)min(L - q0, 64) * row_bytes);
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
+      wait_async_loads();
+      lds_barrier();
+
+      f32x16 o[C::DB];
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) o[db] = zero16();
+      float m_ref = -INFINITY, mc = -INFINITY, l_run = 0.f;
+
+      auto half_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
+        load_tile(t + 1, kv_end, nK, nV);
+        if (!(CAUSAL && t * C::BN + 32 * kh_u > q0 + 32 * rb_u + 31)) {
+          f32x16 s = zero16();
+#pragma unroll
+          for (int cc = 0; cc < C::KC; ++cc) s = mfma32(k_rows.get(tK, 32 * kh, cc), qf[cc], s);
+          bf16x8 vt[2][C::DB];
+#pragma unroll
+          for (int ck = 0; ck < 2; ++ck)
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db) vt[ck][db] = v_cols.get(tV, 32 * kh + 16 * ck, db);
+          if (t >= first_masked) mask_half(s, kv_lim - t * C::BN - 32 * kh);
+          bf16x8 pb[2];
+          float sum;
+          half_exps(s, mc, pb, sum);
+          half_settle(s, pb, sum, m_ref, mc, l_run, o);
+#pragma unroll
+          for (int ck = 0; ck < 2; ++ck)
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db) o[db] = mfma32(vt[ck][db], pb[ck], o[db]);
+        }
+        wait_async_loads();
+        lds_barrier();
+      };
+      for (int t = 0; t < n_tiles; t += 2) {
+        half_tile(t, sK0, sV0, sK1, sV1);
+        if (t + 1 < n_tiles) half_tile(t + 1, sK1, sV1, sK0, sV0);
+      }
+
+      // merge: the waves of the second keys put down reference, sum and output, those of the first take them up
+      // (in the tile buffers, which are free)
+      float* part_o = reinterpret_cast<float*>(rb_u == 0 ? sK1 : sV1);
+      float* part_ml = reinterpret_cast<float*>(sV0) + 128 * rb_u;
+      if (kh_u == 1) {
+        part_ml[lane] = m_ref;
+        part_ml[64 + lane] = l_run;
+#pragma unroll
+        for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = {o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+            *reinterpret_cast<f32x4*>(part_o + ((4 * db + g) * 64 + lane) * 4) = x;
+          }
+      }
+      lds_barrier();
+      if (kh_u == 0) {
+        const float m_other = part_ml[lane], l_other = part_ml[64 + lane];
+        const float m_new = fmaxf(m_ref, m_other);
+        const float a_own = m_new == m_ref ? 1.f : fast_exp2((m_ref - m_new) * c);
+        const float a_other = m_new == m_other ? 1.f : fast_exp2((m_other - m_new) * c);
+        const float l_half = l_run * a_own + l_other * a_other;
+        const float l_tot = l_half + xor32(l_half);
+        const float inv = 1.0f / l_tot;
+        const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
+                                  (uint32_t)min(L - q0, 64) * row_bytes);
+        const auto rl = make_rsrc(lse + (size_t)it.head * T + it.row0 + q0, (uint32_t)min(L - q0, 64) * 4u);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, m_new * scale + __logf(l_tot)), rl,
+                                              hh == 0 ? (32 * rb + l32) * 4 : 4 * 64, 0, 0);
+#pragma unroll
+        for (int db = 0; db < C::DB; ++db) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(part_o + ((4 * db + g) * 64 + lane) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[db][4 * g + e] = o[db][4 * g + e] * a_own + x[e] * a_other;
+          }
+          store_block(ro, off + 64u * db, o[db], inv);
+        }
+      }
+    }
+    if (!queue.draws) return;         // every part was a first ticket
+    if (tid == 0) {
+      const unsigned drawn = atomicAdd(queue.ctr, 1u);
+      s_ticket = queue.later_ticket(drawn);
+    }
+    lds_barrier();                    // (and the tile buffers are no longer read)
+    part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
+    lds_barrier();                    // everyone has the ticket before it is drawn again
   }
 }
 

@@ -15,26 +15,24 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t
 unsigned* fwd_queue_base();
 int fwd_queue_slots();
 
-hipError_t launch_bwd(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq, int H, int d,
-                      float scale, bool causal, const void* out, const float* lse, const void* dout,
-                      void* dq, void* dk, void* dv, float* delta, float* lse2, unsigned* counters,
-                      int dkdv_pairs, int cus, int grid_dq, hipStream_t stream,
-                      hipEvent_t ev_start, hipEvent_t ev_stop);
-
-// dK/dV kernel: `pairs` wave pairs (2 or 4) per workgroup, dkdv_workgroups_per_cu(pairs) workgroups on each CU
-// (two waves per SIMD is what its registers allow).
-struct DkdvArgs {
-  const void *q, *k, *v, *dout;
-  const float *lse2, *delta;
+struct BwdArgs {
+  const void *q, *k, *v, *out, *dout;
+  const float* lse;
   const int32_t* cu;
   int n_seq, H;
   float scale;
-  void *dk, *dv;
-  unsigned* counters;
+  void *dq, *dk, *dv;
+  float *delta, *lse2;      // (H, T) each, handed from the dQ kernel to the dK/dV kernel
+  unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel
 };
+// The dK/dV kernel takes `dkdv_pairs` wave pairs (2 or 4) per workgroup and dkdv_workgroups_per_cu(pairs) workgroups
+// on each CU (two waves per SIMD is what its registers allow).  `draws`: some queue may hold more items than workgroups,
+// so that the counters have to be zero.
 constexpr int dkdv_workgroups_per_cu(int pairs) { return 4 / pairs; }
-hipError_t launch_dkdv(const DkdvArgs& a, int d, int pairs, int cus, hipStream_t stream);
-hipError_t launch_dkdv_causal(const DkdvArgs& a, int d, int pairs, int cus, hipStream_t stream);
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int grid_dq, bool draws,
+                      hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_dq_causal(const BwdArgs& a, int d, int grid, hipStream_t stream);
+hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream);
 
 // Ulysses layout switch, local data movement; rows of U 16-byte units.
 hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t U, uint32_t g, bool pack,
