@@ -155,6 +155,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
       half_exps(s, mc, pb, sum);
+      if (m_new == -INFINITY) mc = -INFINITY;   // scores of -inf alone set no reference: the next half has to settle too
     }
     l_run += sum;
   };

@@ -77,7 +77,7 @@ def test_tiny_bag_full_oracle():
 @pytest.mark.parametrize("d", [64, 128])
 def test_ragged_lengths_span_tiles_and_tails(d):
     # lengths around every tile boundary in use (32-row query steps and 256-row key tiles of the dK/dV kernel,
-    # 64-key and 128-query tiles of the others), query-step counts of every residue modulo the five-buffer
+    # 64-key and 128-query tiles of the others), query-step counts of every residue modulo the three-buffer
     # ring, zero-length and single-token sequences
     lens = [1, 2, 31, 0, 33, 63, 64, 65, 127, 128, 129, 0, 191, 255, 256, 257, 300, 511, 512, 513, 769, 1]
     bag = BagSpec("ragged", lens, H=3, d=d, seed=777 + d)
@@ -500,6 +500,44 @@ def test_four_pair_dkdv_kernel_on_ragged_long_sequences(d, causal):
     32-query step counts of every residue modulo the ring of three buffers."""
     bag = BagSpec("four_pairs", [5121, 4095, 4385, 4130], H=2, d=d, seed=6100 + d)
     _full_compare(bag, heads=[1], strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
+@pytest.mark.parametrize("masked_keys", [32, 64, 96])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_leading_keys_with_scores_of_minus_infinity(d, causal, masked_keys):
+    """Keys that hold -inf are keys left out: out and lse of the rows that see any other key are finite and those of
+    the remaining keys, also when a first half tile (32 keys) or more of a row has no finite score.  Bags of few items
+    (dealt out in parts) and of many.  Tolerances: those of rows that see few keys."""
+    import torch
+    import paper_2508_06001_amd as K
+    for lens, H in (([130, 200], 2), ([400] * 60, 4)):
+        T, n = sum(lens), len(lens)
+        cu = np.concatenate([[0], np.cumsum(lens)])
+        g = torch.Generator(device="cuda")
+        g.manual_seed(8100 + d + masked_keys)
+        q, k, v = (torch.randn((T, H, d), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+        q[:, :, 0] = 1.0
+        for s in range(n):
+            k[cu[s]:cu[s] + masked_keys, :, 0] = float("-inf")
+        attn = K.VarlenAttention([int(c) for c in cu], H, d, d ** -0.5, causal=causal)
+        out, lse = attn.forward(q, k, v)
+        for s in sorted({0, n // 2, n - 1}):
+            a, b = int(cu[s]), int(cu[s + 1])
+            first = masked_keys if causal else 0               # rows before it see no key at all under the mask
+            for h in range(H):
+                Q = q[a + first:b, h].double().cpu()
+                Kk, V = (x[a + masked_keys:b, h].double().cpu() for x in (k, v))
+                S = Q @ Kk.T * d ** -0.5
+                if causal:
+                    S = S.masked_fill(torch.ones_like(S).triu(1).bool(), float("-inf"))
+                ref, ref_lse = torch.softmax(S, dim=1) @ V, torch.logsumexp(S, dim=1)
+                got, got_lse = out[a + first:b, h].double().cpu(), lse[h, a + first:b].double().cpu()
+                assert torch.isfinite(got).all() and torch.isfinite(got_lse).all()
+                err = (got - ref).abs()
+                # rows of one or two keys return values up to 4.5, rounded to bf16 (2^-9) after P's rounding
+                assert float((err - 2.0 ** -7 * ref.abs()).max()) <= FWD_TOL
+                assert float((got_lse - ref_lse).abs().max()) <= LSE_TOL_FEW_KEYS
 
 
 @pytest.mark.timeout(300)
