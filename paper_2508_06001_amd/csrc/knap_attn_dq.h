@@ -237,6 +237,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
 
   // Narrow items: 64 queries, as in the forward kernel.  Waves w and w + 2 share 32 queries, one taking the first 32
   // keys of every tile, the other the second 32; the two gradients are added through LDS at the end.
+  if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
   const int rb = wave & 1;
   const int kh_u = __builtin_amdgcn_readfirstlane(wave >> 1), rb_u = __builtin_amdgcn_readfirstlane(rb);
   for (int part = ticket - queue.wide; part < queue.parts;) {

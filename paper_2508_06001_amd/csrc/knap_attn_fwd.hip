@@ -314,6 +314,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   // its SIMD waits out its own latencies), so where the items are few each is cut in two that run side by side.
   // Waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the second 32; the two
   // halves of the softmax are merged through LDS at the end.
+  if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
   const int rb = wave & 1, kh = wave >> 1;
   const int kh_u = __builtin_amdgcn_readfirstlane(kh), rb_u = __builtin_amdgcn_readfirstlane(rb);
   for (int part = ticket - queue.wide; part >= 0 && part < queue.parts;) {

@@ -502,6 +502,18 @@ def test_four_pair_dkdv_kernel_on_ragged_long_sequences(d, causal):
     _full_compare(bag, heads=[1], strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
+@pytest.mark.parametrize("causal,d,H", [(False, 128, 31), (False, 64, 31), (False, 64, 46),
+                                        (True, 128, 58), (True, 64, 58), (True, 64, 86)])
+def test_thin_last_round_of_long_items(causal, d, H):
+    """Work items a few more than the workgroups (512 on 256 CUs, 768 of the forward at d = 64): whole rounds of
+    128-query items, then a last round that the forward (d = 128, and H of 46 and 86 at d = 64) and the dQ kernel (H of
+    31 and 58) deal out in 64-query parts.  The last heads own those parts: 33 rows in the ragged query tile, 33 keys in
+    the ragged key tile, a part that has no row; under the mask 17 tiles, i.e. a pair without a partner."""
+    bag = BagSpec("thin_round", [2081], H=H, d=d, seed=7300 + H)
+    _full_compare(bag, heads=[0, H - 2, H - 1], strict_fwd=not causal, causal=causal,
+                  lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
 @pytest.mark.parametrize("masked_keys", [32, 64, 96])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
