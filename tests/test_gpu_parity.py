@@ -552,6 +552,23 @@ def test_leading_keys_with_scores_of_minus_infinity(d, causal, masked_keys):
                 assert float((got_lse - ref_lse).abs().max()) <= LSE_TOL_FEW_KEYS
 
 
+@pytest.mark.parametrize("lens,H", [([300], 3), ([2100, 300], 3), ([16 * 128, 9 * 128 + 1], 6), ([4000, 37], 8)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_backward_whatever_the_workspace_holds(causal, lens, H):
+    """Bags on both sides of the line where the kernels draw work items and their counters are cleared first: the
+    gradients do not depend on what the workspace held."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    run = GpuRun(BagSpec("workspace", lens, H=H, d=128, seed=8300 + H), causal=causal)
+    a = run.attn
+    for byte in (0, 1, 0xff):
+        a.workspace.fill_(byte)
+        a.backward(run.dev["q"], run.dev["k"], run.dev["v"], run.dev["dout"])
+        torch.cuda.synchronize()
+        for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+            assert np.array_equal(bf16_device_to_bits(got), want)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
