@@ -315,8 +315,7 @@ int knap_ulysses_plan(const int32_t* cu_seqlens, int n_seq, int64_t total_tokens
       !aligned(workspace, 4))
     return KNAP_ERR_INVALID_ARG;
   if (workspace_bytes < knap_ulysses_plan_workspace_bytes(n_seq, g)) return KNAP_ERR_WORKSPACE_TOO_SMALL;
-  const hipError_t e = knap::launch_ulysses_plan(cu_seqlens, n_seq, g, (int)total_tokens,
-                                                 static_cast<int32_t*>(workspace), row_map,
+  const hipError_t e = knap::launch_ulysses_plan(cu_seqlens, n_seq, g, (int)total_tokens, row_map,
                                                  static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;

@@ -9,6 +9,7 @@
 // are bound by HBM bandwidth.  The row permutation of the second step depends only on the bag's sequence
 // lengths and is built once per bag (ulysses plan) for q, k, v, the output and every layer.
 #include "knap_kernels.h"
+#include "knapattn.h"
 
 #include <stdint.h>
 
@@ -83,50 +84,91 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_rows_kernel(
   }
 }
 
-// chunk r of a sequence of L tokens cut into g chunks, the first L mod g one token longer
-__device__ __forceinline__ int chunk_len(int L, int g, int r) { return L / g + (r < L % g ? 1 : 0); }
-
-// table[s g + r]       rows of slab r that belong to sequences before s      (s = 0 .. n_seq - 1)
-// table[n_seq g + r]   first row of slab r in the receive buffer (slabs in GPU order)
-// One workgroup; thread r walks the sequences for GPU r.  cu_seqlens is staged in LDS first.
-__global__ __launch_bounds__(kCopyThreads) void ulysses_offsets_kernel(
-    const int32_t* __restrict__ cu, int n_seq, int g, int32_t* __restrict__ table) {
-  extern __shared__ int32_t s_cu[];          // n_seq + 1 lengths boundaries, then g slab sizes
-  int32_t* s_rows = s_cu + n_seq + 1;
-  for (int i = threadIdx.x; i <= n_seq; i += kCopyThreads) s_cu[i] = cu[i];
-  __syncthreads();
-  const int r = threadIdx.x;
-  if (r < g) {
-    int run = 0;
-    for (int s = 0; s < n_seq; ++s) {
-      table[s * g + r] = run;
-      run += chunk_len(s_cu[s + 1] - s_cu[s], g, r);
-    }
-    s_rows[r] = run;
-  }
-  __syncthreads();
-  if (r < g) {
-    int start = 0;
-    for (int q = 0; q < r; ++q) start += s_rows[q];
-    table[n_seq * g + r] = start;
-  }
-}
-
-// row_map[t] for every row t of the (full sequences) layout
+// row_map[t] for every row t of the (full sequences) layout.  A sequence of L tokens is cut into g chunks of
+// base = L / g tokens, the first rem = L mod g one token longer; row t is token j of chunk r of sequence s and lies at
+//   (first row of slab r) + (rows of slab r before sequence s) + j.
+// Both follow from the sequences' bases and from how many have rem > r, so every workgroup (256 rows) forms them for
+// itself in LDS: a scan of the bases, and counts of the remainders over the whole bag and over the sequences before
+// the workgroup's first one; the few sequences between that one and s are counted row by row.
+// What bounds it is latency, a chain of LDS steps.  A table of the offsets built by a one-workgroup kernel in front of
+// this one cost a second launch and a serial walk over the sequences: a new two-GPU bag of 5 sequences and 11335 tokens
+// and its 8 copies of 24 x 128 rows 117.1 -> 115.9 us.
 __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
-    const int32_t* __restrict__ cu, int n_seq, int g, const int32_t* __restrict__ table, int T,
-    int32_t* __restrict__ row_map) {
-  const int t = blockIdx.x * kCopyThreads + threadIdx.x;
-  if (t >= T) return;
+    const int32_t* __restrict__ cu, int n_seq, int g, int T, int32_t* __restrict__ row_map) {
+  extern __shared__ int32_t s_cu[];                 // n_seq + 1 boundaries
+  int32_t* s_base = s_cu + n_seq + 1;               // sum of the bases of the sequences before s
+  int32_t* s_rem = s_base + n_seq;
+  __shared__ int32_t s_all[KNAP_ULYSSES_MAX_GPUS];      // sequences with each remainder
+  __shared__ int32_t s_before[KNAP_ULYSSES_MAX_GPUS];   // those before the workgroup's first sequence
+  __shared__ int32_t s_longer[KNAP_ULYSSES_MAX_GPUS];   // sequences whose chunk r is one token longer
+  __shared__ int32_t s_first[KNAP_ULYSSES_MAX_GPUS];    // slab r's first row, plus its longer chunks before that sequence
+  __shared__ int32_t s_wave[kCopyThreads / 64];
+  const int tid = threadIdx.x;
+  for (int i = tid; i <= n_seq; i += kCopyThreads) s_cu[i] = cu[i];
+  if (tid < KNAP_ULYSSES_MAX_GPUS) s_all[tid] = s_before[tid] = 0;
+  __syncthreads();
+
   // the sequence of row t: largest s with cu[s] <= t among the sequences that have rows
-  int lo = 0, hi = n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (cu[mid] <= t) lo = mid; else hi = mid - 1;
+  auto sequence_of = [&](int t) {
+    int lo = 0, hi = n_seq - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (s_cu[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+  };
+  const int s0 = sequence_of(blockIdx.x * kCopyThreads);
+  const int per = (n_seq + kCopyThreads - 1) / kCopyThreads;
+  const int lo = min(tid * per, n_seq), hi = min(lo + per, n_seq);
+  int local = 0;
+  for (int s = lo; s < hi; ++s) {
+    const int L = max(s_cu[s + 1] - s_cu[s], 0);
+    const int base = L / g, rem = L - base * g;
+    s_base[s] = local;
+    s_rem[s] = rem;
+    local += base;
+    if (rem > 0) {
+      atomicAdd(&s_all[rem], 1);
+      if (s < s0) atomicAdd(&s_before[rem], 1);
+    }
   }
-  const int s = lo;
-  const int L = cu[s + 1] - cu[s];
-  const int i = t - cu[s];
+  int sum = local;                                  // inclusive over the wave
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(sum, o);
+    if ((tid & 63) >= o) sum += x;
+  }
+  if ((tid & 63) == 63) s_wave[tid >> 6] = sum;
+  __syncthreads();
+  int before = sum - local, total = 0;
+#pragma unroll
+  for (int w = 0; w < kCopyThreads / 64; ++w) {
+    if (w < tid >> 6) before += s_wave[w];
+    total += s_wave[w];
+  }
+  for (int s = lo; s < hi; ++s) s_base[s] += before;
+  int longer_before = 0;
+  if (tid < g) {
+    int longer = 0;
+    for (int m = tid + 1; m < g; ++m) {
+      longer += s_all[m];
+      longer_before += s_before[m];
+    }
+    s_longer[tid] = longer;
+  }
+  __syncthreads();
+  if (tid < g) {
+    int start = tid * total;
+    for (int r = 0; r < tid; ++r) start += s_longer[r];
+    s_first[tid] = start + longer_before;
+  }
+  __syncthreads();
+
+  const int t = blockIdx.x * kCopyThreads + tid;
+  if (t >= T) return;
+  const int s = sequence_of(t);
+  const int L = s_cu[s + 1] - s_cu[s];
+  const int i = t - s_cu[s];
   const int base = L / g, rem = L % g;
   // chunks 0 .. rem - 1 hold base + 1 tokens, the others base
   int r, j;
@@ -138,9 +180,11 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
     r = rem + k / base;               // base > 0 here: i < L and the longer chunks are used up
     j = k - (r - rem) * base;
   }
-  // rows past cu[n_seq] (a total_tokens larger than the lengths add up to) must not index outside the table
+  // rows past cu[n_seq] (a total_tokens larger than the lengths add up to) must not index outside the tables
   r = min(max(r, 0), g - 1);
-  row_map[t] = table[n_seq * g + r] + table[s * g + r] + j;
+  int row = s_first[r] + s_base[s] + j;
+  for (int q = s0; q < s; ++q) row += s_rem[q] > r ? 1 : 0;
+  row_map[t] = row;
 }
 
 int copy_grid(uint64_t units, int cus) {
@@ -176,15 +220,10 @@ hipError_t launch_ulysses_rows(const void* src, void* dst, const int32_t* row_ma
   return hipGetLastError();
 }
 
-hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32_t* table, int32_t* row_map,
-                               hipStream_t stream) {
-  const size_t dyn = (size_t)(n_seq + 1 + g) * sizeof(int32_t);
-  hipLaunchKernelGGL(ulysses_offsets_kernel, dim3(1), dim3(kCopyThreads), dyn, stream, cu, n_seq, g, table);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int grid = (T + kCopyThreads - 1) / kCopyThreads;
-  hipLaunchKernelGGL(ulysses_row_map_kernel, dim3(grid), dim3(kCopyThreads), 0, stream,
-                     cu, n_seq, g, (const int32_t*)table, T, row_map);
+hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32_t* row_map, hipStream_t stream) {
+  const size_t dyn = (size_t)(3 * n_seq + 1) * sizeof(int32_t);
+  hipLaunchKernelGGL(ulysses_row_map_kernel, dim3((T + kCopyThreads - 1) / kCopyThreads), dim3(kCopyThreads), dyn, stream,
+                     cu, n_seq, g, T, row_map);
   return hipGetLastError();
 }
 

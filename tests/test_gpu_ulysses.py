@@ -93,6 +93,19 @@ def test_single_sequence_and_many_sequences():
     _switch_and_back([int(v) for v in rng.integers(0, 60, size=2048)], 4, 4, 64, seed=73)   # KNAP_MAX_SEQS sequences
 
 
+@pytest.mark.parametrize("g", [1, 2, 7, 64])
+@pytest.mark.parametrize("n_seq,longest", [(1, 256), (1, 257), (63, 700), (257, 3), (2047, 9), (2048, 300)])
+def test_plan_row_map(n_seq, longest, g):
+    """The row map alone: one row past a workgroup's 256, workgroups that start inside a sequence and ones that hold
+    hundreds of sequences (most of them shorter than g, many empty), one sequence and KNAP_MAX_SEQS of them."""
+    import paper_2508_06001_amd as K
+    rng = np.random.default_rng(740 + n_seq + g)
+    seq_lens = [longest] if n_seq == 1 else [int(v) for v in rng.integers(0, longest + 1, size=n_seq)]
+    say(f"[gpu] ulysses plan: n_seq={n_seq} T={sum(seq_lens)} g={g}")
+    got = _plan(K, seq_lens, g).cpu().numpy()[:sum(seq_lens)]
+    assert np.array_equal(got, U.row_map(seq_lens, g))
+
+
 @pytest.mark.timeout(300)
 def test_post_ulysses_share_at_full_size():
     """The 8-GPU bag behind benchmark config 4 (24 heads -> 3 per GPU, 196608 tokens): one rank's pack and
