@@ -123,10 +123,14 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
 //    3057 us).  The causal kernel at d = 64 has little of either to hide and is up to 8 % slower.  The average does not
 //    show one long sequence among many short ones, where two pairs lose (16309 tokens and 54 short, 6 x 128: 1793 against
 //    1692 us), hence the bounds on the whole bag.
+//    Without the mask at d = 128 the line is at an average of 512: above it two pairs win where they pad less and lose
+//    where the lengths are multiples of 256 or one sequence stands out (forward and backward, two against four: 15 of 640
+//    tokens, 24 x 128: 471 against 506 us; but 10 of 1024: 669 against 652; 8 of 1200: 742 against 721; 4405, 619 and 371:
+//    1135 against 1107; 4200 and seven of 300..600, 12 x 128: 611 against 582; 18 of 512: 208 both).
 //  * Otherwise four (65536 and 200 short, 24 x 128: 80.3 against 82.4 ms; 30000 tokens, 3 x 128: 2.90 against 3.13 ms).
 int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
   if (total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
-  const int64_t longest_average = d == 128 && !causal ? 2048 : 4096;
+  const int64_t longest_average = d == 128 && !causal ? 512 : 4096;
   const int64_t largest_bag = d == 64 ? (causal ? 0 : 32768) : (causal ? 65536 : 16384);
   if (total_tokens <= largest_bag && total_tokens < longest_average * n_seq) return 2;
   return 4;
