@@ -552,6 +552,35 @@ def test_leading_keys_with_scores_of_minus_infinity(d, causal, masked_keys):
                 assert float((got_lse - ref_lse).abs().max()) <= LSE_TOL_FEW_KEYS
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_largest_probability_of_the_first_tile_carries_no_rounding_error(d, causal):
+    """The exponent reference of a row comes from the whole first tile (64 keys), so in a sequence of up to 64 keys the
+    largest probability is exactly 1.  lse is then off by at most 2^-8 (the unit roundoff of bf16) of the weight of
+    all the OTHER keys, plus fp32 arithmetic (scores of up to 60 in 128 fp32 products: under 1e-4).  Sequences of 33 to
+    64 tokens, three times the usual q so that one key often dominates; many items and few (whole ones and parts)."""
+    import torch
+    import paper_2508_06001_amd as K
+    for n, H in ((64, 10), (6, 2)):
+        lens = [33 + (7 * i) % 32 for i in range(n)]
+        cu = np.concatenate([[0], np.cumsum(lens)])
+        g = torch.Generator(device="cuda")
+        g.manual_seed(8500 + d + n)
+        q, k, v = (torch.randn((int(cu[-1]), H, d), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+        q *= 3
+        out, lse = K.VarlenAttention([int(c) for c in cu], H, d, d ** -0.5, causal=causal).forward(q, k, v)
+        for s in range(n):
+            a, b = int(cu[s]), int(cu[s + 1])
+            for h in range(H):
+                S = q[a:b, h].double().cpu() @ k[a:b, h].double().cpu().T * d ** -0.5
+                if causal:
+                    S = S.masked_fill(torch.ones_like(S).triu(1).bool(), float("-inf"))
+                ref = torch.logsumexp(S, dim=1)
+                others = 1 - torch.exp(S.max(dim=1).values - ref)
+                err = (lse[h, a:b].double().cpu() - ref).abs()
+                assert float((err - 2.0 ** -8 * others).max()) <= 1e-4, (n, s, h)
+
+
 @pytest.mark.parametrize("lens,H", [([300], 3), ([2100, 300], 3), ([16 * 128, 9 * 128 + 1], 6), ([4000, 37], 8)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_backward_whatever_the_workspace_holds(causal, lens, H):
