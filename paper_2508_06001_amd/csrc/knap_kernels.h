@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "knap_dispatch.h"
+
 namespace knap {
 
 hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq,
@@ -25,10 +27,8 @@ struct BwdArgs {
   float *delta, *lse2;      // (H, T) each, handed from the dQ kernel to the dK/dV kernel
   unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel
 };
-// The dK/dV kernel takes `dkdv_pairs` wave pairs (2 or 4) per workgroup and dkdv_workgroups_per_cu(pairs) workgroups
-// on each CU (two waves per SIMD is what its registers allow).  `draws`: some queue may hold more items than workgroups,
-// so that the counters have to be zero.
-constexpr int dkdv_workgroups_per_cu(int pairs) { return 4 / pairs; }
+// `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `draws`: some queue may hold more items than
+// workgroups, so that the counters have to be zero.
 hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int grid_dq, bool draws,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_dq_causal(const BwdArgs& a, int d, int grid, hipStream_t stream);

@@ -1,0 +1,99 @@
+// Work queues of the persistent attention kernels: which workgroup takes which item of the descending-cost item list.
+// Integer arithmetic on the schedule alone, so that the host can walk through it as well (tests/queue_model.cpp).
+#pragma once
+
+namespace knap {
+
+// Items of a sequence and head: its tiles, or pairs of them (causal attention).
+template <bool PAIRED>
+__device__ __forceinline__ int items_per_head(int tiles) { return PAIRED ? (tiles + 1) >> 1 : tiles; }
+
+// Items of the sequences at least half as long as the longest one, or `enough` if there are that many:
+// the band of dear items that has to be spread over the whole GPU.  Items per sequence fall along the order.
+__device__ __forceinline__ int dear_items(const int* s_start, int n_seq, int enough) {
+  const int top = s_start[1];
+  if (top >= enough) return enough;
+  int lo = 0, hi = n_seq - 1;     // largest rank with at least half the items of rank 0
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (2 * (s_start[mid + 1] - s_start[mid]) >= top) lo = mid; else hi = mid - 1;
+  }
+  return min(enough, s_start[lo + 1]);
+}
+
+// Whether item w belongs to a sequence with at least three quarters of the longest one's items.
+__device__ __forceinline__ bool long_tail(const int* s_start, int n_seq, int w) {
+  int lo = 0, hi = n_seq - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (s_start[mid] <= w) lo = mid; else hi = mid - 1;
+  }
+  return 4 * (s_start[lo + 1] - s_start[lo]) >= 3 * s_start[1];
+}
+
+// Dynamic assignment for kernels that are handed zeroed counters (one unsigned per XCD, 8 in
+// all): the descending-cost item list is cut into chunks of consecutive items, every XCD takes one
+// chunk of each round of 8 (so that the workgroups of an XCD keep meeting on the same K and V in its
+// L2), and the workgroups of an XCD draw that XCD's items in order from its counter: list
+// scheduling, longest first, within the XCD.  The first ticket past the queue's items ends the workgroup.
+//
+// Chunks are G / 8 items (smaller ones cost long sequences up to 7 %: fewer workgroups meet in an L2),
+// except where the dear items are fewer than G: those are then dealt evenly, an eighth to every XCD,
+// instead of filling the first XCDs and leaving the others idle (eight sequences of up to 2101 tokens, two
+// heads of 64: forward 54 -> 41 us, dQ 64 -> 45 us).  Rounds run through the XCDs alternately
+// upwards and downwards: an item costs at most what the one before it costs, and always upwards the first
+// XCD would get the dearest chunk of every round (17 sequences of 328..4533 tokens, 24 heads of 128: forward
+// 1104 -> 1087 us, dQ 1511 -> 1482 us).
+//
+// SPLIT > 0: where the last, partly filled round is at most a 1 / SPLIT full and of long items, its items are dealt
+// out in SPLIT parts each (the kernels' narrow items), so that the round takes the GPU and not one workgroup in
+// SPLIT: tickets from `wide` on stand for parts.  A bag of so few items has no full round at all.  (Short items fill
+// the gaps that long ones leave, and cutting them up only adds work: 6293 tokens in 4 sequences of up to 4385,
+// 24 x 128, forward 283 -> 294 us.)
+template <int SPLIT>
+struct ItemQueue {
+  unsigned* ctr;
+  int q, n_q, per, chunk;
+  int n_wide, wide;         // items dealt out whole, and how many of them this queue has
+  int part0, parts;         // this queue's share of the parts
+  bool draws;               // more tickets than workgroups: somebody has to draw
+  __device__ __forceinline__ void init(unsigned* counters, const int* s_start, int n_seq, int n_items) {
+    const int G = (int)gridDim.x;
+    n_q = (G % 8 == 0) ? 8 : 1;
+    q = (int)(blockIdx.x % n_q);                  // workgroups go to the XCDs round-robin
+    per = G / n_q;
+    const int dear = dear_items(s_start, n_seq, G);
+    chunk = __builtin_amdgcn_readfirstlane(max(1, (dear + n_q - 1) / n_q));
+    ctr = counters + q;
+    n_wide = n_items;
+    part0 = parts = 0;
+    if constexpr (SPLIT > 0) {
+      const int last = n_items % G;
+      if (last * SPLIT <= G && (n_items == last || (chunk == per && long_tail(s_start, n_seq, n_items - last)))) {
+        n_wide = n_items - last;
+        const int share = (last * SPLIT + n_q - 1) / n_q;
+        part0 = q * share;
+        parts = max(0, min(share, last * SPLIT - part0));
+      }
+      n_wide = __builtin_amdgcn_readfirstlane(n_wide);
+      part0 = __builtin_amdgcn_readfirstlane(part0);
+      parts = __builtin_amdgcn_readfirstlane(parts);
+    }
+    // items before n_wide: whole rounds, and the part of this queue's chunk that the last round holds
+    const int round = n_wide / (n_q * chunk);
+    const int in_last = n_wide - (round * n_q + chunk_of(round)) * chunk;
+    wide = __builtin_amdgcn_readfirstlane(round * chunk + max(0, min(chunk, in_last)));
+    draws = wide + parts > per;
+  }
+  // a workgroup's first item needs no draw: the first G / n_q tickets go to the queue's workgroups in order,
+  // and the counter deals out the ones after them
+  __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
+  __device__ __forceinline__ int later_ticket(unsigned drawn) const { return per + (int)drawn; }
+  __device__ __forceinline__ int chunk_of(int round) const { return (round & 1) ? n_q - 1 - q : q; }
+  __device__ __forceinline__ int item(int ticket) const {     // ticket < wide
+    const int round = ticket / chunk;
+    return (round * n_q + chunk_of(round)) * chunk + ticket % chunk;
+  }
+};
+
+}  // namespace knap

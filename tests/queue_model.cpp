@@ -1,0 +1,94 @@
+// The device's work queues (csrc/knap_queue.h) and the host's rules about them (csrc/knap_dispatch.h) compiled for the
+// CPU: the same text, with the few device words it uses defined here.
+#include <algorithm>
+#include <vector>
+
+#define __device__
+#define __forceinline__ inline
+#define __builtin_amdgcn_readfirstlane(x) (x)
+using std::max;
+using std::min;
+static struct { int x; } gridDim, blockIdx;
+
+#include "knap_dispatch.h"
+#include "knap_queue.h"
+
+namespace {
+
+struct Walk {
+  int items, parts, per, most, draws, wrong;
+};
+
+template <int SPLIT>
+Walk walk(int grid, const std::vector<int>& start, int n_seq, int n_items) {
+  Walk r = {n_items, 0, 0, 0, 0, 0};
+  std::vector<int> whole(n_items, 0), part((size_t)n_items * max(SPLIT, 1), 0);
+  std::vector<unsigned> counters(8, 0);
+  gridDim.x = grid;
+  const int n_q = grid % 8 == 0 ? 8 : 1;
+  int n_wide = -1;
+  for (int q = 0; q < n_q; ++q) {
+    blockIdx.x = q;
+    knap::ItemQueue<SPLIT> queue;
+    queue.init(counters.data(), start.data(), n_seq, n_items);
+    if (q == 0) n_wide = queue.n_wide;
+    r.wrong += queue.n_wide != n_wide || queue.ctr != counters.data() + q;
+    const int tickets = queue.wide + queue.parts;
+    // the tickets 0 .. per - 1 come from the workgroups' indexes, `per` and up from the counter, which starts at zero
+    for (int i = 0; i < queue.per; ++i) {
+      blockIdx.x = q + i * n_q;
+      r.wrong += queue.first_ticket() != i;
+    }
+    r.wrong += queue.later_ticket(0u) != queue.per || queue.later_ticket(3u) != queue.per + 3;
+    r.wrong += !queue.draws && tickets > queue.per;
+    for (int t = 0; t < queue.wide; ++t) {
+      const int w = queue.item(t);
+      if (w < 0 || w >= n_wide) ++r.wrong; else ++whole[w];
+    }
+    for (int p = 0; p < queue.parts; ++p) {
+      const int at = n_wide * SPLIT + queue.part0 + p;
+      if (at < 0 || at >= n_items * SPLIT) ++r.wrong; else ++part[at];
+    }
+    r.per = queue.per;
+    r.most = max(r.most, tickets);
+    r.draws |= queue.draws;
+    r.parts += queue.parts;
+  }
+  for (int w = 0; w < n_items; ++w) {
+    r.wrong += whole[w] != (w < n_wide ? 1 : 0);
+    for (int i = 0; i < SPLIT; ++i) r.wrong += part[(size_t)w * SPLIT + i] != (w < n_wide ? 0 : 1);
+  }
+  return r;
+}
+
+}  // namespace
+
+extern "C" {
+
+// lens: the sequences' lengths.  out: items, parts dealt, workgroups per queue, most tickets of a queue, whether some queue
+// draws, and how many items or parts were not dealt exactly once (or tickets not served).
+void queue_walk(const int* lens, int n_seq, int H, int tile, int causal, int split, int grid, int* out) {
+  std::vector<int> sorted(lens, lens + n_seq);
+  std::sort(sorted.begin(), sorted.end(), [](int a, int b) { return a > b; });
+  std::vector<int> start(n_seq + 1, 0);
+  for (int r = 0; r < n_seq; ++r) {
+    const int tiles = (sorted[r] + tile - 1) / tile;
+    start[r + 1] = start[r] + H * (causal ? knap::items_per_head<true>(tiles) : knap::items_per_head<false>(tiles));
+  }
+  const int n = start[n_seq];
+  const Walk w = split == 0 ? walk<0>(grid, start, n_seq, n) : split == 2 ? walk<2>(grid, start, n_seq, n) : walk<4>(grid, start, n_seq, n);
+  const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
+  std::copy(values, values + 6, out);
+}
+
+int queue_dkdv_pairs(long long tokens, int n_seq, int H, int d, int causal, int cus) {
+  return knap::dkdv_pairs(tokens, n_seq, H, d, causal != 0, cus);
+}
+
+int queue_dkdv_workgroups_per_cu(int pairs) { return knap::dkdv_workgroups_per_cu(pairs); }
+
+int queue_bwd_draws(long long tokens, int n_seq, int H, int causal, int pairs, int cus, int grid_dq) {
+  return knap::bwd_draws(tokens, n_seq, H, causal != 0, pairs, cus, grid_dq);
+}
+
+}  // extern "C"

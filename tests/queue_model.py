@@ -1,0 +1,75 @@
+"""The work queues of the attention kernels on the CPU: tests/queue_model.cpp, which compiles the kernels' own queue header
+and the host's own rules with g++, behind a few functions.  Tests use it to show that their bags reach the branch they are
+about."""
+from __future__ import annotations
+
+import atexit
+import ctypes as C
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+from typing import NamedTuple, Sequence
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CUS = 256                                  # compute units of an MI355X
+WORKGROUPS_PER_CU = {"fwd": {64: 3, 128: 2}, "dq": {64: 2, 128: 2}}     # what the kernels' registers allow
+
+
+class Walk(NamedTuple):
+    items: int       # work items
+    parts: int       # parts that items were dealt out in
+    per: int         # workgroups of a queue
+    most: int        # most tickets of a queue
+    draws: bool      # some queue has more tickets than workgroups
+    wrong: int       # items or parts that were not dealt exactly once
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    out = tempfile.mkdtemp(prefix="knap_queue_model_")
+    atexit.register(shutil.rmtree, out, ignore_errors=True)
+    so = os.path.join(out, "queue_model.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wall", "-Wno-unknown-pragmas",
+                    "-I" + os.path.join(ROOT, "paper_2508_06001_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "queue_model.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    lib.queue_walk.restype = None
+    lib.queue_walk.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 6 + [C.POINTER(C.c_int)]
+    lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
+    lib.queue_bwd_draws.argtypes = [C.c_longlong] + [C.c_int] * 6
+    return lib
+
+
+def dkdv_pairs(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> int:
+    return _lib().queue_dkdv_pairs(sum(lens), len(lens), H, d, int(causal), cus)
+
+
+def grid(kernel: str, d: int, pairs: int = 0, cus: int = CUS) -> int:
+    if kernel == "dkdv":
+        return cus * _lib().queue_dkdv_workgroups_per_cu(pairs)
+    return cus * WORKGROUPS_PER_CU[kernel][d]
+
+
+def bwd_draws(lens: Sequence[int], H: int, d: int, causal: bool, pairs: int = 0, cus: int = CUS) -> bool:
+    """Whether the host clears the backward's counters."""
+    pairs = pairs or dkdv_pairs(lens, H, d, causal, cus)
+    return bool(_lib().queue_bwd_draws(sum(lens), len(lens), H, int(causal), pairs, cus, grid("dq", d, cus=cus)))
+
+
+def walk(kernel: str, lens: Sequence[int], H: int, d: int, causal: bool, pairs: int = 0, cus: int = CUS) -> Walk:
+    """The queues of `kernel` ("fwd", "dq" or "dkdv") for a bag."""
+    pairs = pairs or dkdv_pairs(lens, H, d, causal, cus)
+    tile, split = (64 * pairs, 0) if kernel == "dkdv" else (128, 4 if causal else 2)
+    out = (C.c_int * 6)()
+    _lib().queue_walk((C.c_int * len(lens))(*lens), len(lens), H, tile, int(causal), split,
+                      grid(kernel, d, pairs, cus), out)
+    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
+
+
+def assert_draws(lens: Sequence[int], H: int, d: int, causal: bool, kernels=("fwd", "dq", "dkdv")) -> None:
+    """The bag has more items than workgroups in some queue of each of these kernels."""
+    for kernel in kernels:
+        w = walk(kernel, lens, H, d, causal)
+        assert w.draws and w.most > w.per, (kernel, w)
