@@ -22,6 +22,7 @@ import pytest
 from knap_inputs import BagSpec, config_bag, cu_seqlens_of, make_qkv_dout
 from oracle import attention as A
 
+import queue_model as Q
 from gpu_util import GpuRun, rel_fro, say, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -581,21 +582,56 @@ def test_largest_probability_of_the_first_tile_carries_no_rounding_error(d, caus
                 assert float((err - 2.0 ** -8 * others).max()) <= 1e-4, (n, s, h)
 
 
-@pytest.mark.parametrize("lens,H", [([300], 3), ([2100, 300], 3), ([16 * 128, 9 * 128 + 1], 6), ([4000, 37], 8)])
-@pytest.mark.parametrize("causal", [False, True])
-def test_backward_whatever_the_workspace_holds(causal, lens, H):
-    """Bags on both sides of the line where the kernels draw work items and their counters are cleared first: the
-    gradients do not depend on what the workspace held."""
+_LOW_RES = [256 + (151 * i) % 393 for i in range(32)]      # 256 to 648 tokens
+
+
+@pytest.mark.parametrize("causal,lens,H,pairs", [
+    # nothing is drawn, and nothing cleared but for the larger ones
+    (False, [300], 3, 2), (True, [300], 3, 2), (False, [2100, 300], 3, 2), (True, [2100, 300], 3, 2),
+    (False, [16 * 128, 9 * 128 + 1], 6, 2), (True, [16 * 128, 9 * 128 + 1], 6, 2), (False, [4000, 37], 8, 2), (True, [4000, 37], 8, 2),
+    # both kernels draw: barely (17 tiles for 31 heads: 15 items more than the 512 workgroups), and many times over
+    (False, [2081], 31, 4), (False, _LOW_RES, 24, 2), (False, [4096, 2100, 300], 24, 4),
+    (True, _LOW_RES, 24, 2), (True, [8200, 300], 24, 4)])
+def test_backward_whatever_the_workspace_holds(causal, lens, H, pairs):
+    """Bags on both sides of the line where the kernels draw work items and their counters are cleared first, with two and
+    with four wave pairs per workgroup of the dK/dV kernel: the gradients do not depend on what the workspace held."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    assert Q.dkdv_pairs(lens, H, 128, causal) == pairs
+    draws = [Q.walk(kernel, lens, H, 128, causal).draws for kernel in ("dq", "dkdv")]
+    assert draws == [H > 8, H > 8]
     run = GpuRun(BagSpec("workspace", lens, H=H, d=128, seed=8300 + H), causal=causal)
     a = run.attn
     for byte in (0, 1, 0xff):
         a.workspace.fill_(byte)
+        for t in (a.dq, a.dk, a.dv):
+            t.fill_(float("nan"))                              # an item that nobody takes shows
         a.backward(run.dev["q"], run.dev["k"], run.dev["v"], run.dev["dout"])
         torch.cuda.synchronize()
         for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
             assert np.array_equal(bf16_device_to_bits(got), want)
+
+
+def test_two_pair_dkdv_kernel_over_several_items_per_workgroup():
+    """Many short sequences at d = 128 without the mask: 3 to 4 items for each of the 512 workgroups of the dK/dV kernel's
+    two-pair form, so that tickets are handed over, the ring and the P buffers change items, and the workgroups of the
+    upper half of the grid (whose waves have the roles the other way round) do so too.  First and last heads against the
+    oracle, everything bitwise repeatable."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    H = 24
+    assert Q.dkdv_pairs(_LOW_RES, H, 128, False) == 2
+    w = Q.walk("dkdv", _LOW_RES, H, 128, False)
+    assert w.items > 3 * 512 and w.draws
+    run = _full_compare(BagSpec("low_res", _LOW_RES, H=H, d=128, seed=8700), heads=[0, 1, H - 1])
+    a, d = run.attn, run.dev
+    for t in (a.out, a.dq, a.dk, a.dv):
+        t.fill_(float("nan"))
+    a.forward(d["q"], d["k"], d["v"])
+    a.backward(d["q"], d["k"], d["v"], d["dout"])
+    torch.cuda.synchronize()
+    for got, want in zip((a.out, a.dq, a.dk, a.dv), (run.out_bits, run.dq_bits, run.dk_bits, run.dv_bits)):
+        assert np.array_equal(bf16_device_to_bits(got), want)
 
 
 @pytest.mark.timeout(300)
