@@ -161,12 +161,15 @@ def test_repeatable_and_inputs_untouched():
 
 def test_two_streams_at_once_match_one_after_the_other():
     """Calls that overlap on two streams (each with its own outputs and workspace) do not disturb each
-    other: the work queues they draw from are per launch.  Bitwise equality with the sequential run."""
+    other: the work queues they draw from are per launch.  Both bags draw in all three kernels, the counters of a launch
+    are worth nothing to the other.  Bitwise equality with the sequential run."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     rng = np.random.default_rng(5)
-    bags = [BagSpec("stream_a", [int(x) for x in rng.integers(100, 3000, size=9)], H=4, d=128, seed=811),
-            BagSpec("stream_b", [int(x) for x in rng.integers(50, 1500, size=14)], H=6, d=64, seed=812)]
+    bags = [BagSpec("stream_a", [int(x) for x in rng.integers(100, 3000, size=9)], H=12, d=128, seed=811),
+            BagSpec("stream_b", [int(x) for x in rng.integers(50, 1500, size=14)], H=24, d=64, seed=812)]
+    for b in bags:
+        Q.assert_draws(b.seq_lens, b.H, b.d, False)
     runs = [GpuRun(b) for b in bags]                      # sequential reference (default stream)
     ref = [[r.out_bits.copy(), r.dq_bits.copy(), r.dk_bits.copy(), r.dv_bits.copy(), r.lse.copy()] for r in runs]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]  # default priority
@@ -192,13 +195,15 @@ def test_two_streams_at_once_match_one_after_the_other():
 def test_hip_graph_replays_match_eager():
     """Forward + backward captured into a HIP graph (nothing in the calls allocates, synchronises or
     records a memset): every replay, with eager launches and synchronisations in between, reproduces
-    the eager results bit for bit."""
+    the eager results bit for bit.  The captured calls and the eager ones in between draw in all three kernels."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     rng = np.random.default_rng(11)
-    bag = BagSpec("graph", [int(x) for x in rng.integers(64, 2500, size=11)], H=4, d=128, seed=913)
+    bag = BagSpec("graph", [int(x) for x in rng.integers(64, 2500, size=11)], H=12, d=128, seed=913)
     run = GpuRun(bag)                                      # eager reference; also warms up the library
-    other = GpuRun(BagSpec("graph_other", [700, 90, 1300], H=2, d=64, seed=914))
+    other = GpuRun(BagSpec("graph_other", [700, 90, 1300], H=48, d=64, seed=914))
+    for b in (bag, other.bag):
+        Q.assert_draws(b.seq_lens, b.H, b.d, False)
     want = [run.out_bits.copy(), run.dq_bits.copy(), run.dk_bits.copy(), run.dv_bits.copy(), run.lse.copy()]
     a, d = run.attn, run.dev
     side = torch.cuda.Stream()
