@@ -51,6 +51,13 @@ extern "C" {
  * stream) and the call returns at once.  Outputs are fully overwritten for
  * rows < T; inputs are never modified; outputs must not alias inputs.
  *
+ * Reproducibility.  The same calls on the same bag give the same bits every
+ * time.  Between bags a sequence's results (out, lse and the three gradients)
+ * may differ within their rounding errors: where a bag has few work items, or
+ * few in its last round, the kernels cut them in two, and such an item's sums run
+ * in another order and against another softmax reference.  It follows from
+ * the lengths and H alone, and may hold for some heads of a sequence only.
+ *
  * Supported: d in {64, 128}; 0 <= n_seq <= KNAP_MAX_SEQS; H >= 1; scale positive
  * and finite; T < 2^31.
  * n_seq == 0 succeeds and enqueues nothing.  With n_seq > 0 every pointer must be

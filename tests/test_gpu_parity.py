@@ -473,7 +473,8 @@ def test_causal_skewed_bag_sampled():
 
 def test_causal_repeatable_and_independent_of_other_sequences():
     """Bitwise repeatable (no floating-point atomics in the causal path either), and a sequence's
-    results do not change when the other sequences of the bag do."""
+    results do not change when the other sequences of the bag do, as long as its items are dealt out the same way
+    (here: both bags in parts; test_same_sequence_in_parts_and_in_whole_items has the other case)."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     bag = BagSpec("causal_rep", [333, 1290, 64, 700], H=3, d=128, seed=5656)
@@ -489,6 +490,10 @@ def test_causal_repeatable_and_independent_of_other_sequences():
     cu = [int(c) for c in run.cu]
     keep = slice(cu[1], cu[2])
     other = BagSpec("causal_rep2", [5, 1290, 2000], H=3, d=128, seed=5757)
+    for kernel in ("fwd", "dq"):
+        for b in (bag, other):
+            w = Q.walk(kernel, b.seq_lens, b.H, b.d, True)
+            assert w.parts == 4 * w.items
     t2 = make_qkv_dout(other)
     for n in ("q", "k", "v", "dout"):
         t2[n][5:5 + 1290] = run.bits[n][keep]
@@ -496,6 +501,37 @@ def test_causal_repeatable_and_independent_of_other_sequences():
     for a, b in ((run.out_bits, run2.out_bits), (run.dq_bits, run2.dq_bits), (run.dk_bits, run2.dk_bits),
                  (run.dv_bits, run2.dv_bits)):
         assert np.array_equal(a[keep], b[5:5 + 1290])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_same_sequence_in_parts_and_in_whole_items(d, causal):
+    """A sequence's items are whole in a large bag and cut in two in a small one, where the softmax reference and the order of
+    the sums over its keys are others: its results then agree to the precision of bf16 and no longer bit for bit.
+
+    Each side rounds its probabilities (and dS, for dq and dk) to bf16 and stores bf16: relative errors of at most 2^-9
+    each, so two sides are at most 4 (out, dv) or 6 (dq, dk) times 2^-9 apart in the 2-norm.  A sum of probabilities is off
+    by at most 2^-8 of itself (the unit roundoff) on either side, and lse by as much in absolute terms."""
+    small = BagSpec("in_parts", [333, 1290, 64, 700], H=3, d=d, seed=8800 + d)
+    large = BagSpec("whole_items", [1290] + [900] * 70, H=3, d=d, seed=8900 + d)
+    for kernel in ("fwd", "dq"):
+        w = Q.walk(kernel, small.seq_lens, small.H, d, causal)
+        assert w.parts == w.items * (4 if causal else 2)
+        assert Q.walk(kernel, large.seq_lens, large.H, d, causal).parts == 0
+    run = GpuRun(small, causal=causal)
+    at, there = slice(333, 333 + 1290), slice(0, 1290)
+    tensors = make_qkv_dout(large)
+    for n in ("q", "k", "v", "dout"):
+        tensors[n][there] = run.bits[n][at]
+    run2 = GpuRun(large, tensors=tensors, causal=causal)
+    apart = {}
+    for n, bits in (("out", 4), ("dv", 4), ("dq", 6), ("dk", 6)):
+        a, b = to_f64(getattr(run, n + "_bits")[at]), to_f64(getattr(run2, n + "_bits")[there])
+        apart[n] = rel_fro(a, b)
+        assert apart[n] <= bits * 2.0 ** -9, (n, apart)
+    apart["lse"] = float(np.abs(run.lse[:, at] - run2.lse[:, there]).max())
+    say(f"[parity] parts against whole items: {apart}")
+    assert apart["lse"] <= 2 * 2.0 ** -8
 
 
 @pytest.mark.parametrize("causal", [False, True])
