@@ -181,9 +181,10 @@ int knap_varlen_attn_causal_bwd(const void* q, const void* k, const void* v,
  *   scatter_chunks  the inverse (before the second all-to-all).
  * Both use row_map (int32[T], device): z[t] = recv[row_map[t]].  It depends
  * only on the bag's cu_seqlens and g; knap_ulysses_plan builds it on the device
- * (workspace: knap_ulysses_plan_workspace_bytes(n_seq, g) bytes of scratch, free
- * to reuse once the plan kernels have run) and it serves q, k, v, the attention
- * output and their gradients in every layer until the bag changes.
+ * and it serves q, k, v, the attention output and their gradients in every layer
+ * until the bag changes.  `workspace` (knap_ulysses_plan_workspace_bytes(n_seq,
+ * g) bytes) is kept for callers that have one: it is checked as before, and the
+ * plan neither reads nor writes it.
  * ------------------------------------------------------------------------ */
 #define KNAP_ULYSSES_MAX_GPUS 64
 

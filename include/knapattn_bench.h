@@ -19,7 +19,9 @@ extern "C" {
 void knap_bwd_profile_events(void* start, void* stop);
 
 /* Number of persistent workgroups the forward / backward kernels are launched
- * with on the current device (<= 0 on error). */
+ * with on the current device at d = 128 (<= 0 on error); for the dK/dV kernel
+ * those of its four-pair form (256 keys per workgroup; the two-pair form, 128
+ * keys, has twice as many). */
 int knap_launch_workgroups(int which /* 0 = forward, 1 = backward dK/dV, 2 = backward dQ */);
 
 #ifdef __cplusplus

@@ -44,11 +44,6 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
-__device__ __forceinline__ bf16x8 zero_bf16x8() {
-  u32x4 z = {0u, 0u, 0u, 0u};
-  return __builtin_bit_cast(bf16x8, z);
-}
-
 // 4 x 16 transposing LDS read (see the header comment).
 __device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
@@ -219,7 +214,6 @@ __device__ __forceinline__ void lds_barrier() {
 #define KNAP_SG_MFMA 0x008
 #define KNAP_SG_VMEM_READ 0x020
 #define KNAP_SG_DS_READ 0x100
-#define KNAP_SG_DS_WRITE 0x200
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

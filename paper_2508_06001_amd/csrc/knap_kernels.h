@@ -39,7 +39,6 @@ hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t
                                 int cus, hipStream_t stream);
 hipError_t launch_ulysses_rows(const void* src, void* dst, const int32_t* row_map, uint32_t T, uint32_t U,
                                bool gather, int cus, hipStream_t stream);
-// table: (n_seq + 1) g ints of scratch
 hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32_t* row_map, hipStream_t stream);
 
 // resident workgroups per compute unit of the persistent kernels
