@@ -21,8 +21,8 @@
 // stands, and the row sums that come out of it decide whether the reference has to move: only when a
 // lane's 16 probabilities sum to more than 2^8 (the first half always does: the reference starts at
 // -inf), in which case the maximum is taken (of the tile, or of the half if it is the tile's second), the accumulators
-// are rescaled and P is formed again.  So no
-// maximum is taken per tile (a third of the loop's simple vector instructions: 5.1 -> 3.4 per MFMA);
+// are rescaled and P is formed again.  So no maximum is taken per tile (a fifth of the loop's vector instructions: 4.2 -> 3.4
+// per MFMA);
 // P <= 256 all the same, and the final division by the row sum removes the reference exactly as in
 // the textbook recurrence.  The row sum is taken over the bf16-rounded P that the MFMA multiplies, so the
 // effective weights of a row sum to one exactly (a one-hot row returns its v bit for bit); the stored

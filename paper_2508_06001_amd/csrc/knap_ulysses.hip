@@ -91,8 +91,8 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_rows_kernel(
 // itself in LDS: a scan of the bases, and counts of the remainders over the whole bag and over the sequences before
 // the workgroup's first one; the few sequences between that one and s are counted row by row.
 // What bounds it is latency, a chain of LDS steps.  A table of the offsets built by a one-workgroup kernel in front of
-// this one cost a second launch and a serial walk over the sequences: a new two-GPU bag of 5 sequences and 11335 tokens
-// and its 8 copies of 24 x 128 rows 117.1 -> 115.9 us.
+// this one cost a second launch and a serial walk over the sequences.  Plan alone, before -> now: 5 sequences on 2 GPUs
+// 9.6 -> 6.9 us, 200 on 8 19.4 -> 6.6 us, 2000 on 4 150 -> 10.3 us.
 __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
     const int32_t* __restrict__ cu, int n_seq, int g, int T, int32_t* __restrict__ row_map) {
   extern __shared__ int32_t s_cu[];                 // n_seq + 1 boundaries
