@@ -35,7 +35,7 @@ __global__ void bwd_queue_reset_kernel(unsigned* __restrict__ counters) {
   if (threadIdx.x < kQueueCounters) counters[threadIdx.x] = 0u;
 }
 
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int grid_dq, bool draws,
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool draws,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipError_t e = hipSuccess;
   if (draws) {
@@ -43,7 +43,7 @@ hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int 
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // the dQ kernel also produces delta, which the dK/dV kernel needs: it goes first
-  e = causal ? launch_dq_causal(a, d, grid_dq, stream) : launch_dq_m<false>(a, d, grid_dq, stream);
+  e = causal ? launch_dq_causal(a, d, cus, dq_wg_per_cu, stream) : launch_dq_m<false>(a, d, cus, dq_wg_per_cu, stream);
   if (e != hipSuccess) return e;
   if (ev_start && ev_stop && (e = hipEventRecord(ev_start, stream)) != hipSuccess) return e;
   e = causal ? launch_dkdv_causal(a, d, dkdv_pairs, cus, stream) : launch_dkdv_m<false>(a, d, dkdv_pairs, cus, stream);

@@ -4,8 +4,8 @@
 
 namespace knap {
 
-hipError_t launch_dq_causal(const BwdArgs& a, int d, int grid, hipStream_t stream) {
-  return launch_dq_m<true>(a, d, grid, stream);
+hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream) {
+  return launch_dq_m<true>(a, d, cus, wg_per_cu, stream);
 }
 
 hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream) {

@@ -44,6 +44,9 @@ namespace knap {
 // one on long sequences.  PAIRS = 2 (4 waves, 128 keys, two workgroups per CU) hides the start and the end of
 // an item (22 us of K / V rows, first tile and stores, as long as 430 queries take) under the other workgroup's loop,
 // pads sequences to 128 keys instead of 256 and fills the GPU from half as many keys on; dkdv_pairs() chooses.
+// At d = 64 the registers of two pairs (166 of them without a spill) and their 43 KB of LDS leave room for a third
+// workgroup on the CU, and a third wave on a SIMD has its MFMAs while the other two form exponentials, which are twice as
+// many per MFMA there: 10 sequences of 310..6795 tokens, 48 x 64, 2760 -> 2631 us.
 // ---------------------------------------------------------------------------
 template <int D, int PAIRS_>
 struct Bwd2Cfg {
@@ -90,7 +93,7 @@ struct ColReaderX {
 };
 
 template <int D, int PAIRS, bool CAUSAL>
-__global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
+__global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void attn_bwd_dkdv64_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ delta,
     const int32_t* __restrict__ cu, int n_seq, int H, float scale,
@@ -115,9 +118,10 @@ __global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pair = wave & (C::PAIRS - 1);
-  // PAIRS = 2: the two waves of a pair sit on different SIMDs, each next to a wave of the CU's other workgroup; that
-  // one (half the grid further on) has the roles the other way round, so that every SIMD gets one wave of either role
-  const int role = (wave / PAIRS) ^ (PAIRS == 2 && blockIdx.x >= (gridDim.x >> 1) ? 1 : 0);
+  // PAIRS = 2: the two waves of a pair sit on different SIMDs, each next to the waves of the CU's other workgroups; every
+  // other one of those (a half or a third of the grid further on) has the roles the other way round, so that the SIMDs
+  // get waves of either role
+  const int role = (wave / PAIRS) ^ (PAIRS == 2 ? (int)(blockIdx.x * dkdv_workgroups_per_cu(D, PAIRS) / gridDim.x) & 1 : 0);
   const int l32 = lane & 31;
   const int hh = lane >> 5;
   const float c = scale * kLog2e;
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(128 * PAIRS, 2) void attn_bwd_dkdv64_kernel(
 template <int D, int PAIRS, bool CAUSAL>
 static hipError_t launch_dkdv_t(const BwdArgs& a, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
-  hipLaunchKernelGGL((attn_bwd_dkdv64_kernel<D, PAIRS, CAUSAL>), dim3(cus * dkdv_workgroups_per_cu(PAIRS)), dim3(128 * PAIRS),
+  hipLaunchKernelGGL((attn_bwd_dkdv64_kernel<D, PAIRS, CAUSAL>), dim3(cus * dkdv_workgroups_per_cu(D, PAIRS)), dim3(128 * PAIRS),
                      dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout,
                      a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale, (__bf16*)a.dk, (__bf16*)a.dv, a.counters + 8);
   return hipGetLastError();

@@ -1,6 +1,9 @@
 // dQ kernel of the backward: the forward kernel's structure.  S^T = K Q^T and dP^T = V dO^T put one query in each
 // lane, LSE and delta are per-lane scalars, and dS^T is, unchanged, the B operand of dQ^T += K^T dS^T with K^T read
 // transposed from LDS.  One text, compiled for either mask in a translation unit of its own (see build.py).
+// d = 64: 168 registers (5 values spilled outside the loops) let three workgroups share a CU where 174 allowed two; the
+// third wave of a SIMD fills the exponentials of the others (48 x 64, 10 sequences of 310..6795 tokens: 2077 -> 1988 us,
+// 65536 tokens 77.6 -> 73.7 ms).
 #pragma once
 
 #include "knap_device.h"
@@ -20,7 +23,7 @@ struct DqCfg {
 };
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ lse2_out, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
@@ -376,10 +379,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_kernel(
 }
 
 template <bool CAUSAL>
-static hipError_t launch_dq_m(const BwdArgs& a, int d, int grid, hipStream_t stream) {
-  const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
+static hipError_t launch_dq_m(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream) {
+  size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
+  // two workgroups on every CU where three would fit: with 24 KB more LDS each, a third does not (left to itself, a grid of
+  // two for every CU is placed three on one and one on another: 12000 causal tokens, 12 x 64, 409 us against 352)
+  if (d == 64 && wg_per_cu == 2 && dyn < 24 * 1024) dyn = 24 * 1024;
   auto* kernel = d == 64 ? attn_bwd_dq_kernel<64, CAUSAL> : attn_bwd_dq_kernel<128, CAUSAL>;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k,
+  hipLaunchKernelGGL(kernel, dim3(cus * wg_per_cu), dim3(kThreads), dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k,
                      (const __bf16*)a.v, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
                      a.n_seq, a.H, a.scale, (__bf16*)a.dq, a.counters);
   return hipGetLastError();

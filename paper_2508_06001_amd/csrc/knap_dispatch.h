@@ -6,35 +6,65 @@
 
 namespace knap {
 
-// The dK/dV kernel takes 2 or 4 wave pairs per workgroup and this many workgroups on each CU (two waves per SIMD is what
-// its registers allow).
+// The dK/dV kernel takes 2 or 4 wave pairs per workgroup and this many workgroups on each CU: two waves per SIMD is what
+// its registers allow, three with two pairs at d = 64.
 constexpr int dkdv_workgroups_per_cu(int pairs) { return 4 / pairs; }
+constexpr int dkdv_workgroups_per_cu(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : dkdv_workgroups_per_cu(pairs); }
+constexpr int dkdv_waves_per_simd(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 2; }
+
+// Rounds of `slots` workgroups that a bag's items take, its sequences taken to be of one length: whole ones where there
+// are few, and as many as the items fill where there are so many that the shorter sequences even out the last.  `split`
+// parts can stand for an item of a thin last round (see ItemQueue), which then takes little more than half of one; under
+// the mask (four parts) a third behind whole rounds, three quarters where all is parts and the longest of them last.
+inline double rounds(int64_t total_tokens, int n_seq, int H, bool causal, int tile, int64_t slots, int split = 0) {
+  const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + tile - 1) / tile;
+  const int64_t items = (causal ? (tiles + 1) / 2 : tiles) * n_seq * H;
+  if (items >= 8 * slots) return (double)items / slots;
+  const int64_t last = items % slots;
+  return (double)(items / slots) + (last == 0 ? 0.0 : last * split > slots || split == 0 ? 1.0 : split == 2 ? 0.6 : items > slots ? 0.35 : 0.75);
+}
+
+// Workgroups of the dQ kernel on each CU, `resident` being what its registers allow.  At d = 64 that is three, each of which
+// takes 1.4 times as long for an item as one of two: two where their whole rounds come out shorter (forward left out, in us, two
+// against three: 131072 tokens, 2 x 64 13122 against 13902, causal 7142 against 9417, 12000,
+// 12 x 64, causal 352 against 391; but 6 of 4300, 12 x 64 564 against 535;
+// 20000, 2 x 64 442 against 375; 32 of 450, 48 x 64 214 against 195; 65536, 48 x 64 77.6 against 73.7 ms).
+inline int dq_workgroups_per_cu(int64_t total_tokens, int n_seq, int H, bool causal, int cus, int resident) {
+  if (resident < 3) return resident;
+  const int split = causal ? 4 : 2;
+  return rounds(total_tokens, n_seq, H, causal, 128, 2 * (int64_t)cus, split) <
+                 1.36 * rounds(total_tokens, n_seq, H, causal, 128, 3 * (int64_t)cus, split) ? 2 : resident;
+}
 
 // Wave pairs per workgroup of the dK/dV kernel (2 or 4, see there), from what the host knows of a bag: its tokens, heads
 // and number of sequences.  Both sides measured, two pairs against four: times of that kernel where nothing else is said.
 //  * At most half a 256-key tile per CU: two, which spread the keys over twice as many CUs (3 causal sequences of up to
 //    391 tokens, 6 x 128: 38 against 51 us; 2 of up to 4362, 2 x 64: 104 against 150 us).
 //  * Many short sequences: two, which hide the start and the end of every item (32 of 450 tokens, 24 x 128: 249 against
-//    276 us; 17 causal ones of 328..4533 tokens: 1125 against 1240 us; 10 of 310..6795 tokens, 48 x 64: 2806 against
-//    3057 us).  The causal kernel at d = 64 has little of either to hide and is up to 8 % slower.
+//    276 us; 17 causal ones of 328..4533 tokens: 1125 against 1240 us).
 //    The average does not show one long sequence among many short ones, where two pairs lose as soon as the long one's
 //    tiles fill the GPU; the bounds on the whole bag are a compromise between such bags and those of like lengths.  Causal,
 //    d = 128, whole backward in us: 20 of 3000 tokens, 24 heads 3904 against 4023; 128 of 450, 24 heads 1227 against 1332; 30 of
 //    1100, 3 heads 158 against 225; but 30000 and 30 of 300, 12 heads 8752 against 8394; half of 60000 tokens in one
 //    sequence, 24 heads 17234 against 16973, 3 heads 2627 against 2464 (of 30000, 12 heads 3047 against 2930; of 20000, 6 heads,
-//    where the GPU is not full, 686 against 755).  Without the mask at d = 64: 28000 and 8 of 500, 48 heads 31872 against
-//    32436; half of 32000 in one, 48 heads 10575 against 11002, 12 heads 2816 against 2766.
+//    where the GPU is not full, 686 against 755).
 //    Without the mask at d = 128 the line is at an average of 512: above it two pairs win where they pad less and lose
 //    where the lengths are multiples of 256 or one sequence stands out (forward and backward, two against four: 15 of 640
 //    tokens, 24 x 128: 471 against 506 us; but 10 of 1024: 669 against 652; 8 of 1200: 742 against 721; 4405, 619 and 371:
 //    1135 against 1107; 4200 and seven of 300..600, 12 x 128: 611 against 582; 18 of 512: 208 both).  And at 16384 tokens:
 //    beyond, short sequences gain nothing from two pairs (64 of 450, backward, 24 heads 835 against 827, 6 heads 226 against
 //    220; 128 of 450, 24 heads 1619 against 1620), and a long one among them loses (8192 and 45 of 300, 6 heads 779 against 723).
+//  * d = 64, three workgroups of two pairs on a CU: two pairs, unless their rounds are the longer ones (a round of three
+//    takes 1.4 times as long as one of four pairs).  32 of 450 tokens, 48 x 64: 246 against 289 us; 16 of 4096: 6389 against
+//    7163; 65536: 98.1 against 103.3 ms; causal, 20 of 3000: 2637 against 2970 us, 65536: 51.6 against 52.1 ms.  But 6 of 4300,
+//    12 x 64: 786 against 737 us; 131072, 2 x 64: 18320 against 17195, causal 13719 against 9399.
 //  * Otherwise four (65536 and 200 short, 24 x 128: 80.3 against 82.4 ms; 30000 tokens, 3 x 128: 2.90 against 3.13 ms).
 inline int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
   if (total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
-  const int64_t longest_average = d == 128 && !causal ? 512 : 4096;
-  const int64_t largest_bag = d == 64 ? (causal ? 0 : 32768) : (causal ? 65536 : 16384);
+  if (d == 64)
+    return 1.4 * rounds(total_tokens, n_seq, H, causal, 128, 3 * (int64_t)cus) < rounds(total_tokens, n_seq, H, causal, 256, cus) ? 2 : 4;
+  const int64_t longest_average = causal ? 4096 : 512;
+  const int64_t largest_bag = causal ? 65536 : 16384;
   if (total_tokens <= largest_bag && total_tokens < longest_average * n_seq) return 2;
   return 4;
 }

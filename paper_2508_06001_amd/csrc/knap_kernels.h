@@ -29,9 +29,9 @@ struct BwdArgs {
 };
 // `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `draws`: some queue may hold more items than
 // workgroups, so that the counters have to be zero.
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int grid_dq, bool draws,
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool draws,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
-hipError_t launch_dq_causal(const BwdArgs& a, int d, int grid, hipStream_t stream);
+hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream);
 hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream);
 
 // Ulysses layout switch, local data movement; rows of U 16-byte units.

@@ -675,6 +675,17 @@ def test_two_pair_dkdv_kernel_over_several_items_per_workgroup():
         assert np.array_equal(bf16_device_to_bits(got), want)
 
 
+@pytest.mark.parametrize("causal,lens,H,pairs", [(False, _LOW_RES, 48, 2), (True, _LOW_RES, 48, 2), (False, [2081], 46, 4),
+                                                 (False, [4300] * 2, 12, 4), (True, [2081, 1100], 58, 4)])
+def test_three_backward_workgroups_per_cu_at_d_64(causal, lens, H, pairs):
+    """d = 64, where three workgroups share a CU: several items for each of the 768 (tickets handed over, roles of every
+    third of the grid), a thin last round of dQ parts (782 items), bags whose rounds favour four pairs, and causal pairs.
+    First and last heads against the oracle."""
+    assert Q.dkdv_pairs(lens, H, 64, causal) == pairs
+    _full_compare(BagSpec("three_per_cu", lens, H=H, d=64, seed=8800 + H), heads=[0, H - 1], strict_fwd=not causal, causal=causal,
+                  lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
