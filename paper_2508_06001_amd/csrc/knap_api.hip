@@ -10,7 +10,7 @@
 #include <mutex>
 
 // Scratch of knap_varlen_attn_bwd_noalloc: the per-row dot products of dout and out and the base-2
-// log-sum-exp (fp32, (H, T) each) and, in the last 256 bytes, the work-queue counters of the dQ kernel.  Part of the library's device image:
+// log-sum-exp (fp32, (H, T) each) and, in the last 256 bytes, the work-queue counters of a captured call.  Part of the library's device image:
 // every GPU the library runs on holds its own copy until the process ends.  Host code never uses this
 // name as an address; it uses the pointer hipGetSymbolAddress returned on that device (DeviceInfo::scratch).
 static __device__ __align__(256) unsigned char scratch[2 * KNAP_NOALLOC_MAX_ROWS * sizeof(float) + 256];
@@ -25,15 +25,15 @@ struct DeviceInfo {
   int cus = 0;
   int fwd_wg[2] = {0, 0};   // workgroups per CU, index 0: d = 64, 1: d = 128
   int dq_wg[2] = {0, 0};
-  unsigned* fwd_queue = nullptr;   // this device's copy of the forward work-queue counters
+  unsigned* queues = nullptr;      // this device's copy of the work-queue counters
   unsigned char* scratch = nullptr;   // this device's copy of `scratch`
 };
 
-// Counter sets of the forward's work queue: the lower half is handed out in rotation to eager launches,
-// the upper half to launches recorded under stream capture.  A captured launch keeps its set for every
-// replay of its graph, so it must never be one that eager launches rotate through.
-std::atomic<unsigned> g_fwd_launches{0};
-std::atomic<unsigned> g_fwd_captured{0};
+// Counter sets of the work queues: the lower half is handed out in rotation to eager launches, the upper half to forward
+// launches recorded under stream capture.  A captured launch keeps its set for every replay of its graph, so it must
+// never be one that eager launches rotate through.  (A captured backward keeps its counters in its own workspace.)
+std::atomic<unsigned> g_launches{0};
+std::atomic<unsigned> g_captured{0};
 
 constexpr int kMaxDevices = 64;
 
@@ -47,8 +47,8 @@ void fill_device_info(DeviceInfo& di, int dev) {
   di.fwd_wg[1] = knap::fwd_workgroups_per_cu(128);
   di.dq_wg[0] = knap::bwd_dq_workgroups_per_cu(64);
   di.dq_wg[1] = knap::bwd_dq_workgroups_per_cu(128);
-  di.fwd_queue = knap::fwd_queue_base();
-  if (!di.fwd_queue) return;
+  di.queues = knap::queue_base();
+  if (!di.queues) return;
   void* p = nullptr;
   if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
     (void)hipGetLastError();
@@ -84,6 +84,15 @@ int check_common(const void* q, const void* k, const void* v, const int32_t* cu,
   return KNAP_OK;
 }
 
+bool capturing(void* stream) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return capture != hipStreamCaptureStatusNone;
+}
+
 int fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seqlens, int n_seq,
              int H, int d, float scale, bool causal, void* out, float* lse, void* stream) {
   const int rc = check_common(q, k, v, cu_seqlens, n_seq, H, d, scale);
@@ -94,15 +103,8 @@ int fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   DeviceInfo* di = device_info();
   if (!di) return KNAP_ERR_LAUNCH_FAILED;
   const int grid = di->cus * di->fwd_wg[d == 128];
-  const unsigned half = (unsigned)knap::fwd_queue_slots() / 2u;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusNone;
-  }
-  const unsigned slot = capture == hipStreamCaptureStatusNone ? g_fwd_launches.fetch_add(1u) % half
-                                                              : half + g_fwd_captured.fetch_add(1u) % half;
-  unsigned* counters = di->fwd_queue + 8u * slot;
+  const unsigned half = (unsigned)knap::queue_sets() / 2u;
+  unsigned* counters = di->queues + 16u * (capturing(stream) ? half + g_captured.fetch_add(1u) % half : g_launches.fetch_add(1u) % half);
   const hipError_t e = knap::launch_fwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, counters,
                                         grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
@@ -201,12 +203,16 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
 
   float* delta = static_cast<float*>(workspace);
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + (need - 256) / 2);
-  unsigned* counters = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256);
+  // counters at zero from the library's sets; a captured launch, which keeps its counters for every replay, clears 16 words
+  // of the workspace instead
+  const bool captured = capturing(stream);
+  unsigned* counters = captured ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256)
+                                : di->queues + 16u * (g_launches.fetch_add(1u) % ((unsigned)knap::queue_sets() / 2u));
   const int dq_wg = knap::dq_workgroups_per_cu(total_tokens, n_seq, H, causal, di->cus, di->dq_wg[d == 128]);
   const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
   const int pairs = knap::dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus);
   const hipError_t e = knap::launch_bwd(args, d, causal, pairs, di->cus, dq_wg,
-                                        knap::bwd_draws(total_tokens, n_seq, H, causal, pairs, di->cus, di->cus * dq_wg),
+                                        captured && knap::bwd_draws(total_tokens, n_seq, H, causal, pairs, di->cus, di->cus * dq_wg),
                                         static_cast<hipStream_t>(stream), g_prof_start, g_prof_stop);
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;

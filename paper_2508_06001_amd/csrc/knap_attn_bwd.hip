@@ -30,15 +30,15 @@ namespace knap {
 
 constexpr int kQueueCounters = 16;    // one work-queue counter per XCD for the dQ kernel, then one for the dK/dV kernel
 
-// the work queues of the kernels that follow on the stream start at zero
+// the work queues of the kernels that follow on the stream start at zero (counters in a caller's workspace)
 __global__ void bwd_queue_reset_kernel(unsigned* __restrict__ counters) {
   if (threadIdx.x < kQueueCounters) counters[threadIdx.x] = 0u;
 }
 
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool draws,
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool clear,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipError_t e = hipSuccess;
-  if (draws) {
+  if (clear) {
     hipLaunchKernelGGL(bwd_queue_reset_kernel, dim3(1), dim3(64), 0, stream, a.counters);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

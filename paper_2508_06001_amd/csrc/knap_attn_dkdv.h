@@ -393,7 +393,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
     issue_tile(0, sQ0, sdO0, sLse0, sDelta0);
     if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
     step_sync();      // tile 0 has landed (and the K / V rows requested before it)
-    if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket);
+    if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket);
 
     if (role == 0) KNAP_ROLE_LOOP(0);
     else KNAP_ROLE_LOOP(1);

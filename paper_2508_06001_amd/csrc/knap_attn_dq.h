@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
       }
     }
     if (!queue.draws) return;
-    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);   // every wave took its copy of the old one many barriers ago
+    if (tid == 0) s_ticket = drawn_ticket(queue, next_ticket);   // every wave took its copy of the old one many barriers ago
     lds_barrier();
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
   }
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
       }
     }
     if (!queue.draws) return;         // every part was a first ticket
-    if (tid == 0) s_ticket = queue.later_ticket(atomicAdd(queue.ctr, 1u));
+    if (tid == 0) s_ticket = drawn_ticket(queue, atomicAdd(queue.ctr, 1u));
     lds_barrier();                    // (and part_acc is no longer read)
     part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
     lds_barrier();                    // everyone has the ticket before the next one is put down

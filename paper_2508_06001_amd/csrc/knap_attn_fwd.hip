@@ -48,7 +48,7 @@ struct FwdCfg {
 };
 
 constexpr float kMaxHalfSum = 256.f;        // of a lane's 16 probabilities against the present reference
-constexpr int kFwdQueueSlots = 256;
+constexpr int kQueueSets = 8192;
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
       more = false;
     } else {
       if (tid == 0) {
-        s_ticket = queue.later_ticket(next_ticket);   // every wave read the old one many barriers ago
+        s_ticket = drawn_ticket(queue, next_ticket);   // every wave read the old one many barriers ago
       }
       lds_barrier();
       ticket = __builtin_amdgcn_readfirstlane(s_ticket);
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
     if (!queue.draws) return;         // every part was a first ticket
     if (tid == 0) {
       const unsigned drawn = atomicAdd(queue.ctr, 1u);
-      s_ticket = queue.later_ticket(drawn);
+      s_ticket = drawn_ticket(queue, drawn);
     }
     lds_barrier();                    // (and the tile buffers are no longer read)
     part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
@@ -444,22 +444,17 @@ KNAP_FWD_INSTANCE(64, true)
 KNAP_FWD_INSTANCE(128, true)
 #undef KNAP_FWD_INSTANCE
 
-// The forward entry point has no workspace argument, so the counters of its work queue live
-// in the library's device image: kFwdQueueSlots sets of 8 (one per XCD), handed out in rotation
-// by the host and zeroed on the launch stream right before the kernel that uses them.  Two
-// launches share a set only if kFwdQueueSlots other forward launches were enqueued between
-// them while the first was still running.
-static __device__ __align__(256) unsigned g_fwd_queue[kFwdQueueSlots * 8];
+// Counters of the work queues, in the library's device image (512 KB that start at zero): kQueueSets sets of 16, 8 for a
+// forward or dQ kernel and 8 for a dK/dV kernel (one per XCD), handed out in rotation by the host.  Every kernel
+// leaves its counters at zero, so no launch has to clear them.  Two launches share a set only if half of kQueueSets
+// others were enqueued between them while the first was still running.
+static __device__ __align__(256) unsigned g_queues[kQueueSets * 16];
 
-__global__ void fwd_queue_reset_kernel(unsigned* __restrict__ counters) {
-  if (threadIdx.x < 8) counters[threadIdx.x] = 0u;
-}
+int queue_sets() { return kQueueSets; }
 
-int fwd_queue_slots() { return kFwdQueueSlots; }
-
-unsigned* fwd_queue_base() {
+unsigned* queue_base() {
   unsigned* p = nullptr;
-  if (hipGetSymbolAddress(reinterpret_cast<void**>(&p), HIP_SYMBOL(g_fwd_queue)) != hipSuccess) {
+  if (hipGetSymbolAddress(reinterpret_cast<void**>(&p), HIP_SYMBOL(g_queues)) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
@@ -470,9 +465,6 @@ template <int D, bool CAUSAL>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq,
                                int H, float scale, void* out, float* lse, unsigned* counters, int grid,
                                hipStream_t stream) {
-  hipLaunchKernelGGL(fwd_queue_reset_kernel, dim3(1), dim3(64), 0, stream, counters);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const size_t dyn = (size_t)(2 * n_seq + 1) * sizeof(int);
   hipLaunchKernelGGL((attn_fwd_kernel<D, CAUSAL>), dim3(grid), dim3(kThreads), dyn, stream,
                      (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, cu, n_seq, H, scale,

@@ -332,6 +332,13 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
   return s_start[n_seq];
 }
 
+// The ticket that a draw of one lane stands for; the queue's last draw puts its counter back to zero.
+template <int SPLIT>
+__device__ __forceinline__ int drawn_ticket(const ItemQueue<SPLIT>& queue, unsigned drawn) {
+  if (queue.last_draw(drawn)) atomicExch(queue.ctr, 0u);
+  return queue.later_ticket(drawn);
+}
+
 template <int TILE, bool PAIRED = false>
 __device__ __forceinline__ WorkItem decode_item(int w, const int32_t* __restrict__ cu, int n_seq,
                                                 const int* s_order, const int* s_start) {

@@ -12,10 +12,10 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t
                       int H, int d, float scale, bool causal, void* out, float* lse, unsigned* counters,
                       int grid, hipStream_t stream);
 
-// Device address (on the current device) of the forward kernel's work-queue counters:
-// fwd_queue_slots() sets of 8, one set per launch in flight; nullptr on failure.
-unsigned* fwd_queue_base();
-int fwd_queue_slots();
+// Device address (on the current device) of the library's work-queue counters: queue_sets() sets of 16, at zero
+// whenever no kernel uses them; nullptr on failure.
+unsigned* queue_base();
+int queue_sets();
 
 struct BwdArgs {
   const void *q, *k, *v, *out, *dout;
@@ -27,9 +27,9 @@ struct BwdArgs {
   float *delta, *lse2;      // (H, T) each, handed from the dQ kernel to the dK/dV kernel
   unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel
 };
-// `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `draws`: some queue may hold more items than
-// workgroups, so that the counters have to be zero.
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool draws,
+// `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `clear`: the counters' contents are unknown, and
+// some queue may hold more items than workgroups: they have to be cleared first.
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool clear,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream);
 hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream);

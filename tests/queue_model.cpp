@@ -49,6 +49,17 @@ Walk walk(int grid, const std::vector<int>& start, int n_seq, int n_items) {
       const int at = n_wide * SPLIT + queue.part0 + p;
       if (at < 0 || at >= n_items * SPLIT) ++r.wrong; else ++part[at];
     }
+    // every workgroup of a queue that draws draws until a ticket is past the queue's: the last draw, which puts the counter
+    // back to zero, is known as such, and nobody draws after it
+    if (queue.draws) {
+      int at_work = queue.per;
+      unsigned drawn = 0;
+      for (; at_work > 0 && drawn <= (unsigned)tickets; ++drawn) {
+        if (queue.later_ticket(drawn) >= tickets) --at_work;
+        r.wrong += queue.last_draw(drawn) != (at_work == 0);
+      }
+      r.wrong += at_work != 0;
+    }
     r.per = queue.per;
     r.most = max(r.most, tickets);
     r.draws |= queue.draws;

@@ -686,6 +686,27 @@ def test_three_backward_workgroups_per_cu_at_d_64(causal, lens, H, pairs):
                   lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+def test_counters_of_the_work_queues_come_back_to_zero(causal):
+    """Eager calls take the library's 4096 counter sets in rotation and nothing clears them but the kernels that used them:
+    more calls than sets, each forward and backward drawing in all three kernels, and the last results are the first."""
+    import torch
+    lens, H, d = [1 + (5 * i) % 9 for i in range(500)], 4, 64
+    Q.assert_draws(lens, H, d, causal)
+    run = GpuRun(BagSpec("sets", lens, H=H, d=d, seed=8900), causal=causal)
+    a, x = run.attn, run.dev
+    first = [t.clone() for t in (a.out, a.lse, a.dq, a.dk, a.dv)]
+    for i in range(2100):
+        if i == 2099:
+            for t in (a.out, a.lse, a.dq, a.dk, a.dv):
+                t.fill_(float("nan"))
+        a.forward(x["q"], x["k"], x["v"])
+        a.backward(x["q"], x["k"], x["v"], x["dout"])
+    torch.cuda.synchronize()
+    for got, want in zip((a.out, a.lse, a.dq, a.dk, a.dv), first):
+        assert torch.equal(got, want)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
