@@ -112,8 +112,8 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
   __shared__ __attribute__((aligned(256))) float sSink[64];
   __shared__ __attribute__((aligned(16))) u32x4 sP[C::PAIRS][2][2 * C::KB][64];
 
-  const int n_items = build_schedule<C::BN, C::THREADS, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sP[0][0][0][0]));
   const int T = cu[n_seq];
+  const int n_items = build_schedule<C::BN, C::THREADS, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sP[0][0][0][0]));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

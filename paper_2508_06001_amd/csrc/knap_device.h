@@ -287,11 +287,42 @@ struct WorkItem {
   int tile;
 };
 
+// sum over the lanes up to this one
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: within 16 lanes
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31: lane 15 (31) of the rows before
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
 template <int TILE, int NT = kThreads, bool PAIRED = false>
 __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, int n_seq, int H,
                                               int* s_order, int* s_start, int* s_part /* NT ints */) {
   constexpr int kThreads = NT;   // threads of the calling workgroup
   const int tid = threadIdx.x;
+  // Up to 64 sequences: one wave, one load of the boundaries, no barrier but the last.  What bounds it is latency, which
+  // every launch pays; the walk below it has three dependent loads and twenty barriers (4 sequences of up to 311 tokens,
+  // 2 x 64: forward 10.4 -> 9.7 us, dQ 12.5 -> 11.4, dK/dV 17.9 -> 16.3).
+  if (n_seq <= 64) {
+    if (tid < 64) {
+      const int len = tid < n_seq ? cu[tid + 1] - cu[tid] : -1;
+      int rank = 0;
+      for (int j = 0; j < n_seq; ++j) rank += __builtin_amdgcn_readlane(len, j) > len - (j < tid ? 1 : 0) ? 1 : 0;
+      if (tid < n_seq) {
+        s_order[rank] = tid;
+        s_start[rank] = items_per_head<PAIRED>((len + TILE - 1) / TILE) * H;
+      }
+      const int items = tid < n_seq ? s_start[tid] : 0;
+      const int sum = wave_scan(items);
+      if (tid < n_seq) s_start[tid] = sum - items;
+      if (tid == 63) s_start[n_seq] = sum;
+    }
+    __syncthreads();
+    return s_start[n_seq];
+  }
   for (int i = tid; i < n_seq; i += kThreads) s_start[i] = cu[i + 1] - cu[i];
   __syncthreads();
   // rank sort, descending length, ties by original index

@@ -707,6 +707,16 @@ def test_counters_of_the_work_queues_come_back_to_zero(causal):
         assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("n_seq", [1, 2, 15, 16, 17, 31, 33, 63, 64, 65])
+def test_schedule_of_bags_on_both_sides_of_64_sequences(n_seq):
+    """Up to 64 sequences one wave sorts them and adds up their items, beyond that the workgroup does: numbers of sequences
+    at the edges of that scan's steps, equal and empty ones among them, both masks."""
+    for causal in (False, True):
+        lens = [(37 * i * i) % 201 if i % 5 else 64 for i in range(n_seq)]
+        lens[-1] = 150
+        _full_compare(BagSpec("schedule", lens, H=2, d=64, seed=9000 + n_seq), strict_fwd=False, causal=causal, lse_tol=LSE_TOL_FEW_KEYS)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
