@@ -32,11 +32,9 @@ HIP_FLAGS = [
 
 # flags of single sources
 FILE_FLAGS = {
-    # the scheduler's exact register-pressure tracking: without it the causal dK/dV kernel (d = 128) reloads spilled
-    # registers in every step; with it the two-pair form does not (17 sequences of 328..4533 tokens, 24 x 128: 1302 us
-    # against 1202 us), the four-pair form still does (7 reloads in its step loops instead of 9).  Without it the causal
-    # dQ kernel is 5 % slower; the bidirectional kernels have no such reload and are up to 1 % slower with it on long
-    # sequences
+    # the scheduler's exact register-pressure tracking: without it the causal dQ kernel is up to 4 % slower (17 sequences
+    # of 328..4533 tokens, 24 x 128: 844 us against 871); the causal dK/dV kernel is the same with it, the bidirectional one
+    # 1 % slower on long sequences
     "knap_attn_bwd_causal.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
 }
 

@@ -16,14 +16,21 @@ namespace knap {
 //            with the partner's P, dK += dS^T Q.
 // Each wave holds one accumulator, so two waves fit on a SIMD and each one's MFMAs run against the
 // other's exponentials, LDS reads and waits.  With S = Q K^T in the MFMA result layout a lane holds one
-// key and its registers run over queries, so P and dS are, unchanged, the A operands of the second
-// products; dO and Q enter those through transposing LDS reads.
+// key and its registers run over queries, so P and dS are, unchanged, operands of the second
+// products' key side (MFMA takes rows and columns alike); dO and Q enter those through transposing LDS reads.
 //
 // Every fragment of Q or dO that a wave reads from LDS, row-wise for S / dP and transposed for dV /
 // dK, feeds TWO MFMAs, one per key block: 512 bytes of LDS operand per MFMA.  The registers just allow
 // it because the accumulators sit on the key side: per wave 128 (dV or dK, 64 x d fp32) + 64 (its K or
 // V rows) + 32 (scores of a step) + operands in flight, within the 256 of two waves per SIMD (every
-// base address in scalar registers, every LDS address formed next to its read).
+// base address in scalar registers, every LDS address formed next to its read, and everything else that depends on the
+// lane taken out of one register: see LaneWord).  Without a spilled register in a step: a reload there waits for the tile
+// copy issued just before it (17 causal sequences of 328..4533 tokens, 24 x 128: 1216 -> 1139 us, 14 of 406..14415: 6.42 ->
+// 6.27 ms).
+//
+// The second products are formed as dV^T += dO^T P and dK^T += Q^T dS, so that a lane holds one key and its registers run
+// along the row of the result: 16 stores of 16 bytes per wave, where dV itself would take 128 of 2 bytes, predicated by
+// row (32 sequences of 256..648 tokens, 24 x 128: 231 -> 215 us; the causal 17 of 328..4533: 1126 -> 1079 us).
 //
 // Query-side tiles (32 rows of Q and dO, their LSE in base 2 and delta) go global -> LDS
 // asynchronously, one tile ahead, into a ring of three buffers (being filled / dV role / dK
@@ -42,7 +49,7 @@ namespace knap {
 //
 // PAIRS = 4 (8 waves, 256 keys, one workgroup per CU) copies the fewest bytes into LDS per MFMA and is the faster
 // one on long sequences.  PAIRS = 2 (4 waves, 128 keys, two workgroups per CU) hides the start and the end of
-// an item (22 us of K / V rows, first tile and stores, as long as 430 queries take) under the other workgroup's loop,
+// an item (K / V rows, first tile and stores) under the other workgroup's loop,
 // pads sequences to 128 keys instead of 256 and fills the GPU from half as many keys on; dkdv_pairs() chooses.
 // At d = 64 the registers of two pairs (166 of them without a spill) and their 43 KB of LDS leave room for a third
 // workgroup on the CU, and a third wave on a SIMD has its MFMAs while the other two form exponentials, which are twice as
@@ -92,6 +99,15 @@ struct ColReaderX {
   }
 };
 
+// 16 times the lane's number, plus a multiple of 1024
+struct LaneWord {
+  int word;
+  __device__ __forceinline__ int fresh() const { int w = word; asm volatile("" : "+v"(w)); return w; }
+  __device__ static __forceinline__ int l32(int w) { return (w >> 4) & 31; }
+  __device__ static __forceinline__ int hh16(int w) { return (w >> 5) & 16; }       // 16 for the upper 32 lanes
+  __device__ static __forceinline__ int lane4(int w) { return (w >> 2) & 252; }
+};
+
 template <int D, int PAIRS, bool CAUSAL>
 __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void attn_bwd_dkdv64_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -122,8 +138,6 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
   // other one of those (a half or a third of the grid further on) has the roles the other way round, so that the SIMDs
   // get waves of either role
   const int role = (wave / PAIRS) ^ (PAIRS == 2 ? (int)(blockIdx.x * dkdv_workgroups_per_cu(D, PAIRS) / gridDim.x) & 1 : 0);
-  const int l32 = lane & 31;
-  const int hh = lane >> 5;
   const float c = scale * kLog2e;
   const size_t row_stride = (size_t)H * D;
   const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
@@ -131,6 +145,10 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
   ColReaderX<D> cols;
   rows.init(lane);
   cols.init(lane);
+  // where this lane's 16 bytes of its pair's P lie; its number and its halves are bits of that word, taken out of it where
+  // they are needed (a step has no register to spare for each of them)
+  LaneWord at;
+  at.word = (int)sizeof(sP[0]) * pair + 16 * lane;
 
   constexpr int ROWS_PER_INSTR = 512 / D;
   // one instruction copies 1 KB: ROWS_PER_INSTR rows.  Q and dO of a tile are 16 (D = 128) or 8 of them, dealt to
@@ -180,9 +198,10 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       const uint32_t kv_bytes = (uint32_t)min(L - kv0, C::BN) * row_bytes;
       const __bf16* src = (role == 0 ? k : v) + (size_t)(it.row0 + kv0) * row_stride + head_off;
       const auto r = make_rsrc(src, kv_bytes);
+      const int w = at.fresh();
 #pragma unroll
       for (int kb = 0; kb < C::KB; ++kb) {
-        const uint32_t off = (uint32_t)(64 * pair + 32 * kb + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+        const uint32_t off = (uint32_t)(64 * pair + 32 * kb + LaneWord::l32(w)) * row_bytes + (uint32_t)LaneWord::hh16(w);
 #pragma unroll
         for (int cc = 0; cc < C::KC; ++cc) kvf[kb][cc] = __builtin_bit_cast(bf16x8, buffer_load16(r, off + 32u * cc));
       }
@@ -221,7 +240,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       const float* src = wave == 0 ? lse_base + q0 : delta_base + q0;
       float* dst = wave == 0 ? tLse : wave == 1 ? tDelta : sSink;
       const auto rs = make_rsrc(src, wave < 2 ? (uint32_t)n_rows * 4u : 0u);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)dst, 4, lane * 4, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)dst, 4, LaneWord::lane4(at.fresh()), 0, 0, 0);
     };
 
     // End of a step: this wave's copies of the next tile have landed, its LDS writes (P) are done, then the
@@ -261,16 +280,20 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) {
 #pragma unroll
-        for (int kb = 0; kb < C::KB; ++kb) acc[kb][nb] = mfma32(op[kb], bf[nb], acc[kb][nb]);
+        for (int kb = 0; kb < C::KB; ++kb) acc[kb][nb] = mfma32(bf[nb], op[kb], acc[kb][nb]);
         if (nb + AH2 < C::NB) bf[nb + AH2] = cols.get(tB, cb, 16 * cq, nb + AH2);
         between(nb);
         KNAP_SCHED_FENCE();
       }
     };
 
+    // 16 bytes of this lane in block `b` of its pair's P of tile t
+    auto p_at = [&](int w, int t, int b) {
+      return reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&sP[0][0][b][0]) + (w + (t & 1) * (int)sizeof(sP[0][0])));
+    };
     // dV wave, tile t: S, P, hand P over, dV += P^T dO
     auto dv_step = [&](int t, const __bf16* tQ, const __bf16* tdO, const float* tLse) {
-      const int rb = rows.fresh(), cb = cols.fresh();
+      const int rb = rows.fresh(), cb = cols.fresh(), w = at.fresh();
       f32x16 s[C::KB];
 #pragma unroll
       for (int kb = 0; kb < C::KB; ++kb) s[kb] = zero16();
@@ -281,8 +304,9 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       bf16x4 ph[2][C::KB][2];
       f32x4 lq[2][2];
       auto lse_of = [&](int cq) {
-        lq[cq][0] = *reinterpret_cast<const f32x4*>(&tLse[16 * cq + 4 * hh]);
-        lq[cq][1] = *reinterpret_cast<const f32x4*>(&tLse[16 * cq + 8 + 4 * hh]);
+        const char* row = reinterpret_cast<const char*>(tLse + 16 * cq) + LaneWord::hh16(w);
+        lq[cq][0] = *reinterpret_cast<const f32x4*>(row);
+        lq[cq][1] = *reinterpret_cast<const f32x4*>(row + 32);
       };
       // CAUSAL, tiles that cross the diagonal (the first BN / BM from q_first): a query before this lane's key
       // gets P = 0.  Counted from the tile's first query, the lane's key of block kb is the first one that
@@ -292,7 +316,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       if constexpr (CAUSAL) {
         diag = n_tiles - 1 - t < C::BN / C::BM;
 #pragma unroll
-        for (int kb = 0; kb < C::KB; ++kb) first_seen[kb] = 64 * pair + 32 * kb + l32 - (n_tiles - 1 - t) * C::BM - 4 * hh;
+        for (int kb = 0; kb < C::KB; ++kb) first_seen[kb] = 64 * pair + 32 * kb + LaneWord::l32(w) - (n_tiles - 1 - t) * C::BM - LaneWord::hh16(w) / 4;
       }
       auto exp_slice = [&](int cq, int kb, int half) {
         float p[4];
@@ -307,7 +331,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
         ph[cq][kb][half] = pack4(p[0], p[1], p[2], p[3]);
         if (half == 1) {
           pa[cq][kb] = join(ph[cq][kb][0], ph[cq][kb][1]);
-          sP[pair][t & 1][2 * kb + cq][lane] = __builtin_bit_cast(u32x4, pa[cq][kb]);
+          *p_at(w, t, 2 * kb + cq) = __builtin_bit_cast(u32x4, pa[cq][kb]);
         }
       };
       lse_of(0);
@@ -324,7 +348,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
     };
     // dK wave, tile u: dP, dS = P (dP - delta) with the partner's P, dK += dS^T Q
     auto dk_step = [&](int u, const __bf16* tQ, const __bf16* tdO, const float* tDelta) {
-      const int rb = rows.fresh();
+      const int rb = rows.fresh(), w = at.fresh();
       f32x16 dp[C::KB];
 #pragma unroll
       for (int kb = 0; kb < C::KB; ++kb) dp[kb] = zero16();
@@ -335,10 +359,11 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       f32x4 dq4[2][2];
       u32x4 pw[2][C::KB];
       auto fetch_of = [&](int cq) {
-        dq4[cq][0] = *reinterpret_cast<const f32x4*>(&tDelta[16 * cq + 4 * hh]);
-        dq4[cq][1] = *reinterpret_cast<const f32x4*>(&tDelta[16 * cq + 8 + 4 * hh]);
+        const char* row = reinterpret_cast<const char*>(tDelta + 16 * cq) + LaneWord::hh16(w);
+        dq4[cq][0] = *reinterpret_cast<const f32x4*>(row);
+        dq4[cq][1] = *reinterpret_cast<const f32x4*>(row + 32);
 #pragma unroll
-        for (int kb = 0; kb < C::KB; ++kb) pw[cq][kb] = sP[pair][u & 1][2 * kb + cq][lane];
+        for (int kb = 0; kb < C::KB; ++kb) pw[cq][kb] = *p_at(w, u, 2 * kb + cq);
       };
       auto ds_slice = [&](int cq, int kb, int half) {
         float ds[4];
@@ -400,18 +425,16 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
 #undef KNAP_ROLE_LOOP
 #undef KNAP_STEP
 
-    __bf16* dst = role == 0 ? dv : dk;
+    const auto rg = make_rsrc((role == 0 ? dv : dk) + (size_t)(it.row0 + kv0) * row_stride + head_off,
+                              (uint32_t)min(L - kv0, C::BN) * row_bytes);
     const float out_scale = role == 0 ? 1.0f : scale;
+    const int w_out = at.fresh();
 #pragma unroll
-    for (int kb = 0; kb < C::KB; ++kb)
+    for (int kb = 0; kb < C::KB; ++kb) {
+      const uint32_t off = (uint32_t)(64 * pair + 32 * kb + LaneWord::l32(w_out)) * row_bytes + (uint32_t)LaneWord::hh16(w_out);
 #pragma unroll
-      for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = kv0 + 64 * pair + 32 * kb + 8 * (r >> 2) + 4 * hh + (r & 3);
-          if (kv < L)
-            dst[(size_t)(it.row0 + kv) * row_stride + head_off + 32 * nb + l32] = (__bf16)(acc[kb][nb][r] * out_scale);
-        }
+      for (int nb = 0; nb < C::NB; ++nb) store_block(rg, off + 64u * nb, acc[kb][nb], out_scale);
+    }
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != kv_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;
