@@ -48,12 +48,13 @@ inline int dq_workgroups_per_cu(int64_t total_tokens, int n_seq, int H, bool cau
 //    1100, 3 heads 158 against 225; but 30000 and 30 of 300, 12 heads 8752 against 8394; half of 60000 tokens in one
 //    sequence, 24 heads 17234 against 16973, 3 heads 2627 against 2464 (of 30000, 12 heads 3047 against 2930; of 20000, 6 heads,
 //    where the GPU is not full, 686 against 755).
-//    Without the mask at d = 128 the line is at an average of 512: above it two pairs win where they pad less and lose
-//    where the lengths are multiples of 256 or one sequence stands out (forward and backward, two against four: 15 of 640
-//    tokens, 24 x 128: 471 against 506 us; but 10 of 1024: 669 against 652; 8 of 1200: 742 against 721; 4405, 619 and 371:
-//    1135 against 1107; 4200 and seven of 300..600, 12 x 128: 611 against 582; 18 of 512: 208 both).  And at 16384 tokens:
-//    beyond, short sequences gain nothing from two pairs (64 of 450, backward, 24 heads 835 against 827, 6 heads 226 against
-//    220; 128 of 450, 24 heads 1619 against 1620), and a long one among them loses (8192 and 45 of 300, 6 heads 779 against 723).
+//    Without the mask at d = 128: up to 16384 tokens at an average below 512 (32 of 450, 24 x 128: 233 against 267 us; but
+//    4405, 619 and 371: 490 against 463; 4200 and seven of 450, 12 x 128: 247 against 229).  Where four pairs would have six
+//    rounds or more, at averages below 3000 (12 of 2600, 24 x 128: 1704 against 1818 us; 17 of 328..4533: 1806 against
+//    1837; 60 of 800: 1011 against 1154; 64 of 450: 409 against 433, with 6 heads and three rounds 122 against 114; 20 of
+//    3000: 3796 against 3778) but those from 512 to 640, which are mostly one long sequence among short ones (16384 and
+//    30 of 300: 5358 against 5117; 65536 and 200 short 84.4 against 81.4 ms; but 60 of 600: 592 against 700 us).  And where
+//    the smaller tiles save a round (15 of 640: 174 against 216 us).
 //  * d = 64, three workgroups of two pairs on a CU: two pairs, unless their rounds are the longer ones (a round of three
 //    takes 1.4 times as long as one of four pairs).  32 of 450 tokens, 48 x 64: 246 against 289 us; 16 of 4096: 6389 against
 //    7163; 65536: 98.1 against 103.3 ms; causal, 20 of 3000: 2637 against 2970 us, 65536: 51.6 against 52.1 ms.  But 6 of 4300,
@@ -63,10 +64,13 @@ inline int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal
   if (total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
   if (d == 64)
     return 1.4 * rounds(total_tokens, n_seq, H, causal, 128, 3 * (int64_t)cus) < rounds(total_tokens, n_seq, H, causal, 256, cus) ? 2 : 4;
-  const int64_t longest_average = causal ? 4096 : 512;
-  const int64_t largest_bag = causal ? 65536 : 16384;
-  if (total_tokens <= largest_bag && total_tokens < longest_average * n_seq) return 2;
-  return 4;
+  const int64_t n = n_seq;
+  if (causal) return total_tokens <= 65536 && total_tokens < 4096 * n ? 2 : 4;
+  if (total_tokens < 512 * n && total_tokens <= 16384) return 2;
+  const double four = rounds(total_tokens, n_seq, H, causal, 256, cus);
+  if (four >= 6.0)
+    return total_tokens < 512 * n || (total_tokens >= 640 * n && total_tokens < 3000 * n) ? 2 : 4;
+  return total_tokens >= 640 * n && rounds(total_tokens, n_seq, H, causal, 128, 2 * (int64_t)cus) < 0.9 * four ? 2 : 4;
 }
 
 // Whether some queue of the backward's kernels may hold more items than workgroups, so that counters of unknown contents
