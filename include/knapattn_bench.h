@@ -14,7 +14,9 @@ extern "C" {
 /* While both are non-NULL, every backward call made by this thread records
  * `start` right before and `stop` right after its dK/dV kernel (the longest
  * kernel of the path) on the call's stream; the dQ kernel, which runs before
- * it, stays outside the pair.  hipEvent_t passed as void*, owned by the
+ * it, stays outside the pair.  Where the items of both kernels share one launch
+ * (bags that fill the GPU a few times), the pair brackets that launch and the
+ * small one in front of it.  hipEvent_t passed as void*, owned by the
  * caller.  Pass NULLs to switch it off.  Not for use under graph capture. */
 void knap_bwd_profile_events(void* start, void* stop);
 

@@ -208,8 +208,14 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   const bool captured = capturing(stream);
   unsigned* counters = captured ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256)
                                 : di->queues + 16u * (g_launches.fetch_add(1u) % ((unsigned)knap::queue_sets() / 2u));
-  const int dq_wg = knap::dq_workgroups_per_cu(total_tokens, n_seq, H, causal, di->cus, di->dq_wg[d == 128]);
+  const int dq_wg = di->dq_wg[d == 128];
   const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
+  if (knap::bwd_joint(total_tokens, n_seq, H, d, causal, di->cus)) {
+    const hipError_t e = knap::launch_joint(args, d, causal, (int)total_tokens, di->cus, captured, static_cast<hipStream_t>(stream),
+                                            g_prof_start, g_prof_stop);
+    if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
+    return KNAP_OK;
+  }
   const int pairs = knap::dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus);
   const hipError_t e = knap::launch_bwd(args, d, causal, pairs, di->cus, dq_wg,
                                         captured && knap::bwd_draws(total_tokens, n_seq, H, causal, pairs, di->cus, di->cus * dq_wg),

@@ -1,6 +1,5 @@
 // The backward's kernels under the causal mask.
-#include "knap_attn_dkdv.h"
-#include "knap_attn_dq.h"
+#include "knap_attn_joint.h"
 
 namespace knap {
 
@@ -10,6 +9,10 @@ hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hip
 
 hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream) {
   return launch_dkdv_m<true>(a, d, pairs, cus, stream);
+}
+
+hipError_t launch_joint_causal(const BwdArgs& a, int d, int T, int cus, hipStream_t stream) {
+  return launch_joint_m<true>(a, d, T, cus, stream);
 }
 
 }  // namespace knap

@@ -108,77 +108,62 @@ struct LaneWord {
   __device__ static __forceinline__ int lane4(int w) { return (w >> 2) & 252; }
 };
 
-template <int D, int PAIRS, bool CAUSAL>
-__global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void attn_bwd_dkdv64_kernel(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-    const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ delta,
-    const int32_t* __restrict__ cu, int n_seq, int H, float scale,
-    __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
-  using C = Bwd2Cfg<D, PAIRS>;
-  extern __shared__ int s_dyn[];
-  int* s_order = s_dyn;
-  int* s_start = s_dyn + n_seq;
-#define KNAP_RING(i)                                                                    \
-  __shared__ __attribute__((aligned(1024))) __bf16 sQ##i[C::TILE_ELEMS];                \
-  __shared__ __attribute__((aligned(1024))) __bf16 sdO##i[C::TILE_ELEMS];               \
-  __shared__ __attribute__((aligned(256))) float sLse##i[64];                           \
-  __shared__ __attribute__((aligned(256))) float sDelta##i[64];
-  KNAP_RING(0) KNAP_RING(1) KNAP_RING(2)
-#undef KNAP_RING
-  __shared__ __attribute__((aligned(256))) float sSink[64];
-  __shared__ __attribute__((aligned(16))) u32x4 sP[C::PAIRS][2][2 * C::KB][64];
+// LDS of a dK/dV workgroup: the ring (i: 0, 1, 2), the P of its pairs, and a place for copies that nobody needs
+struct DkdvLds {
+  __bf16 *q0, *do0, *q1, *do1, *q2, *do2;
+  float *lse0, *delta0, *lse1, *delta1, *lse2, *delta2, *sink;
+  u32x4* p;
+};
 
-  const int T = cu[n_seq];
-  const int n_items = build_schedule<C::BN, C::THREADS, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sP[0][0][0][0]));
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pair = wave & (C::PAIRS - 1);
-  // PAIRS = 2: the two waves of a pair sit on different SIMDs, each next to the waves of the CU's other workgroups; every
-  // other one of those (a half or a third of the grid further on) has the roles the other way round, so that the SIMDs
-  // get waves of either role
-  const int role = (wave / PAIRS) ^ (PAIRS == 2 ? (int)(blockIdx.x * dkdv_workgroups_per_cu(D, PAIRS) / gridDim.x) & 1 : 0);
-  const float c = scale * kLog2e;
-  const size_t row_stride = (size_t)H * D;
-  const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
+// what a lane keeps between key tiles
+template <int D, int PAIRS>
+struct DkdvLane {
+  using C = Bwd2Cfg<D, PAIRS>;
+  static constexpr int ROWS_PER_INSTR = 512 / D;
+  // one instruction copies 1 KB: ROWS_PER_INSTR rows; Q and dO of a tile are dealt to the waves in one or more passes
+  static_assert(C::BM % (2 * PAIRS * ROWS_PER_INSTR) == 0, "a pass of the waves is whole rows of a tile");
+  static constexpr int P_BLOCK = 64 * 16, P_TILE = 2 * C::KB * P_BLOCK, P_PAIR = 2 * P_TILE;     // bytes of sP
   RowReaderX<D> rows;
   ColReaderX<D> cols;
-  rows.init(lane);
-  cols.init(lane);
   // where this lane's 16 bytes of its pair's P lie; its number and its halves are bits of that word, taken out of it where
   // they are needed (a step has no register to spare for each of them)
   LaneWord at;
-  at.word = (int)sizeof(sP[0]) * pair + 16 * lane;
+  uint32_t cp_off;
+  int cp_row0, wave, pair, role;     // wave-uniform
+  __device__ __forceinline__ void init(int lane, int wave_, int role_, uint32_t row_bytes) {
+    wave = wave_;
+    role = role_;
+    pair = wave & (PAIRS - 1);
+    rows.init(lane);
+    cols.init(lane);
+    at.word = P_PAIR * pair + 16 * lane;
+    cp_row0 = wave * ROWS_PER_INSTR;
+    const int cp_row = cp_row0 + lane / Tile<D>::CPR;
+    cp_off = (uint32_t)cp_row * row_bytes + (uint32_t)Tile<D>::chunk_pos(cp_row, lane % Tile<D>::CPR) * 16u;
+  }
+};
 
-  constexpr int ROWS_PER_INSTR = 512 / D;
-  // one instruction copies 1 KB: ROWS_PER_INSTR rows.  Q and dO of a tile are 16 (D = 128) or 8 of them, dealt to
-  // the waves in passes; with eight waves and D = 64 one pass covers both tensors
-  constexpr bool SPLIT = 2 * C::PAIRS * ROWS_PER_INSTR > C::BM;
-  const int cp_row0 = (SPLIT ? wave & 3 : wave) * ROWS_PER_INSTR;
-  const int cp_row = cp_row0 + lane / Tile<D>::CPR;
-  const uint32_t cp_off = (uint32_t)cp_row * row_bytes + (uint32_t)Tile<D>::chunk_pos(cp_row, lane % Tile<D>::CPR) * 16u;
-
-  // work items from this XCD's queue, the next one's ticket drawn behind the item's first loads and put down after
-  // the barrier that every wave reaches with its copy of the old one
-  __shared__ int s_ticket;
-  ItemQueue<0> queue;
-  queue.init(counters, s_start, n_seq, n_items);
-  for (int ticket = queue.first_ticket(); ticket < queue.wide;) {
-    const int w = queue.item(ticket);
-    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
-    WorkItem it = decode_item<C::BN, CAUSAL>(w, cu, n_seq, s_order, s_start);
-    // head and tile come out of a division, i.e. of vector instructions: say that they are wave-uniform, so
-    // that every base address below lives in scalar registers
-    it.head = __builtin_amdgcn_readfirstlane(it.head);
-    it.tile = __builtin_amdgcn_readfirstlane(it.tile);
-    const int L = it.len;
+// One key tile of an item.  `draw` is called behind its first loads, `drawn` when they have landed.
+template <int D, int PAIRS, bool CAUSAL, class Draw, class Drawn>
+__device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, const DkdvLane<D, PAIRS>& me, const WorkItem& it,
+                                          int kv_tile, Draw draw, Drawn drawn) {
+    using C = Bwd2Cfg<D, PAIRS>;
+    using W = DkdvLane<D, PAIRS>;
+    const auto *q = g.q, *k = g.k, *v = g.v, *dout = g.dout;
+    const float *lse2 = g.lse2, *delta = g.delta;
+    const int L = it.len, T = g.T;
+    const float scale = g.scale, c = scale * kLog2e;
+    const size_t row_stride = (size_t)g.H * D;
+    const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
     const size_t head_off = (size_t)it.head * D;
-    // CAUSAL: the item is the pair of key tiles {p, kv_tiles - 1 - p} (equal cost together, see build_schedule),
-    // the one that meets more queries first; the middle tile of an odd count stands alone
-    const int kv_tiles = (L + C::BN - 1) / C::BN;
-    int sub = 0;
-  second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
-    const int kv_tile = (!CAUSAL || sub == 0) ? it.tile : kv_tiles - 1 - it.tile;
+    const auto& rows = me.rows;
+    const auto& cols = me.cols;
+    const auto& at = me.at;
+    const uint32_t cp_off = me.cp_off;
+    const int cp_row0 = me.cp_row0, wave = me.wave, pair = me.pair, role = me.role;
+    __bf16 *const sQ0 = lds.q0, *const sdO0 = lds.do0, *const sQ1 = lds.q1, *const sdO1 = lds.do1, *const sQ2 = lds.q2, *const sdO2 = lds.do2;
+    float *const sLse0 = lds.lse0, *const sDelta0 = lds.delta0, *const sLse1 = lds.lse1, *const sDelta1 = lds.delta1,
+          *const sLse2 = lds.lse2, *const sDelta2 = lds.delta2, *const sSink = lds.sink;
     const int kv0 = kv_tile * C::BN;
     // queries this key tile meets: rows q_first .. L - 1 of the sequence; tiles and rows below count from q_first
     const int q_first = CAUSAL ? kv0 : 0;
@@ -224,18 +209,13 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
       }
       const auto rq = make_rsrc(q_base + (size_t)q0 * row_stride, (uint32_t)n_rows * row_bytes);
       const auto rd = make_rsrc(do_base + (size_t)q0 * row_stride, (uint32_t)n_rows * row_bytes);
-      if constexpr (SPLIT) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(wave < 4 ? rq : rd,
-            (__attribute__((address_space(3))) void*)((wave < 4 ? tQ : tdO) + cp_row0 * Tile<D>::LD), 16, (int)cp_off, 0, 0, 0);
-      } else {
 #pragma unroll
-        for (int r = 0; r < C::BM; r += 2 * C::PAIRS * ROWS_PER_INSTR) {
-          uint32_t off = cp_off;
-          if (r) asm volatile("" : "+v"(off));     // formed here, not kept in a register of its own through the loop
-          off += (uint32_t)r * row_bytes;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (__attribute__((address_space(3))) void*)(tQ + (cp_row0 + r) * Tile<D>::LD), 16, (int)off, 0, 0, 0);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (__attribute__((address_space(3))) void*)(tdO + (cp_row0 + r) * Tile<D>::LD), 16, (int)off, 0, 0, 0);
-        }
+      for (int r = 0; r < C::BM; r += 2 * PAIRS * W::ROWS_PER_INSTR) {
+        uint32_t off = cp_off;
+        if (r) asm volatile("" : "+v"(off));     // formed here, not kept in a register of its own through the loop
+        off += (uint32_t)r * row_bytes;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (__attribute__((address_space(3))) void*)(tQ + (cp_row0 + r) * Tile<D>::LD), 16, (int)off, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (__attribute__((address_space(3))) void*)(tdO + (cp_row0 + r) * Tile<D>::LD), 16, (int)off, 0, 0, 0);
       }
       const float* src = wave == 0 ? lse_base + q0 : delta_base + q0;
       float* dst = wave == 0 ? tLse : wave == 1 ? tDelta : sSink;
@@ -289,7 +269,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
 
     // 16 bytes of this lane in block `b` of its pair's P of tile t
     auto p_at = [&](int w, int t, int b) {
-      return reinterpret_cast<u32x4*>(reinterpret_cast<char*>(&sP[0][0][b][0]) + (w + (t & 1) * (int)sizeof(sP[0][0])));
+      return reinterpret_cast<u32x4*>(reinterpret_cast<char*>(lds.p) + W::P_BLOCK * b + (w + (t & 1) * W::P_TILE));
     };
     // dV wave, tile t: S, P, hand P over, dV += P^T dO
     auto dv_step = [&](int t, const __bf16* tQ, const __bf16* tdO, const float* tLse) {
@@ -416,16 +396,16 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
     } while (0)
 
     issue_tile(0, sQ0, sdO0, sLse0, sDelta0);
-    if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
+    draw();
     step_sync();      // tile 0 has landed (and the K / V rows requested before it)
-    if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket);
+    drawn();
 
     if (role == 0) KNAP_ROLE_LOOP(0);
     else KNAP_ROLE_LOOP(1);
 #undef KNAP_ROLE_LOOP
 #undef KNAP_STEP
 
-    const auto rg = make_rsrc((role == 0 ? dv : dk) + (size_t)(it.row0 + kv0) * row_stride + head_off,
+    const auto rg = make_rsrc((role == 0 ? g.dv : g.dk) + (size_t)(it.row0 + kv0) * row_stride + head_off,
                               (uint32_t)min(L - kv0, C::BN) * row_bytes);
     const float out_scale = role == 0 ? 1.0f : scale;
     const int w_out = at.fresh();
@@ -435,6 +415,64 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
 #pragma unroll
       for (int nb = 0; nb < C::NB; ++nb) store_block(rg, off + 64u * nb, acc[kb][nb], out_scale);
     }
+}
+
+template <int D, int PAIRS, bool CAUSAL>
+__global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void attn_bwd_dkdv64_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+    const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ delta,
+    const int32_t* __restrict__ cu, int n_seq, int H, float scale,
+    __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
+  using C = Bwd2Cfg<D, PAIRS>;
+  extern __shared__ int s_dyn[];
+  int* s_order = s_dyn;
+  int* s_start = s_dyn + n_seq;
+#define KNAP_RING(i)                                                                    \
+  __shared__ __attribute__((aligned(1024))) __bf16 sQ##i[C::TILE_ELEMS];                \
+  __shared__ __attribute__((aligned(1024))) __bf16 sdO##i[C::TILE_ELEMS];               \
+  __shared__ __attribute__((aligned(256))) float sLse##i[64];                           \
+  __shared__ __attribute__((aligned(256))) float sDelta##i[64];
+  KNAP_RING(0) KNAP_RING(1) KNAP_RING(2)
+#undef KNAP_RING
+  __shared__ __attribute__((aligned(256))) float sSink[64];
+  __shared__ __attribute__((aligned(16))) u32x4 sP[C::PAIRS][2][2 * C::KB][64];
+
+  const int T = cu[n_seq];
+  const int n_items = build_schedule<C::BN, C::THREADS, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sP[0][0][0][0]));
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // PAIRS = 2: the two waves of a pair sit on different SIMDs, each next to the waves of the CU's other workgroups; every
+  // other one of those (a half or a third of the grid further on) has the roles the other way round, so that the SIMDs
+  // get waves of either role
+  const int role = (wave / PAIRS) ^ (PAIRS == 2 ? (int)(blockIdx.x * dkdv_workgroups_per_cu(D, PAIRS) / gridDim.x) & 1 : 0);
+  const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
+  DkdvLane<D, PAIRS> me;
+  me.init(lane, wave, role, row_bytes);
+  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, const_cast<float*>(lse2), const_cast<float*>(delta), nullptr, dk, dv, T, H, scale};
+  const DkdvLds lds = {sQ0, sdO0, sQ1, sdO1, sQ2, sdO2, sLse0, sDelta0, sLse1, sDelta1, sLse2, sDelta2, sSink, &sP[0][0][0][0]};
+
+  // work items from this XCD's queue, the next one's ticket drawn behind the item's first loads and put down after
+  // the barrier that every wave reaches with its copy of the old one
+  __shared__ int s_ticket;
+  ItemQueue<0> queue;
+  queue.init(counters, s_start, n_seq, n_items);
+  for (int ticket = queue.first_ticket(); ticket < queue.wide;) {
+    const int w = queue.item(ticket);
+    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
+    WorkItem it = decode_item<C::BN, CAUSAL>(w, cu, n_seq, s_order, s_start);
+    // head and tile come out of a division, i.e. of vector instructions: say that they are wave-uniform, so
+    // that every base address below lives in scalar registers
+    it.head = __builtin_amdgcn_readfirstlane(it.head);
+    it.tile = __builtin_amdgcn_readfirstlane(it.tile);
+    // CAUSAL: the item is the pair of key tiles {p, kv_tiles - 1 - p} (equal cost together, see build_schedule),
+    // the one that meets more queries first; the middle tile of an odd count stands alone
+    const int kv_tiles = (it.len + C::BN - 1) / C::BN;
+    int sub = 0;
+  second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
+    dkdv_tile<D, PAIRS, CAUSAL>(g, lds, me, it, (!CAUSAL || sub == 0) ? it.tile : kv_tiles - 1 - it.tile,
+        [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
+        [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket); });
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != kv_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;
@@ -457,8 +495,8 @@ static hipError_t launch_dkdv_t(const BwdArgs& a, int cus, hipStream_t stream) {
 
 template <bool CAUSAL>
 static hipError_t launch_dkdv_m(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream) {
-  if (pairs == 2) return d == 64 ? launch_dkdv_t<64, 2, CAUSAL>(a, cus, stream) : launch_dkdv_t<128, 2, CAUSAL>(a, cus, stream);
-  return d == 64 ? launch_dkdv_t<64, 4, CAUSAL>(a, cus, stream) : launch_dkdv_t<128, 4, CAUSAL>(a, cus, stream);
+  if (d == 64) return launch_dkdv_t<64, 2, CAUSAL>(a, cus, stream);
+  return pairs == 2 ? launch_dkdv_t<128, 2, CAUSAL>(a, cus, stream) : launch_dkdv_t<128, 4, CAUSAL>(a, cus, stream);
 }
 
 }  // namespace knap

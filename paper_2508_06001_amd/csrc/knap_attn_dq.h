@@ -22,60 +22,56 @@ struct DqCfg {
   static constexpr int TILE_ELEMS = BN * Tile<D>::LD;
 };
 
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-    const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ lse2_out, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
-    __bf16* __restrict__ dq, unsigned* __restrict__ counters) {
-  using C = DqCfg<D>;
-  extern __shared__ int s_dyn[];
-  int* s_order = s_dyn;
-  int* s_start = s_dyn + n_seq;
-  // K is read row-wise (S^T) and transposed (dQ^T), V row-wise (dP^T); two buffers each, as
-  // separate arrays so that reads of one are known not to depend on the copy into the other
-  __shared__ __attribute__((aligned(1024))) __bf16 sK0[C::TILE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) __bf16 sK1[C::TILE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) __bf16 sV0[C::TILE_ELEMS];
-  __shared__ __attribute__((aligned(1024))) __bf16 sV1[C::TILE_ELEMS];
-  static_assert(sizeof(__bf16) * C::TILE_ELEMS >= sizeof(int) * kThreads, "scan scratch must fit in a tile");
+struct DqLds {
+  __bf16 *k0, *k1, *v0, *v1;
+};
 
-  const int T = cu[n_seq];
-  const int n_items = build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wave_u = CAUSAL ? __builtin_amdgcn_readfirstlane(wave) : 0;   // the same number, known to be wave-uniform
-  const int l32 = lane & 31;
-  const int hh = lane >> 5;
-  const float c = scale * kLog2e;
-  const size_t row_stride = (size_t)H * D;
-  const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
+// what a lane keeps between query tiles
+template <int D>
+struct DqLane {
   RowReader<D> rows;     // K and V tile rows -> A operands of S^T and dP^T
   ColReader<D> cols;     // K tile columns -> A operands of dQ^T += K^T dS^T
-  rows.init(lane);
-  cols.init(lane);
+  int lane, wave, wave_u;       // wave_u: the same number as wave, known to be wave-uniform (CAUSAL only)
+  __device__ __forceinline__ void init(int lane_, int wave_, int wave_u_) {
+    lane = lane_;
+    wave = wave_;
+    wave_u = wave_u_;
+    rows.init(lane);
+    cols.init(lane);
+  }
+};
 
-  // Work items come from this XCD's queue.  The ticket for the NEXT item is requested right
-  // after the item's first loads (vector-memory operations complete in issue order: requested
-  // before them, the slow counter update would hold up the whole prologue) and only looked at
-  // when the item is done, so the counter's latency is never waited for.
-  __shared__ int s_ticket;
-  constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a wide one
-  ItemQueue<SPLIT> queue;
-  queue.init(counters, s_start, n_seq, n_items);
-  int ticket = queue.first_ticket();
-  while (ticket < queue.wide) {
-    const int w = queue.item(ticket);
-    const WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
-    const int L = it.len;
+// delta = sum_c dO_c O_c of a lane's query: the lane holds half of the row's elements (8 of every 16),
+// its partner at lane ^ 32 the other half
+template <int D>
+__device__ __forceinline__ float row_delta(const bf16x8 (&dof)[D / 16], const bf16x8 (&of)[D / 16]) {
+  float dl = 0.f;
+#pragma unroll
+  for (int cc = 0; cc < D / 16; ++cc)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dl = __builtin_fmaf((float)dof[cc][e], (float)of[cc][e], dl);
+  return dl + xor32(dl);
+}
+
+// One query tile (128 rows) of an item.  DELTA: delta and the LSE in base 2 are formed here and handed on in memory; else
+// they are read from there.  `draw` is called behind the first loads.
+template <int D, bool CAUSAL, bool DELTA, class Draw>
+__device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q_tile, Draw draw) {
+    using C = DqCfg<D>;
+    const auto *q = g.q, *k = g.k, *v = g.v, *out = g.out, *dout = g.dout;
+    const float* lse = g.lse;
+    float *delta = g.delta, *lse2_out = g.lse2;
+    __bf16* dq = g.dq;
+    const int L = it.len, T = g.T;
+    const float scale = g.scale, c = scale * kLog2e;
+    const size_t row_stride = (size_t)g.H * D;
+    const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
     const size_t head_off = (size_t)it.head * D;
-    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
-    // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
-    const int q_tiles = (L + C::BM - 1) / C::BM;
-    int sub = 0;
-  second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
-    const int q_tile = !CAUSAL ? it.tile : sub == 0 ? q_tiles - 1 - it.tile : it.tile;
+    const auto& rows = me.rows;
+    const auto& cols = me.cols;
+    const int lane = me.lane, wave = me.wave, l32 = lane & 31, hh = lane >> 5;
+    __bf16 *const sK0 = lds.k0, *const sK1 = lds.k1, *const sV0 = lds.v0, *const sV1 = lds.v1;
+    const int wave_u = me.wave_u;
     const int q0 = q_tile * C::BM;
     const int q_row = q0 + wave * 32 + l32;
     const bool q_valid = q_row < L;
@@ -91,28 +87,31 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
       const uint32_t bytes = (uint32_t)min(L - q0, C::BM) * row_bytes;
       const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
       const auto rd = make_rsrc(dout + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
-      const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
+      const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);   // DELTA only
       const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
       bf16x8 of[C::KC];
 #pragma unroll
       for (int cc = 0; cc < C::KC; ++cc) {
         qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
         dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
-        of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+        if constexpr (DELTA) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
       }
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dl = __builtin_fmaf((float)dof[cc][e], (float)of[cc][e], dl);
-      dl += xor32(dl);
+      if constexpr (DELTA) dl = row_delta<D>(dof, of);
     }
     // per-lane scalars of this lane's query; +inf LSE turns rows past the end into P = 0
     const int q_idx = q_valid ? q_row : 0;
-    const float lse_raw = lse[(size_t)it.head * T + it.row0 + q_idx];
-    const float lse2 = q_valid ? lse_raw * kLog2e : INFINITY;
-    if (q_valid && hh == 0) {     // for the dK/dV kernel: delta, and the LSE in base 2 (it copies both straight into LDS)
-      delta[(size_t)it.head * T + it.row0 + q_row] = dl;
-      lse2_out[(size_t)it.head * T + it.row0 + q_row] = lse_raw * kLog2e;
+    const size_t row_at = (size_t)it.head * T + it.row0 + q_idx;
+    float lse2;
+    if constexpr (DELTA) {
+      const float own = lse[row_at] * kLog2e;
+      lse2 = q_valid ? own : INFINITY;
+      if (q_valid && hh == 0) {     // for the dK/dV kernel: delta, and the LSE in base 2 (it copies both straight into LDS)
+        delta[row_at] = dl;
+        lse2_out[row_at] = own;
+      }
+    } else {
+      dl = delta[row_at];
+      lse2 = q_valid ? lse2_out[row_at] : INFINITY;
     }
 
     f32x16 acc[C::DB];
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 
     load_tile(0, sK0, sV0);    // a barrier stands between the last reads of either buffer (or the schedule build) and this
     wait_async_loads();
-    if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
+    draw();
     __syncthreads();
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> ragged_end{};
@@ -226,6 +225,195 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 #pragma unroll
       for (int db = 0; db < C::DB; ++db) store_block(rg, off + 64u * db, acc[db], scale);
     }
+}
+
+// 64 query rows, from q0 on: waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the
+// second 32; the two gradients are added through LDS at the end.
+template <int D, bool CAUSAL, bool DELTA>
+__device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q0) {
+    using C = DqCfg<D>;
+    const auto *q = g.q, *k = g.k, *v = g.v, *out = g.out, *dout = g.dout;
+    const float* lse = g.lse;
+    float *delta = g.delta, *lse2_out = g.lse2;
+    __bf16* dq = g.dq;
+    const int L = it.len, T = g.T;
+    const float scale = g.scale, c = scale * kLog2e;
+    const size_t row_stride = (size_t)g.H * D;
+    const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
+    const size_t head_off = (size_t)it.head * D;
+    const auto& rows = me.rows;
+    const auto& cols = me.cols;
+    const int lane = me.lane, wave = me.wave, l32 = lane & 31, hh = lane >> 5;
+    __bf16 *const sK0 = lds.k0, *const sK1 = lds.k1, *const sV0 = lds.v0, *const sV1 = lds.v1;
+    const int rb = wave & 1;
+    const int kh_u = __builtin_amdgcn_readfirstlane(wave >> 1), rb_u = __builtin_amdgcn_readfirstlane(rb);
+    const int q_row = q0 + 32 * rb + l32;
+    const bool q_valid = q_row < L;
+    const int kv_end = CAUSAL ? min(L, q0 + 64) : L;
+    const int n_tiles = (kv_end + C::BN - 1) / C::BN;
+    const int first_masked = CAUSAL ? q0 / C::BN : L / C::BN;
+    const int kv_lim = CAUSAL ? q_row + 1 : L;
+    const __bf16* k_base = k + (size_t)it.row0 * row_stride + head_off;
+    const __bf16* v_base = v + (size_t)it.row0 * row_stride + head_off;
+    auto load_tile = [&](int t, __bf16* dK, __bf16* dV) {
+      const int kv0 = t * C::BN;
+      const uint32_t bytes = (uint32_t)max(0, min(kv_end - kv0, C::BN)) * row_bytes;
+      tile_load_async<D>(dK, make_rsrc(k_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
+      tile_load_async<D>(dV, make_rsrc(v_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
+    };
+    const uint32_t off = (uint32_t)(32 * rb + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+    const size_t q_at = (size_t)(it.row0 + q0) * row_stride + head_off;
+    const uint32_t bytes = (uint32_t)min(L - q0, 64) * row_bytes;
+    bf16x8 qf[C::KC], dof[C::KC];
+    float dl = 0.f;
+    {
+      const auto rq = make_rsrc(q + q_at, bytes);
+      const auto rd = make_rsrc(dout + q_at, bytes);
+      const auto ro = make_rsrc(out + q_at, bytes);
+      bf16x8 of[C::KC];
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) {
+        qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
+        dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
+        if constexpr (DELTA) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+      }
+      load_tile(0, sK0, sV0);
+      if constexpr (DELTA) dl = row_delta<D>(dof, of);
+    }
+    const size_t row_at = (size_t)it.head * T + it.row0 + (q_valid ? q_row : 0);
+    float lse2;
+    if constexpr (DELTA) {
+      const float own = lse[row_at] * kLog2e;
+      lse2 = q_valid ? own : INFINITY;
+      if (q_valid && hh == 0 && kh_u == 0) {
+        delta[row_at] = dl;
+        lse2_out[row_at] = own;
+      }
+    } else {
+      dl = delta[row_at];
+      lse2 = q_valid ? lse2_out[row_at] : INFINITY;
+    }
+    f32x16 acc[C::DB];
+#pragma unroll
+    for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
+    wait_async_loads();
+    lds_barrier();
+
+    auto half_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
+      load_tile(t + 1, nK, nV);
+      const int k0 = t * C::BN + 32 * kh_u;
+      if (!(CAUSAL && k0 > q0 + 32 * rb_u + 31)) {
+        f32x16 s = zero16(), dp = zero16();
+#pragma unroll
+        for (int cc = 0; cc < C::KC; ++cc) {
+          s = mfma32(rows.get(tK, 32 * kh_u, cc), qf[cc], s);
+          dp = mfma32(rows.get(tV, 32 * kh_u, cc), dof[cc], dp);
+        }
+        bf16x8 kt0[C::DB];
+#pragma unroll
+        for (int db = 0; db < C::DB; ++db) kt0[db] = cols.get(tK, 32 * kh_u, db);
+        KNAP_STREAM_READS(2 * C::KC, 1, 4);
+        KNAP_SCHED_FENCE();
+        float ds[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(__builtin_fmaf(s[r], c, -lse2)) * (dp[r] - dl);
+        if (t >= first_masked) {
+          const int seen = kv_lim - k0 - 4 * hh;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ds[r] = 8 * (r >> 2) + (r & 3) < seen ? ds[r] : 0.f;
+        }
+        const bf16x8 d0 = pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+        const bf16x8 d1 = pack8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
+        KNAP_SCHED_FENCE();
+#pragma unroll
+        for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(kt0[db], d0, acc[db]);
+#pragma unroll
+        for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(cols.get(tK, 32 * kh_u + 16, db), d1, acc[db]);
+        KNAP_SGB(KNAP_SG_DS_READ, 2 * C::DB);          // the second chunk's K^T fragments go out first
+        KNAP_SGB(KNAP_SG_MFMA, 2 * C::DB);
+        KNAP_SCHED_FENCE();
+      }
+      wait_async_loads();
+      lds_barrier();
+    };
+    for (int t = 0; t < n_tiles; t += 2) {
+      half_tile(t, sK0, sV0, sK1, sV1);
+      if (t + 1 < n_tiles) half_tile(t + 1, sK1, sV1, sK0, sV0);
+    }
+
+    float* part_acc = reinterpret_cast<float*>(rb_u == 0 ? sK1 : sV1);
+    if (kh_u == 1) {
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = {acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]};
+          *reinterpret_cast<f32x4*>(part_acc + ((4 * db + g) * 64 + lane) * 4) = x;
+        }
+    }
+    lds_barrier();
+    if (kh_u == 0) {
+      const auto rg = make_rsrc(dq + q_at, bytes);
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(part_acc + ((4 * db + g) * 64 + lane) * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[db][4 * g + e] += x[e];
+        }
+        store_block(rg, off + 64u * db, acc[db], scale);
+      }
+    }
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+    const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ lse2_out, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
+    __bf16* __restrict__ dq, unsigned* __restrict__ counters) {
+  using C = DqCfg<D>;
+  extern __shared__ int s_dyn[];
+  int* s_order = s_dyn;
+  int* s_start = s_dyn + n_seq;
+  // K is read row-wise (S^T) and transposed (dQ^T), V row-wise (dP^T); two buffers each, as
+  // separate arrays so that reads of one are known not to depend on the copy into the other
+  __shared__ __attribute__((aligned(1024))) __bf16 sK0[C::TILE_ELEMS];
+  __shared__ __attribute__((aligned(1024))) __bf16 sK1[C::TILE_ELEMS];
+  __shared__ __attribute__((aligned(1024))) __bf16 sV0[C::TILE_ELEMS];
+  __shared__ __attribute__((aligned(1024))) __bf16 sV1[C::TILE_ELEMS];
+  static_assert(sizeof(__bf16) * C::TILE_ELEMS >= sizeof(int) * kThreads, "scan scratch must fit in a tile");
+
+  const int T = cu[n_seq];
+  const int n_items = build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  DqLane<D> me;
+  me.init(lane, wave, CAUSAL ? __builtin_amdgcn_readfirstlane(wave) : 0);
+  const BwdPtrs g = {q, k, v, out, dout, lse, lse2_out, delta, dq, nullptr, nullptr, T, H, scale};
+  const DqLds lds = {sK0, sK1, sV0, sV1};
+
+  // Work items come from this XCD's queue.  The ticket for the NEXT item is requested right
+  // after the item's first loads (vector-memory operations complete in issue order: requested
+  // before them, the slow counter update would hold up the whole prologue) and only looked at
+  // when the item is done, so the counter's latency is never waited for.
+  __shared__ int s_ticket;
+  constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a wide one
+  ItemQueue<SPLIT> queue;
+  queue.init(counters, s_start, n_seq, n_items);
+  int ticket = queue.first_ticket();
+  while (ticket < queue.wide) {
+    const int w = queue.item(ticket);
+    const WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
+    // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
+    const int q_tiles = (it.len + C::BM - 1) / C::BM;
+    int sub = 0;
+  second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
+    dq_tile<D, CAUSAL, true>(g, lds, me, it, !CAUSAL ? it.tile : sub == 0 ? q_tiles - 1 - it.tile : it.tile,
+                             [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); });
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != q_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;
@@ -238,138 +426,16 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
   }
 
-  // Narrow items: 64 queries, as in the forward kernel.  Waves w and w + 2 share 32 queries, one taking the first 32
-  // keys of every tile, the other the second 32; the two gradients are added through LDS at the end.
+  // Narrow items: 64 queries, as in the forward kernel.
   if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
-  const int rb = wave & 1;
-  const int kh_u = __builtin_amdgcn_readfirstlane(wave >> 1), rb_u = __builtin_amdgcn_readfirstlane(rb);
   for (int part = ticket - queue.wide; part < queue.parts;) {
     const int p = queue.part0 + part;
     const WorkItem it = decode_item<C::BM, CAUSAL>(queue.n_wide + p / SPLIT, cu, n_seq, s_order, s_start);
-    const int L = it.len;
-    const size_t head_off = (size_t)it.head * D;
-    const int q_tiles = (L + C::BM - 1) / C::BM;
+    const int q_tiles = (it.len + C::BM - 1) / C::BM;
     const int member = (p % SPLIT) >> 1;
     const int q0 = __builtin_amdgcn_readfirstlane((!CAUSAL ? it.tile : member == 0 ? q_tiles - 1 - it.tile : it.tile) * C::BM + 64 * (p & 1));
-    const bool exists = q0 < L && !(CAUSAL && member == 1 && it.tile == q_tiles - 1 - it.tile);
-    if (exists) {
-      const int q_row = q0 + 32 * rb + l32;
-      const bool q_valid = q_row < L;
-      const int kv_end = CAUSAL ? min(L, q0 + 64) : L;
-      const int n_tiles = (kv_end + C::BN - 1) / C::BN;
-      const int first_masked = CAUSAL ? q0 / C::BN : L / C::BN;
-      const int kv_lim = CAUSAL ? q_row + 1 : L;
-      const __bf16* k_base = k + (size_t)it.row0 * row_stride + head_off;
-      const __bf16* v_base = v + (size_t)it.row0 * row_stride + head_off;
-      auto load_tile = [&](int t, __bf16* dK, __bf16* dV) {
-        const int kv0 = t * C::BN;
-        const uint32_t bytes = (uint32_t)max(0, min(kv_end - kv0, C::BN)) * row_bytes;
-        tile_load_async<D>(dK, make_rsrc(k_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
-        tile_load_async<D>(dV, make_rsrc(v_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
-      };
-      const uint32_t off = (uint32_t)(32 * rb + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
-      const size_t q_at = (size_t)(it.row0 + q0) * row_stride + head_off;
-      const uint32_t bytes = (uint32_t)min(L - q0, 64) * row_bytes;
-      bf16x8 qf[C::KC], dof[C::KC];
-      float dl = 0.f;
-      {
-        const auto rq = make_rsrc(q + q_at, bytes);
-        const auto rd = make_rsrc(dout + q_at, bytes);
-        const auto ro = make_rsrc(out + q_at, bytes);
-        bf16x8 of[C::KC];
-#pragma unroll
-        for (int cc = 0; cc < C::KC; ++cc) {
-          qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
-          dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
-          of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
-        }
-        load_tile(0, sK0, sV0);
-#pragma unroll
-        for (int cc = 0; cc < C::KC; ++cc)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dl = __builtin_fmaf((float)dof[cc][e], (float)of[cc][e], dl);
-        dl += xor32(dl);
-      }
-      const size_t row_at = (size_t)it.head * T + it.row0 + (q_valid ? q_row : 0);
-      const float lse_raw = lse[row_at];
-      const float lse2 = q_valid ? lse_raw * kLog2e : INFINITY;
-      if (q_valid && hh == 0 && kh_u == 0) {
-        delta[row_at] = dl;
-        lse2_out[row_at] = lse_raw * kLog2e;
-      }
-      f32x16 acc[C::DB];
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
-      wait_async_loads();
-      lds_barrier();
-
-      auto half_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
-        load_tile(t + 1, nK, nV);
-        const int k0 = t * C::BN + 32 * kh_u;
-        if (!(CAUSAL && k0 > q0 + 32 * rb_u + 31)) {
-          f32x16 s = zero16(), dp = zero16();
-#pragma unroll
-          for (int cc = 0; cc < C::KC; ++cc) {
-            s = mfma32(rows.get(tK, 32 * kh_u, cc), qf[cc], s);
-            dp = mfma32(rows.get(tV, 32 * kh_u, cc), dof[cc], dp);
-          }
-          bf16x8 kt0[C::DB];
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db) kt0[db] = cols.get(tK, 32 * kh_u, db);
-          KNAP_STREAM_READS(2 * C::KC, 1, 4);
-          KNAP_SCHED_FENCE();
-          float ds[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(__builtin_fmaf(s[r], c, -lse2)) * (dp[r] - dl);
-          if (t >= first_masked) {
-            const int seen = kv_lim - k0 - 4 * hh;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) ds[r] = 8 * (r >> 2) + (r & 3) < seen ? ds[r] : 0.f;
-          }
-          const bf16x8 d0 = pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
-          const bf16x8 d1 = pack8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
-          KNAP_SCHED_FENCE();
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(kt0[db], d0, acc[db]);
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(cols.get(tK, 32 * kh_u + 16, db), d1, acc[db]);
-          KNAP_SGB(KNAP_SG_DS_READ, 2 * C::DB);          // the second chunk's K^T fragments go out first
-          KNAP_SGB(KNAP_SG_MFMA, 2 * C::DB);
-          KNAP_SCHED_FENCE();
-        }
-        wait_async_loads();
-        lds_barrier();
-      };
-      for (int t = 0; t < n_tiles; t += 2) {
-        half_tile(t, sK0, sV0, sK1, sV1);
-        if (t + 1 < n_tiles) half_tile(t + 1, sK1, sV1, sK0, sV0);
-      }
-
-      float* part_acc = reinterpret_cast<float*>(rb_u == 0 ? sK1 : sV1);
-      if (kh_u == 1) {
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 x = {acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]};
-            *reinterpret_cast<f32x4*>(part_acc + ((4 * db + g) * 64 + lane) * 4) = x;
-          }
-      }
-      lds_barrier();
-      if (kh_u == 0) {
-        const auto rg = make_rsrc(dq + q_at, bytes);
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(part_acc + ((4 * db + g) * 64 + lane) * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[db][4 * g + e] += x[e];
-          }
-          store_block(rg, off + 64u * db, acc[db], scale);
-        }
-      }
-    }
+    const bool exists = q0 < it.len && !(CAUSAL && member == 1 && it.tile == q_tiles - 1 - it.tile);
+    if (exists) dq_part<D, CAUSAL, true>(g, lds, me, it, q0);
     if (!queue.draws) return;         // every part was a first ticket
     if (tid == 0) s_ticket = drawn_ticket(queue, atomicAdd(queue.ctr, 1u));
     lds_barrier();                    // (and part_acc is no longer read)
@@ -380,10 +446,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
 
 template <bool CAUSAL>
 static hipError_t launch_dq_m(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream) {
-  size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
-  // two workgroups on every CU where three would fit: with 24 KB more LDS each, a third does not (left to itself, a grid of
-  // two for every CU is placed three on one and one on another: 12000 causal tokens, 12 x 64, 409 us against 352)
-  if (d == 64 && wg_per_cu == 2 && dyn < 24 * 1024) dyn = 24 * 1024;
+  const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
   auto* kernel = d == 64 ? attn_bwd_dq_kernel<64, CAUSAL> : attn_bwd_dq_kernel<128, CAUSAL>;
   hipLaunchKernelGGL(kernel, dim3(cus * wg_per_cu), dim3(kThreads), dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k,
                      (const __bf16*)a.v, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,

@@ -1,0 +1,172 @@
+// Backward of bags whose items fill the GPU only a few times: the items of the dK/dV kernel (128 keys, two wave pairs) and of
+// the dQ kernel (128 queries) in one launch, so that there is one thin last round instead of two and the second kind starts
+// where the first one runs out.  delta and the LSE in base 2, which both need, come from a kernel of their own in front
+// (otherwise the dQ kernel forms them on the way; 3 us where out is still in the caches).  bwd_joint() chooses, and has both
+// sides measured.  One text, compiled for either mask in a translation unit of its own.
+#pragma once
+
+#include "knap_attn_dkdv.h"
+#include "knap_attn_dq.h"
+
+namespace knap {
+
+// delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once.  The sums run in the order in which
+// the dQ kernel forms them.
+template <int D>
+__global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
+    const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ lse2, const int32_t* __restrict__ cu, int n_seq, int H) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
+  const int t0 = blockIdx.x * 128, head = blockIdx.y, T = cu[n_seq];
+  if (t0 >= T) return;
+  const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
+  const size_t at = ((size_t)t0 * H + head) * D;
+  const uint32_t bytes = (uint32_t)min(T - t0, 128) * row_bytes;
+  const auto ro = make_rsrc(out + at, bytes);
+  const auto rd = make_rsrc(dout + at, bytes);
+  const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+  bf16x8 of[D / 16], dof[D / 16];
+#pragma unroll
+  for (int cc = 0; cc < D / 16; ++cc) {
+    of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+    dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
+  }
+  const float dl = row_delta<D>(dof, of);
+  const int t = t0 + wave * 32 + l32;
+  if (t < T && hh == 0) {
+    const size_t row_at = (size_t)head * T + t;
+    delta[row_at] = dl;
+    lse2[row_at] = lse[row_at] * kLog2e;
+  }
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
+    float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
+    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
+  using KV = Bwd2Cfg<D, 2>;
+  constexpr int BM = 128;                          // rows of a tile of either kind
+  static_assert(KV::BN == BM && DqCfg<D>::BM == BM, "one schedule serves both");
+  extern __shared__ int s_dyn[];
+  int* s_order = s_dyn;
+  int* s_start = s_dyn + n_seq;
+  int* s_mine = s_start + n_seq + 1;
+  // Four arrays that hold a K or V tile each for one kind, and a tile of Q and of dO (or the P of the pairs) for the other:
+  // whatever is copied into while another is read is an array of its own, so that the reads are known not to depend on it.
+  constexpr int HALF = KV::TILE_ELEMS, P_ELEMS = 2 * DkdvLane<D, 2>::P_PAIR / (int)sizeof(__bf16);
+  static_assert(DqCfg<D>::TILE_ELEMS == 2 * HALF && P_ELEMS >= 2 * HALF, "the arrays serve both kinds");
+  __shared__ __attribute__((aligned(1024))) __bf16 sA0[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA1[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA2[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA3[P_ELEMS];
+  __shared__ __attribute__((aligned(256))) float sLse0[64], sDelta0[64], sLse1[64], sDelta1[64], sLse2[64], sDelta2[64], sSink[64];
+  __shared__ int s_ticket;
+
+  const int T = cu[n_seq];
+  build_schedule<BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sA0[0]));
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int role = (wave >> 1) ^ ((int)(blockIdx.x * dkdv_workgroups_per_cu(D, 2) / gridDim.x) & 1);
+  const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
+  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, T, H, scale};
+  const DkdvLds kv_lds = {sA0, sA0 + HALF, sA1, sA1 + HALF, sA2, sA2 + HALF, sLse0, sDelta0, sLse1, sDelta1, sLse2, sDelta2, sSink,
+                          reinterpret_cast<u32x4*>(sA3)};
+  const DqLds q_lds = {sA0, sA1, sA2, sA3};
+
+  // the first kind are the key tiles (the dearer ones), the second the query tiles
+  constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a query tile, or of a pair of them
+  JointQueue<SPLIT> queue;
+  queue.init(counters);
+  if (wave == 0) {
+    int before = 0;
+    for (int r0 = 0; r0 < n_seq; r0 += 64) {
+      const int r = r0 + lane;
+      const int n = r < n_seq ? queue.share(s_start[r + 1] - s_start[r], r) : 0;
+      const int sum = wave_scan(n);
+      if (r < n_seq) s_mine[r] = before + sum - n;
+      before += __builtin_amdgcn_readlane(sum, 63);
+    }
+    if (lane == 0) s_mine[n_seq] = before;
+  }
+  __syncthreads();
+  queue.deal(s_mine, n_seq);
+  // item i of this queue's, of either kind
+  auto take = [&](int i) {
+    const int r = __builtin_amdgcn_readfirstlane(rank_of_item(s_mine, n_seq, i));
+    const int rem = queue.share_from(s_start[r + 1] - s_start[r], r) + i - s_mine[r];
+    WorkItem it = item_of_rank<BM, CAUSAL>(r, __builtin_amdgcn_readfirstlane(rem), cu, s_order);
+    it.head = __builtin_amdgcn_readfirstlane(it.head);
+    it.tile = __builtin_amdgcn_readfirstlane(it.tile);
+    return it;
+  };
+  int ticket = queue.first_ticket();
+  while (ticket < queue.wide) {
+    const bool keys = queue.first_kind(ticket);
+    const WorkItem it = take(queue.item(ticket));
+    unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
+    // CAUSAL: the item is the pair of tiles {p, tiles - 1 - p}, the dearer one first; the middle tile of an odd count stands alone
+    const int other = (it.len + BM - 1) / BM - 1 - it.tile;
+    const int n_sub = CAUSAL && other != it.tile ? 2 : 1;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));      // what follows from the lane is formed per item, not kept through the other kind's
+    if (keys) {
+      DkdvLane<D, 2> me;
+      me.init(ln, wave, role, row_bytes);
+#pragma unroll 1
+      for (int sub = 0; sub < n_sub; ++sub)
+        dkdv_tile<D, 2, CAUSAL>(g, kv_lds, me, it, sub == 0 ? it.tile : other,
+                                [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
+                                [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket); });
+    } else {
+      DqLane<D> me;
+      me.init(ln, wave, wave);
+#pragma unroll 1
+      for (int sub = 0; sub < n_sub; ++sub)
+        dq_tile<D, CAUSAL, false>(g, q_lds, me, it, CAUSAL && sub == 0 ? other : it.tile,
+                                  [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); });
+    }
+    if (!queue.draws) return;
+    if (tid == 0 && !keys) s_ticket = drawn_ticket(queue, next_ticket);   // every wave took its copy of the old one many barriers ago
+    lds_barrier();
+    ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+  }
+
+  if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
+  for (int part = ticket - queue.wide; part < queue.parts;) {
+    const WorkItem it = take(queue.item_of_part(part));
+    const int other = (it.len + BM - 1) / BM - 1 - it.tile, member = (part % SPLIT) >> 1;
+    const int q0 = (CAUSAL && member == 0 ? other : it.tile) * BM + 64 * (part & 1);
+    if (q0 < it.len && !(member == 1 && it.tile == other)) {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      DqLane<D> me;
+      me.init(ln, wave, wave);
+      dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0);
+    }
+    if (!queue.draws) return;         // every part was a first ticket
+    if (tid == 0) s_ticket = drawn_ticket(queue, atomicAdd(queue.ctr, 1u));
+    lds_barrier();                    // (and the partial sums are no longer read)
+    part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
+    lds_barrier();                    // everyone has the ticket before the next one is put down
+  }
+}
+
+template <bool CAUSAL>
+static hipError_t launch_joint_m(const BwdArgs& a, int d, int T, int cus, hipStream_t stream) {
+  const dim3 rows((T + 127) / 128, a.H);
+  auto* delta = d == 64 ? attn_bwd_delta_kernel<64> : attn_bwd_delta_kernel<128>;
+  hipLaunchKernelGGL(delta, rows, dim3(kThreads), 0, stream, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
+                     a.n_seq, a.H);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t dyn = (size_t)(3 * a.n_seq + 2) * sizeof(int);
+  auto* joint = d == 64 ? attn_bwd_joint_kernel<64, CAUSAL> : attn_bwd_joint_kernel<128, CAUSAL>;
+  hipLaunchKernelGGL(joint, dim3(cus * dkdv_workgroups_per_cu(d, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q,
+                     (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale,
+                     (__bf16*)a.dq, (__bf16*)a.dk, (__bf16*)a.dv, a.counters);
+  return hipGetLastError();
+}
+
+}  // namespace knap

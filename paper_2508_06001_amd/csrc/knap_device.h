@@ -364,33 +364,42 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
 }
 
 // The ticket that a draw of one lane stands for; the queue's last draw puts its counter back to zero.
-template <int SPLIT>
-__device__ __forceinline__ int drawn_ticket(const ItemQueue<SPLIT>& queue, unsigned drawn) {
+template <class Queue>
+__device__ __forceinline__ int drawn_ticket(const Queue& queue, unsigned drawn) {
   if (queue.last_draw(drawn)) atomicExch(queue.ctr, 0u);
   return queue.later_ticket(drawn);
+}
+
+// item `rem` of the sequence of rank r
+template <int TILE, bool PAIRED = false>
+__device__ __forceinline__ WorkItem item_of_rank(int r, int rem, const int32_t* __restrict__ cu, const int* s_order) {
+  // every lane computed the same values; say so, so that addresses and buffer
+  // descriptors derived from the item live in scalar registers
+  const int s = __builtin_amdgcn_readfirstlane(s_order[r]);
+  WorkItem it;
+  it.row0 = __builtin_amdgcn_readfirstlane(cu[s]);
+  it.len = __builtin_amdgcn_readfirstlane(cu[s + 1]) - it.row0;
+  const int per_head = items_per_head<PAIRED>((it.len + TILE - 1) / TILE);
+  it.head = rem / per_head;
+  it.tile = rem - it.head * per_head;
+  return it;
 }
 
 template <int TILE, bool PAIRED = false>
 __device__ __forceinline__ WorkItem decode_item(int w, const int32_t* __restrict__ cu, int n_seq,
                                                 const int* s_order, const int* s_start) {
-  // largest r with s_start[r] <= w (sequences without items share their successor's start)
-  int lo = 0, hi = n_seq - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (s_start[mid] <= w) lo = mid; else hi = mid - 1;
-  }
-  // every lane computed the same values; say so, so that addresses and buffer
-  // descriptors derived from the item live in scalar registers
-  const int s = __builtin_amdgcn_readfirstlane(s_order[lo]);
-  const int first = __builtin_amdgcn_readfirstlane(s_start[lo]);
-  WorkItem it;
-  it.row0 = __builtin_amdgcn_readfirstlane(cu[s]);
-  it.len = __builtin_amdgcn_readfirstlane(cu[s + 1]) - it.row0;
-  const int per_head = items_per_head<PAIRED>((it.len + TILE - 1) / TILE);
-  const int rem = w - first;
-  it.head = rem / per_head;
-  it.tile = rem - it.head * per_head;
-  return it;
+  const int r = rank_of_item(s_start, n_seq, w);
+  return item_of_rank<TILE, PAIRED>(r, w - __builtin_amdgcn_readfirstlane(s_start[r]), cu, s_order);
 }
+
+// what the kernels of the backward read and write; delta and lse2 are handed from one to the next
+struct BwdPtrs {
+  const __bf16 *q, *k, *v, *out, *dout;
+  const float* lse;
+  float *lse2, *delta;
+  __bf16 *dq, *dk, *dv;
+  int T, H;
+  float scale;
+};
 
 }  // namespace knap

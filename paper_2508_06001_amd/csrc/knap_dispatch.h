@@ -13,27 +13,11 @@ constexpr int dkdv_workgroups_per_cu(int d, int pairs) { return d == 64 && pairs
 constexpr int dkdv_waves_per_simd(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 2; }
 
 // Rounds of `slots` workgroups that a bag's items take, its sequences taken to be of one length: whole ones where there
-// are few, and as many as the items fill where there are so many that the shorter sequences even out the last.  `split`
-// parts can stand for an item of a thin last round (see ItemQueue), which then takes little more than half of one; under
-// the mask (four parts) a third behind whole rounds, three quarters where all is parts and the longest of them last.
-inline double rounds(int64_t total_tokens, int n_seq, int H, bool causal, int tile, int64_t slots, int split = 0) {
+// are few, and as many as the items fill where there are so many that the shorter sequences even out the last.
+inline double rounds(int64_t total_tokens, int n_seq, int H, bool causal, int tile, int64_t slots) {
   const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + tile - 1) / tile;
   const int64_t items = (causal ? (tiles + 1) / 2 : tiles) * n_seq * H;
-  if (items >= 8 * slots) return (double)items / slots;
-  const int64_t last = items % slots;
-  return (double)(items / slots) + (last == 0 ? 0.0 : last * split > slots || split == 0 ? 1.0 : split == 2 ? 0.6 : items > slots ? 0.35 : 0.75);
-}
-
-// Workgroups of the dQ kernel on each CU, `resident` being what its registers allow.  At d = 64 that is three, each of which
-// takes 1.4 times as long for an item as one of two: two where their whole rounds come out shorter (forward left out, in us, two
-// against three: 131072 tokens, 2 x 64 13122 against 13902, causal 7142 against 9417, 12000,
-// 12 x 64, causal 352 against 391; but 6 of 4300, 12 x 64 564 against 535;
-// 20000, 2 x 64 442 against 375; 32 of 450, 48 x 64 214 against 195; 65536, 48 x 64 77.6 against 73.7 ms).
-inline int dq_workgroups_per_cu(int64_t total_tokens, int n_seq, int H, bool causal, int cus, int resident) {
-  if (resident < 3) return resident;
-  const int split = causal ? 4 : 2;
-  return rounds(total_tokens, n_seq, H, causal, 128, 2 * (int64_t)cus, split) <
-                 1.36 * rounds(total_tokens, n_seq, H, causal, 128, 3 * (int64_t)cus, split) ? 2 : resident;
+  return items >= 8 * slots ? (double)items / slots : (double)((items + slots - 1) / slots);
 }
 
 // Wave pairs per workgroup of the dK/dV kernel (2 or 4, see there), from what the host knows of a bag: its tokens, heads
@@ -55,15 +39,12 @@ inline int dq_workgroups_per_cu(int64_t total_tokens, int n_seq, int H, bool cau
 //    3000: 3796 against 3778) but those from 512 to 640, which are mostly one long sequence among short ones (16384 and
 //    30 of 300: 5358 against 5117; 65536 and 200 short 84.4 against 81.4 ms; but 60 of 600: 592 against 700 us).  And where
 //    the smaller tiles save a round (15 of 640: 174 against 216 us).
-//  * d = 64, three workgroups of two pairs on a CU: two pairs, unless their rounds are the longer ones (a round of three
-//    takes 1.4 times as long as one of four pairs).  32 of 450 tokens, 48 x 64: 246 against 289 us; 16 of 4096: 6389 against
-//    7163; 65536: 98.1 against 103.3 ms; causal, 20 of 3000: 2637 against 2970 us, 65536: 51.6 against 52.1 ms.  But 6 of 4300,
-//    12 x 64: 786 against 737 us; 131072, 2 x 64: 18320 against 17195, causal 13719 against 9399.
+//  * d = 64, where three workgroups of two pairs share a CU: always two (the bags that leave it to be chosen have many
+//    rounds or short sequences.  32 of 450 tokens, 48 x 64: 246 against 289 us; 16 of 4096: 6389 against 7163; 65536: 98.1
+//    against 103.3 ms; causal, 20 of 3000: 2637 against 2970 us, 65536: 51.6 against 52.1 ms).
 //  * Otherwise four (65536 and 200 short, 24 x 128: 80.3 against 82.4 ms; 30000 tokens, 3 x 128: 2.90 against 3.13 ms).
 inline int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
-  if (total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
-  if (d == 64)
-    return 1.4 * rounds(total_tokens, n_seq, H, causal, 128, 3 * (int64_t)cus) < rounds(total_tokens, n_seq, H, causal, 256, cus) ? 2 : 4;
+  if (d == 64 || total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
   const int64_t n = n_seq;
   if (causal) return total_tokens <= 65536 && total_tokens < 4096 * n ? 2 : 4;
   if (total_tokens < 512 * n && total_tokens <= 16384) return 2;
@@ -71,6 +52,26 @@ inline int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal
   if (four >= 6.0)
     return total_tokens < 512 * n || (total_tokens >= 640 * n && total_tokens < 3000 * n) ? 2 : 4;
   return total_tokens >= 640 * n && rounds(total_tokens, n_seq, H, causal, 128, 2 * (int64_t)cus) < 0.9 * four ? 2 : 4;
+}
+
+// Whether both kinds of items go out in one launch (knap_attn_joint.h), behind the kernel that forms delta, or the dQ kernel
+// and then the dK/dV kernel.  One launch has one last round to fill where two have two, spreads every sequence over the XCDs,
+// and takes two wave pairs per workgroup for the keys.  Backward in us, two launches against one, at n rounds of 128-row
+// tiles: 4 sequences of up to 311 tokens, 2 x 64, 28 against 22; 4000, 3 x 128 (0.2): 184 against 145; one of 4292, 24 x 128
+// (1.6): 828 against 762; 3000 (1.1): 506 against 369; 5 of up to 4346 (2.9): 951 against 851; 21 of up to 6108 (4.6): 1805
+// against 1451; 17 of 328..4533 (11.5): 3356 against 3306, causal (6): 2036 against 1952; 10 of up to 6795, 48 x 64 (11):
+// 4559 against 4477; 16 of up to 4393 (15.6): 4931 against 4865.  Two where
+//  * the rounds are many: 20 of up to 4479 (20.9): 7016 against 7029; 16 causal ones of up to 25431 (13.9): 17860 against 18017,
+//    and at d = 128, where four wave pairs are the better ones for long sequences, fewer of those: 131072, 32768 and 4 of 8192,
+//    3 heads (9) 76.8 ms against 80.5; but 60000, 3 heads (2.7) 16.7 against 16.0;
+//  * short sequences fill several: 32 of 450 (6): 423 against 437, 128 of 450, 12 x 128, causal (7): 643 against 660;
+//  * each kernel has one round that is nearly full, of one sequence: 4825 causal (0.9): 487 against 510.
+inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
+  const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + 127) / 128;
+  const double r = (double)((causal ? (tiles + 1) / 2 : tiles) * n_seq * H) / (double)((int64_t)cus * dkdv_workgroups_per_cu(d, 2));
+  if (r > 13.0 || (r > 4.5 && total_tokens < 500 * (int64_t)n_seq)) return false;
+  if (d == 128 && r > 4.0 && total_tokens > 16384 * (int64_t)n_seq) return false;
+  return !(n_seq == 1 && r > 0.8 && r <= 1.0);
 }
 
 // Whether some queue of the backward's kernels may hold more items than workgroups, so that counters of unknown contents

@@ -21,14 +21,21 @@ __device__ __forceinline__ int dear_items(const int* s_start, int n_seq, int eno
   return min(enough, s_start[lo + 1]);
 }
 
-// Whether item w belongs to a sequence with at least three quarters of the longest one's items.
-__device__ __forceinline__ bool long_tail(const int* s_start, int n_seq, int w) {
+// Rank of the sequence that item w belongs to: the largest r with s_start[r] <= w (sequences without items share their
+// successor's start).
+__device__ __forceinline__ int rank_of_item(const int* s_start, int n_seq, int w) {
   int lo = 0, hi = n_seq - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (s_start[mid] <= w) lo = mid; else hi = mid - 1;
   }
-  return 4 * (s_start[lo + 1] - s_start[lo]) >= 3 * s_start[1];
+  return lo;
+}
+
+// Whether item w belongs to a sequence with at least three quarters of the longest one's items.
+__device__ __forceinline__ bool long_tail(const int* s_start, int n_seq, int w) {
+  const int r = rank_of_item(s_start, n_seq, w);
+  return 4 * (s_start[r + 1] - s_start[r]) >= 3 * s_start[1];
 }
 
 // Dynamic assignment for kernels that are handed counters at zero (one unsigned per XCD, 8 in
@@ -97,6 +104,54 @@ struct ItemQueue {
     const int round = ticket / chunk;
     return (round * n_q + chunk_of(round)) * chunk + ticket % chunk;
   }
+};
+
+// The queues of a launch that holds two kinds of items, every kind the same number of every sequence (knap_attn_joint.h).  Every
+// XCD gets an eighth of each sequence's items of either kind, consecutive ones, and takes its first kind before its second,
+// each by falling length.  (Chunks of the whole list, as above, give one XCD a long sequence's items of both kinds and
+// another only short ones: sequences of 4096, 2300, 1024, 256 and 256 tokens, 12 x 128, 572 us
+// against 472.)  Parts stand for items of the second kind: for all of them, where they find a workgroup each, or for those of
+// a thin last round.
+template <int SPLIT>
+struct JointQueue {
+  unsigned* ctr;
+  int q, n_q, per;
+  int mine;                 // items of each kind that are this queue's
+  int wide, parts;          // items dealt out whole, and parts
+  bool draws;               // more tickets than workgroups: somebody has to draw
+  __device__ __forceinline__ void init(unsigned* counters) {
+    n_q = (gridDim.x % 8 == 0) ? 8 : 1;
+    q = (int)(blockIdx.x % n_q);
+    per = (int)gridDim.x / n_q;
+    ctr = counters + q;
+  }
+  // this queue's items of the sequence of rank r, which has `count`: from here on ...
+  __device__ __forceinline__ int share_from(int count, int r) const { return count * ((q + r) % n_q) / n_q; }
+  // ... and so many (the odd ones go round with the rank)
+  __device__ __forceinline__ int share(int count, int r) const { return count * ((q + r) % n_q + 1) / n_q - share_from(count, r); }
+  // s_mine[r]: this queue's items of the ranks before r; s_mine[n_seq] all of them
+  __device__ __forceinline__ void deal(const int* s_mine, int n_seq) {
+    mine = s_mine[n_seq];
+    int last = 0;           // items of the second kind that parts stand for
+    if (mine * (1 + SPLIT) <= per) {
+      last = mine;
+    } else {
+      const int thin = 2 * mine % per;
+      const int r = rank_of_item(s_mine, n_seq, max(0, mine - max(thin, 1)));      // of a thin round's first
+      if (thin <= mine && thin * SPLIT <= per && 4 * (s_mine[r + 1] - s_mine[r]) >= 3 * (s_mine[1] - s_mine[0])) last = thin;
+    }
+    mine = __builtin_amdgcn_readfirstlane(mine);
+    wide = __builtin_amdgcn_readfirstlane(2 * mine - last);
+    parts = __builtin_amdgcn_readfirstlane(last * SPLIT);
+    draws = wide + parts > per;
+  }
+  // the item's number among this queue's items of its kind
+  __device__ __forceinline__ bool first_kind(int ticket) const { return ticket < mine; }
+  __device__ __forceinline__ int item(int ticket) const { return ticket < mine ? ticket : ticket - mine; }
+  __device__ __forceinline__ int item_of_part(int part) const { return wide - mine + part / SPLIT; }
+  __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
+  __device__ __forceinline__ int later_ticket(unsigned drawn) const { return per + (int)drawn; }
+  __device__ __forceinline__ bool last_draw(unsigned drawn) const { return (int)drawn == wide + parts - 1; }
 };
 
 }  // namespace knap

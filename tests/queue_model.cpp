@@ -72,6 +72,61 @@ Walk walk(int grid, const std::vector<int>& start, int n_seq, int n_items) {
   return r;
 }
 
+// the launch of both kinds of items: every item of the first kind whole, every one of the second whole or all its parts
+template <int SPLIT>
+Walk walk_joint(int grid, const std::vector<int>& start, int n_seq, int n_items) {
+  Walk r = {n_items, 0, 0, 0, 0, 0};
+  std::vector<int> first(n_items, 0), second(n_items, 0), part((size_t)n_items * SPLIT, 0), mine(n_seq + 1);
+  std::vector<unsigned> counters(8, 0);
+  gridDim.x = grid;
+  const int n_q = grid % 8 == 0 ? 8 : 1;
+  for (int q = 0; q < n_q; ++q) {
+    blockIdx.x = q;
+    knap::JointQueue<SPLIT> queue;
+    queue.init(counters.data());
+    mine[0] = 0;
+    for (int s = 0; s < n_seq; ++s) mine[s + 1] = mine[s] + queue.share(start[s + 1] - start[s], s);
+    queue.deal(mine.data(), n_seq);
+    const int tickets = queue.wide + queue.parts;
+    auto global = [&](int i) {        // item i of this queue's
+      const int k = knap::rank_of_item(mine.data(), n_seq, i);
+      const int w = start[k] + queue.share_from(start[k + 1] - start[k], k) + i - mine[k];
+      return i < 0 || i >= mine[n_seq] || w < start[k] || w >= start[k + 1] ? -1 : w;
+    };
+    for (int t = 0; t < queue.wide; ++t) {
+      const int w = global(queue.item(t));
+      if (w < 0) ++r.wrong; else ++(queue.first_kind(t) ? first : second)[w];
+    }
+    for (int p = 0; p < queue.parts; ++p) {
+      const int w = global(queue.item_of_part(p));
+      if (w < 0) ++r.wrong; else ++part[(size_t)w * SPLIT + p % SPLIT];
+    }
+    for (int i = 0; i < queue.per; ++i) {
+      blockIdx.x = q + i * n_q;
+      r.wrong += queue.first_ticket() != i;
+    }
+    r.wrong += queue.later_ticket(0u) != queue.per || queue.ctr != counters.data() + q || (!queue.draws && tickets > queue.per);
+    if (queue.draws) {
+      int at_work = queue.per;
+      for (unsigned drawn = 0; at_work > 0 && drawn <= (unsigned)tickets; ++drawn) {
+        if (queue.later_ticket(drawn) >= tickets) --at_work;
+        r.wrong += queue.last_draw(drawn) != (at_work == 0);
+      }
+      r.wrong += at_work != 0;
+    }
+    r.per = queue.per;
+    r.most = max(r.most, tickets);
+    r.draws |= queue.draws;
+    r.parts += queue.parts;
+  }
+  for (int w = 0; w < n_items; ++w) {
+    int parts = 0;
+    for (int i = 0; i < SPLIT; ++i) parts += part[(size_t)w * SPLIT + i] == 1 ? 1 : part[(size_t)w * SPLIT + i] == 0 ? 0 : 100;
+    r.wrong += first[w] != 1 || !((second[w] == 1 && parts == 0) || (second[w] == 0 && parts == SPLIT));
+  }
+  return r;
+}
+
 }  // namespace
 
 extern "C" {
@@ -90,6 +145,24 @@ void queue_walk(const int* lens, int n_seq, int H, int tile, int causal, int spl
   const Walk w = split == 0 ? walk<0>(grid, start, n_seq, n) : split == 2 ? walk<2>(grid, start, n_seq, n) : walk<4>(grid, start, n_seq, n);
   const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
   std::copy(values, values + 6, out);
+}
+
+// the same for the launch of both kinds of items (tiles of 128)
+void queue_walk_joint(const int* lens, int n_seq, int H, int causal, int grid, int* out) {
+  std::vector<int> sorted(lens, lens + n_seq);
+  std::sort(sorted.begin(), sorted.end(), [](int a, int b) { return a > b; });
+  std::vector<int> start(n_seq + 1, 0);
+  for (int r = 0; r < n_seq; ++r) {
+    const int tiles = (sorted[r] + 127) / 128;
+    start[r + 1] = start[r] + H * (causal ? knap::items_per_head<true>(tiles) : knap::items_per_head<false>(tiles));
+  }
+  const Walk w = causal ? walk_joint<4>(grid, start, n_seq, start[n_seq]) : walk_joint<2>(grid, start, n_seq, start[n_seq]);
+  const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
+  std::copy(values, values + 6, out);
+}
+
+int queue_bwd_joint(long long tokens, int n_seq, int H, int d, int causal, int cus) {
+  return knap::bwd_joint(tokens, n_seq, H, d, causal != 0, cus);
 }
 
 int queue_dkdv_pairs(long long tokens, int n_seq, int H, int d, int causal, int cus) {

@@ -37,6 +37,9 @@ def _lib():
     lib = C.CDLL(so)
     lib.queue_walk.restype = None
     lib.queue_walk.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 6 + [C.POINTER(C.c_int)]
+    lib.queue_walk_joint.restype = None
+    lib.queue_walk_joint.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 4 + [C.POINTER(C.c_int)]
+    lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_bwd_draws.argtypes = [C.c_longlong] + [C.c_int] * 6
     return lib
@@ -65,6 +68,18 @@ def walk(kernel: str, lens: Sequence[int], H: int, d: int, causal: bool, pairs: 
     out = (C.c_int * 6)()
     _lib().queue_walk((C.c_int * len(lens))(*lens), len(lens), H, tile, int(causal), split,
                       grid(kernel, d, pairs, cus), out)
+    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
+
+
+def bwd_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> bool:
+    """Whether the backward of this bag is one launch of both kinds of items."""
+    return bool(_lib().queue_bwd_joint(sum(lens), len(lens), H, d, int(causal), cus))
+
+
+def walk_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> Walk:
+    """The queues of that launch; `items` are those of one kind, `parts` those of query tiles."""
+    out = (C.c_int * 6)()
+    _lib().queue_walk_joint((C.c_int * len(lens))(*lens), len(lens), H, int(causal), cus * (3 if d == 64 else 2), out)
     return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
 
 

@@ -675,13 +675,13 @@ def test_two_pair_dkdv_kernel_over_several_items_per_workgroup():
         assert np.array_equal(bf16_device_to_bits(got), want)
 
 
-@pytest.mark.parametrize("causal,lens,H,pairs", [(False, _LOW_RES, 48, 2), (True, _LOW_RES, 48, 2), (False, [2081], 46, 4),
-                                                 (False, [4300] * 2, 12, 4), (True, [2081, 1100], 58, 4)])
-def test_three_backward_workgroups_per_cu_at_d_64(causal, lens, H, pairs):
+@pytest.mark.parametrize("causal,lens,H", [(False, _LOW_RES, 48), (True, _LOW_RES, 80), (False, [2081], 46),
+                                           (False, [4300] * 2, 12), (True, [2081, 1100], 58)])
+def test_three_backward_workgroups_per_cu_at_d_64(causal, lens, H):
     """d = 64, where three workgroups share a CU: several items for each of the 768 (tickets handed over, roles of every
-    third of the grid), a thin last round of dQ parts (782 items), bags whose rounds favour four pairs, and causal pairs.
-    First and last heads against the oracle."""
-    assert Q.dkdv_pairs(lens, H, 64, causal) == pairs
+    third of the grid) in two launches (the short sequences) and in one, and causal pairs.  First and last heads against
+    the oracle."""
+    assert Q.bwd_joint(lens, H, 64, causal) == (lens != _LOW_RES)
     _full_compare(BagSpec("three_per_cu", lens, H=H, d=64, seed=8800 + H), heads=[0, H - 1], strict_fwd=not causal, causal=causal,
                   lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
@@ -715,6 +715,48 @@ def test_schedule_of_bags_on_both_sides_of_64_sequences(n_seq):
         lens = [(37 * i * i) % 201 if i % 5 else 64 for i in range(n_seq)]
         lens[-1] = 150
         _full_compare(BagSpec("schedule", lens, H=2, d=64, seed=9000 + n_seq), strict_fwd=False, causal=causal, lse_tol=LSE_TOL_FEW_KEYS)
+
+
+_UNEQUAL = [0, 1290, 333, 64, 700, 1, 129, 128, 127, 0]
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,lens,H,parts", [
+    (64, _UNEQUAL, 5, "all"), (128, [300, 37], 3, "all"),                      # every query tile in parts, nothing drawn
+    (64, [2081], 31, None), (128, [2081], 31, "thin"), (128, [1290, 333, 64, 700], 9, None),
+    (128, _UNEQUAL, 48, None), (64, _UNEQUAL, 90, None),                       # several draws, odd shares of the XCDs
+    (128, [1 + (37 * i) % 300 for i in range(70)], 7, None)])                  # more than one scan step of the shares
+def test_both_kinds_of_items_in_one_launch(causal, d, lens, H, parts):
+    """The backward whose key tiles and query tiles share a launch: whole items, parts of a thin last round and of all
+    items, items drawn, sequences without rows and of one tile, pairs without a partner.  First, middle and last heads
+    against the oracle; the same bits again with another workspace."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    assert Q.bwd_joint(lens, H, d, causal)
+    w = Q.walk_joint(lens, H, d, causal)
+    if parts == "all": assert w.parts == w.items * (4 if causal else 2) and not w.draws
+    if parts == "thin": assert 0 < w.parts < w.items and w.draws
+    run = _full_compare(BagSpec("joint", lens, H=H, d=d, seed=9100 + H + d), heads=sorted({0, H // 2, H - 1}), strict_fwd=False,
+                        causal=causal, lse_tol=LSE_TOL_FEW_KEYS)
+    a, x = run.attn, run.dev
+    a.workspace.fill_(0xff)
+    for t in (a.dq, a.dk, a.dv):
+        t.fill_(float("nan"))
+    a.backward(x["q"], x["k"], x["v"], x["dout"])
+    torch.cuda.synchronize()
+    for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+        assert np.array_equal(bf16_device_to_bits(got), want)
+
+
+@pytest.mark.parametrize("causal,d,lens,H,pairs", [
+    (False, 128, [2300], 24, 4), (True, 128, [4385], 24, 4), (False, 64, [1718], 48, 2), (True, 64, [3201], 48, 2),
+    (True, 128, _LOW_RES, 48, 2)])
+def test_backward_in_two_launches_on_small_bags(causal, d, lens, H, pairs):
+    """The dQ and the dK/dV kernels as launches of their own where a bag's items fill the GPU about once, and where short
+    sequences fill it several times."""
+    assert not Q.bwd_joint(lens, H, d, causal) and Q.dkdv_pairs(lens, H, d, causal) == pairs
+    _full_compare(BagSpec("two_launches", lens, H=H, d=d, seed=9300 + H), heads=[0, H - 1],
+                  strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
 @pytest.mark.timeout(300)

@@ -81,3 +81,18 @@ def test_bags_that_the_kernels_deal_out_in_each_way():
     assert w.items == 17 * 31 and w.parts == 2 * (17 * 31 - 512) and w.draws
     w = Q.walk("dkdv", [450] * 32, 24, 128, False)
     assert Q.dkdv_pairs([450] * 32, 24, 128, False) == 2 and w.items == 32 * 24 * 4 and w.draws and not w.parts
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_every_item_of_both_kinds_once(causal):
+    """The launch of both kinds of items: random bags and grids, all parts, thin last rounds and none."""
+    rng = random.Random(30 + causal)
+    seen = {"all": 0, "thin": 0, "none": 0}
+    for _ in range(1500):
+        lens, H, d = _random_bag(rng), rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128))
+        cus = rng.choice((256, 256, 256, 304, 80, 37))
+        w = Q.walk_joint(lens, H, d, causal, cus)
+        assert w.wrong == 0, (lens, H, d, causal, cus, w)
+        split = 4 if causal else 2
+        seen["none" if w.parts == 0 else "all" if w.parts == w.items * split else "thin"] += 1
+    assert min(seen.values()) > 20, seen
