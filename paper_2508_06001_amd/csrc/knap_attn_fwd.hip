@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
 
   // the scan scratch of the schedule lives in the first K buffer, which is not in use yet
   const int T = cu[n_seq];
-  const int n_items = build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
+  build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -90,8 +90,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   // when the item is done, so the counter's latency is never waited for.
   __shared__ int s_ticket;
   constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a wide one
-  ItemQueue<SPLIT> queue;
-  queue.init(counters, s_start, n_seq, n_items);
+  EvenQueue<SPLIT, 1> queue;
+  queue.init(counters);
+  if (tid < 64) even_shares(queue, n_seq, s_start, lane);
+  __syncthreads();
+  deal_even<C::BM, CAUSAL>(queue, cu, n_seq, s_order, s_start);
+  auto take = [&](int i) { return decode_even<C::BM, CAUSAL>(i, queue, cu, n_seq, H, s_order, s_start); };
   int ticket = queue.first_ticket();
   WorkItem it;
   unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   };
 
   if (ticket < queue.wide) {
-  it = decode_item<C::BM, CAUSAL>(queue.item(ticket), cu, n_seq, s_order, s_start);
+  it = take(ticket);
   load_first();
   wait_async_loads();
   lds_barrier();
@@ -297,7 +301,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
       lds_barrier();
       ticket = __builtin_amdgcn_readfirstlane(s_ticket);
       more = ticket < queue.wide;
-      if (more) it = decode_item<C::BM, CAUSAL>(queue.item(ticket), cu, n_seq, s_order, s_start);
+      if (more) it = take(ticket);
       sub = 0;
     }
     if (more) load_first();
@@ -325,12 +329,11 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   const int rb = wave & 1, kh = wave >> 1;
   const int kh_u = __builtin_amdgcn_readfirstlane(kh), rb_u = __builtin_amdgcn_readfirstlane(rb);
   for (int part = ticket - queue.wide; part >= 0 && part < queue.parts;) {
-    const int p = queue.part0 + part;
-    it = decode_item<C::BM, CAUSAL>(queue.n_wide + p / SPLIT, cu, n_seq, s_order, s_start);
+    it = take(queue.item_of_part(part));
     const int L = it.len;
     const int q_tiles = (L + C::BM - 1) / C::BM;
-    const int member = (p % SPLIT) >> 1;
-    const int q0 = __builtin_amdgcn_readfirstlane((!CAUSAL ? it.tile : member == 0 ? q_tiles - 1 - it.tile : it.tile) * C::BM + 64 * (p & 1));
+    const int member = (part % SPLIT) >> 1;
+    const int q0 = __builtin_amdgcn_readfirstlane((!CAUSAL ? it.tile : member == 0 ? q_tiles - 1 - it.tile : it.tile) * C::BM + 64 * (part & 1));
     const bool exists = q0 < L && !(CAUSAL && member == 1 && it.tile == q_tiles - 1 - it.tile);
     if (exists) {
       const int q_row = q0 + 32 * rb + l32;

@@ -51,7 +51,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
   extern __shared__ int s_dyn[];
   int* s_order = s_dyn;
   int* s_start = s_dyn + n_seq;
-  int* s_mine = s_start + n_seq + 1;
   // Four arrays that hold a K or V tile each for one kind, and a tile of Q and of dO (or the P of the pairs) for the other:
   // whatever is copied into while another is read is an array of its own, so that the reads are known not to depend on it.
   constexpr int HALF = KV::TILE_ELEMS, P_ELEMS = 2 * DkdvLane<D, 2>::P_PAIR / (int)sizeof(__bf16);
@@ -77,26 +76,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
 
   // the first kind are the key tiles (the dearer ones), the second the query tiles
   constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a query tile, or of a pair of them
-  JointQueue<SPLIT> queue;
+  EvenQueue<SPLIT, 2> queue;
   queue.init(counters);
-  if (wave == 0) {
-    int before = 0;
-    for (int r0 = 0; r0 < n_seq; r0 += 64) {
-      const int r = r0 + lane;
-      const int n = r < n_seq ? queue.share(s_start[r + 1] - s_start[r], r) : 0;
-      const int sum = wave_scan(n);
-      if (r < n_seq) s_mine[r] = before + sum - n;
-      before += __builtin_amdgcn_readlane(sum, 63);
-    }
-    if (lane == 0) s_mine[n_seq] = before;
-  }
+  if (wave == 0) even_shares(queue, n_seq, s_start, lane);
   __syncthreads();
-  queue.deal(s_mine, n_seq);
+  deal_even<BM, CAUSAL>(queue, cu, n_seq, s_order, s_start);
   // item i of this queue's, of either kind
   auto take = [&](int i) {
-    const int r = __builtin_amdgcn_readfirstlane(rank_of_item(s_mine, n_seq, i));
-    const int rem = queue.share_from(s_start[r + 1] - s_start[r], r) + i - s_mine[r];
-    WorkItem it = item_of_rank<BM, CAUSAL>(r, __builtin_amdgcn_readfirstlane(rem), cu, s_order);
+    WorkItem it = decode_even<BM, CAUSAL>(i, queue, cu, n_seq, H, s_order, s_start);
     it.head = __builtin_amdgcn_readfirstlane(it.head);
     it.tile = __builtin_amdgcn_readfirstlane(it.tile);
     return it;
@@ -161,7 +148,7 @@ static hipError_t launch_joint_m(const BwdArgs& a, int d, int T, int cus, hipStr
                      a.n_seq, a.H);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t dyn = (size_t)(3 * a.n_seq + 2) * sizeof(int);
+  const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
   auto* joint = d == 64 ? attn_bwd_joint_kernel<64, CAUSAL> : attn_bwd_joint_kernel<128, CAUSAL>;
   hipLaunchKernelGGL(joint, dim3(cus * dkdv_workgroups_per_cu(d, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q,
                      (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale,

@@ -363,6 +363,21 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
   return s_start[n_seq];
 }
 
+// s_start turned into an even queue's table: its items of the sequences of lower rank, for every rank.  By one wave; a barrier
+// has to follow.
+template <class Queue>
+__device__ __forceinline__ void even_shares(const Queue& queue, int n_seq, int* s_start, int lane) {
+  int before = 0;
+  for (int r0 = 0; r0 < n_seq; r0 += 64) {
+    const int r = r0 + lane;
+    const int n = r < n_seq ? queue.share(s_start[r + 1] - s_start[r], r) : 0;
+    const int sum = wave_scan(n);
+    if (r < n_seq) s_start[r] = before + sum - n;
+    before += __builtin_amdgcn_readlane(sum, 63);
+  }
+  if (lane == 0) s_start[n_seq] = before;
+}
+
 // The ticket that a draw of one lane stands for; the queue's last draw puts its counter back to zero.
 template <class Queue>
 __device__ __forceinline__ int drawn_ticket(const Queue& queue, unsigned drawn) {
@@ -370,18 +385,14 @@ __device__ __forceinline__ int drawn_ticket(const Queue& queue, unsigned drawn) 
   return queue.later_ticket(drawn);
 }
 
-// item `rem` of the sequence of rank r
-template <int TILE, bool PAIRED = false>
-__device__ __forceinline__ WorkItem item_of_rank(int r, int rem, const int32_t* __restrict__ cu, const int* s_order) {
+// the sequence of rank r
+__device__ __forceinline__ WorkItem sequence_of_rank(int r, const int32_t* __restrict__ cu, const int* s_order) {
   // every lane computed the same values; say so, so that addresses and buffer
   // descriptors derived from the item live in scalar registers
   const int s = __builtin_amdgcn_readfirstlane(s_order[r]);
   WorkItem it;
   it.row0 = __builtin_amdgcn_readfirstlane(cu[s]);
   it.len = __builtin_amdgcn_readfirstlane(cu[s + 1]) - it.row0;
-  const int per_head = items_per_head<PAIRED>((it.len + TILE - 1) / TILE);
-  it.head = rem / per_head;
-  it.tile = rem - it.head * per_head;
   return it;
 }
 
@@ -389,7 +400,33 @@ template <int TILE, bool PAIRED = false>
 __device__ __forceinline__ WorkItem decode_item(int w, const int32_t* __restrict__ cu, int n_seq,
                                                 const int* s_order, const int* s_start) {
   const int r = rank_of_item(s_start, n_seq, w);
-  return item_of_rank<TILE, PAIRED>(r, w - __builtin_amdgcn_readfirstlane(s_start[r]), cu, s_order);
+  const int rem = w - __builtin_amdgcn_readfirstlane(s_start[r]);
+  WorkItem it = sequence_of_rank(r, cu, s_order);
+  const int per_head = items_per_head<PAIRED>((it.len + TILE - 1) / TILE);
+  it.head = rem / per_head;
+  it.tile = rem - it.head * per_head;
+  return it;
+}
+
+// the queue's shares dealt out, once they stand in s_start
+template <int TILE, bool PAIRED, class Queue>
+__device__ __forceinline__ void deal_even(Queue& queue, const int32_t* __restrict__ cu, int n_seq, const int* s_order,
+                                          const int* s_mine) {
+  queue.deal(s_mine, n_seq, [&](int r) { return items_per_head<PAIRED>((sequence_of_rank(r, cu, s_order).len + TILE - 1) / TILE); });
+}
+
+// item i of an even queue (s_mine: see even_shares)
+template <int TILE, bool PAIRED, class Queue>
+__device__ __forceinline__ WorkItem decode_even(int i, const Queue& queue, const int32_t* __restrict__ cu, int n_seq, int H,
+                                                const int* s_order, const int* s_mine) {
+  const int r = __builtin_amdgcn_readfirstlane(rank_of_item(s_mine, n_seq, i));
+  const int at = i - __builtin_amdgcn_readfirstlane(s_mine[r]);
+  WorkItem it = sequence_of_rank(r, cu, s_order);
+  const int per_head = items_per_head<PAIRED>((it.len + TILE - 1) / TILE);
+  const int rem = queue.locate(per_head * H, r, at);
+  it.head = rem / per_head;
+  it.tile = rem - it.head * per_head;
+  return it;
 }
 
 // what the kernels of the backward read and write; delta and lse2 are handed from one to the next

@@ -106,14 +106,21 @@ struct ItemQueue {
   }
 };
 
-// The queues of a launch that holds two kinds of items, every kind the same number of every sequence (knap_attn_joint.h).  Every
-// XCD gets an eighth of each sequence's items of either kind, consecutive ones, and takes its first kind before its second,
-// each by falling length.  (Chunks of the whole list, as above, give one XCD a long sequence's items of both kinds and
-// another only short ones: sequences of 4096, 2300, 1024, 256 and 256 tokens, 12 x 128, 572 us
-// against 472.)  Parts stand for items of the second kind: for all of them, where they find a workgroup each, or for those of
-// a thin last round.
-template <int SPLIT>
-struct JointQueue {
+// Even shares: every XCD gets an eighth of each sequence's items and takes them by falling length.  Of a sequence that fills the
+// GPU several times the XCDs take a round's worth of chunks in turn, so that they meet on the same heads (an eighth of its
+// heads for each instead cost one of 65536 and 200 short 2.9 %, forward); what is left of it, or all of a shorter one, is cut
+// in eight.  Chunks of the whole list, as above, can give one XCD the long sequences of a small bag and another the short
+// ones.  Forward in us, chunks -> shares: 3512 tokens in 2 sequences, 24 x 128, 121 -> 95; 12417 in 21 of up to 6290 613 -> 491;
+// 12 of up to 2673, 12 x 128, 190 -> 151; one of 4292, 24 x 128, 273 -> 259; 17 of 328..4533 1070 -> 1052; 10 of up to 6795,
+// 48 x 64, 1514 -> 1491; but where little more than one round is left over, of shorter sequences, these run beside long ones and
+// end late: 2 of 8192 and 2 of 4096, 3 x 128, 248 -> 275.
+//
+// KINDS = 2: the launch holds two kinds of items, every sequence as many of one as of the other (knap_attn_joint.h); a queue
+// takes its first kind before its second.  (4096, 2300, 1024, 256 and 256 tokens, 12 x 128, backward 572 us in chunks, 472 in
+// shares.)  Parts stand for items of the last kind: for all of them, where they find a workgroup each, or for those of a
+// thin last round.
+template <int SPLIT, int KINDS>
+struct EvenQueue {
   unsigned* ctr;
   int q, n_q, per;
   int mine;                 // items of each kind that are this queue's
@@ -125,30 +132,39 @@ struct JointQueue {
     per = (int)gridDim.x / n_q;
     ctr = counters + q;
   }
-  // this queue's items of the sequence of rank r, which has `count`: from here on ...
-  __device__ __forceinline__ int share_from(int count, int r) const { return count * ((q + r) % n_q) / n_q; }
-  // ... and so many (the odd ones go round with the rank)
-  __device__ __forceinline__ int share(int count, int r) const { return count * ((q + r) % n_q + 1) / n_q - share_from(count, r); }
-  // s_mine[r]: this queue's items of the ranks before r; s_mine[n_seq] all of them
-  __device__ __forceinline__ void deal(const int* s_mine, int n_seq) {
+  // how many of the `count` items of the sequence of rank r are this queue's (the odd ones go round with the rank) ...
+  __device__ __forceinline__ int share(int count, int r) const {
+    const int k = (q + r) % n_q, whole = count / (n_q * per), rest = count - whole * n_q * per;
+    return whole * per + rest * (k + 1) / n_q - rest * k / n_q;
+  }
+  // ... and which of them its i-th is
+  __device__ __forceinline__ int locate(int count, int r, int i) const {
+    const int k = (q + r) % n_q, whole = count / (n_q * per), rest = count - whole * n_q * per;
+    if (i < whole * per) return (i / per * n_q + k) * per + i % per;
+    return whole * n_q * per + rest * k / n_q + i - whole * per;
+  }
+  // s_mine[r]: this queue's items of the ranks before r; s_mine[n_seq] all of them.  length(r): of the sequence of rank r, in
+  // tiles or in items, all of them (a queue's shares are too few to tell three quarters).
+  template <class Length>
+  __device__ __forceinline__ void deal(const int* s_mine, int n_seq, Length length) {
     mine = s_mine[n_seq];
-    int last = 0;           // items of the second kind that parts stand for
-    if (mine * (1 + SPLIT) <= per) {
+    int last = 0;           // items of the last kind that parts stand for
+    if (mine * (KINDS - 1 + SPLIT) <= per) {
       last = mine;
     } else {
-      const int thin = 2 * mine % per;
-      const int r = rank_of_item(s_mine, n_seq, max(0, mine - max(thin, 1)));      // of a thin round's first
-      if (thin <= mine && thin * SPLIT <= per && 4 * (s_mine[r + 1] - s_mine[r]) >= 3 * (s_mine[1] - s_mine[0])) last = thin;
+      const int thin = KINDS * mine % per;
+      if (thin > 0 && thin <= mine && thin * SPLIT <= per &&
+          4 * length(rank_of_item(s_mine, n_seq, mine - thin)) >= 3 * length(0)) last = thin;
     }
     mine = __builtin_amdgcn_readfirstlane(mine);
-    wide = __builtin_amdgcn_readfirstlane(2 * mine - last);
+    wide = __builtin_amdgcn_readfirstlane(KINDS * mine - last);
     parts = __builtin_amdgcn_readfirstlane(last * SPLIT);
     draws = wide + parts > per;
   }
   // the item's number among this queue's items of its kind
   __device__ __forceinline__ bool first_kind(int ticket) const { return ticket < mine; }
-  __device__ __forceinline__ int item(int ticket) const { return ticket < mine ? ticket : ticket - mine; }
-  __device__ __forceinline__ int item_of_part(int part) const { return wide - mine + part / SPLIT; }
+  __device__ __forceinline__ int item(int ticket) const { return KINDS == 1 || ticket < mine ? ticket : ticket - mine; }
+  __device__ __forceinline__ int item_of_part(int part) const { return wide - (KINDS - 1) * mine + part / SPLIT; }
   __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
   __device__ __forceinline__ int later_ticket(unsigned drawn) const { return per + (int)drawn; }
   __device__ __forceinline__ bool last_draw(unsigned drawn) const { return (int)drawn == wide + parts - 1; }

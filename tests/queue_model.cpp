@@ -72,9 +72,9 @@ Walk walk(int grid, const std::vector<int>& start, int n_seq, int n_items) {
   return r;
 }
 
-// the launch of both kinds of items: every item of the first kind whole, every one of the second whole or all its parts
-template <int SPLIT>
-Walk walk_joint(int grid, const std::vector<int>& start, int n_seq, int n_items) {
+// even shares: every item of a first kind of two whole, every one of the last kind whole or all its parts
+template <int SPLIT, int KINDS>
+Walk walk_even(int grid, const std::vector<int>& start, int n_seq, int n_items) {
   Walk r = {n_items, 0, 0, 0, 0, 0};
   std::vector<int> first(n_items, 0), second(n_items, 0), part((size_t)n_items * SPLIT, 0), mine(n_seq + 1);
   std::vector<unsigned> counters(8, 0);
@@ -82,20 +82,20 @@ Walk walk_joint(int grid, const std::vector<int>& start, int n_seq, int n_items)
   const int n_q = grid % 8 == 0 ? 8 : 1;
   for (int q = 0; q < n_q; ++q) {
     blockIdx.x = q;
-    knap::JointQueue<SPLIT> queue;
+    knap::EvenQueue<SPLIT, KINDS> queue;
     queue.init(counters.data());
     mine[0] = 0;
     for (int s = 0; s < n_seq; ++s) mine[s + 1] = mine[s] + queue.share(start[s + 1] - start[s], s);
-    queue.deal(mine.data(), n_seq);
+    queue.deal(mine.data(), n_seq, [&](int k) { return start[k + 1] - start[k]; });
     const int tickets = queue.wide + queue.parts;
     auto global = [&](int i) {        // item i of this queue's
       const int k = knap::rank_of_item(mine.data(), n_seq, i);
-      const int w = start[k] + queue.share_from(start[k + 1] - start[k], k) + i - mine[k];
+      const int w = start[k] + queue.locate(start[k + 1] - start[k], k, i - mine[k]);
       return i < 0 || i >= mine[n_seq] || w < start[k] || w >= start[k + 1] ? -1 : w;
     };
     for (int t = 0; t < queue.wide; ++t) {
       const int w = global(queue.item(t));
-      if (w < 0) ++r.wrong; else ++(queue.first_kind(t) ? first : second)[w];
+      if (w < 0) ++r.wrong; else ++(KINDS == 2 && queue.first_kind(t) ? first : second)[w];
     }
     for (int p = 0; p < queue.parts; ++p) {
       const int w = global(queue.item_of_part(p));
@@ -122,7 +122,7 @@ Walk walk_joint(int grid, const std::vector<int>& start, int n_seq, int n_items)
   for (int w = 0; w < n_items; ++w) {
     int parts = 0;
     for (int i = 0; i < SPLIT; ++i) parts += part[(size_t)w * SPLIT + i] == 1 ? 1 : part[(size_t)w * SPLIT + i] == 0 ? 0 : 100;
-    r.wrong += first[w] != 1 || !((second[w] == 1 && parts == 0) || (second[w] == 0 && parts == SPLIT));
+    r.wrong += first[w] != KINDS - 1 || !((second[w] == 1 && parts == 0) || (second[w] == 0 && parts == SPLIT));
   }
   return r;
 }
@@ -147,8 +147,8 @@ void queue_walk(const int* lens, int n_seq, int H, int tile, int causal, int spl
   std::copy(values, values + 6, out);
 }
 
-// the same for the launch of both kinds of items (tiles of 128)
-void queue_walk_joint(const int* lens, int n_seq, int H, int causal, int grid, int* out) {
+// the same for even shares (tiles of 128) of one kind of items (the forward) or of two (the backward in one launch)
+void queue_walk_even(const int* lens, int n_seq, int H, int causal, int kinds, int grid, int* out) {
   std::vector<int> sorted(lens, lens + n_seq);
   std::sort(sorted.begin(), sorted.end(), [](int a, int b) { return a > b; });
   std::vector<int> start(n_seq + 1, 0);
@@ -156,7 +156,9 @@ void queue_walk_joint(const int* lens, int n_seq, int H, int causal, int grid, i
     const int tiles = (sorted[r] + 127) / 128;
     start[r + 1] = start[r] + H * (causal ? knap::items_per_head<true>(tiles) : knap::items_per_head<false>(tiles));
   }
-  const Walk w = causal ? walk_joint<4>(grid, start, n_seq, start[n_seq]) : walk_joint<2>(grid, start, n_seq, start[n_seq]);
+  const int n = start[n_seq];
+  const Walk w = kinds == 2 ? (causal ? walk_even<4, 2>(grid, start, n_seq, n) : walk_even<2, 2>(grid, start, n_seq, n))
+                            : (causal ? walk_even<4, 1>(grid, start, n_seq, n) : walk_even<2, 1>(grid, start, n_seq, n));
   const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
   std::copy(values, values + 6, out);
 }

@@ -37,8 +37,8 @@ def _lib():
     lib = C.CDLL(so)
     lib.queue_walk.restype = None
     lib.queue_walk.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 6 + [C.POINTER(C.c_int)]
-    lib.queue_walk_joint.restype = None
-    lib.queue_walk_joint.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 4 + [C.POINTER(C.c_int)]
+    lib.queue_walk_even.restype = None
+    lib.queue_walk_even.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_bwd_draws.argtypes = [C.c_longlong] + [C.c_int] * 6
@@ -61,8 +61,16 @@ def bwd_draws(lens: Sequence[int], H: int, d: int, causal: bool, pairs: int = 0,
     return bool(_lib().queue_bwd_draws(sum(lens), len(lens), H, int(causal), pairs, cus, grid("dq", d, cus=cus)))
 
 
+def _walk_even(lens: Sequence[int], H: int, causal: bool, kinds: int, grid_: int) -> Walk:
+    out = (C.c_int * 6)()
+    _lib().queue_walk_even((C.c_int * len(lens))(*lens), len(lens), H, int(causal), kinds, grid_, out)
+    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
+
+
 def walk(kernel: str, lens: Sequence[int], H: int, d: int, causal: bool, pairs: int = 0, cus: int = CUS) -> Walk:
     """The queues of `kernel` ("fwd", "dq" or "dkdv") for a bag."""
+    if kernel == "fwd":
+        return _walk_even(lens, H, causal, 1, grid("fwd", d, cus=cus))
     pairs = pairs or dkdv_pairs(lens, H, d, causal, cus)
     tile, split = (64 * pairs, 0) if kernel == "dkdv" else (128, 4 if causal else 2)
     out = (C.c_int * 6)()
@@ -78,9 +86,7 @@ def bwd_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS)
 
 def walk_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> Walk:
     """The queues of that launch; `items` are those of one kind, `parts` those of query tiles."""
-    out = (C.c_int * 6)()
-    _lib().queue_walk_joint((C.c_int * len(lens))(*lens), len(lens), H, int(causal), cus * (3 if d == 64 else 2), out)
-    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
+    return _walk_even(lens, H, causal, 2, cus * (3 if d == 64 else 2))
 
 
 def assert_draws(lens: Sequence[int], H: int, d: int, causal: bool, kernels=("fwd", "dq", "dkdv")) -> None:
