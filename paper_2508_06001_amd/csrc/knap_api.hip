@@ -247,10 +247,9 @@ int ulysses_heads(const void* src, void* dst, int64_t local_tokens, int H, int d
   if (local_tokens == 0) return KNAP_OK;
   if ((uint64_t)local_tokens * g * U > (1ull << 31)) return KNAP_ERR_INVALID_ARG;
   if (!src || !dst || src == dst || !aligned(src, 16) || !aligned(dst, 16)) return KNAP_ERR_INVALID_ARG;
-  DeviceInfo* di = device_info();
-  if (!di) return KNAP_ERR_LAUNCH_FAILED;
+  if (!device_info()) return KNAP_ERR_LAUNCH_FAILED;
   const hipError_t e = knap::launch_ulysses_heads(src, dst, (uint32_t)local_tokens, (uint32_t)U, (uint32_t)g, pack,
-                                                  di->cus, static_cast<hipStream_t>(stream));
+                                                  static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
 }
@@ -264,10 +263,9 @@ int ulysses_rows(const void* src, void* dst, const int32_t* row_map, int64_t tot
   if ((uint64_t)total_tokens * U > (1ull << 31)) return KNAP_ERR_INVALID_ARG;
   if (!src || !dst || !row_map || src == dst || !aligned(src, 16) || !aligned(dst, 16) || !aligned(row_map, 4))
     return KNAP_ERR_INVALID_ARG;
-  DeviceInfo* di = device_info();
-  if (!di) return KNAP_ERR_LAUNCH_FAILED;
+  if (!device_info()) return KNAP_ERR_LAUNCH_FAILED;
   const hipError_t e = knap::launch_ulysses_rows(src, dst, row_map, (uint32_t)total_tokens, (uint32_t)U, gather,
-                                                 di->cus, static_cast<hipStream_t>(stream));
+                                                 static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
 }

@@ -40,9 +40,9 @@ hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipSt
 
 // Ulysses layout switch, local data movement; rows of U 16-byte units.
 hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t U, uint32_t g, bool pack,
-                                int cus, hipStream_t stream);
+                                hipStream_t stream);
 hipError_t launch_ulysses_rows(const void* src, void* dst, const int32_t* row_map, uint32_t T, uint32_t U,
-                               bool gather, int cus, hipStream_t stream);
+                               bool gather, hipStream_t stream);
 hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32_t* row_map, hipStream_t stream);
 
 // resident workgroups per compute unit of the persistent kernels

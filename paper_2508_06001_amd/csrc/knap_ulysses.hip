@@ -19,12 +19,14 @@ namespace {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kCopyThreads = 256;
-// Tuned on an MI355X (one (24576, 24, 128) bf16 tensor, buffers rotated out of the Infinity Cache):
-// non-temporal loads and stores +12 % over plain ones, 32 workgroups per CU +4 % over 16, two units per
-// thread and trip as good as four or eight; 5.7 TB/s against 5.3 TB/s of the runtime's device copy.
-constexpr int kUnroll = 2;           // 16-byte units per thread and loop trip
-constexpr int kWorkgroupsPerCu = 32; // grid cap; beyond it the kernels loop with a grid stride
+// The copies are bound by HBM; what they ask for is many independent accesses in flight at any time.  One unit per thread and a
+// workgroup for every 512 of them: the chip takes a new workgroup whenever one has stored, and its loads are under way while
+// others wait for theirs.  (Two units per thread in a grid of 32 workgroups per CU that strides over the tensor has every thread
+// wait for its loads before it asks for the next ones.)  Non-temporal loads and stores: +12 % over plain ones.
+// Two units in a striding grid -> this, us, buffers rotated out of the Infinity Cache, packing | gathering:
+// 150 MB 52.9 -> 49.2 | 51.9 -> 47.7 (6.3 TB/s); 100 MB 34.3 -> 33.6 | 35.4 -> 32.8; 32 MB 12.9 -> 12.4 | 13.6 -> 12.3;
+// up to 12 MB the same within 0.4 us.  256 or 1024 threads: the same or up to 4 % slower.
+constexpr int kCopyThreads = 512;
 
 __device__ __forceinline__ u32x4_t ld_unit(const u32x4_t* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void st_unit(u32x4_t* p, u32x4_t v) { __builtin_nontemporal_store(v, p); }
@@ -35,27 +37,13 @@ template <bool PACK>
 __global__ __launch_bounds__(kCopyThreads) void ulysses_heads_kernel(
     const u32x4_t* __restrict__ src, u32x4_t* __restrict__ dst, uint32_t T, uint32_t U, uint32_t g) {
   const uint32_t GU = g * U;
-  const uint32_t N = T * GU;
-  const uint32_t stride = gridDim.x * kCopyThreads;
-  for (uint32_t e0 = blockIdx.x * kCopyThreads + threadIdx.x; e0 < N; e0 += kUnroll * stride) {
-    uint32_t xi[kUnroll], yi[kUnroll];
-    u32x4_t val[kUnroll];
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) {
-      const uint32_t e = e0 + k * stride;
-      const uint32_t t = e / GU;
-      const uint32_t w = e - t * GU;
-      const uint32_t r = w / U;
-      xi[k] = e;
-      yi[k] = (r * T + t) * U + (w - r * U);
-    }
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k)
-      if (xi[k] < N) val[k] = ld_unit(&src[PACK ? xi[k] : yi[k]]);
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k)
-      if (xi[k] < N) st_unit(&dst[PACK ? yi[k] : xi[k]], val[k]);
-  }
+  const uint32_t xi = blockIdx.x * kCopyThreads + threadIdx.x;
+  if (xi >= T * GU) return;
+  const uint32_t t = xi / GU;
+  const uint32_t w = xi - t * GU;
+  const uint32_t r = w / U;
+  const uint32_t yi = (r * T + t) * U + (w - r * U);
+  st_unit(&dst[PACK ? yi : xi], ld_unit(&src[PACK ? xi : yi]));
 }
 
 // gather: z[t] = recv[row_map[t]]; scatter: send[row_map[t]] = z[t]; rows of U units.
@@ -63,26 +51,14 @@ template <bool GATHER>
 __global__ __launch_bounds__(kCopyThreads) void ulysses_rows_kernel(
     const u32x4_t* __restrict__ src, u32x4_t* __restrict__ dst, const int32_t* __restrict__ row_map,
     uint32_t T, uint32_t U) {
-  const uint32_t N = T * U;
-  const uint32_t stride = gridDim.x * kCopyThreads;
-  for (uint32_t e0 = blockIdx.x * kCopyThreads + threadIdx.x; e0 < N; e0 += kUnroll * stride) {
-    uint32_t zi[kUnroll], mi[kUnroll];
-    u32x4_t val[kUnroll];
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) {
-      const uint32_t e = e0 + k * stride;
-      const uint32_t t = e / U;
-      zi[k] = e;
-      mi[k] = e < N ? (uint32_t)row_map[t] * U + (e - t * U) : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k)
-      if (zi[k] < N) val[k] = ld_unit(&src[GATHER ? mi[k] : zi[k]]);
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k)
-      if (zi[k] < N) st_unit(&dst[GATHER ? zi[k] : mi[k]], val[k]);
-  }
+  const uint32_t zi = blockIdx.x * kCopyThreads + threadIdx.x;
+  if (zi >= T * U) return;
+  const uint32_t t = zi / U;
+  const uint32_t mi = (uint32_t)row_map[t] * U + (zi - t * U);
+  st_unit(&dst[GATHER ? zi : mi], ld_unit(&src[GATHER ? mi : zi]));
 }
+
+constexpr int kPlanThreads = 256;
 
 // row_map[t] for every row t of the (full sequences) layout.  A sequence of L tokens is cut into g chunks of
 // base = L / g tokens, the first rem = L mod g one token longer; row t is token j of chunk r of sequence s and lies at
@@ -93,7 +69,7 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_rows_kernel(
 // What bounds it is latency, a chain of LDS steps.  A table of the offsets built by a one-workgroup kernel in front of
 // this one cost a second launch and a serial walk over the sequences.  Plan alone, before -> now: 5 sequences on 2 GPUs
 // 9.6 -> 6.9 us, 200 on 8 19.4 -> 6.6 us, 2000 on 4 150 -> 10.3 us.
-__global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
+__global__ __launch_bounds__(kPlanThreads) void ulysses_row_map_kernel(
     const int32_t* __restrict__ cu, int n_seq, int g, int T, int32_t* __restrict__ row_map) {
   extern __shared__ int32_t s_cu[];                 // n_seq + 1 boundaries
   int32_t* s_base = s_cu + n_seq + 1;               // sum of the bases of the sequences before s
@@ -102,9 +78,9 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
   __shared__ int32_t s_before[KNAP_ULYSSES_MAX_GPUS];   // those before the workgroup's first sequence
   __shared__ int32_t s_longer[KNAP_ULYSSES_MAX_GPUS];   // sequences whose chunk r is one token longer
   __shared__ int32_t s_first[KNAP_ULYSSES_MAX_GPUS];    // slab r's first row, plus its longer chunks before that sequence
-  __shared__ int32_t s_wave[kCopyThreads / 64];
+  __shared__ int32_t s_wave[kPlanThreads / 64];
   const int tid = threadIdx.x;
-  for (int i = tid; i <= n_seq; i += kCopyThreads) s_cu[i] = cu[i];
+  for (int i = tid; i <= n_seq; i += kPlanThreads) s_cu[i] = cu[i];
   if (tid < KNAP_ULYSSES_MAX_GPUS) s_all[tid] = s_before[tid] = 0;
   __syncthreads();
 
@@ -117,8 +93,8 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
     }
     return lo;
   };
-  const int s0 = sequence_of(blockIdx.x * kCopyThreads);
-  const int per = (n_seq + kCopyThreads - 1) / kCopyThreads;
+  const int s0 = sequence_of(blockIdx.x * kPlanThreads);
+  const int per = (n_seq + kPlanThreads - 1) / kPlanThreads;
   const int lo = min(tid * per, n_seq), hi = min(lo + per, n_seq);
   int local = 0;
   for (int s = lo; s < hi; ++s) {
@@ -142,7 +118,7 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
   __syncthreads();
   int before = sum - local, total = 0;
 #pragma unroll
-  for (int w = 0; w < kCopyThreads / 64; ++w) {
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
     if (w < tid >> 6) before += s_wave[w];
     total += s_wave[w];
   }
@@ -164,7 +140,7 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
   }
   __syncthreads();
 
-  const int t = blockIdx.x * kCopyThreads + tid;
+  const int t = blockIdx.x * kPlanThreads + tid;
   if (t >= T) return;
   const int s = sequence_of(t);
   const int L = s_cu[s + 1] - s_cu[s];
@@ -187,18 +163,14 @@ __global__ __launch_bounds__(kCopyThreads) void ulysses_row_map_kernel(
   row_map[t] = row;
 }
 
-int copy_grid(uint64_t units, int cus) {
-  const uint64_t per_wg = (uint64_t)kCopyThreads * kUnroll;
-  const uint64_t want = (units + per_wg - 1) / per_wg;
-  const uint64_t cap = (uint64_t)cus * kWorkgroupsPerCu;
-  return (int)(want < cap ? (want ? want : 1) : cap);
-}
+// at most 2^22: the API takes up to 2^31 units
+int copy_grid(uint64_t units) { return (int)((units + kCopyThreads - 1) / kCopyThreads); }
 
 }  // namespace
 
 hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t U, uint32_t g, bool pack,
-                                int cus, hipStream_t stream) {
-  const int grid = copy_grid((uint64_t)T * g * U, cus);
+                                hipStream_t stream) {
+  const int grid = copy_grid((uint64_t)T * g * U);
   if (pack)
     hipLaunchKernelGGL(ulysses_heads_kernel<true>, dim3(grid), dim3(kCopyThreads), 0, stream,
                        (const u32x4_t*)src, (u32x4_t*)dst, T, U, g);
@@ -209,8 +181,8 @@ hipError_t launch_ulysses_heads(const void* src, void* dst, uint32_t T, uint32_t
 }
 
 hipError_t launch_ulysses_rows(const void* src, void* dst, const int32_t* row_map, uint32_t T, uint32_t U,
-                               bool gather, int cus, hipStream_t stream) {
-  const int grid = copy_grid((uint64_t)T * U, cus);
+                               bool gather, hipStream_t stream) {
+  const int grid = copy_grid((uint64_t)T * U);
   if (gather)
     hipLaunchKernelGGL(ulysses_rows_kernel<true>, dim3(grid), dim3(kCopyThreads), 0, stream,
                        (const u32x4_t*)src, (u32x4_t*)dst, row_map, T, U);
@@ -222,7 +194,7 @@ hipError_t launch_ulysses_rows(const void* src, void* dst, const int32_t* row_ma
 
 hipError_t launch_ulysses_plan(const int32_t* cu, int n_seq, int g, int T, int32_t* row_map, hipStream_t stream) {
   const size_t dyn = (size_t)(3 * n_seq + 1) * sizeof(int32_t);
-  hipLaunchKernelGGL(ulysses_row_map_kernel, dim3((T + kCopyThreads - 1) / kCopyThreads), dim3(kCopyThreads), dyn, stream,
+  hipLaunchKernelGGL(ulysses_row_map_kernel, dim3((T + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads), dyn, stream,
                      cu, n_seq, g, T, row_map);
   return hipGetLastError();
 }

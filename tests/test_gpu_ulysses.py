@@ -93,6 +93,13 @@ def test_single_sequence_and_many_sequences():
     _switch_and_back([int(v) for v in rng.integers(0, 60, size=2048)], 4, 4, 64, seed=73)   # KNAP_MAX_SEQS sequences
 
 
+@pytest.mark.parametrize("g", [1, 2])
+@pytest.mark.parametrize("units", [1, 511, 512, 513, 1024])
+def test_copies_at_the_edges_of_a_workgroup(units, g):
+    """Tensors of one unit, and of one unit less, as many as and one more than a copying workgroup moves (rows of one unit)."""
+    _switch_and_back([units], g, g, 8, seed=620 + units + g)
+
+
 @pytest.mark.parametrize("g", [1, 2, 7, 64])
 @pytest.mark.parametrize("n_seq,longest", [(1, 256), (1, 257), (63, 700), (257, 3), (2047, 9), (2048, 300)])
 def test_plan_row_map(n_seq, longest, g):
