@@ -234,7 +234,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
     // between the groups, so that the order below is the order issued): LDS fragments are requested
     // AHEAD groups before the MFMAs that use them, and the arithmetic of the second half of the tile
     // (16 queries) is cut into slices that sit between the MFMAs of the first half.
-    constexpr int AHEAD = 2;
+    // (Four groups at four pairs: 65536 tokens and 200 short ones, 24 x 128, 82.8 -> 82.4 ms, three heads of up to 131072 44.4 ->
+    // 44.1; at two pairs no gain, and up to 2 % worse on short sequences.)
+    constexpr int AHEAD = PAIRS == 4 ? 4 : 2;
     // first product: x[kb] = sum over d of tile rows (A, from LDS) x this wave's K or V rows (B, registers / LDS)
     auto first_product = [&](const __bf16* tA, int rb, f32x16 (&x)[C::KB]) {
       bf16x8 af[C::KC];
