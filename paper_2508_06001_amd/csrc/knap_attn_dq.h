@@ -1,7 +1,7 @@
 // dQ kernel of the backward: the forward kernel's structure.  S^T = K Q^T and dP^T = V dO^T put one query in each
 // lane, LSE and delta are per-lane scalars, and dS^T is, unchanged, the B operand of dQ^T += K^T dS^T with K^T read
 // transposed from LDS.  One text, compiled for either mask in a translation unit of its own (see build.py).
-// d = 64: 168 registers (5 values spilled outside the loops) let three workgroups share a CU where 174 allowed two; the
+// d = 64: 168 registers (5 values spilled outside the loops, bidirectional) let three workgroups share a CU where 174 allowed two; the
 // third wave of a SIMD fills the exponentials of the others (48 x 64, 10 sequences of 310..6795 tokens: 2077 -> 1988 us,
 // 65536 tokens 77.6 -> 73.7 ms).
 #pragma once
@@ -53,6 +53,12 @@ __device__ __forceinline__ float row_delta(const bf16x8 (&dof)[D / 16], const bf
   return dl + xor32(dl);
 }
 
+// Whether a whole query tile goes through the narrow form (dq_part): the last one of its sequence, of at most 64 rows, where
+// two waves of four would have nothing but padding.  From the third tile on: the narrow form needs more than half of the time.
+// (64 sequences, 24 x 128, us: of 448 tokens 339 -> 331, of 400 under the mask 286 -> 279, of 300, 48 x 64, 205 -> 199; but of
+// 180 109 -> 115.)
+__device__ __forceinline__ bool dq_narrow(int len, int q_tile) { return q_tile >= 2 && len - q_tile * 128 <= 64; }
+
 // One query tile (128 rows) of an item.  DELTA: delta and the LSE in base 2 are formed here and handed on in memory; else
 // they are read from there.  `draw` is called behind the first loads.
 template <int D, bool CAUSAL, bool DELTA, class Draw>
@@ -78,46 +84,6 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     // keys this query tile sees at all
     const int kv_end = CAUSAL ? min(L, q0 + C::BM) : L;
 
-    // this lane's q and dO rows as B operands (rows past the end read as zero), and
-    // delta = sum_c dO_c O_c of its query: the lane holds half of the row's elements (8 of every 16),
-    // its partner at lane ^ 32 the other half.  The dK/dV kernel reads delta from memory afterwards.
-    bf16x8 qf[C::KC], dof[C::KC];
-    float dl = 0.f;
-    {
-      const uint32_t bytes = (uint32_t)min(L - q0, C::BM) * row_bytes;
-      const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
-      const auto rd = make_rsrc(dout + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
-      const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);   // DELTA only
-      const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
-      bf16x8 of[C::KC];
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) {
-        qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
-        dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
-        if constexpr (DELTA) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
-      }
-      if constexpr (DELTA) dl = row_delta<D>(dof, of);
-    }
-    // per-lane scalars of this lane's query; +inf LSE turns rows past the end into P = 0
-    const int q_idx = q_valid ? q_row : 0;
-    const size_t row_at = (size_t)it.head * T + it.row0 + q_idx;
-    float lse2;
-    if constexpr (DELTA) {
-      const float own = lse[row_at] * kLog2e;
-      lse2 = q_valid ? own : INFINITY;
-      if (q_valid && hh == 0) {     // for the dK/dV kernel: delta, and the LSE in base 2 (it copies both straight into LDS)
-        delta[row_at] = dl;
-        lse2_out[row_at] = own;
-      }
-    } else {
-      dl = delta[row_at];
-      lse2 = q_valid ? lse2_out[row_at] : INFINITY;
-    }
-
-    f32x16 acc[C::DB];
-#pragma unroll
-    for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
-
     const __bf16* k_base = k + (size_t)it.row0 * row_stride + head_off;
     const __bf16* v_base = v + (size_t)it.row0 * row_stride + head_off;
     const int n_tiles = (kv_end + C::BN - 1) / C::BN;
@@ -129,6 +95,46 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       tile_load_async<D>(dK, make_rsrc(k_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
       tile_load_async<D>(dV, make_rsrc(v_base + (size_t)kv0 * row_stride, bytes), row_bytes, C::BN, wave, lane);
     };
+
+    // this lane's q and dO rows as B operands (rows past the end read as zero), and
+    // delta = sum_c dO_c O_c of its query: the lane holds half of the row's elements (8 of every 16),
+    // its partner at lane ^ 32 the other half.  The dK/dV kernel reads delta from memory afterwards.
+    // One tensor after the other: an access takes 32 bytes of each of 32 rows, and the four that share their 128-byte lines
+    // find them in the L1 only if they follow each other (the three tensors of the CU's waves are several times its size).  Taken
+    // in turn, dQ alone, us: 32 sequences of 256..648 tokens, 24 x 128, 201 against 192; 32 of 450, 48 x 64, 205 against 191.
+    // The first tile is under way before delta is formed.
+    // per-lane scalars of this lane's query; +inf LSE turns rows past the end into P = 0
+    const size_t row_at = (size_t)it.head * T + it.row0 + (q_valid ? q_row : 0);
+    float lse2 = DELTA ? lse[row_at] * kLog2e : lse2_out[row_at];
+    bf16x8 qf[C::KC], dof[C::KC];
+    float dl = DELTA ? 0.f : delta[row_at];
+    {
+      const uint32_t bytes = (uint32_t)min(L - q0, C::BM) * row_bytes;
+      const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
+      const auto rd = make_rsrc(dout + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
+      const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);   // DELTA only
+      const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+      bf16x8 of[C::KC];
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
+      KNAP_SCHED_FENCE();
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
+      KNAP_SCHED_FENCE();
+      if constexpr (DELTA) {
+#pragma unroll
+        for (int cc = 0; cc < C::KC; ++cc) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+        KNAP_SCHED_FENCE();
+      }
+      load_tile(0, sK0, sV0);    // a barrier stands between the last reads of either buffer (or the schedule build) and this
+      KNAP_SCHED_FENCE();
+      if constexpr (DELTA) dl = row_delta<D>(dof, of);
+    }
+    const float own = lse2;
+    if (!q_valid) lse2 = INFINITY;
+    f32x16 acc[C::DB];
+#pragma unroll
+    for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
 
     // One tile: 64 keys as two halves of 32, one after the other (the register file is full with
     // the q and dO fragments and the dQ accumulator; the second wave of the SIMD fills the gaps).
@@ -179,8 +185,11 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
         for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(kt0[db], d0, acc[db]);
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) acc[db] = mfma32(cols.get(tK, 32 * half + 16, db), d1, acc[db]);
-        KNAP_SGB(KNAP_SG_DS_READ, 2 * C::DB);          // the second chunk's K^T fragments go out first
-        KNAP_SGB(KNAP_SG_MFMA, 2 * C::DB);
+        // the second chunk's K^T fragments between the first chunk's MFMAs (all of them in front: 65536 tokens and 200 short
+        // ones, 24 x 128, 63.7 against 62.3 ms)
+#pragma unroll
+        for (int i = 0; i < C::DB; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 2); }
+        KNAP_SGB(KNAP_SG_MFMA, C::DB);
         KNAP_SCHED_FENCE();
       }
       }
@@ -188,10 +197,15 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       __syncthreads();     // next tile visible; this tile no longer read
     };
 
-    load_tile(0, sK0, sV0);    // a barrier stands between the last reads of either buffer (or the schedule build) and this
     wait_async_loads();
     draw();
-    __syncthreads();
+    if constexpr (DELTA) {          // behind the wait, which would wait for these stores as well
+      if (q_valid && hh == 0) {     // for the dK/dV kernel: delta, and the LSE in base 2 (it copies both straight into LDS)
+        delta[row_at] = dl;
+        lse2_out[row_at] = own;
+      }
+    }
+    lds_barrier();
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> ragged_end{};
     constexpr std::integral_constant<int, 2> diagonal{};
@@ -228,9 +242,9 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
 }
 
 // 64 query rows, from q0 on: waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the
-// second 32; the two gradients are added through LDS at the end.
-template <int D, bool CAUSAL, bool DELTA>
-__device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q0) {
+// second 32; the two gradients are added through LDS at the end.  `draw` is called behind the first loads.
+template <int D, bool CAUSAL, bool DELTA, class Draw>
+__device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q0, Draw draw) {
     using C = DqCfg<D>;
     const auto *q = g.q, *k = g.k, *v = g.v, *out = g.out, *dout = g.dout;
     const float* lse = g.lse;
@@ -272,10 +286,15 @@ __device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, cons
       const auto ro = make_rsrc(out + q_at, bytes);
       bf16x8 of[C::KC];
 #pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) {
-        qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
-        dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
-        if constexpr (DELTA) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+      for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, off + 32u * cc));
+      KNAP_SCHED_FENCE();
+#pragma unroll
+      for (int cc = 0; cc < C::KC; ++cc) dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
+      KNAP_SCHED_FENCE();
+      if constexpr (DELTA) {
+#pragma unroll
+        for (int cc = 0; cc < C::KC; ++cc) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+        KNAP_SCHED_FENCE();
       }
       load_tile(0, sK0, sV0);
       if constexpr (DELTA) dl = row_delta<D>(dof, of);
@@ -297,6 +316,7 @@ __device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, cons
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
     wait_async_loads();
+    draw();
     lds_barrier();
 
     auto half_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
@@ -390,8 +410,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  DqLane<D> me;
-  me.init(lane, wave, CAUSAL ? __builtin_amdgcn_readfirstlane(wave) : 0);
   const BwdPtrs g = {q, k, v, out, dout, lse, lse2_out, delta, dq, nullptr, nullptr, T, H, scale};
   const DqLds lds = {sK0, sK1, sV0, sV1};
 
@@ -404,43 +422,40 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
   ItemQueue<SPLIT> queue;
   queue.init(counters, s_start, n_seq, n_items);
   int ticket = queue.first_ticket();
-  while (ticket < queue.wide) {
-    const int w = queue.item(ticket);
-    const WorkItem it = decode_item<C::BM, CAUSAL>(w, cu, n_seq, s_order, s_start);
+  while (ticket < queue.wide + queue.parts) {
+    const bool whole = ticket < queue.wide;
+    const int p = queue.part0 + ticket - queue.wide;       // of the parts
+    const WorkItem it = decode_item<C::BM, CAUSAL>(whole ? queue.item(ticket) : queue.n_wide + p / SPLIT, cu, n_seq, s_order, s_start);
     unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
     // CAUSAL: the item is the pair of query tiles {q_tiles - 1 - p, p}, the long one first
-    const int q_tiles = (it.len + C::BM - 1) / C::BM;
-    int sub = 0;
+    const int other = (it.len + C::BM - 1) / C::BM - 1 - it.tile;
+    int sub = !CAUSAL || whole ? 0 : (p % SPLIT) >> 1;
+    bool first = true;
   second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
-    dq_tile<D, CAUSAL, true>(g, lds, me, it, !CAUSAL ? it.tile : sub == 0 ? q_tiles - 1 - it.tile : it.tile,
-                             [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); });
+    auto draw = [&] { if (tid == 0 && first && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); };
+    const int q_tile = !CAUSAL ? it.tile : sub == 0 ? other : it.tile;
+    const int q0 = __builtin_amdgcn_readfirstlane(q_tile * C::BM + (whole ? 0 : 64 * (p & 1)));
+    int ln = lane, wv = wave;
+    // what follows from them is formed per tile, not kept in registers through the other form's (45 values were spilled at d =
+    // 128, now 23, none in a loop over keys: 32 sequences of 450 tokens, 24 x 128, 200 -> 195 us)
+    asm volatile("" : "+v"(ln), "+v"(wv));
+    DqLane<D> me;
+    me.init(ln, wv, CAUSAL ? __builtin_amdgcn_readfirstlane(wv) : 0);
+    if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, true>(g, lds, me, it, q_tile, draw);
+    else if (q0 < it.len && !(CAUSAL && !whole && sub == 1 && it.tile == other)) dq_part<D, CAUSAL, true>(g, lds, me, it, q0, draw);
+    else draw();
     if constexpr (CAUSAL) {
-      if (sub == 0 && it.tile != q_tiles - 1 - it.tile) {   // not the middle tile of an odd count
+      if (whole && first && it.tile != other) {   // not the middle tile of an odd count
+        first = false;
         sub = 1;
         goto second_tile_of_pair;
       }
     }
     if (!queue.draws) return;
-    if (tid == 0) s_ticket = drawn_ticket(queue, next_ticket);   // every wave took its copy of the old one many barriers ago
-    lds_barrier();
+    if (tid == 0) s_ticket = drawn_ticket(queue, next_ticket);
+    lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
-  }
-
-  // Narrow items: 64 queries, as in the forward kernel.
-  if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
-  for (int part = ticket - queue.wide; part < queue.parts;) {
-    const int p = queue.part0 + part;
-    const WorkItem it = decode_item<C::BM, CAUSAL>(queue.n_wide + p / SPLIT, cu, n_seq, s_order, s_start);
-    const int q_tiles = (it.len + C::BM - 1) / C::BM;
-    const int member = (p % SPLIT) >> 1;
-    const int q0 = __builtin_amdgcn_readfirstlane((!CAUSAL ? it.tile : member == 0 ? q_tiles - 1 - it.tile : it.tile) * C::BM + 64 * (p & 1));
-    const bool exists = q0 < it.len && !(CAUSAL && member == 1 && it.tile == q_tiles - 1 - it.tile);
-    if (exists) dq_part<D, CAUSAL, true>(g, lds, me, it, q0);
-    if (!queue.draws) return;         // every part was a first ticket
-    if (tid == 0) s_ticket = drawn_ticket(queue, atomicAdd(queue.ctr, 1u));
-    lds_barrier();                    // (and part_acc is no longer read)
-    part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
-    lds_barrier();                    // everyone has the ticket before the next one is put down
+    if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows
   }
 }
 

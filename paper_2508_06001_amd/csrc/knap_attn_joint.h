@@ -10,8 +10,9 @@
 
 namespace knap {
 
-// delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once.  The sums run in the order in which
-// the dQ kernel forms them.
+// delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once (31464 tokens, 24 x 128: 77 us, 5.0
+// TB/s; 95 with the two tensors in turn, see dq_tile.  16 lanes side by side on a row: 75, but 59 against 55 us at 18356 tokens,
+// 48 x 64).  The sums run in the order in which the dQ kernel forms them.
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
     const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
@@ -27,10 +28,11 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
   const uint32_t off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
   bf16x8 of[D / 16], dof[D / 16];
 #pragma unroll
-  for (int cc = 0; cc < D / 16; ++cc) {
-    of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
-    dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
-  }
+  for (int cc = 0; cc < D / 16; ++cc) of[cc] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + 32u * cc));
+  KNAP_SCHED_FENCE();
+#pragma unroll
+  for (int cc = 0; cc < D / 16; ++cc) dof[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + 32u * cc));
+  KNAP_SCHED_FENCE();
   const float dl = row_delta<D>(dof, of);
   const int t = t0 + wave * 32 + l32;
   if (t < T && hh == 0) {
@@ -89,9 +91,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
     return it;
   };
   int ticket = queue.first_ticket();
-  while (ticket < queue.wide) {
-    const bool keys = queue.first_kind(ticket);
-    const WorkItem it = take(queue.item(ticket));
+  while (ticket < queue.wide + queue.parts) {
+    const bool whole = ticket < queue.wide, keys = whole && queue.first_kind(ticket);
+    const int part = ticket - queue.wide;
+    const WorkItem it = take(whole ? queue.item(ticket) : queue.item_of_part(part));
     unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
     // CAUSAL: the item is the pair of tiles {p, tiles - 1 - p}, the dearer one first; the middle tile of an odd count stands alone
     const int other = (it.len + BM - 1) / BM - 1 - it.tile;
@@ -107,36 +110,25 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
                                 [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
                                 [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket); });
     } else {
-      DqLane<D> me;
-      me.init(ln, wave, wave);
+      const int from = whole ? 0 : (part % SPLIT) >> 1, to = whole ? n_sub : from + 1;
 #pragma unroll 1
-      for (int sub = 0; sub < n_sub; ++sub)
-        dq_tile<D, CAUSAL, false>(g, q_lds, me, it, CAUSAL && sub == 0 ? other : it.tile,
-                                  [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); });
+      for (int sub = from; sub < to; ++sub) {
+        auto draw = [&] { if (tid == 0 && sub == from && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); };
+        const int q_tile = CAUSAL && sub == 0 ? other : it.tile;
+        const int q0 = q_tile * BM + (whole ? 0 : 64 * (part & 1));
+        asm volatile("" : "+v"(ln));
+        DqLane<D> me;
+        me.init(ln, wave, wave);
+        if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, false>(g, q_lds, me, it, q_tile, draw);
+        else if (q0 < it.len && sub < n_sub) dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0, draw);
+        else draw();
+      }
     }
     if (!queue.draws) return;
-    if (tid == 0 && !keys) s_ticket = drawn_ticket(queue, next_ticket);   // every wave took its copy of the old one many barriers ago
-    lds_barrier();
+    if (tid == 0 && !keys) s_ticket = drawn_ticket(queue, next_ticket);
+    lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
-  }
-
-  if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
-  for (int part = ticket - queue.wide; part < queue.parts;) {
-    const WorkItem it = take(queue.item_of_part(part));
-    const int other = (it.len + BM - 1) / BM - 1 - it.tile, member = (part % SPLIT) >> 1;
-    const int q0 = (CAUSAL && member == 0 ? other : it.tile) * BM + 64 * (part & 1);
-    if (q0 < it.len && !(member == 1 && it.tile == other)) {
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      DqLane<D> me;
-      me.init(ln, wave, wave);
-      dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0);
-    }
-    if (!queue.draws) return;         // every part was a first ticket
-    if (tid == 0) s_ticket = drawn_ticket(queue, atomicAdd(queue.ctr, 1u));
-    lds_barrier();                    // (and the partial sums are no longer read)
-    part = __builtin_amdgcn_readfirstlane(s_ticket) - queue.wide;
-    lds_barrier();                    // everyone has the ticket before the next one is put down
+    if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows
   }
 }
 

@@ -759,6 +759,21 @@ def test_backward_in_two_launches_on_small_bags(causal, d, lens, H, pairs):
                   strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,H", [(128, 9), (128, 30), (64, 15), (64, 30)])     # in one launch, and in two
+def test_short_last_query_tiles_of_whole_items(causal, d, H):
+    """Sequences whose last query tile has 1, 64 and 65 rows: the first two go through the dQ kernels' narrow form although
+    their items are whole, from the third tile on; the last ones, and tiles before the third, do not.  Many draws."""
+    lens = [257, 320, 321, 384, 448, 449, 385, 192, 129, 576] * 6
+    assert Q.bwd_joint(lens, H, d, causal) == (H < 20)
+    w = Q.walk_joint(lens, H, d, causal) if H < 20 else Q.walk("dq", lens, H, d, causal)
+    assert w.draws and w.parts == 0
+    # lse: a sum of at most 576 probabilities of relative error 2^-9 each is off by at most that, so lse by at most 2^-9 = 1.95e-3
+    # (LSE_TOL counts on the errors of more keys cancelling; measured here 1.002e-3)
+    _full_compare(BagSpec("short_last", lens, H=H, d=d, seed=9400 + H + d), heads=[0, H - 1],
+                  strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else 2.0 ** -9)
+
+
 @pytest.mark.timeout(300)
 def test_random_bags_both_masks():
     """A sweep of random small bags (log-uniform lengths 1..3000, 1..40 sequences, H in {1, 2, 5}, both head
