@@ -137,7 +137,7 @@ int knap_varlen_attn_causal_fwd(const void* q, const void* k, const void* v,
 size_t knap_varlen_attn_bwd_workspace_bytes(int64_t total_tokens, int n_seq, int H, int d) {
   (void)n_seq;
   if (total_tokens <= 0 || H <= 0 || d <= 0) return 0;
-  // delta and the base-2 log-sum-exp, fp32 (H, T) each, then 256 bytes of work-queue counters
+  // -delta and the base-2 log-sum-exp, fp32 (H, T) each, then 256 bytes of work-queue counters
   return 2 * round_up(static_cast<size_t>(total_tokens) * H * sizeof(float), 256) + 256;
 }
 

@@ -98,7 +98,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
 
     // this lane's q and dO rows as B operands (rows past the end read as zero), and
     // delta = sum_c dO_c O_c of its query: the lane holds half of the row's elements (8 of every 16),
-    // its partner at lane ^ 32 the other half.  The dK/dV kernel reads delta from memory afterwards.
+    // its partner at lane ^ 32 the other half.  The dK/dV kernel reads -delta from memory afterwards.
     // One tensor after the other: an access takes 32 bytes of each of 32 rows, and the four that share their 128-byte lines
     // find them in the L1 only if they follow each other (the three tensors of the CU's waves are several times its size).  Taken
     // in turn, dQ alone, us: 32 sequences of 256..648 tokens, 24 x 128, 201 against 192; 32 of 450, 48 x 64, 205 against 191.
@@ -107,7 +107,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     const size_t row_at = (size_t)it.head * T + it.row0 + (q_valid ? q_row : 0);
     float lse2 = DELTA ? lse[row_at] * kLog2e : lse2_out[row_at];
     bf16x8 qf[C::KC], dof[C::KC];
-    float dl = DELTA ? 0.f : delta[row_at];
+    float dl = DELTA ? 0.f : -delta[row_at];
     {
       const uint32_t bytes = (uint32_t)min(L - q0, C::BM) * row_bytes;
       const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + head_off, bytes);
@@ -200,8 +200,8 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     wait_async_loads();
     draw();
     if constexpr (DELTA) {          // behind the wait, which would wait for these stores as well
-      if (q_valid && hh == 0) {     // for the dK/dV kernel: delta, and the LSE in base 2 (it copies both straight into LDS)
-        delta[row_at] = dl;
+      if (q_valid && hh == 0) {     // for the dK/dV kernel: -delta, and the LSE in base 2 (it copies both straight into LDS)
+        delta[row_at] = -dl;
         lse2_out[row_at] = own;
       }
     }
@@ -305,11 +305,11 @@ __device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, cons
       const float own = lse[row_at] * kLog2e;
       lse2 = q_valid ? own : INFINITY;
       if (q_valid && hh == 0 && kh_u == 0) {
-        delta[row_at] = dl;
+        delta[row_at] = -dl;
         lse2_out[row_at] = own;
       }
     } else {
-      dl = delta[row_at];
+      dl = -delta[row_at];
       lse2 = q_valid ? lse2_out[row_at] : INFINITY;
     }
     f32x16 acc[C::DB];

@@ -10,7 +10,7 @@
 
 namespace knap {
 
-// delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once (31464 tokens, 24 x 128: 77 us, 5.0
+// -delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once (31464 tokens, 24 x 128: 77 us, 5.0
 // TB/s; 95 with the two tensors in turn, see dq_tile.  16 lanes side by side on a row: 75, but 59 against 55 us at 18356 tokens,
 // 48 x 64).  The sums run in the order in which the dQ kernel forms them.
 template <int D>
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
   const int t = t0 + wave * 32 + l32;
   if (t < T && hh == 0) {
     const size_t row_at = (size_t)head * T + t;
-    delta[row_at] = dl;
+    delta[row_at] = -dl;
     lse2[row_at] = lse[row_at] * kLog2e;
   }
 }

@@ -429,7 +429,7 @@ __device__ __forceinline__ WorkItem decode_even(int i, const Queue& queue, const
   return it;
 }
 
-// what the kernels of the backward read and write; delta and lse2 are handed from one to the next
+// what the kernels of the backward read and write; delta (negated, as the dK waves take it) and lse2 are handed from one to the next
 struct BwdPtrs {
   const __bf16 *q, *k, *v, *out, *dout;
   const float* lse;

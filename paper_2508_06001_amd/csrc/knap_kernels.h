@@ -24,7 +24,7 @@ struct BwdArgs {
   int n_seq, H;
   float scale;
   void *dq, *dk, *dv;
-  float *delta, *lse2;      // (H, T) each, handed from the dQ kernel to the dK/dV kernel
+  float *delta, *lse2;      // (H, T) each, -delta and the base-2 LSE, handed from the dQ kernel to the dK/dV kernel
   unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel
 };
 // `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `clear`: the counters' contents are unknown, and
