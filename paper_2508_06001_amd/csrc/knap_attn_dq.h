@@ -1,7 +1,7 @@
 // dQ kernel of the backward: the forward kernel's structure.  S^T = K Q^T and dP^T = V dO^T put one query in each
 // lane, LSE and delta are per-lane scalars, and dS^T is, unchanged, the B operand of dQ^T += K^T dS^T with K^T read
 // transposed from LDS.  One text, compiled for either mask in a translation unit of its own (see build.py).
-// d = 64: 168 registers (5 values spilled outside the loops, bidirectional) let three workgroups share a CU where 174 allowed two; the
+// d = 64: 168 registers (no value spilled) let three workgroups share a CU where 174 allowed two; the
 // third wave of a SIMD fills the exponentials of the others (48 x 64, 10 sequences of 310..6795 tokens: 2077 -> 1988 us,
 // 65536 tokens 77.6 -> 73.7 ms).
 #pragma once
@@ -31,11 +31,10 @@ template <int D>
 struct DqLane {
   RowReader<D> rows;     // K and V tile rows -> A operands of S^T and dP^T
   ColReader<D> cols;     // K tile columns -> A operands of dQ^T += K^T dS^T
-  int lane, wave, wave_u;       // wave_u: the same number as wave, known to be wave-uniform (CAUSAL only)
-  __device__ __forceinline__ void init(int lane_, int wave_, int wave_u_) {
+  int lane, wave;        // the wave known to be wave-uniform
+  __device__ __forceinline__ void init(int lane_, int wave_) {
     lane = lane_;
     wave = wave_;
-    wave_u = wave_u_;
     rows.init(lane);
     cols.init(lane);
   }
@@ -77,7 +76,6 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     const auto& cols = me.cols;
     const int lane = me.lane, wave = me.wave, l32 = lane & 31, hh = lane >> 5;
     __bf16 *const sK0 = lds.k0, *const sK1 = lds.k1, *const sV0 = lds.v0, *const sV1 = lds.v1;
-    const int wave_u = me.wave_u;
     const int q0 = q_tile * C::BM;
     const int q_row = q0 + wave * 32 + l32;
     const bool q_valid = q_row < L;
@@ -149,7 +147,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       constexpr int MODE = decltype(mode_tag)::value;
       constexpr bool DIAG = MODE == 2;
       load_tile(t + 1, nK, nV);
-      if (!(DIAG && t * C::BN > q0 + 32 * wave_u + 31)) {
+      if (!(DIAG && t * C::BN > q0 + 32 * wave + 31)) {
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         f32x16 s = zero16(), dp = zero16();
@@ -409,7 +407,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
   const int n_items = build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  // known to be wave-uniform, also behind the barrier to the compiler below: the LDS address of each of a tile's eight copies
+  // would go through a vector register, 8 to 16 of 155 vector instructions per tile (with the forward's alike, forward and
+  // backward of 60 sequences of 300 tokens, 24 x 128: 582 -> 573 us; 60 causal ones of 400 717 -> 705)
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const BwdPtrs g = {q, k, v, out, dout, lse, lse2_out, delta, dq, nullptr, nullptr, T, H, scale};
   const DqLds lds = {sK0, sK1, sV0, sV1};
 
@@ -437,10 +438,10 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
     const int q0 = __builtin_amdgcn_readfirstlane(q_tile * C::BM + (whole ? 0 : 64 * (p & 1)));
     int ln = lane, wv = wave;
     // what follows from them is formed per tile, not kept in registers through the other form's (45 values were spilled at d =
-    // 128, now 23, none in a loop over keys: 32 sequences of 450 tokens, 24 x 128, 200 -> 195 us)
-    asm volatile("" : "+v"(ln), "+v"(wv));
+    // 128, now 10, none in a loop over keys: 32 sequences of 450 tokens, 24 x 128, 200 -> 195 us)
+    asm volatile("" : "+v"(ln), "+s"(wv));
     DqLane<D> me;
-    me.init(ln, wv, CAUSAL ? __builtin_amdgcn_readfirstlane(wv) : 0);
+    me.init(ln, wv);
     if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, true>(g, lds, me, it, q_tile, draw);
     else if (q0 < it.len && !(CAUSAL && !whole && sub == 1 && it.tile == other)) dq_part<D, CAUSAL, true>(g, lds, me, it, q0, draw);
     else draw();

@@ -72,8 +72,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   build_schedule<C::BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sK0[0]));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wave_u = CAUSAL ? __builtin_amdgcn_readfirstlane(wave) : 0;   // the same number, known to be wave-uniform
+  // known to be wave-uniform: the LDS address of each of a tile's eight copies otherwise goes through a vector register (dQ
+  // kernel: there)
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int hh = lane >> 5;
   const float c = scale * kLog2e;
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
     auto process_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
       load_tile(t + 1, kv_end, nK, nV);
       const bool masked = t >= first_masked;
-      if (!(CAUSAL && t * C::BN > q0 + 32 * wave_u + 31)) {
+      if (!(CAUSAL && t * C::BN > q0 + 32 * wave + 31)) {
 
       bf16x8 ak0[C::KC], ak1[C::KC];
 #pragma unroll

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
         const int q0 = q_tile * BM + (whole ? 0 : 64 * (part & 1));
         asm volatile("" : "+v"(ln));
         DqLane<D> me;
-        me.init(ln, wave, wave);
+        me.init(ln, wave);
         if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, false>(g, q_lds, me, it, q_tile, draw);
         else if (q0 < it.len && sub < n_sub) dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0, draw);
         else draw();
