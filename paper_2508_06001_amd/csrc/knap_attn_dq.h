@@ -1,7 +1,7 @@
 // dQ kernel of the backward: the forward kernel's structure.  S^T = K Q^T and dP^T = V dO^T put one query in each
 // lane, LSE and delta are per-lane scalars, and dS^T is, unchanged, the B operand of dQ^T += K^T dS^T with K^T read
 // transposed from LDS.  One text, compiled for either mask in a translation unit of its own (see build.py).
-// d = 64: 168 registers (no value spilled) let three workgroups share a CU where 174 allowed two; the
+// d = 64: 168 registers (10 values spilled outside the loops, bidirectional) let three workgroups share a CU where 174 allowed two; the
 // third wave of a SIMD fills the exponentials of the others (48 x 64, 10 sequences of 310..6795 tokens: 2077 -> 1988 us,
 // 65536 tokens 77.6 -> 73.7 ms).
 #pragma once
@@ -134,6 +134,13 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) acc[db] = zero16();
 
+    // d = 64: dP^T starts from -delta, which sits in 16 registers through the loop, so that nothing is subtracted per score: 115
+    // vector instructions per tile instead of 147, beside 24 MFMAs (48 x 64, forward and backward in us: 10 sequences of
+    // 310..6795 tokens 5855 -> 5749, 16 of 4096 14010 -> 13746, 20 causal ones of 3000 5662 -> 5573; 32 of 450 the same).  At d =
+    // 128 the 16 registers are not there: 54 to 129 values spilled around the loop, long sequences 0.8 to 1.4 % faster, 9 of
+    // 1000 tokens, 12 heads, 2.3 % slower, 60 of 300, 24 heads, 2.2 %.
+    constexpr bool SEEDED = D == 64;
+    f32x16 dp_start;
     // One tile: 64 keys as two halves of 32, one after the other (the register file is full with
     // the q and dO fragments and the dQ accumulator; the second wave of the SIMD fills the gaps).
     // Within a half the LDS reads are streamed a few MFMAs ahead of their use.
@@ -150,7 +157,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       if (!(DIAG && t * C::BN > q0 + 32 * wave + 31)) {
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        f32x16 s = zero16(), dp = zero16();
+        f32x16 s = zero16(), dp = SEEDED ? dp_start : zero16();
         if constexpr (MODE == 1) {
           const int first_past = L - t * C::BN - 32 * half - 4 * hh;   // counted from this half's first key
 #pragma unroll
@@ -173,7 +180,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
         const int last_seen = q_row - t * C::BN - 32 * half - 4 * hh;   // counted from this half's first key
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float x = fast_exp2(__builtin_fmaf(s[r], c, -lse2)) * (dp[r] - dl);
+          const float x = fast_exp2(__builtin_fmaf(s[r], c, -lse2)) * (SEEDED ? dp[r] : dp[r] - dl);
           ds[r] = (DIAG && 8 * (r >> 2) + (r & 3) > last_seen) ? 0.f : x;
         }
         const bf16x8 d0 = pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
@@ -204,6 +211,11 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       }
     }
     lds_barrier();
+    if constexpr (SEEDED) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp_start[r] = -dl;
+      asm volatile("" : "+v"(dp_start));         // 16 registers, not one that is copied 16 times per half tile
+    }
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> ragged_end{};
     constexpr std::integral_constant<int, 2> diagonal{};
