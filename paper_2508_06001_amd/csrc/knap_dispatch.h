@@ -75,7 +75,7 @@ inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal
 }
 
 // Whether some queue of the backward's kernels may hold more items than workgroups, so that counters of unknown contents
-// have to be cleared first.  A bag has at most T / tile + n_seq tiles per head.  Few enough that all parts of all items
+// (a captured call's, in the caller's workspace) have to be cleared first.  A bag has at most T / tile + n_seq tiles per head.  Few enough that all parts of all items
 // (four each under the mask, two without) find a workgroup: the dQ kernel deals out parts and draws none (see
 // ItemQueue).  The dK/dV kernel's items, at most half as many as its workgroups, fill at most per / 2 tickets of a
 // queue in whole rounds and a chunk of at most as many in the last.  The clearing launch costs 2 to 5 us.
