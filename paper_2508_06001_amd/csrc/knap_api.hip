@@ -203,16 +203,16 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
 
   float* delta = static_cast<float*>(workspace);
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + (need - 256) / 2);
-  // counters at zero from the library's sets; a captured launch, which keeps its counters for every replay, clears 16 words
-  // of the workspace instead
+  // counters at zero from the library's sets; a captured launch, which keeps its counters for every replay, has 16 words of
+  // the workspace instead, which are cleared first
   const bool captured = capturing(stream);
   unsigned* counters = captured ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256)
                                 : di->queues + 16u * (g_launches.fetch_add(1u) % ((unsigned)knap::queue_sets() / 2u));
   const int dq_wg = di->dq_wg[d == 128];
   const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
   if (knap::bwd_joint(total_tokens, n_seq, H, d, causal, di->cus)) {
-    const hipError_t e = knap::launch_joint(args, d, causal, (int)total_tokens, di->cus, captured, static_cast<hipStream_t>(stream),
-                                            g_prof_start, g_prof_stop);
+    const hipError_t e = knap::launch_joint(args, d, causal, (int)total_tokens, di->cus, static_cast<hipStream_t>(stream), g_prof_start,
+                                            g_prof_stop);
     if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
     return KNAP_OK;
   }

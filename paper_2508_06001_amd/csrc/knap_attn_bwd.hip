@@ -51,13 +51,8 @@ hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int 
   return hipSuccess;
 }
 
-hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, bool clear, hipStream_t stream, hipEvent_t ev_start,
-                        hipEvent_t ev_stop) {
+hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipError_t e = hipSuccess;
-  if (clear) {
-    hipLaunchKernelGGL(bwd_queue_reset_kernel, dim3(1), dim3(64), 0, stream, a.counters);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   if (ev_start && ev_stop && (e = hipEventRecord(ev_start, stream)) != hipSuccess) return e;
   e = causal ? launch_joint_causal(a, d, T, cus, stream) : launch_joint_m<false>(a, d, T, cus, stream);
   if (e != hipSuccess) return e;

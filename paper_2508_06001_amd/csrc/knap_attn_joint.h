@@ -12,11 +12,14 @@ namespace knap {
 
 // -delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once (31464 tokens, 24 x 128: 77 us, 5.0
 // TB/s; 95 with the two tensors in turn, see dq_tile.  16 lanes side by side on a row: 75, but 59 against 55 us at 18356 tokens,
-// 48 x 64).  The sums run in the order in which the dQ kernel forms them.
+// 48 x 64).  The sums run in the order in which the dQ kernel forms them.  It also clears the counters of the queues of the
+// launch behind it, which therefore may hold anything (a caller's workspace) and need no launch of their own.
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
     const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ lse2, const int32_t* __restrict__ cu, int n_seq, int H) {
+    float* __restrict__ delta, float* __restrict__ lse2, const int32_t* __restrict__ cu, int n_seq, int H,
+    unsigned* __restrict__ counters) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
   const int t0 = blockIdx.x * 128, head = blockIdx.y, T = cu[n_seq];
   if (t0 >= T) return;
@@ -137,7 +140,7 @@ static hipError_t launch_joint_m(const BwdArgs& a, int d, int T, int cus, hipStr
   const dim3 rows((T + 127) / 128, a.H);
   auto* delta = d == 64 ? attn_bwd_delta_kernel<64> : attn_bwd_delta_kernel<128>;
   hipLaunchKernelGGL(delta, rows, dim3(kThreads), 0, stream, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
-                     a.n_seq, a.H);
+                     a.n_seq, a.H, a.counters);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);

@@ -31,8 +31,8 @@ struct BwdArgs {
 // some queue may hold more items than workgroups: they have to be cleared first.
 hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool clear,
                       hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
-// the backward of a small bag: T tokens, both kinds of items in one launch (knap_attn_joint.h)
-hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, bool clear, hipStream_t stream, hipEvent_t ev_start,
+// the backward of a small bag: T tokens, both kinds of items in one launch (knap_attn_joint.h), whose counters may hold anything
+hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, hipStream_t stream, hipEvent_t ev_start,
                         hipEvent_t ev_stop);
 hipError_t launch_joint_causal(const BwdArgs& a, int d, int T, int cus, hipStream_t stream);
 hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream);

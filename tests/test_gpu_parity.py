@@ -16,6 +16,8 @@ Where the plain bars cannot hold, the relaxed ones are asked for explicitly:
   bags), but a row dominated by one or two keys (peaky bags, very short or causal rows) keeps up to
   2^-9 = 2e-3 of relative error in its sum.
 """
+import os
+
 import numpy as np
 import pytest
 
@@ -227,6 +229,45 @@ def test_hip_graph_replays_match_eager():
                bf16_device_to_bits(a.dv), a.lse.cpu().numpy().astype(np.float64)]
         for g, w_, name in zip(got, want, ("out", "dq", "dk", "dv", "lse")):
             assert np.array_equal(g, w_), (rep, name)
+
+
+def _graph_nodes(graph) -> int:
+    """Nodes of a captured graph (kept for this: keep_graph=True)."""
+    import ctypes as C
+    hip = C.CDLL("libamdhip64.so.7", mode=os.RTLD_NOLOAD | C.RTLD_GLOBAL)      # the runtime that is loaded, never a second one
+    hip.hipGraphGetNodes.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_size_t)]
+    n = C.c_size_t()
+    assert hip.hipGraphGetNodes(graph.raw_cuda_graph(), None, C.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("causal,d,lens,H,nodes", [
+    (False, 64, [37, 128, 200, 311], 2, 2), (True, 128, [300], 3, 2),                          # one launch, nothing drawn
+    (False, 128, [700, 90, 1300], 48, 2), (True, 64, [1290, 333, 64, 700], 90, 2),             # one launch, items drawn
+    (False, 128, [1 + i % 9 for i in range(640)], 4, 3), (True, 64, [1 + i % 9 for i in range(900)], 4, 3)])   # two launches
+def test_captured_backward_whatever_the_workspace_holds(causal, d, lens, H, nodes):
+    """A captured backward draws from counters in its workspace: replays reproduce the eager gradients bit for bit whatever
+    stands there, and the counters cost a launch of their own only in front of the dQ and dK/dV kernels.  One launch of both
+    kinds of items comes behind the one that forms delta, which clears them."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    assert Q.bwd_joint(lens, H, d, causal) == (nodes == 2)
+    run = GpuRun(BagSpec("captured", lens, H=H, d=d, seed=9500 + H + d), causal=causal)
+    a, x = run.attn, run.dev
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        a.backward(x["q"], x["k"], x["v"], x["dout"])
+    assert _graph_nodes(graph) == nodes
+    graph.instantiate()
+    for byte in (0, 1, 0xff, 0x80):
+        a.workspace.fill_(byte)
+        for t in (a.dq, a.dk, a.dv):
+            t.fill_(float("nan"))                              # an item that nobody takes shows
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+            assert np.array_equal(bf16_device_to_bits(got), want), byte
 
 
 # ---------------------------------------------------------------------------
