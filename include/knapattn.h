@@ -66,17 +66,16 @@ extern "C" {
 
 /* out = softmax(scale * q k^T) v per (sequence, head); also writes lse.
  *
- * Concurrency.  The kernels of the forward and the backward draw their work items
- * from counters that live in the library's device image: 8192 sets, which every
- * kernel leaves at zero.  Eager launches take sets 0..4095 in rotation: calls
+ * Concurrency.  The kernel draws its work items from counters that live in the
+ * library's device image: 8192 sets, which it leaves at zero.  Eager launches
+ * take sets 0..4095 in rotation: calls
  * from several threads and on several streams may overlap freely as long as no
- * launch is still running when the 4096th eager call after it runs.
- * A forward launch recorded under stream capture takes one of sets 4096..8191
+ * launch is still running when the 4096th eager forward call after it runs.
+ * A launch recorded under stream capture takes one of sets 4096..8191
  * and keeps it for every replay of its graph, so replays never share a set with
  * eager launches; two captured launches share a set only once more than 4096
  * forward launches have been captured in the process, and graphs that hold such
- * a pair must then not be replayed at the same time.  (A captured backward has
- * its counters in its workspace.)  The first call on a device (it
+ * a pair must then not be replayed at the same time.  The first call on a device (it
  * looks up device properties, once, under a lock) must not be made under
  * stream capture; later calls may be captured. */
 int knap_varlen_attn_fwd(const void* q, const void* k, const void* v,
@@ -94,9 +93,9 @@ int knap_varlen_attn_fwd(const void* q, const void* k, const void* v,
  * knap_varlen_attn_bwd_workspace_bytes(total_tokens, n_seq, H, d) bytes,
  * 256-byte aligned; its contents on entry are ignored and on return are
  * unspecified.  It holds the per-row dot products of dout and out, the
- * log-sum-exp in base 2 and, for a captured call, the counters of the kernels'
- * work queues, so two calls that may run at the same time (different streams)
- * need a workspace each. */
+ * log-sum-exp in base 2 and the counters of the kernels' work queues, so two
+ * calls that may run at the same time (different streams) need a workspace
+ * each; with one each, any number of calls may. */
 int knap_varlen_attn_bwd(const void* q, const void* k, const void* v,
                          const int32_t* cu_seqlens, int n_seq,
                          int H, int d, float scale,

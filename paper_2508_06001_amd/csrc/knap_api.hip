@@ -10,7 +10,7 @@
 #include <mutex>
 
 // Scratch of knap_varlen_attn_bwd_noalloc: the per-row dot products of dout and out and the base-2
-// log-sum-exp (fp32, (H, T) each) and, in the last 256 bytes, the work-queue counters of a captured call.  Part of the library's device image:
+// log-sum-exp (fp32, (H, T) each) and, in the last 256 bytes, the work-queue counters.  Part of the library's device image:
 // every GPU the library runs on holds its own copy until the process ends.  Host code never uses this
 // name as an address; it uses the pointer hipGetSymbolAddress returned on that device (DeviceInfo::scratch).
 static __device__ __align__(256) unsigned char scratch[2 * KNAP_NOALLOC_MAX_ROWS * sizeof(float) + 256];
@@ -29,9 +29,9 @@ struct DeviceInfo {
   unsigned char* scratch = nullptr;   // this device's copy of `scratch`
 };
 
-// Counter sets of the work queues: the lower half is handed out in rotation to eager launches, the upper half to forward
+// Counter sets of the forward's work queues: the lower half is handed out in rotation to eager launches, the upper half to
 // launches recorded under stream capture.  A captured launch keeps its set for every replay of its graph, so it must
-// never be one that eager launches rotate through.  (A captured backward keeps its counters in its own workspace.)
+// never be one that eager launches rotate through.  (A backward has its counters in its own workspace.)
 std::atomic<unsigned> g_launches{0};
 std::atomic<unsigned> g_captured{0};
 
@@ -104,7 +104,7 @@ int fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   if (!di) return KNAP_ERR_LAUNCH_FAILED;
   const int grid = di->cus * di->fwd_wg[d == 128];
   const unsigned half = (unsigned)knap::queue_sets() / 2u;
-  unsigned* counters = di->queues + 16u * (capturing(stream) ? half + g_captured.fetch_add(1u) % half : g_launches.fetch_add(1u) % half);
+  unsigned* counters = di->queues + 8u * (capturing(stream) ? half + g_captured.fetch_add(1u) % half : g_launches.fetch_add(1u) % half);
   const hipError_t e = knap::launch_fwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, counters,
                                         grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
@@ -203,11 +203,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
 
   float* delta = static_cast<float*>(workspace);
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + (need - 256) / 2);
-  // counters at zero from the library's sets; a captured launch, which keeps its counters for every replay, has 16 words of
-  // the workspace instead, which are cleared first
-  const bool captured = capturing(stream);
-  unsigned* counters = captured ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256)
-                                : di->queues + 16u * (g_launches.fetch_add(1u) % ((unsigned)knap::queue_sets() / 2u));
+  unsigned* counters = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + need - 256);
   const int dq_wg = di->dq_wg[d == 128];
   const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
   if (knap::bwd_joint(total_tokens, n_seq, H, d, causal, di->cus)) {
@@ -217,9 +213,8 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
     return KNAP_OK;
   }
   const int pairs = knap::dkdv_pairs(total_tokens, n_seq, H, d, causal, di->cus);
-  const hipError_t e = knap::launch_bwd(args, d, causal, pairs, di->cus, dq_wg,
-                                        captured && knap::bwd_draws(total_tokens, n_seq, H, causal, pairs, di->cus, di->cus * dq_wg),
-                                        static_cast<hipStream_t>(stream), g_prof_start, g_prof_stop);
+  const hipError_t e = knap::launch_bwd(args, d, causal, pairs, di->cus, dq_wg, static_cast<hipStream_t>(stream),
+                                        g_prof_start, g_prof_stop);
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
 }

@@ -29,18 +29,17 @@ namespace knap {
 
 constexpr int kQueueCounters = 16;    // one work-queue counter per XCD for the dQ kernel, then one for the dK/dV kernel
 
-// the work queues of the kernels that follow on the stream start at zero (counters in a caller's workspace)
+// The work queues of the kernels that follow on the stream start at zero.  The counters lie in the call's workspace, as the
+// kernels' results do: whatever else runs, no other call draws from them.
 __global__ void bwd_queue_reset_kernel(unsigned* __restrict__ counters) {
   if (threadIdx.x < kQueueCounters) counters[threadIdx.x] = 0u;
 }
 
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool clear,
-                      hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  hipError_t e = hipSuccess;
-  if (clear) {
-    hipLaunchKernelGGL(bwd_queue_reset_kernel, dim3(1), dim3(64), 0, stream, a.counters);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, hipStream_t stream,
+                      hipEvent_t ev_start, hipEvent_t ev_stop) {
+  hipLaunchKernelGGL(bwd_queue_reset_kernel, dim3(1), dim3(64), 0, stream, a.counters);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   // the dQ kernel also produces delta, which the dK/dV kernel needs: it goes first
   e = causal ? launch_dq_causal(a, d, cus, dq_wg_per_cu, stream) : launch_dq_m<false>(a, d, cus, dq_wg_per_cu, stream);
   if (e != hipSuccess) return e;

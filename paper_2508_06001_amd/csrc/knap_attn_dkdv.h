@@ -479,7 +479,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
   second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
     dkdv_tile<D, PAIRS, CAUSAL>(g, lds, me, it, (!CAUSAL || sub == 0) ? it.tile : kv_tiles - 1 - it.tile,
         [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
-        [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket); });
+        [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket); });
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != kv_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;

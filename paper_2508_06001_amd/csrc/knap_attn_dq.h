@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
       }
     }
     if (!queue.draws) return;
-    if (tid == 0) s_ticket = drawn_ticket(queue, next_ticket);
+    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);
     lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows

@@ -448,11 +448,11 @@ KNAP_FWD_INSTANCE(64, true)
 KNAP_FWD_INSTANCE(128, true)
 #undef KNAP_FWD_INSTANCE
 
-// Counters of the work queues, in the library's device image (512 KB that start at zero): kQueueSets sets of 16, 8 for a
-// forward or dQ kernel and 8 for a dK/dV kernel (one per XCD), handed out in rotation by the host.  Every kernel
+// The forward entry points have no workspace, so the counters of their work queues live in the library's device image (256 KB
+// that start at zero): kQueueSets sets of 8 (one counter per XCD), handed out in rotation by the host.  The kernel
 // leaves its counters at zero, so no launch has to clear them.  Two launches share a set only if half of kQueueSets
 // others were enqueued between them while the first was still running.
-static __device__ __align__(256) unsigned g_queues[kQueueSets * 16];
+static __device__ __align__(256) unsigned g_queues[kQueueSets * 8];
 
 int queue_sets() { return kQueueSets; }
 

@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
       for (int sub = 0; sub < n_sub; ++sub)
         dkdv_tile<D, 2, CAUSAL>(g, kv_lds, me, it, sub == 0 ? it.tile : other,
                                 [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
-                                [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = drawn_ticket(queue, next_ticket); });
+                                [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket); });
     } else {
       const int from = whole ? 0 : (part % SPLIT) >> 1, to = whole ? n_sub : from + 1;
 #pragma unroll 1
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
       }
     }
     if (!queue.draws) return;
-    if (tid == 0 && !keys) s_ticket = drawn_ticket(queue, next_ticket);
+    if (tid == 0 && !keys) s_ticket = queue.later_ticket(next_ticket);
     lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows

@@ -74,15 +74,4 @@ inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal
   return !(n_seq == 1 && r > 0.8 && r <= 1.0);
 }
 
-// Whether some queue of the backward's kernels may hold more items than workgroups, so that counters of unknown contents
-// (a captured call's, in the caller's workspace) have to be cleared first.  A bag has at most T / tile + n_seq tiles per head.  Few enough that all parts of all items
-// (four each under the mask, two without) find a workgroup: the dQ kernel deals out parts and draws none (see
-// ItemQueue).  The dK/dV kernel's items, at most half as many as its workgroups, fill at most per / 2 tickets of a
-// queue in whole rounds and a chunk of at most as many in the last.  The clearing launch costs 2 to 5 us.
-inline bool bwd_draws(int64_t total_tokens, int n_seq, int H, bool causal, int pairs, int cus, int grid_dq) {
-  const int64_t items_dq = (total_tokens / 128 + n_seq) * H;
-  const int64_t items_dkdv = (total_tokens / (64 * pairs) + n_seq) * H;
-  return items_dq * (causal ? 4 : 2) > grid_dq || items_dkdv * 2 > cus * dkdv_workgroups_per_cu(pairs);
-}
-
 }  // namespace knap

@@ -12,7 +12,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t
                       int H, int d, float scale, bool causal, void* out, float* lse, unsigned* counters,
                       int grid, hipStream_t stream);
 
-// Device address (on the current device) of the library's work-queue counters: queue_sets() sets of 16, at zero
+// Device address (on the current device) of the forward's work-queue counters: queue_sets() sets of 8, at zero
 // whenever no kernel uses them; nullptr on failure.
 unsigned* queue_base();
 int queue_sets();
@@ -25,13 +25,12 @@ struct BwdArgs {
   float scale;
   void *dq, *dk, *dv;
   float *delta, *lse2;      // (H, T) each, -delta and the base-2 LSE, handed from the dQ kernel to the dK/dV kernel
-  unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel
+  unsigned* counters;       // 8 for the dQ kernel, 8 for the dK/dV kernel; the launches clear them, they may hold anything
 };
-// `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel.  `clear`: the counters' contents are unknown, and
-// some queue may hold more items than workgroups: they have to be cleared first.
-hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, bool clear,
-                      hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
-// the backward of a small bag: T tokens, both kinds of items in one launch (knap_attn_joint.h), whose counters may hold anything
+// `dkdv_pairs`: wave pairs (2 or 4) per workgroup of the dK/dV kernel
+hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int cus, int dq_wg_per_cu, hipStream_t stream,
+                      hipEvent_t ev_start, hipEvent_t ev_stop);
+// the backward of a small bag: T tokens, both kinds of items in one launch (knap_attn_joint.h)
 hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, hipStream_t stream, hipEvent_t ev_start,
                         hipEvent_t ev_stop);
 hipError_t launch_joint_causal(const BwdArgs& a, int d, int T, int cus, hipStream_t stream);

@@ -39,12 +39,10 @@ __device__ __forceinline__ bool long_tail(const int* s_start, int n_seq, int w) 
 }
 
 // Dynamic assignment for kernels that are handed counters at zero (one unsigned per XCD, 8 in
-// all) and leave them at zero: the descending-cost item list is cut into chunks of consecutive items, every XCD takes one
+// all): the descending-cost item list is cut into chunks of consecutive items, every XCD takes one
 // chunk of each round of 8 (so that the workgroups of an XCD keep meeting on the same K and V in its
 // L2), and the workgroups of an XCD draw that XCD's items in order from its counter: list
 // scheduling, longest first, within the XCD.  The first ticket past the queue's items ends the workgroup.
-// Every workgroup of a queue that draws draws until then, so a queue's draws are as many as its tickets, and whoever
-// draws the last one puts the counter back: no launch in front of the kernel has to (5 us on a busy stream).
 //
 // Chunks are G / 8 items (smaller ones cost long sequences up to 7 %: fewer workgroups meet in an L2),
 // except where the dear items are fewer than G: those are then dealt evenly, an eighth to every XCD,
@@ -98,7 +96,6 @@ struct ItemQueue {
   // and the counter deals out the ones after them
   __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
   __device__ __forceinline__ int later_ticket(unsigned drawn) const { return per + (int)drawn; }
-  __device__ __forceinline__ bool last_draw(unsigned drawn) const { return (int)drawn == wide + parts - 1; }
   __device__ __forceinline__ int chunk_of(int round) const { return (round & 1) ? n_q - 1 - q : q; }
   __device__ __forceinline__ int item(int ticket) const {     // ticket < wide
     const int round = ticket / chunk;
@@ -167,6 +164,9 @@ struct EvenQueue {
   __device__ __forceinline__ int item_of_part(int part) const { return wide - (KINDS - 1) * mine + part / SPLIT; }
   __device__ __forceinline__ int first_ticket() const { return (int)blockIdx.x / n_q; }
   __device__ __forceinline__ int later_ticket(unsigned drawn) const { return per + (int)drawn; }
+  // Every workgroup of a queue that draws draws until a ticket is past the queue's, so its draws are as many as its tickets:
+  // whoever draws the last one can put the counter back to zero, and no launch in front of the kernel has to (5 us on a busy
+  // stream)
   __device__ __forceinline__ bool last_draw(unsigned drawn) const { return (int)drawn == wide + parts - 1; }
 };
 

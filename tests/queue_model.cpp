@@ -49,17 +49,6 @@ Walk walk(int grid, const std::vector<int>& start, int n_seq, int n_items) {
       const int at = n_wide * SPLIT + queue.part0 + p;
       if (at < 0 || at >= n_items * SPLIT) ++r.wrong; else ++part[at];
     }
-    // every workgroup of a queue that draws draws until a ticket is past the queue's: the last draw, which puts the counter
-    // back to zero, is known as such, and nobody draws after it
-    if (queue.draws) {
-      int at_work = queue.per;
-      unsigned drawn = 0;
-      for (; at_work > 0 && drawn <= (unsigned)tickets; ++drawn) {
-        if (queue.later_ticket(drawn) >= tickets) --at_work;
-        r.wrong += queue.last_draw(drawn) != (at_work == 0);
-      }
-      r.wrong += at_work != 0;
-    }
     r.per = queue.per;
     r.most = max(r.most, tickets);
     r.draws |= queue.draws;
@@ -106,6 +95,8 @@ Walk walk_even(int grid, const std::vector<int>& start, int n_seq, int n_items) 
       r.wrong += queue.first_ticket() != i;
     }
     r.wrong += queue.later_ticket(0u) != queue.per || queue.ctr != counters.data() + q || (!queue.draws && tickets > queue.per);
+    // every workgroup of a queue that draws draws until a ticket is past the queue's: the last draw, which puts the counter
+    // back to zero, is known as such, and nobody draws after it
     if (queue.draws) {
       int at_work = queue.per;
       for (unsigned drawn = 0; at_work > 0 && drawn <= (unsigned)tickets; ++drawn) {
@@ -172,9 +163,5 @@ int queue_dkdv_pairs(long long tokens, int n_seq, int H, int d, int causal, int 
 }
 
 int queue_dkdv_workgroups_per_cu(int pairs) { return knap::dkdv_workgroups_per_cu(pairs); }
-
-int queue_bwd_draws(long long tokens, int n_seq, int H, int causal, int pairs, int cus, int grid_dq) {
-  return knap::bwd_draws(tokens, n_seq, H, causal != 0, pairs, cus, grid_dq);
-}
 
 }  // extern "C"

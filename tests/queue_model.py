@@ -41,7 +41,6 @@ def _lib():
     lib.queue_walk_even.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
-    lib.queue_bwd_draws.argtypes = [C.c_longlong] + [C.c_int] * 6
     return lib
 
 
@@ -53,12 +52,6 @@ def grid(kernel: str, d: int, pairs: int = 0, cus: int = CUS) -> int:
     if kernel == "dkdv":
         return cus * _lib().queue_dkdv_workgroups_per_cu(pairs)
     return cus * WORKGROUPS_PER_CU[kernel][d]
-
-
-def bwd_draws(lens: Sequence[int], H: int, d: int, causal: bool, pairs: int = 0, cus: int = CUS) -> bool:
-    """Whether the host clears the backward's counters."""
-    pairs = pairs or dkdv_pairs(lens, H, d, causal, cus)
-    return bool(_lib().queue_bwd_draws(sum(lens), len(lens), H, int(causal), pairs, cus, grid("dq", d, cus=cus)))
 
 
 def _walk_even(lens: Sequence[int], H: int, causal: bool, kinds: int, grid_: int) -> Walk:

@@ -270,6 +270,64 @@ def test_captured_backward_whatever_the_workspace_holds(causal, d, lens, H, node
             assert np.array_equal(bf16_device_to_bits(got), want), byte
 
 
+_DRAW_JOINT = [1 + (5 * i) % 9 for i in range(500)], 4, 64        # one launch of the backward
+_DRAW_TWO = [1 + i % 9 for i in range(640)], 4, 128               # two
+
+
+@pytest.mark.parametrize("entry", ["bwd", "noalloc", "causal_bwd"])
+@pytest.mark.parametrize("lens,H,d", [_DRAW_JOINT, _DRAW_TWO])
+def test_backward_draws_from_counters_of_its_own_workspace(lens, H, d, entry):
+    """No call draws from counters that another call with a workspace of its own may draw from: an eager backward whose kernels
+    draw leaves its draws in the last 256 bytes of the workspace it was given (8 counters of one launch, 8 of each of two)."""
+    import torch
+    import paper_2508_06001_amd as K
+    causal = entry == "causal_bwd"
+    joint = Q.bwd_joint(lens, H, d, causal)
+    assert joint == (len(lens) == 500)
+    assert Q.walk_joint(lens, H, d, causal).draws if joint else Q.walk("dq", lens, H, d, causal).draws and Q.walk("dkdv", lens, H, d, causal).draws
+    run = GpuRun(BagSpec("own_counters", lens, H=H, d=d, seed=9600 + d), causal=causal)
+    a, x = run.attn, run.dev
+    want = [t.clone() for t in (a.dq, a.dk, a.dv)]
+    a.workspace.fill_(0xff)
+    if entry == "noalloc":                       # the library's own scratch, with the draws of the call before
+        for i in range(3):
+            K.knap_varlen_attn_bwd_noalloc(x["q"], x["k"], x["v"], a.cu, a.n_seq, H, d, a.scale, a.out, a.lse, x["dout"],
+                                           a.dq, a.dk, a.dv, a.T)
+    else:
+        a.backward(x["q"], x["k"], x["v"], x["dout"])
+    torch.cuda.synchronize()
+    for got, w in zip((a.dq, a.dk, a.dv), want):
+        assert torch.equal(got, w)
+    words = a.workspace[K.knap_varlen_attn_bwd_workspace_bytes(a.T, a.n_seq, H, d) - 256:].view(torch.int32).tolist()
+    if entry == "noalloc":
+        assert words[:16] == [-1] * 16
+    else:
+        n = 8 if joint else 16
+        assert all(0 < w < 1 << 20 for w in words[:n]) and words[n:64] == [-1] * (64 - n)
+
+
+def test_backward_that_runs_while_thousands_of_others_do():
+    """Long backwards on a stream of their own, 4200 short ones that draw on another: any number of calls may be in flight."""
+    import torch
+    assert Q.bwd_joint(_DRAW_JOINT[0], 4, 64, False) and not Q.bwd_joint([30000], 12, 128, False)
+    long = GpuRun(BagSpec("long_one", [30000], H=12, d=128, seed=9701))
+    short = GpuRun(BagSpec("short_ones", _DRAW_JOINT[0], H=_DRAW_JOINT[1], d=_DRAW_JOINT[2], seed=9702))
+    want = [[t.clone() for t in (r.attn.dq, r.attn.dk, r.attn.dv)] for r in (long, short)]
+    for r in (long, short):
+        for t in (r.attn.dq, r.attn.dk, r.attn.dv):
+            t.fill_(float("nan"))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]  # default priority
+    torch.cuda.synchronize()
+    for i in range(4200):
+        if i % 70 == 0:
+            long.attn.backward(long.dev["q"], long.dev["k"], long.dev["v"], long.dev["dout"], stream=streams[0])
+        short.attn.backward(short.dev["q"], short.dev["k"], short.dev["v"], short.dev["dout"], stream=streams[1])
+    torch.cuda.synchronize()
+    for r, ws in zip((long, short), want):
+        for got, w in zip((r.attn.dq, r.attn.dk, r.attn.dv), ws):
+            assert torch.equal(got, w), r.bag.name
+
+
 # ---------------------------------------------------------------------------
 # Full-size benchmark bags: the oracle evaluates sampled outputs exactly
 # (query rows -> out, lse, dq; key rows -> dk, dv), plus invariants that hold

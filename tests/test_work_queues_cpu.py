@@ -1,6 +1,5 @@
 """The kernels' work queues and the host's rules about them, walked through on the CPU (tests/queue_model.cpp compiles the same
-headers): every item, or every part of it, is dealt out exactly once, and where the host leaves out the launch that clears
-the backward's counters no queue of its kernels draws."""
+headers): every item, or every part of it, is dealt out exactly once."""
 import random
 
 import pytest
@@ -19,59 +18,19 @@ def _random_bag(rng):
     return lens
 
 
-def _same_total(rng, total, n):
-    """Bags of n sequences and `total` tokens, as a captured launch may meet them on replay."""
-    yield [total - (n - 1)] + [1] * (n - 1) if total >= n else [total] + [0] * (n - 1)
-    yield [total] + [0] * (n - 1)
-    yield [total // n + (1 if i < total % n else 0) for i in range(n)]
-    cuts = sorted(rng.randint(0, total) for _ in range(n - 1))
-    yield [b - a for a, b in zip([0] + cuts, cuts + [total])]
-
-
-def _check(lens, H, d, causal, pairs, cus):
-    host = Q.bwd_draws(lens, H, d, causal, pairs, cus)
-    for kernel in ("fwd", "dq", "dkdv"):
-        w = Q.walk(kernel, lens, H, d, causal, pairs, cus)
-        assert w.wrong == 0, (kernel, lens, H, d, causal, pairs, cus, w)
-        if kernel != "fwd" and not host:
-            assert not w.draws and w.most <= w.per, (kernel, lens, H, d, causal, pairs, cus, w)
-    return host
-
-
 @pytest.mark.parametrize("causal", [False, True])
-def test_every_item_once_and_no_draw_from_counters_that_were_not_cleared(causal):
+def test_every_item_of_one_kind_once(causal):
     rng = random.Random(1 + causal)
-    seen = {True: 0, False: 0}
+    draws = {True: 0, False: 0}
     for _ in range(600):
         lens, H, d = _random_bag(rng), rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128))
         cus = rng.choice((256, 256, 256, 304, 80, 37))          # 37: no multiple of eight workgroups, one queue
         for pairs in (2, 4):
-            seen[_check(lens, H, d, causal, pairs, cus)] += 1
-    assert min(seen.values()) > 100, seen
-
-
-@pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("pairs", [2, 4])
-def test_largest_bags_whose_counters_are_not_cleared(causal, pairs):
-    """Right below the host's line, whatever the lengths that make up the total."""
-    rng = random.Random(10 * pairs + causal)
-    full = 0
-    for n in (1, 2, 3, 5, 8, 20, 40):
-        for H in (1, 2, 3, 5, 8):
-            if Q.bwd_draws([1] * n, H, 128, causal, pairs):
-                continue
-            lo, hi = n, 1 << 20                                  # the last total that is not cleared
-            while hi - lo > 1:
-                mid = (lo + hi) // 2
-                if Q.bwd_draws([mid] + [0] * (n - 1), H, 128, causal, pairs): hi = mid
-                else: lo = mid
-            for total in (lo, lo - 1, lo - 127):
-                for lens in _same_total(rng, max(0, total), n):
-                    assert not _check(lens, H, 128, causal, pairs, Q.CUS)
-                    w = Q.walk("dq", lens, H, 128, causal, pairs)
-                    full += w.parts > 0 and w.most >= w.per * 3 // 4
-            assert _check([lo + 128] + [0] * (n - 1), H, 128, causal, pairs, Q.CUS)
-    assert full > 20                                             # the line is not far from where the queues are full
+            for kernel in ("fwd", "dq", "dkdv"):
+                w = Q.walk(kernel, lens, H, d, causal, pairs, cus)
+                assert w.wrong == 0, (kernel, lens, H, d, causal, pairs, cus, w)
+                draws[w.draws] += 1
+    assert min(draws.values()) > 300, draws
 
 
 def test_bags_that_the_kernels_deal_out_in_each_way():
