@@ -67,14 +67,17 @@ extern "C" {
 /* out = softmax(scale * q k^T) v per (sequence, head); also writes lse.
  *
  * Concurrency.  The kernel draws its work items from counters that live in the
- * library's device image: 8192 sets, which it leaves at zero.  Eager launches
- * take sets 0..4095 in rotation: calls
+ * library's device image, in sets that it leaves at zero.  Eager launches
+ * take 12288 sets in rotation: calls
  * from several threads and on several streams may overlap freely as long as no
- * launch is still running when the 4096th eager forward call after it runs.
- * A launch recorded under stream capture takes one of sets 4096..8191
+ * eager forward call on a device runs beside one that came 4096 or more such
+ * calls later.  Results of calls that break this are undefined, those of calls
+ * 12288 later are not: every 4096th call clears the sets of the 4096 to 8191
+ * after it (a small launch of its own).
+ * A launch recorded under stream capture takes one of 4096 other sets
  * and keeps it for every replay of its graph, so replays never share a set with
  * eager launches; two captured launches share a set only once more than 4096
- * forward launches have been captured in the process, and graphs that hold such
+ * forward launches have been captured on a device, and graphs that hold such
  * a pair must then not be replayed at the same time.  The first call on a device (it
  * looks up device properties, once, under a lock) must not be made under
  * stream capture; later calls may be captured. */

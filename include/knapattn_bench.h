@@ -26,6 +26,11 @@ void knap_bwd_profile_events(void* start, void* stop);
  * keys, has twice as many). */
 int knap_launch_workgroups(int which /* 0 = forward, 1 = backward dK/dV, 2 = backward dQ */);
 
+/* Device address of the counters that forward launches draw their work items
+ * from, on the current device (NULL on error), and their number.  All zero
+ * while no forward runs. */
+unsigned* knap_fwd_queue_counters(int* count);
+
 #ifdef __cplusplus
 }
 #endif

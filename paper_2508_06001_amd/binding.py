@@ -59,6 +59,7 @@ _SIGNATURES = {
     "knap_strerror": (C.c_char_p, [_i]),
     "knap_last_hip_error": (_i, []),
     "knap_launch_workgroups": (_i, [_i]),
+    "knap_fwd_queue_counters": (_vp, [C.POINTER(_i)]),
     "knap_bwd_profile_events": (None, [_vp, _vp]),
     "knap_seq_cost": (_d, [_i64, _d, _d]),
     "knap_flux_workload": (_d, [_i64, _i64, _d]),

@@ -25,15 +25,10 @@ struct DeviceInfo {
   int cus = 0;
   int fwd_wg[2] = {0, 0};   // workgroups per CU, index 0: d = 64, 1: d = 128
   int dq_wg[2] = {0, 0};
-  unsigned* queues = nullptr;      // this device's copy of the work-queue counters
+  unsigned* queues = nullptr;      // this device's copy of the forward's work-queue counters (a backward has its own in its workspace)
+  std::atomic<uint64_t> fwd_calls{0}, fwd_captured{0};      // eager and captured forward calls so far, which take the sets in turn
   unsigned char* scratch = nullptr;   // this device's copy of `scratch`
 };
-
-// Counter sets of the forward's work queues: the lower half is handed out in rotation to eager launches, the upper half to
-// launches recorded under stream capture.  A captured launch keeps its set for every replay of its graph, so it must
-// never be one that eager launches rotate through.  (A backward has its counters in its own workspace.)
-std::atomic<unsigned> g_launches{0};
-std::atomic<unsigned> g_captured{0};
 
 constexpr int kMaxDevices = 64;
 
@@ -103,9 +98,18 @@ int fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   DeviceInfo* di = device_info();
   if (!di) return KNAP_ERR_LAUNCH_FAILED;
   const int grid = di->cus * di->fwd_wg[d == 128];
-  const unsigned half = (unsigned)knap::queue_sets() / 2u;
-  unsigned* counters = di->queues + 8u * (capturing(stream) ? half + g_captured.fetch_add(1u) % half : g_launches.fetch_add(1u) % half);
-  const hipError_t e = knap::launch_fwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, counters,
+  unsigned set;
+  hipError_t e = hipSuccess;
+  if (capturing(stream)) {
+    set = knap::captured_set(di->fwd_captured.fetch_add(1));
+  } else {
+    const knap::EagerSet s = knap::eager_set(di->fwd_calls.fetch_add(1));
+    set = s.set;
+    if (s.clear >= 0) e = knap::clear_queue_sets(di->queues + 8 * s.clear, knap::kSetsPerThird, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
+  }
+  unsigned* counters = di->queues + 8 * set;
+  e = knap::launch_fwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, counters,
                                         grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
@@ -331,6 +335,13 @@ int knap_launch_workgroups(int which) {
   DeviceInfo* di = device_info();
   if (!di) return -1;
   return di->cus * (which == 0 ? di->fwd_wg[1] : which == 1 ? knap::dkdv_workgroups_per_cu(4) : di->dq_wg[1]);
+}
+
+unsigned* knap_fwd_queue_counters(int* count) {
+  DeviceInfo* di = device_info();
+  if (!di) return nullptr;
+  *count = 8 * knap::kQueueSets;
+  return di->queues;
 }
 
 }  // extern "C"

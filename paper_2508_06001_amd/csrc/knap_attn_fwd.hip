@@ -48,7 +48,6 @@ struct FwdCfg {
 };
 
 constexpr float kMaxHalfSum = 256.f;        // of a lane's 16 probabilities against the present reference
-constexpr int kQueueSets = 8192;
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
@@ -448,13 +447,20 @@ KNAP_FWD_INSTANCE(64, true)
 KNAP_FWD_INSTANCE(128, true)
 #undef KNAP_FWD_INSTANCE
 
-// The forward entry points have no workspace, so the counters of their work queues live in the library's device image (256 KB
-// that start at zero): kQueueSets sets of 8 (one counter per XCD), handed out in rotation by the host.  The kernel
-// leaves its counters at zero, so no launch has to clear them.  Two launches share a set only if half of kQueueSets
-// others were enqueued between them while the first was still running.
+// Counters of the work queues, in the library's device image (512 KB that start at zero): sets of 8, one counter per XCD,
+// handed out by the host (eager_set(), captured_set()).  The kernel leaves its counters at zero, so no launch has to clear
+// them in front of it.
 static __device__ __align__(256) unsigned g_queues[kQueueSets * 8];
 
-int queue_sets() { return kQueueSets; }
+__global__ __launch_bounds__(kThreads) void queue_clear_kernel(unsigned* __restrict__ counters, unsigned n) {
+  const unsigned i = blockIdx.x * kThreads + threadIdx.x;
+  if (i < n) counters[i] = 0u;
+}
+
+hipError_t clear_queue_sets(unsigned* first, unsigned sets, hipStream_t stream) {
+  hipLaunchKernelGGL(queue_clear_kernel, dim3((8 * sets + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, first, 8 * sets);
+  return hipGetLastError();
+}
 
 unsigned* queue_base() {
   unsigned* p = nullptr;

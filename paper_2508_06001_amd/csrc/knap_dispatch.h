@@ -74,4 +74,26 @@ inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal
   return !(n_seq == 1 && r > 0.8 && r <= 1.0);
 }
 
+// Counter sets of the forward's work queues.  The forward entry points have no workspace: a launch draws from one of these sets
+// (8 counters each, at zero in the device image), which it leaves at zero.  Eager calls take the first 3 kSetsPerThird in
+// rotation.  Calls that share a set because too many were enqueued while one ran lose items and may leave the set at
+// another value than zero; so that this ends, and does not spoil a launch of every later turn, the call that
+// enters a third clears the one that follows.  Nobody draws from that one as long as no call runs beside one that is
+// kSetsPerThird calls younger: it was left that many calls ago, and is entered that many later.  One launch of 128
+// workgroups in 4096 calls.  The sets behind belong to launches recorded under stream capture, which keep theirs for every
+// replay.
+constexpr unsigned kSetsPerThird = 4096, kCapturedSets = 4096, kQueueSets = 3 * kSetsPerThird + kCapturedSets;
+
+struct EagerSet {
+  unsigned set;
+  int clear;        // the first of kSetsPerThird sets to clear on the call's stream before its launch, or -1
+};
+
+inline EagerSet eager_set(uint64_t call) {
+  const uint64_t third = call / kSetsPerThird;
+  return {(unsigned)(call % (3 * kSetsPerThird)), call % kSetsPerThird == 0 ? (int)((third + 1) % 3 * kSetsPerThird) : -1};
+}
+
+inline unsigned captured_set(uint64_t call) { return 3 * kSetsPerThird + (unsigned)(call % kCapturedSets); }
+
 }  // namespace knap

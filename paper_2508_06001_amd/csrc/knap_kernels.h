@@ -12,10 +12,10 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t
                       int H, int d, float scale, bool causal, void* out, float* lse, unsigned* counters,
                       int grid, hipStream_t stream);
 
-// Device address (on the current device) of the forward's work-queue counters: queue_sets() sets of 8, at zero
+// Device address (on the current device) of the forward's work-queue counters: kQueueSets sets of 8, at zero
 // whenever no kernel uses them; nullptr on failure.
 unsigned* queue_base();
-int queue_sets();
+hipError_t clear_queue_sets(unsigned* first, unsigned sets, hipStream_t stream);
 
 struct BwdArgs {
   const void *q, *k, *v, *out, *dout;

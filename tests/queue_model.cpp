@@ -162,6 +162,15 @@ int queue_dkdv_pairs(long long tokens, int n_seq, int H, int d, int causal, int 
   return knap::dkdv_pairs(tokens, n_seq, H, d, causal != 0, cus);
 }
 
+// set of eager forward call `call`, and the first of the sets it clears (-1: none)
+void queue_eager_set(unsigned long long call, int* out) {
+  const knap::EagerSet s = knap::eager_set(call);
+  out[0] = (int)s.set;
+  out[1] = s.clear;
+}
+
+int queue_captured_set(unsigned long long call) { return (int)knap::captured_set(call); }
+
 int queue_dkdv_workgroups_per_cu(int pairs) { return knap::dkdv_workgroups_per_cu(pairs); }
 
 }  // extern "C"

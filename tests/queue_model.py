@@ -40,6 +40,9 @@ def _lib():
     lib.queue_walk_even.restype = None
     lib.queue_walk_even.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
+    lib.queue_eager_set.restype = None
+    lib.queue_eager_set.argtypes = [C.c_ulonglong, C.POINTER(C.c_int)]
+    lib.queue_captured_set.argtypes = [C.c_ulonglong]
     lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
     return lib
 
@@ -52,6 +55,17 @@ def grid(kernel: str, d: int, pairs: int = 0, cus: int = CUS) -> int:
     if kernel == "dkdv":
         return cus * _lib().queue_dkdv_workgroups_per_cu(pairs)
     return cus * WORKGROUPS_PER_CU[kernel][d]
+
+
+def eager_set(call: int) -> tuple:
+    """Counter set of an eager forward call, and the first of the sets that the call clears (None: it clears none)."""
+    out = (C.c_int * 2)()
+    _lib().queue_eager_set(call, out)
+    return out[0], None if out[1] < 0 else out[1]
+
+
+def captured_set(call: int) -> int:
+    return int(_lib().queue_captured_set(call))
 
 
 def _walk_even(lens: Sequence[int], H: int, causal: bool, kinds: int, grid_: int) -> Walk:

@@ -306,6 +306,42 @@ def test_backward_draws_from_counters_of_its_own_workspace(lens, H, d, entry):
         assert all(0 < w < 1 << 20 for w in words[:n]) and words[n:64] == [-1] * (64 - n)
 
 
+def test_forward_recovers_from_counters_that_are_not_zero():
+    """Counter sets that a misuse left at some value (the header's limit on calls in flight) spoil the forwards that draw from
+    them next, and no later ones: every counter set off, results are right again once the rotation has come round."""
+    import ctypes as C
+    import torch
+    import paper_2508_06001_amd as K
+    lens, H, d = _DRAW_JOINT
+    Q.assert_draws(lens, H, d, False, kernels=("fwd",))
+    run = GpuRun(BagSpec("spoiled", lens, H=H, d=d, seed=9800), backward=False)
+    a, x = run.attn, run.dev
+    want, want_lse = a.out.clone(), a.lse.clone()
+    hip = C.CDLL("libamdhip64.so.7", mode=os.RTLD_NOLOAD | C.RTLD_GLOBAL)      # the runtime that is loaded, never a second one
+    hip.hipMemset.argtypes = [C.c_void_p, C.c_int, C.c_size_t]
+    n = C.c_int()
+    counters = K.lib.knap_fwd_queue_counters(C.byref(n))
+    torch.cuda.synchronize()
+    try:
+        assert hip.hipMemset(counters, 1, 4 * n.value) == 0
+        torch.cuda.synchronize()
+        a.out.fill_(float("nan"))
+        a.forward(x["q"], x["k"], x["v"])
+        torch.cuda.synchronize()
+        assert torch.isnan(a.out).any()          # the counters are those that are drawn from
+        for _ in range(12288):
+            a.forward(x["q"], x["k"], x["v"])
+        for _ in range(50):
+            a.out.fill_(float("nan"))
+            a.lse.fill_(float("nan"))
+            a.forward(x["q"], x["k"], x["v"])
+            assert bool((a.out == want).all()) and bool((a.lse == want_lse).all())
+    finally:                                     # also those of captured launches, which nobody clears
+        torch.cuda.synchronize()
+        assert hip.hipMemset(counters, 0, 4 * n.value) == 0
+        torch.cuda.synchronize()
+
+
 def test_backward_that_runs_while_thousands_of_others_do():
     """Long backwards on a stream of their own, 4200 short ones that draw on another: any number of calls may be in flight."""
     import torch

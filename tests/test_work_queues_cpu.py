@@ -55,3 +55,23 @@ def test_every_item_of_both_kinds_once(causal):
         split = 4 if causal else 2
         seen["none" if w.parts == 0 else "all" if w.parts == w.items * split else "thin"] += 1
     assert min(seen.values()) > 20, seen
+
+
+@pytest.mark.parametrize("start", [0, (1 << 32) - 20000])
+def test_counter_sets_are_cleared_between_two_uses_far_from_either(start):
+    """Eager forward calls: between two calls that draw from one set some call clears it, and calls that touch a set (draw from
+    it or clear it) are at least 4096 apart, so that none of them meet as long as no call runs beside one that much younger.
+    Captured calls have sets of their own."""
+    start -= start % 12288
+    touched, cleared = {}, {}
+    for call in range(start, start + 5 * 12288):
+        got, clear = Q.eager_set(call)
+        for s in ([] if clear is None else range(clear, clear + 4096)):
+            assert call - touched.get(s, call - 4096) >= 4096
+            touched[s] = call
+            cleared[s] = True
+        assert 0 <= got < 12288 and call - touched.get(got, call - 4096) >= 4096
+        if call >= start + 12288:
+            assert cleared[got]
+        touched[got], cleared[got] = call, False
+    assert {Q.captured_set(c) for c in range(9000)} == set(range(12288, 16384))
