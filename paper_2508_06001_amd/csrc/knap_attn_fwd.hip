@@ -84,10 +84,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   k_rows.init(lane);
   v_cols.init(lane);
 
-  // Work items come from this XCD's queue.  The ticket for the NEXT item is requested right
-  // after the item's first loads (vector-memory operations complete in issue order: requested
-  // before them, the slow counter update would hold up the whole prologue) and only looked at
-  // when the item is done, so the counter's latency is never waited for.
+  // Work items come from this XCD's queue.  The ticket for the NEXT item is drawn in front of the item's last two tiles and
+  // looked at behind them, so that the counter's latency is covered (vector-memory operations complete in issue order: in
+  // front of the first loads it would hold up the whole prologue) and the items go to the workgroups that end first.  Drawn at
+  // the item's start, what is left behind a full round went to those that had started first, with the longest items.  Drawn at
+  // the start -> at the end, us: 8192 and 3 of 4096 and one of 2048 tokens, 3 x 128, 214 -> 182; 2 of 8192 and 2 of 4096 271 ->
+  // 244; 4096, 2 of 2048 and 3 of 1024, 6 x 128, 110 -> 93; one round, or many, the same within 0.5 %.
   __shared__ int s_ticket;
   constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a wide one
   EvenQueue<SPLIT, 1> queue;
@@ -184,7 +186,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
     // keys this query tile sees at all
     const int kv_end = CAUSAL ? min(L, q0 + C::BM) : L;
     const int n_tiles = (kv_end + C::BN - 1) / C::BN;
-    if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u);
+    // the last pair of tiles of the item; of both its query tiles under the mask
+    const int t_draw = queue.draws && !(CAUSAL && sub == 0 && it.tile != q_tile) ? (n_tiles - 1) & ~1 : -1;
 
     f32x16 o[C::DB];
 #pragma unroll
@@ -280,6 +283,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
     };
 
     for (int t = 0; t < n_tiles; t += 2) {
+      if (t == t_draw && tid == 0) next_ticket = atomicAdd(queue.ctr, 1u);
       process_tile(t, sK0, sV0, sK1, sV1);
       if (t + 1 < n_tiles) process_tile(t + 1, sK1, sV1, sK0, sV0);
     }
@@ -321,8 +325,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_kernel(
   }
   }
 
-  // Narrow items: 64 queries.  A lone workgroup on a CU takes as long for a wide item as one of two (a wave alone on
-  // its SIMD waits out its own latencies), so where the items are few each is cut in two that run side by side.
+  // Narrow items: 64 queries.  Where the items are few, or the last round is thin, each is cut in two that run on two CUs (a
+  // CU's matrix units are nearly as busy with one workgroup as with two: an item of 4096 keys beside another of twice
+  // the length 145 us, alone 67).
   // Waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the second 32; the two
   // halves of the softmax are merged through LDS at the end.
   if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down

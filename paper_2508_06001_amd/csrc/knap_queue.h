@@ -109,13 +109,15 @@ struct ItemQueue {
 // in eight.  Chunks of the whole list, as above, can give one XCD the long sequences of a small bag and another the short
 // ones.  Forward in us, chunks -> shares: 3512 tokens in 2 sequences, 24 x 128, 121 -> 95; 12417 in 21 of up to 6290 613 -> 491;
 // 12 of up to 2673, 12 x 128, 190 -> 151; one of 4292, 24 x 128, 273 -> 259; 17 of 328..4533 1070 -> 1052; 10 of up to 6795,
-// 48 x 64, 1514 -> 1491; but where little more than one round is left over, of shorter sequences, these run beside long ones and
-// end late: 2 of 8192 and 2 of 4096, 3 x 128, 248 -> 275.
+// 48 x 64, 1514 -> 1491.
 //
 // KINDS = 2: the launch holds two kinds of items, every sequence as many of one as of the other (knap_attn_joint.h); a queue
 // takes its first kind before its second.  (4096, 2300, 1024, 256 and 256 tokens, 12 x 128, backward 572 us in chunks, 472 in
 // shares.)  Parts stand for items of the last kind: for all of them, where they find a workgroup each, or for those of a
-// thin last round.
+// thin last round that would end late: long ones, and behind a single round of one kind also those that together with the
+// round's shortest item, whose workgroup takes them, are longer than the longest (by a sixteenth: whole -> in parts at a sum of
+// n longest, forward in us: 1.06, 2 of 8192 and 2 of 4300, 3 x 128, 252 -> 262; 1.09, 8192, 6000, 4500 and 4400 229 -> 220;
+// 1.33, 1536 and 1000, 27 x 128, 63.7 -> 60.0; under the mask 81 -> 72).
 template <int SPLIT, int KINDS>
 struct EvenQueue {
   unsigned* ctr;
@@ -150,8 +152,11 @@ struct EvenQueue {
       last = mine;
     } else {
       const int thin = KINDS * mine % per;
-      if (thin > 0 && thin <= mine && thin * SPLIT <= per &&
-          4 * length(rank_of_item(s_mine, n_seq, mine - thin)) >= 3 * length(0)) last = thin;
+      if (thin > 0 && thin <= mine && thin * SPLIT <= per) {
+        const int top = length(0), own = length(rank_of_item(s_mine, n_seq, mine - thin));
+        const bool late = KINDS == 1 && mine < 2 * per && 16 * (length(rank_of_item(s_mine, n_seq, per - 1)) + own) > 17 * top;
+        if (late || 4 * own >= 3 * top) last = thin;
+      }
     }
     mine = __builtin_amdgcn_readfirstlane(mine);
     wide = __builtin_amdgcn_readfirstlane(KINDS * mine - last);

@@ -648,7 +648,7 @@ def test_same_sequence_in_parts_and_in_whole_items(d, causal):
     each, so two sides are at most 4 (out, dv) or 6 (dq, dk) times 2^-9 apart in the 2-norm.  A sum of probabilities is off
     by at most 2^-8 of itself (the unit roundoff) on either side, and lse by as much in absolute terms."""
     small = BagSpec("in_parts", [333, 1290, 64, 700], H=3, d=d, seed=8800 + d)
-    large = BagSpec("whole_items", [1290] + [900] * 70, H=3, d=d, seed=8900 + d)
+    large = BagSpec("whole_items", [1290] + [900] * 90, H=3, d=d, seed=8900 + d)
     for kernel in ("fwd", "dq"):
         w = Q.walk(kernel, small.seq_lens, small.H, d, causal)
         assert w.parts == w.items * (4 if causal else 2)
@@ -689,6 +689,18 @@ def test_thin_last_round_of_long_items(causal, d, H):
     bag = BagSpec("thin_round", [2081], H=H, d=d, seed=7300 + H)
     _full_compare(bag, heads=[0, H - 2, H - 1], strict_fwd=not causal, causal=causal,
                   lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
+@pytest.mark.parametrize("causal,d,H", [(False, 128, 31), (False, 64, 49), (True, 128, 59), (True, 64, 88)])
+def test_thin_second_round_of_shorter_items(causal, d, H):
+    """Forward: a few items more than workgroups, of a sequence shorter than the longest by less than would let them end with
+    it: they go out in 64-query parts behind the one round.  10 rows in the ragged query tile of the long sequence, 65 in that
+    of the short one, so that one part has a single row; under the mask tiles without a partner.  First and last heads."""
+    lens = [1162, 833]
+    w = Q.walk("fwd", lens, H, d, causal)
+    assert 0 < w.parts < w.items and w.draws
+    _full_compare(BagSpec("thin_second", lens, H=H, d=d, seed=7400 + H), heads=[0, H // 2, H - 2, H - 1], strict_fwd=not causal,
+                  causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
 @pytest.mark.parametrize("masked_keys", [32, 64, 96])

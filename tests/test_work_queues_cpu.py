@@ -40,6 +40,13 @@ def test_bags_that_the_kernels_deal_out_in_each_way():
     assert w.items == 17 * 31 and w.parts == 2 * (17 * 31 - 512) and w.draws
     w = Q.walk("dkdv", [450] * 32, 24, 128, False)
     assert Q.dkdv_pairs([450] * 32, 24, 128, False) == 2 and w.items == 32 * 24 * 4 and w.draws and not w.parts
+    # few items behind a single round: in parts where the round's shortest item and one of them take longer than the longest
+    w = Q.walk("fwd", [1536, 1000], 27, 128, False)
+    assert w.items == 20 * 27 and 0 < w.parts < w.items and w.draws
+    assert Q.walk("fwd", [8192, 6000, 4500, 4400], 3, 128, False).parts > 0
+    for lens, H in (([8192, 8192, 4300, 4300], 3), ([8192, 8192, 4096, 4096], 3), ([3000, 1500, 1000], 12)):
+        w = Q.walk("fwd", lens, H, 128, False)
+        assert w.items > 512 and w.draws and not w.parts
 
 
 @pytest.mark.parametrize("causal", [False, True])
