@@ -143,10 +143,11 @@ struct DkdvLane {
   }
 };
 
-// One key tile of an item.  `draw` is called behind its first loads, `drawn` when they have landed.
-template <int D, int PAIRS, bool CAUSAL, class Draw, class Drawn>
+// One key tile of an item.  `draw` is called behind its first loads, `drawn` when they have landed, `ending` in front of its
+// stores.
+template <int D, int PAIRS, bool CAUSAL, class Draw, class Drawn, class Ending>
 __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, const DkdvLane<D, PAIRS>& me, const WorkItem& it,
-                                          int kv_tile, Draw draw, Drawn drawn) {
+                                          int kv_tile, Draw draw, Drawn drawn, Ending ending) {
     using C = Bwd2Cfg<D, PAIRS>;
     using W = DkdvLane<D, PAIRS>;
     const auto *q = g.q, *k = g.k, *v = g.v, *dout = g.dout;
@@ -412,6 +413,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
 #undef KNAP_ROLE_LOOP
 #undef KNAP_STEP
 
+    ending();
     const auto rg = make_rsrc((role == 0 ? g.dv : g.dk) + (size_t)(it.row0 + kv0) * row_stride + head_off,
                               (uint32_t)min(L - kv0, C::BN) * row_bytes);
     const float out_scale = role == 0 ? 1.0f : scale;
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(128 * PAIRS, dkdv_waves_per_simd(D, PAIRS)) void at
   second_tile_of_pair:;     // CAUSAL only: jumped back to once, from the end of the first tile
     dkdv_tile<D, PAIRS, CAUSAL>(g, lds, me, it, (!CAUSAL || sub == 0) ? it.tile : kv_tiles - 1 - it.tile,
         [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
-        [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket); });
+        [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket); }, [] {});
     if constexpr (CAUSAL) {
       if (sub == 0 && it.tile != kv_tiles - 1 - it.tile) {   // not the middle tile of an odd count
         sub = 1;

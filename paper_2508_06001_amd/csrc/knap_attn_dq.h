@@ -59,9 +59,10 @@ __device__ __forceinline__ float row_delta(const bf16x8 (&dof)[D / 16], const bf
 __device__ __forceinline__ bool dq_narrow(int len, int q_tile) { return q_tile >= 2 && len - q_tile * 128 <= 64; }
 
 // One query tile (128 rows) of an item.  DELTA: delta and the LSE in base 2 are formed here and handed on in memory; else
-// they are read from there.  `draw` is called behind the first loads.
-template <int D, bool CAUSAL, bool DELTA, class Draw>
-__device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q_tile, Draw draw) {
+// they are read from there.  `draw` is called behind the first loads, `ending` in front of the stores.
+template <int D, bool CAUSAL, bool DELTA, class Draw, class Ending>
+__device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q_tile, Draw draw,
+                                        Ending ending) {
     using C = DqCfg<D>;
     const auto *q = g.q, *k = g.k, *v = g.v, *out = g.out, *dout = g.dout;
     const float* lse = g.lse;
@@ -242,6 +243,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       if (n_below + 1 < n_tiles) process_tile(diagonal, n_below + 1, sK1, sV1, sK0, sV0);
     }
 
+    ending();
     {
       const auto rg = make_rsrc(dq + (size_t)(it.row0 + q0) * row_stride + head_off,
                                 (uint32_t)min(L - q0, C::BM) * row_bytes);
@@ -252,9 +254,10 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
 }
 
 // 64 query rows, from q0 on: waves w and w + 2 share 32 queries, one taking the first 32 keys of every tile, the other the
-// second 32; the two gradients are added through LDS at the end.  `draw` is called behind the first loads.
-template <int D, bool CAUSAL, bool DELTA, class Draw>
-__device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q0, Draw draw) {
+// second 32; the two gradients are added through LDS at the end.  `draw` and `ending` as above.
+template <int D, bool CAUSAL, bool DELTA, class Draw, class Ending>
+__device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, const DqLane<D>& me, const WorkItem& it, int q0, Draw draw,
+                                        Ending ending) {
     using C = DqCfg<D>;
     const auto *q = g.q, *k = g.k, *v = g.v, *out = g.out, *dout = g.dout;
     const float* lse = g.lse;
@@ -371,6 +374,7 @@ __device__ __forceinline__ void dq_part(const BwdPtrs& g, const DqLds& lds, cons
       if (t + 1 < n_tiles) half_tile(t + 1, sK1, sV1, sK0, sV0);
     }
 
+    ending();
     float* part_acc = reinterpret_cast<float*>(rb_u == 0 ? sK1 : sV1);
     if (kh_u == 1) {
 #pragma unroll
@@ -454,8 +458,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_dq_kernel(
     asm volatile("" : "+v"(ln), "+s"(wv));
     DqLane<D> me;
     me.init(ln, wv);
-    if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, true>(g, lds, me, it, q_tile, draw);
-    else if (q0 < it.len && !(CAUSAL && !whole && sub == 1 && it.tile == other)) dq_part<D, CAUSAL, true>(g, lds, me, it, q0, draw);
+    if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, true>(g, lds, me, it, q_tile, draw, [] {});
+    else if (q0 < it.len && !(CAUSAL && !whole && sub == 1 && it.tile == other)) dq_part<D, CAUSAL, true>(g, lds, me, it, q0, draw, [] {});
     else draw();
     if constexpr (CAUSAL) {
       if (whole && first && it.tile != other) {   // not the middle tile of an odd count

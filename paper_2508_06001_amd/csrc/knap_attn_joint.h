@@ -98,7 +98,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
     const bool whole = ticket < queue.wide, keys = whole && queue.first_kind(ticket);
     const int part = ticket - queue.wide;
     const WorkItem it = take(whole ? queue.item(ticket) : queue.item_of_part(part));
+    // The next ticket is drawn in front of the item's stores, under which it arrives.  Drawn at the item's start, the items
+    // behind the first round went to the workgroups that had started first, with the longest ones.  Forward and backward in
+    // us, start -> end: 7250 tokens and 24 short sequences, 6 x 128, 842 -> 713; 4292, 24 x 128, 964 -> 923; 10000 and 33
+    // short ones, 12 x 128, 2660 -> 2498; 10 of 310..6795, 48 x 64, 5760 -> 5692; but 9000 and 30, 6 x 128, 1143 -> 1175.
     unsigned next_ticket;      // thread 0 only; no initial value, which would be merged in (and waited for) at once
+    auto draw = [&] { if (tid == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); };
     // CAUSAL: the item is the pair of tiles {p, tiles - 1 - p}, the dearer one first; the middle tile of an odd count stands alone
     const int other = (it.len + BM - 1) / BM - 1 - it.tile;
     const int n_sub = CAUSAL && other != it.tile ? 2 : 1;
@@ -109,26 +114,24 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
       me.init(ln, wave, role, row_bytes);
 #pragma unroll 1
       for (int sub = 0; sub < n_sub; ++sub)
-        dkdv_tile<D, 2, CAUSAL>(g, kv_lds, me, it, sub == 0 ? it.tile : other,
-                                [&] { if (tid == 0 && sub == 0 && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); },
-                                [&] { if (tid == 0 && sub == 0 && queue.draws) s_ticket = queue.later_ticket(next_ticket); });
+        dkdv_tile<D, 2, CAUSAL>(g, kv_lds, me, it, sub == 0 ? it.tile : other, [] {}, [] {}, [&] { if (sub == n_sub - 1) draw(); });
     } else {
       const int from = whole ? 0 : (part % SPLIT) >> 1, to = whole ? n_sub : from + 1;
 #pragma unroll 1
       for (int sub = from; sub < to; ++sub) {
-        auto draw = [&] { if (tid == 0 && sub == from && queue.draws) next_ticket = atomicAdd(queue.ctr, 1u); };
         const int q_tile = CAUSAL && sub == 0 ? other : it.tile;
         const int q0 = q_tile * BM + (whole ? 0 : 64 * (part & 1));
         asm volatile("" : "+v"(ln));
         DqLane<D> me;
         me.init(ln, wave);
-        if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, false>(g, q_lds, me, it, q_tile, draw);
-        else if (q0 < it.len && sub < n_sub) dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0, draw);
-        else draw();
+        auto ending = [&] { if (sub == to - 1) draw(); };
+        if (whole && !dq_narrow(it.len, q_tile)) dq_tile<D, CAUSAL, false>(g, q_lds, me, it, q_tile, [] {}, ending);
+        else if (q0 < it.len && sub < n_sub) dq_part<D, CAUSAL, false>(g, q_lds, me, it, q0, [] {}, ending);
+        else ending();
       }
     }
     if (!queue.draws) return;
-    if (tid == 0 && !keys) s_ticket = queue.later_ticket(next_ticket);
+    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);
     lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows
