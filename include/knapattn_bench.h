@@ -21,10 +21,10 @@ extern "C" {
 void knap_bwd_profile_events(void* start, void* stop);
 
 /* Number of persistent workgroups the forward / backward kernels are launched
- * with on the current device at d = 128 (<= 0 on error); for the dK/dV kernel
+ * with on the current device (<= 0 on error); for the dK/dV kernel at d = 128
  * those of its four-pair form (256 keys per workgroup; the two-pair form, 128
- * keys, has twice as many). */
-int knap_launch_workgroups(int which /* 0 = forward, 1 = backward dK/dV, 2 = backward dQ */);
+ * keys, has twice as many), at d = 64 of the two-pair form, its only one there. */
+int knap_launch_workgroups(int which /* d = 128: 0 = forward, 1 = backward dK/dV, 2 = backward dQ; d = 64: 3, 4, 5 */);
 
 /* Device address of the counters that forward launches draw their work items
  * from, on the current device (NULL on error), and their number.  All zero

@@ -334,7 +334,14 @@ void knap_bwd_profile_events(void* start, void* stop) {
 int knap_launch_workgroups(int which) {
   DeviceInfo* di = device_info();
   if (!di) return -1;
-  return di->cus * (which == 0 ? di->fwd_wg[1] : which == 1 ? knap::dkdv_workgroups_per_cu(4) : di->dq_wg[1]);
+  switch (which) {
+    case 0: return di->cus * di->fwd_wg[1];
+    case 1: return di->cus * knap::dkdv_workgroups_per_cu(128, 4);
+    case 3: return di->cus * di->fwd_wg[0];
+    case 4: return di->cus * knap::dkdv_workgroups_per_cu(64, 2);
+    case 5: return di->cus * di->dq_wg[0];
+    default: return di->cus * di->dq_wg[1];
+  }
 }
 
 unsigned* knap_fwd_queue_counters(int* count) {

@@ -8,8 +8,7 @@ namespace knap {
 
 // The dK/dV kernel takes 2 or 4 wave pairs per workgroup and this many workgroups on each CU: two waves per SIMD is what
 // its registers allow, three with two pairs at d = 64.
-constexpr int dkdv_workgroups_per_cu(int pairs) { return 4 / pairs; }
-constexpr int dkdv_workgroups_per_cu(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : dkdv_workgroups_per_cu(pairs); }
+constexpr int dkdv_workgroups_per_cu(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 4 / pairs; }
 constexpr int dkdv_waves_per_simd(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 2; }
 
 // Rounds of `slots` workgroups that a bag's items take, its sequences taken to be of one length: whole ones where there

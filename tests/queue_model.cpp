@@ -171,6 +171,6 @@ void queue_eager_set(unsigned long long call, int* out) {
 
 int queue_captured_set(unsigned long long call) { return (int)knap::captured_set(call); }
 
-int queue_dkdv_workgroups_per_cu(int pairs) { return knap::dkdv_workgroups_per_cu(pairs); }
+int queue_dkdv_workgroups_per_cu(int d, int pairs) { return knap::dkdv_workgroups_per_cu(d, pairs); }
 
 }  // extern "C"

@@ -14,7 +14,7 @@ from typing import NamedTuple, Sequence
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CUS = 256                                  # compute units of an MI355X
-WORKGROUPS_PER_CU = {"fwd": {64: 3, 128: 2}, "dq": {64: 2, 128: 2}}     # what the kernels' registers allow
+WORKGROUPS_PER_CU = {"fwd": {64: 3, 128: 2}, "dq": {64: 3, 128: 2}}     # what the kernels' registers allow
 
 
 class Walk(NamedTuple):
@@ -43,6 +43,7 @@ def _lib():
     lib.queue_eager_set.restype = None
     lib.queue_eager_set.argtypes = [C.c_ulonglong, C.POINTER(C.c_int)]
     lib.queue_captured_set.argtypes = [C.c_ulonglong]
+    lib.queue_dkdv_workgroups_per_cu.argtypes = [C.c_int] * 2
     lib.queue_dkdv_pairs.argtypes = [C.c_longlong] + [C.c_int] * 5
     return lib
 
@@ -53,7 +54,7 @@ def dkdv_pairs(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS
 
 def grid(kernel: str, d: int, pairs: int = 0, cus: int = CUS) -> int:
     if kernel == "dkdv":
-        return cus * _lib().queue_dkdv_workgroups_per_cu(pairs)
+        return cus * _lib().queue_dkdv_workgroups_per_cu(d, pairs)
     return cus * WORKGROUPS_PER_CU[kernel][d]
 
 
@@ -93,11 +94,22 @@ def bwd_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS)
 
 def walk_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> Walk:
     """The queues of that launch; `items` are those of one kind, `parts` those of query tiles."""
-    return _walk_even(lens, H, causal, 2, cus * (3 if d == 64 else 2))
+    return _walk_even(lens, H, causal, 2, grid("dkdv", d, 2, cus))
 
 
-def assert_draws(lens: Sequence[int], H: int, d: int, causal: bool, kernels=("fwd", "dq", "dkdv")) -> None:
-    """The bag has more items than workgroups in some queue of each of these kernels."""
-    for kernel in kernels:
-        w = walk(kernel, lens, H, d, causal)
+def launched(lens: Sequence[int], H: int, d: int, causal: bool) -> tuple:
+    """The kernels with a work queue that a forward and a backward of this bag launch: "fwd", and "joint" or "dq" and "dkdv"."""
+    return ("fwd", "joint") if bwd_joint(lens, H, d, causal) else ("fwd", "dq", "dkdv")
+
+
+def walk_launched(kernel: str, lens: Sequence[int], H: int, d: int, causal: bool) -> Walk:
+    """The queues of a kernel that this bag launches."""
+    assert kernel in launched(lens, H, d, causal), (kernel, lens, H, d, causal)
+    return walk_joint(lens, H, d, causal) if kernel == "joint" else walk(kernel, lens, H, d, causal)
+
+
+def assert_draws(lens: Sequence[int], H: int, d: int, causal: bool, kernels=None) -> None:
+    """The bag has more items than workgroups in some queue of each of these kernels (of all it launches)."""
+    for kernel in kernels or launched(lens, H, d, causal):
+        w = walk_launched(kernel, lens, H, d, causal)
         assert w.draws and w.most > w.per, (kernel, w)

@@ -73,6 +73,17 @@ def _full_compare(bag: BagSpec, heads=None, strict_fwd=True, causal=False, lse_t
     return run
 
 
+def test_queue_model_has_the_grids_of_the_library():
+    """What other tests say of a bag's draws and parts (queue_model.py) holds for the grids that the library launches."""
+    import torch
+    import paper_2508_06001_amd as K
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus == Q.CUS
+    for i, d in ((0, 128), (3, 64)):
+        for j, kernel in enumerate(("fwd", "dkdv", "dq")):
+            assert K.knap_launch_workgroups(i + j) == Q.grid(kernel, d, 4 if d == 128 else 2), (kernel, d)
+
+
 def test_tiny_bag_full_oracle():
     _full_compare(config_bag(0))
 
@@ -161,17 +172,30 @@ def test_repeatable_and_inputs_untouched():
     assert torch.equal(q0, run.dev["q"])
 
 
-def test_two_streams_at_once_match_one_after_the_other():
+# bags that draw in every kernel they launch: the backward in one launch of both kinds of items, and in two
+_DRAW_JOINT = [1 + (5 * i) % 9 for i in range(500)], 4, 64
+_DRAW_TWO = [1 + i % 9 for i in range(640)], 4, 128
+_DRAW_TWO_64 = [1 + i % 9 for i in range(900)], 4, 64
+
+
+def _bag(name, bag, seed):
+    return BagSpec(name, bag[0], H=bag[1], d=bag[2], seed=seed)
+
+
+@pytest.mark.parametrize("kernels", [("fwd", "joint"), ("fwd", "dq", "dkdv")])
+def test_two_streams_at_once_match_one_after_the_other(kernels):
     """Calls that overlap on two streams (each with its own outputs and workspace) do not disturb each
-    other: the work queues they draw from are per launch.  Both bags draw in all three kernels, the counters of a launch
+    other: the work queues they draw from are per launch.  Both bags draw in all kernels, the counters of a launch
     are worth nothing to the other.  Bitwise equality with the sequential run."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     rng = np.random.default_rng(5)
     bags = [BagSpec("stream_a", [int(x) for x in rng.integers(100, 3000, size=9)], H=12, d=128, seed=811),
             BagSpec("stream_b", [int(x) for x in rng.integers(50, 1500, size=14)], H=24, d=64, seed=812)]
+    if "joint" not in kernels:
+        bags = [_bag("stream_c", _DRAW_TWO, 813), _bag("stream_d", _DRAW_TWO_64, 814)]
     for b in bags:
-        Q.assert_draws(b.seq_lens, b.H, b.d, False)
+        Q.assert_draws(b.seq_lens, b.H, b.d, False, kernels)
     runs = [GpuRun(b) for b in bags]                      # sequential reference (default stream)
     ref = [[r.out_bits.copy(), r.dq_bits.copy(), r.dk_bits.copy(), r.dv_bits.copy(), r.lse.copy()] for r in runs]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]  # default priority
@@ -194,18 +218,22 @@ def test_two_streams_at_once_match_one_after_the_other():
                 assert np.array_equal(g, w_), (rep, r.bag.name, name)
 
 
-def test_hip_graph_replays_match_eager():
+@pytest.mark.parametrize("kernels", [("fwd", "joint"), ("fwd", "dq", "dkdv")])
+def test_hip_graph_replays_match_eager(kernels):
     """Forward + backward captured into a HIP graph (nothing in the calls allocates, synchronises or
     records a memset): every replay, with eager launches and synchronisations in between, reproduces
-    the eager results bit for bit.  The captured calls and the eager ones in between draw in all three kernels."""
+    the eager results bit for bit.  The captured calls and the eager ones in between draw in all kernels."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     rng = np.random.default_rng(11)
     bag = BagSpec("graph", [int(x) for x in rng.integers(64, 2500, size=11)], H=12, d=128, seed=913)
+    other = BagSpec("graph_other", [700, 90, 1300], H=48, d=64, seed=914)
+    if "joint" not in kernels:
+        bag, other = _bag("graph_two", _DRAW_TWO, 915), _bag("graph_two_other", _DRAW_TWO_64, 916)
+    for b in (bag, other):
+        Q.assert_draws(b.seq_lens, b.H, b.d, False, kernels)
     run = GpuRun(bag)                                      # eager reference; also warms up the library
-    other = GpuRun(BagSpec("graph_other", [700, 90, 1300], H=48, d=64, seed=914))
-    for b in (bag, other.bag):
-        Q.assert_draws(b.seq_lens, b.H, b.d, False)
+    other = GpuRun(other)
     want = [run.out_bits.copy(), run.dq_bits.copy(), run.dk_bits.copy(), run.dv_bits.copy(), run.lse.copy()]
     a, d = run.attn, run.dev
     side = torch.cuda.Stream()
@@ -270,10 +298,6 @@ def test_captured_backward_whatever_the_workspace_holds(causal, d, lens, H, node
             assert np.array_equal(bf16_device_to_bits(got), want), byte
 
 
-_DRAW_JOINT = [1 + (5 * i) % 9 for i in range(500)], 4, 64        # one launch of the backward
-_DRAW_TWO = [1 + i % 9 for i in range(640)], 4, 128               # two
-
-
 @pytest.mark.parametrize("entry", ["bwd", "noalloc", "causal_bwd"])
 @pytest.mark.parametrize("lens,H,d", [_DRAW_JOINT, _DRAW_TWO])
 def test_backward_draws_from_counters_of_its_own_workspace(lens, H, d, entry):
@@ -282,9 +306,8 @@ def test_backward_draws_from_counters_of_its_own_workspace(lens, H, d, entry):
     import torch
     import paper_2508_06001_amd as K
     causal = entry == "causal_bwd"
-    joint = Q.bwd_joint(lens, H, d, causal)
-    assert joint == (len(lens) == 500)
-    assert Q.walk_joint(lens, H, d, causal).draws if joint else Q.walk("dq", lens, H, d, causal).draws and Q.walk("dkdv", lens, H, d, causal).draws
+    joint = len(lens) == 500
+    Q.assert_draws(lens, H, d, causal, ("joint",) if joint else ("dq", "dkdv"))
     run = GpuRun(BagSpec("own_counters", lens, H=H, d=d, seed=9600 + d), causal=causal)
     a, x = run.attn, run.dev
     want = [t.clone() for t in (a.dq, a.dk, a.dv)]
@@ -312,9 +335,8 @@ def test_forward_recovers_from_counters_that_are_not_zero():
     import ctypes as C
     import torch
     import paper_2508_06001_amd as K
-    lens, H, d = _DRAW_JOINT
-    Q.assert_draws(lens, H, d, False, kernels=("fwd",))
-    run = GpuRun(BagSpec("spoiled", lens, H=H, d=d, seed=9800), backward=False)
+    Q.assert_draws(*_DRAW_JOINT, False, kernels=("fwd",))
+    run = GpuRun(_bag("spoiled", _DRAW_JOINT, 9800), backward=False)
     a, x = run.attn, run.dev
     want, want_lse = a.out.clone(), a.lse.clone()
     hip = C.CDLL("libamdhip64.so.7", mode=os.RTLD_NOLOAD | C.RTLD_GLOBAL)      # the runtime that is loaded, never a second one
@@ -345,9 +367,10 @@ def test_forward_recovers_from_counters_that_are_not_zero():
 def test_backward_that_runs_while_thousands_of_others_do():
     """Long backwards on a stream of their own, 4200 short ones that draw on another: any number of calls may be in flight."""
     import torch
-    assert Q.bwd_joint(_DRAW_JOINT[0], 4, 64, False) and not Q.bwd_joint([30000], 12, 128, False)
+    Q.assert_draws(*_DRAW_JOINT, False, kernels=("joint",))
+    Q.assert_draws([30000], 12, 128, False, kernels=("dq", "dkdv"))
     long = GpuRun(BagSpec("long_one", [30000], H=12, d=128, seed=9701))
-    short = GpuRun(BagSpec("short_ones", _DRAW_JOINT[0], H=_DRAW_JOINT[1], d=_DRAW_JOINT[2], seed=9702))
+    short = GpuRun(_bag("short_ones", _DRAW_JOINT, 9702))
     want = [[t.clone() for t in (r.attn.dq, r.attn.dk, r.attn.dv)] for r in (long, short)]
     for r in (long, short):
         for t in (r.attn.dq, r.attn.dk, r.attn.dv):
@@ -625,9 +648,9 @@ def test_causal_repeatable_and_independent_of_other_sequences():
     cu = [int(c) for c in run.cu]
     keep = slice(cu[1], cu[2])
     other = BagSpec("causal_rep2", [5, 1290, 2000], H=3, d=128, seed=5757)
-    for kernel in ("fwd", "dq"):
+    for kernel in ("fwd", "joint"):
         for b in (bag, other):
-            w = Q.walk(kernel, b.seq_lens, b.H, b.d, True)
+            w = Q.walk_launched(kernel, b.seq_lens, b.H, b.d, True)
             assert w.parts == 4 * w.items
     t2 = make_qkv_dout(other)
     for n in ("q", "k", "v", "dout"):
@@ -649,10 +672,10 @@ def test_same_sequence_in_parts_and_in_whole_items(d, causal):
     by at most 2^-8 of itself (the unit roundoff) on either side, and lse by as much in absolute terms."""
     small = BagSpec("in_parts", [333, 1290, 64, 700], H=3, d=d, seed=8800 + d)
     large = BagSpec("whole_items", [1290] + [900] * 90, H=3, d=d, seed=8900 + d)
-    for kernel in ("fwd", "dq"):
-        w = Q.walk(kernel, small.seq_lens, small.H, d, causal)
+    for kernel in ("fwd", "joint"):
+        w = Q.walk_launched(kernel, small.seq_lens, small.H, d, causal)
         assert w.parts == w.items * (4 if causal else 2)
-        assert Q.walk(kernel, large.seq_lens, large.H, d, causal).parts == 0
+        assert Q.walk_launched(kernel, large.seq_lens, large.H, d, causal).parts == 0
     run = GpuRun(small, causal=causal)
     at, there = slice(333, 333 + 1290), slice(0, 1290)
     tensors = make_qkv_dout(large)
@@ -669,26 +692,51 @@ def test_same_sequence_in_parts_and_in_whole_items(d, causal):
     assert apart["lse"] <= 2 * 2.0 ** -8
 
 
+@pytest.mark.parametrize("causal,L,H", [(False, 5121, 12), (False, 4095, 15), (False, 4385, 14), (False, 4130, 15),
+                                        (True, 5121, 23), (True, 4385, 27), (True, 4130, 29)])
+def test_four_pair_dkdv_kernel_on_ragged_long_sequences(causal, L, H):
+    """The dK/dV kernel's 256-key tiles (d = 128): sequences one key past a tile, one short of it and in between, 32-query step
+    counts of every residue modulo the ring of three buffers; bags that launch it."""
+    Q.walk_launched("dkdv", [L], H, 128, causal)
+    assert Q.dkdv_pairs([L], H, 128, causal) == 4
+    bag = BagSpec("four_pairs", [L], H=H, d=128, seed=6100 + L)
+    _full_compare(bag, heads=[H - 1], strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-def test_four_pair_dkdv_kernel_on_ragged_long_sequences(d, causal):
-    """Sequences long enough (4096 tokens and more on average) and a bag large enough (over 32768 rows of all heads)
-    for the dK/dV kernel's 256-key tiles, which smaller bags no longer reach: one key past a tile, one short of it,
-    32-query step counts of every residue modulo the ring of three buffers."""
-    bag = BagSpec("four_pairs", [5121, 4095, 4385, 4130], H=2, d=d, seed=6100 + d)
+def test_backward_in_one_launch_on_ragged_long_sequences(d, causal):
+    """Key tiles of 128 rows over sequences of 4095 to 5121 tokens: one key past a tile, one short of it, 32-query step counts of
+    every residue modulo the ring of three buffers."""
+    bag = BagSpec("long_ragged", [5121, 4095, 4385, 4130], H=2, d=d, seed=6100 + d)
+    Q.walk_launched("joint", bag.seq_lens, bag.H, d, causal)
     _full_compare(bag, heads=[1], strict_fwd=not causal, causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
 @pytest.mark.parametrize("causal,d,H", [(False, 128, 31), (False, 64, 31), (False, 64, 46),
                                         (True, 128, 58), (True, 64, 58), (True, 64, 86)])
 def test_thin_last_round_of_long_items(causal, d, H):
-    """Work items a few more than the workgroups (512 on 256 CUs, 768 of the forward at d = 64): whole rounds of
-    128-query items, then a last round that the forward (d = 128, and H of 46 and 86 at d = 64) and the dQ kernel (H of
-    31 and 58) deal out in 64-query parts.  The last heads own those parts: 33 rows in the ragged query tile, 33 keys in
-    the ragged key tile, a part that has no row; under the mask 17 tiles, i.e. a pair without a partner."""
+    """Work items of the forward a few more than its workgroups (512 on 256 CUs, 768 at d = 64): whole rounds of
+    128-query items, then a last round that goes out in 64-query parts (d = 128, and H of 46 and 86 at d = 64), as does that of
+    the backward's query tiles (all but H of 58 at d = 64).  33 rows in the ragged query tile, 33 keys in
+    the ragged key tile, a part that has no row; under the mask 17 tiles, i.e. a pair without a partner.  First and last
+    heads."""
     bag = BagSpec("thin_round", [2081], H=H, d=d, seed=7300 + H)
+    fwd, joint = (Q.walk_launched(kernel, bag.seq_lens, H, d, causal) for kernel in ("fwd", "joint"))
+    assert (0 < fwd.parts < fwd.items) == (d == 128 or H in (46, 86)) and (joint.parts > 0) == ((d, H) != (64, 58)) and joint.draws
     _full_compare(bag, heads=[0, H - 2, H - 1], strict_fwd=not causal, causal=causal,
                   lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
+
+
+@pytest.mark.parametrize("causal,d,n", [(False, 128, 21), (True, 128, 42), (False, 64, 32), (True, 64, 64)])
+def test_thin_last_round_of_the_dq_kernel(causal, d, n):
+    """Sequences of 450 tokens (two rows in the last 64-query part, the part behind it without any), 31 heads: five rounds and a
+    few items in parts, which are those of the last heads of the last sequence."""
+    lens, H = [450] * n, 31
+    w = Q.walk_launched("dq", lens, H, d, causal)
+    assert 0 < w.parts < w.items and w.draws and w.most > 4 * w.per
+    _full_compare(BagSpec("thin_dq", lens, H=H, d=d, seed=7600 + d), heads=[0, H - 2, H - 1], strict_fwd=not causal,
+                  causal=causal, lse_tol=LSE_TOL_FEW_KEYS if causal else LSE_TOL)
 
 
 @pytest.mark.parametrize("causal,d,H", [(False, 128, 31), (False, 64, 49), (True, 128, 59), (True, 64, 88)])
@@ -774,20 +822,23 @@ _LOW_RES = [256 + (151 * i) % 393 for i in range(32)]      # 256 to 648 tokens
 
 
 @pytest.mark.parametrize("causal,lens,H,pairs", [
-    # nothing is drawn, and nothing cleared but for the larger ones
-    (False, [300], 3, 2), (True, [300], 3, 2), (False, [2100, 300], 3, 2), (True, [2100, 300], 3, 2),
-    (False, [16 * 128, 9 * 128 + 1], 6, 2), (True, [16 * 128, 9 * 128 + 1], 6, 2), (False, [4000, 37], 8, 2), (True, [4000, 37], 8, 2),
-    # both kernels draw: barely (17 tiles for 31 heads: 15 items more than the 512 workgroups), and many times over
-    (False, [2081], 31, 4), (False, _LOW_RES, 24, 2), (False, [4096, 2100, 300], 24, 4),
-    (True, _LOW_RES, 24, 2), (True, [8200, 300], 24, 4)])
+    # one launch (pairs = 0), in which nothing is drawn ...
+    (False, [300], 3, 0), (True, [300], 3, 0), (False, [2100, 300], 3, 0), (True, [2100, 300], 3, 0),
+    (False, [16 * 128, 9 * 128 + 1], 6, 0), (True, [16 * 128, 9 * 128 + 1], 6, 0), (True, [4000, 37], 8, 0),
+    # ... barely, and many times over
+    (False, [4000, 37], 8, 0), (False, [2081], 31, 0), (False, [4096, 2100, 300], 24, 0), (True, _LOW_RES, 24, 0), (True, [8200, 300], 24, 0),
+    # two launches, both of which draw
+    (False, _LOW_RES, 24, 2), (True, _LOW_RES, 48, 2), (False, [20000], 14, 4)])
 def test_backward_whatever_the_workspace_holds(causal, lens, H, pairs):
-    """Bags on both sides of the line where the kernels draw work items and their counters are cleared first, with two and
-    with four wave pairs per workgroup of the dK/dV kernel: the gradients do not depend on what the workspace held."""
+    """Bags on both sides of the line where the kernels draw work items, from counters in the workspace that are cleared first,
+    in one launch and with two and four wave pairs per workgroup of the dK/dV kernel: the gradients do not depend on what the
+    workspace held."""
     import torch
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
-    assert Q.dkdv_pairs(lens, H, 128, causal) == pairs
-    draws = [Q.walk(kernel, lens, H, 128, causal).draws for kernel in ("dq", "dkdv")]
-    assert draws == [H > 8, H > 8]
+    kernels = Q.launched(lens, H, 128, causal)[1:]
+    assert kernels == (("dq", "dkdv") if pairs else ("joint",)) and (not pairs or Q.dkdv_pairs(lens, H, 128, causal) == pairs)
+    draws = {Q.walk_launched(kernel, lens, H, 128, causal).draws for kernel in kernels}
+    assert draws == {H > 8 or (H == 8 and not causal)}
     run = GpuRun(BagSpec("workspace", lens, H=H, d=128, seed=8300 + H), causal=causal)
     a = run.attn
     for byte in (0, 1, 0xff):
@@ -809,7 +860,7 @@ def test_two_pair_dkdv_kernel_over_several_items_per_workgroup():
     from paper_2508_06001_amd.runtime import bf16_device_to_bits
     H = 24
     assert Q.dkdv_pairs(_LOW_RES, H, 128, False) == 2
-    w = Q.walk("dkdv", _LOW_RES, H, 128, False)
+    w = Q.walk_launched("dkdv", _LOW_RES, H, 128, False)
     assert w.items > 3 * 512 and w.draws
     run = _full_compare(BagSpec("low_res", _LOW_RES, H=H, d=128, seed=8700), heads=[0, 1, H - 1])
     a, d = run.attn, run.dev
@@ -835,23 +886,33 @@ def test_three_backward_workgroups_per_cu_at_d_64(causal, lens, H):
 
 @pytest.mark.parametrize("causal", [False, True])
 def test_counters_of_the_work_queues_come_back_to_zero(causal):
-    """Eager calls take the library's 4096 counter sets in rotation and nothing clears them but the kernels that used them:
-    more calls than sets, each forward and backward drawing in all three kernels, and the last results are the first."""
+    """Eager forwards take the library's counter sets in rotation and what leaves them at zero are the kernels that used them:
+    every counter is zero after launches that drew, whole items and parts, and after more of them than there are sets the
+    results are still the first."""
+    import ctypes as C
     import torch
-    lens, H, d = [1 + (5 * i) % 9 for i in range(500)], 4, 64
-    Q.assert_draws(lens, H, d, causal)
-    run = GpuRun(BagSpec("sets", lens, H=H, d=d, seed=8900), causal=causal)
-    a, x = run.attn, run.dev
-    first = [t.clone() for t in (a.out, a.lse, a.dq, a.dk, a.dv)]
-    for i in range(2100):
-        if i == 2099:
-            for t in (a.out, a.lse, a.dq, a.dk, a.dv):
-                t.fill_(float("nan"))
-        a.forward(x["q"], x["k"], x["v"])
-        a.backward(x["q"], x["k"], x["v"], x["dout"])
-    torch.cuda.synchronize()
-    for got, want in zip((a.out, a.lse, a.dq, a.dk, a.dv), first):
-        assert torch.equal(got, want)
+    import paper_2508_06001_amd as K
+    hip = C.CDLL("libamdhip64.so.7", mode=os.RTLD_NOLOAD | C.RTLD_GLOBAL)      # the runtime that is loaded, never a second one
+    hip.hipMemcpy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_int]
+    n = C.c_int()
+    counters = K.lib.knap_fwd_queue_counters(C.byref(n))
+    words = np.ones(n.value, dtype=np.uint32)
+    for (lens, H, d), calls in ((_DRAW_JOINT, 12300), (([1162, 833], 88 if causal else 49, 64), 30), (([1162, 833], 59 if causal else 31, 128), 30)):
+        w = Q.walk("fwd", lens, H, d, causal)
+        assert w.draws and (w.parts > 0) == (len(lens) == 2)
+        run = GpuRun(BagSpec("sets", lens, H=H, d=d, seed=8900), causal=causal, backward=False)
+        a, x = run.attn, run.dev
+        first = [t.clone() for t in (a.out, a.lse)]
+        for i in range(calls):
+            if i == calls - 1:
+                for t in (a.out, a.lse):
+                    t.fill_(float("nan"))
+            a.forward(x["q"], x["k"], x["v"])
+        torch.cuda.synchronize()
+        for got, want in zip((a.out, a.lse), first):
+            assert torch.equal(got, want)
+        assert hip.hipMemcpy(words.ctypes.data, counters, 4 * n.value, 2) == 0      # device to host
+        assert not words.any()
 
 
 @pytest.mark.parametrize("n_seq", [1, 2, 15, 16, 17, 31, 33, 63, 64, 65])

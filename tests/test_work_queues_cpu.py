@@ -25,7 +25,7 @@ def test_every_item_of_one_kind_once(causal):
     for _ in range(600):
         lens, H, d = _random_bag(rng), rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128))
         cus = rng.choice((256, 256, 256, 304, 80, 37))          # 37: no multiple of eight workgroups, one queue
-        for pairs in (2, 4):
+        for pairs in (2, 4) if d == 128 else (2,):              # d = 64: no form with four
             for kernel in ("fwd", "dq", "dkdv"):
                 w = Q.walk(kernel, lens, H, d, causal, pairs, cus)
                 assert w.wrong == 0, (kernel, lens, H, d, causal, pairs, cus, w)
