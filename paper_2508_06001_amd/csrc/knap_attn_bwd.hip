@@ -3,34 +3,37 @@
 // the forward's log-sum-exp (the training loop of Sec. 4 backpropagates through
 // the attention of Sec. 3.4; Sec. 4.2 counts the backward as twice the forward).
 //
-//   delta_i = sum_c dO_ic O_ic                        (dQ kernel, which holds the dO rows of its queries anyway)
+//   delta_i = sum_c dO_ic O_ic
 //   S = Q K^T, P = exp(scale S - LSE), dP = dO V^T, dS = P (dP - delta)
-//   dQ = scale dS K                                    (dQ kernel, query-tile major; runs first)
-//   dV = P^T dO, dK = scale dS^T Q                     (dK/dV kernel, key-tile major)
+//   dQ = scale dS K                                    (by query tiles)
+//   dV = P^T dO, dK = scale dS^T Q                     (by key tiles)
 //
 // dQ sums over keys and dK, dV sum over queries.  Doing all three in one pass
 // needs a cross-workgroup reduction of one of them; on MI355X fp32 atomics into
 // HBM-resident accumulators cap that design far below the MFMA rate (every
-// atomic is a read-modify-write that leaves the XCD).  The backward is therefore
-// two kernels that each keep their accumulators in registers and recompute S and
+// atomic is a read-modify-write that leaves the XCD).  The backward therefore has
+// two kinds of work items that each keep their accumulators in registers and recompute S and
 // dP: seven contractions are issued for the five the mathematics needs, nothing
 // is reduced across workgroups, and the result is bitwise reproducible.
 //
-// dK/dV kernel (knap_attn_dkdv.h): a persistent workgroup of 8 or 4 waves owns a 256- or 128-row key/value tile of
+// dK/dV items (knap_attn_dkdv.h): a workgroup of 8 or 4 waves owns a 256- or 128-row key/value tile of
 // one (sequence, head) and walks over that sequence's queries 32 rows at a time; wave pairs split the work by
 // output (one wave S, P, dV; its partner dP, dS, dK, one tile behind) so that each wave holds a
 // single accumulator and two waves fit on a SIMD.  Details there.
 //
-// dQ kernel (knap_attn_dq.h): the forward kernel's structure.  This file holds the bidirectional kernels and the
-// launches of both masks.
+// dQ items (knap_attn_dq.h): the forward kernel's structure.
+//
+// Bags that fill the GPU up to a dozen times hand out both kinds in one launch (knap_attn_joint.h), with delta from a kernel in
+// front of it; larger ones in two, dQ first, which forms delta on the way.  bwd_joint() in knap_dispatch.h chooses.  This
+// file holds the bidirectional kernels and the launches of both masks.
 #include "knap_attn_joint.h"
 
 namespace knap {
 
 constexpr int kQueueCounters = 16;    // one work-queue counter per XCD for the dQ kernel, then one for the dK/dV kernel
 
-// The work queues of the kernels that follow on the stream start at zero.  The counters lie in the call's workspace, as the
-// kernels' results do: whatever else runs, no other call draws from them.
+// The work queues of the kernels that follow on the stream start at zero.  The counters lie in the call's workspace, as delta
+// does: whatever else runs, no other call draws from them.
 __global__ void bwd_queue_reset_kernel(unsigned* __restrict__ counters) {
   if (threadIdx.x < kQueueCounters) counters[threadIdx.x] = 0u;
 }

@@ -51,7 +51,7 @@ namespace knap {
 // one on long sequences.  PAIRS = 2 (4 waves, 128 keys, two workgroups per CU) hides the start and the end of
 // an item (K / V rows, first tile and stores) under the other workgroup's loop,
 // pads sequences to 128 keys instead of 256 and fills the GPU from half as many keys on; dkdv_pairs() chooses.
-// At d = 64 the registers of two pairs (166 of them without a spill) and their 43 KB of LDS leave room for a third
+// At d = 64 the registers of two pairs (152 of them, 157 under the mask, without a spill) and their 43 KB of LDS leave room for a third
 // workgroup on the CU, and a third wave on a SIMD has its MFMAs while the other two form exponentials, which are twice as
 // many per MFMA there: 10 sequences of 310..6795 tokens, 48 x 64, 2760 -> 2631 us.
 // ---------------------------------------------------------------------------

@@ -32,7 +32,7 @@
 // The arithmetic of a half therefore runs in the slot of the next half's MFMAs, and an item's first loads
 // go out under the previous item's epilogue.  Measured at 24 heads of 128 when both came in
 // (before -> after, us): 32 sequences of 256..648 tokens 172 -> 144, one of 4292 tokens 305 -> 283, 17 of 328..4533 tokens
-// 1104 -> 1040, one of 65536 and 200 short ones 47500 -> 46600.  Now: 251 for the one of 4292 (even shares), 1040 and 46200.
+// 1104 -> 1040, one of 65536 and 200 short ones 47500 -> 46600.  Now: 136, 254, 1025 and 45500.
 #include "knap_device.h"
 #include "knap_kernels.h"
 

@@ -11,60 +11,57 @@ namespace knap {
 constexpr int dkdv_workgroups_per_cu(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 4 / pairs; }
 constexpr int dkdv_waves_per_simd(int d, int pairs) { return d == 64 && pairs == 2 ? 3 : 2; }
 
-// Rounds of `slots` workgroups that a bag's items take, its sequences taken to be of one length: whole ones where there
-// are few, and as many as the items fill where there are so many that the shorter sequences even out the last.
-inline double rounds(int64_t total_tokens, int n_seq, int H, bool causal, int tile, int64_t slots) {
-  const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + tile - 1) / tile;
-  const int64_t items = (causal ? (tiles + 1) / 2 : tiles) * n_seq * H;
+// Rounds of `slots` workgroups that a bag's items take without the mask, its sequences taken to be of one length: whole ones
+// where there are few, and as many as the items fill where there are so many that the shorter sequences even out the last.
+inline double rounds(int64_t total_tokens, int n_seq, int H, int tile, int64_t slots) {
+  const int64_t items = ((total_tokens + n_seq - 1) / n_seq + tile - 1) / tile * n_seq * H;
   return items >= 8 * slots ? (double)items / slots : (double)((items + slots - 1) / slots);
 }
 
-// Wave pairs per workgroup of the dK/dV kernel (2 or 4, see there), from what the host knows of a bag: its tokens, heads
-// and number of sequences.  Both sides measured, two pairs against four: times of that kernel where nothing else is said.
-//  * At most half a 256-key tile per CU: two, which spread the keys over twice as many CUs (3 causal sequences of up to
-//    391 tokens, 6 x 128: 38 against 51 us; 2 of up to 4362, 2 x 64: 104 against 150 us).
-//  * Many short sequences: two, which hide the start and the end of every item (32 of 450 tokens, 24 x 128: 249 against
-//    276 us; 17 causal ones of 328..4533 tokens: 1125 against 1240 us).
-//    The average does not show one long sequence among many short ones, where two pairs lose as soon as the long one's
-//    tiles fill the GPU; the bounds on the whole bag are a compromise between such bags and those of like lengths.  Causal,
-//    d = 128, whole backward in us: 20 of 3000 tokens, 24 heads 3904 against 4023; 128 of 450, 24 heads 1227 against 1332; 30 of
-//    1100, 3 heads 158 against 225; but 30000 and 30 of 300, 12 heads 8752 against 8394; half of 60000 tokens in one
-//    sequence, 24 heads 17234 against 16973, 3 heads 2627 against 2464 (of 30000, 12 heads 3047 against 2930; of 20000, 6 heads,
-//    where the GPU is not full, 686 against 755).
-//    Without the mask at d = 128: up to 16384 tokens at an average below 512 (32 of 450, 24 x 128: 233 against 267 us; but
-//    4405, 619 and 371: 490 against 463; 4200 and seven of 450, 12 x 128: 247 against 229).  Where four pairs would have six
-//    rounds or more, at averages below 3000 (12 of 2600, 24 x 128: 1704 against 1818 us; 17 of 328..4533: 1806 against
-//    1837; 60 of 800: 1011 against 1154; 64 of 450: 409 against 433, with 6 heads and three rounds 122 against 114; 20 of
-//    3000: 3796 against 3778) but those from 512 to 640, which are mostly one long sequence among short ones (16384 and
-//    30 of 300: 5358 against 5117; 65536 and 200 short 84.4 against 81.4 ms; but 60 of 600: 592 against 700 us).  And where
-//    the smaller tiles save a round (15 of 640: 174 against 216 us).
-//  * d = 64, where three workgroups of two pairs share a CU: always two (the bags that leave it to be chosen have many
-//    rounds or short sequences.  32 of 450 tokens, 48 x 64: 246 against 289 us; 16 of 4096: 6389 against 7163; 65536: 98.1
-//    against 103.3 ms; causal, 20 of 3000: 2637 against 2970 us, 65536: 51.6 against 52.1 ms).
-//  * Otherwise four (65536 and 200 short, 24 x 128: 80.3 against 82.4 ms; 30000 tokens, 3 x 128: 2.90 against 3.13 ms).
+// Wave pairs per workgroup of the dK/dV kernel where it is a launch of its own (2 or 4, see there), from what the host knows of
+// a bag: its tokens, heads and number of sequences.  Both sides measured on bags that bwd_joint() leaves to two launches,
+// four pairs | two, forward and backward in us at 24 heads of 128 where nothing else is said.
+//  * At most half a 256-key tile per CU: two, which spread the keys over twice as many CUs (hundreds of sequences of a few
+//    tokens each).
+//  * Short sequences: two, which hide the start and the end of every item: 60 of 350 tokens 730 | 671, 32 of 450 548 | 545; under
+//    the mask 128 of 450 1654 | 1592.  The average does not show one long sequence among many short ones, where two pairs lose as
+//    soon as the long one's tiles fill the GPU (half of 60000 tokens in one, under the mask, 23359 | 24010); the bounds on the
+//    whole bag are a compromise between such bags and those of like lengths.
+//  * Without the mask, where four pairs would have six rounds or more: two at averages below 3000 (60 of 800 2563 | 2474, 20 of
+//    2600 6881 | 6887; 20 of 3000 8818 | 8877, 16 of 4096 12526 | 12689), but not from 512 to 640.  That band is kept for one long
+//    sequence among short ones (half of 60000 tokens in one 42090 | 42985; 65536 and 200 short, dK/dV alone, 81.4 | 84.4 ms), and
+//    bags of like lengths pay for it: 60 of 600 1565 | 1494, 80 of 560 1910 | 1821.  By tokens and number of sequences they
+//    are the same bags.
+//  * Fewer than six rounds: two where the smaller tiles save one (a single sequence of 2680 tokens: 465 | 373).
+//  * d = 64, where three workgroups of two pairs share a CU: always two (dK/dV alone, 32 of 450 tokens, 48 heads, 289 | 246; 65536
+//    103.3 | 98.1 ms).
+//  * Otherwise four: one of 30000, 12 heads, 21968 | 22633; of 4292, 14 heads, 540 | 555; of 4825 under the mask 638 | 658.
 inline int dkdv_pairs(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
   if (d == 64 || total_tokens * H <= (int64_t)cus / 2 * 256) return 2;
   const int64_t n = n_seq;
   if (causal) return total_tokens <= 65536 && total_tokens < 4096 * n ? 2 : 4;
   if (total_tokens < 512 * n && total_tokens <= 16384) return 2;
-  const double four = rounds(total_tokens, n_seq, H, causal, 256, cus);
+  const double four = rounds(total_tokens, n_seq, H, 256, cus);
   if (four >= 6.0)
     return total_tokens < 512 * n || (total_tokens >= 640 * n && total_tokens < 3000 * n) ? 2 : 4;
-  return total_tokens >= 640 * n && rounds(total_tokens, n_seq, H, causal, 128, 2 * (int64_t)cus) < 0.9 * four ? 2 : 4;
+  return total_tokens >= 640 * n && rounds(total_tokens, n_seq, H, 128, 2 * (int64_t)cus) < 0.9 * four ? 2 : 4;
 }
 
 // Whether both kinds of items go out in one launch (knap_attn_joint.h), behind the kernel that forms delta, or the dQ kernel
 // and then the dK/dV kernel.  One launch has one last round to fill where two have two, spreads every sequence over the XCDs,
-// and takes two wave pairs per workgroup for the keys.  Backward in us, two launches against one, at n rounds of 128-row
-// tiles: 4 sequences of up to 311 tokens, 2 x 64, 28 against 22; 4000, 3 x 128 (0.2): 184 against 145; one of 4292, 24 x 128
-// (1.6): 828 against 762; 3000 (1.1): 506 against 369; 5 of up to 4346 (2.9): 951 against 851; 21 of up to 6108 (4.6): 1805
-// against 1451; 17 of 328..4533 (11.5): 3356 against 3306, causal (6): 2036 against 1952; 10 of up to 6795, 48 x 64 (11):
-// 4559 against 4477; 16 of up to 4393 (15.6): 4931 against 4865.  Two where
-//  * the rounds are many: 20 of up to 4479 (20.9): 7016 against 7029; 16 causal ones of up to 25431 (13.9): 17860 against 18017,
-//    and at d = 128, where four wave pairs are the better ones for long sequences, fewer of those: 131072, 32768 and 4 of 8192,
-//    3 heads (9) 76.8 ms against 80.5; but 60000, 3 heads (2.7) 16.7 against 16.0;
-//  * short sequences fill several: 32 of 450 (6): 423 against 437, 128 of 450, 12 x 128, causal (7): 643 against 660;
-//  * each kernel has one round that is nearly full, of one sequence: 4825 causal (0.9): 487 against 510.
+// and takes two wave pairs per workgroup for the keys.  Two launches | one, forward and backward in us at 24 heads of 128 where
+// nothing else is said, n rounds of 128-row tiles: 4 sequences of up to 311 tokens, 2 x 64, 29.6 | 23.5; 4000, 3 x 128 (0.2), 229 |
+// 188; one of 3000 (1.1) 578 | 489, of 4292 (1.6) 1077 | 944; 5 of up to 4346 (4.2) 1617 | 1600; 40 of 600 (9.4) 1080 | 1025; 10 of
+// up to 6795, 48 x 64 (11), 5936 | 5814; 17 of 328..4533 (12) 4354 | 4353, under the mask (6.4) 2566 | 2527.  Two where
+//  * the rounds are many, above 13, where one launch no longer gains on every kind of bag: 16 of 4096 (24) 12534 | 12681, images and
+//    videos (25) 25844 | 26058, but 23 of 328..4533 (17) 6444 | 6416, half of 40000 tokens in one (16) 19838 | 18615;
+//    and at d = 128, where four wave pairs are the better ones for long sequences, above 4 of those: 131072, 32768 and 4 of 8192,
+//    3 heads (9), 101.3 ms | 106.2; but 40000, 12 heads (7.3), 37.7 | 37.4, and 60000, 3 heads (2.7), 22.3 | 21.5;
+//  * short sequences fill several: 128 of 450 under the mask, 12 heads (6), 822 | 850; 32 of 450 (6) 547 | 546;
+//  * each kernel has one round that is nearly full, of one sequence: 4000, 15 heads (0.9), 503 | 547; 4825, 12 heads (0.9), 585 | 632,
+//    under the mask, 24 heads, 636 | 668.
+// One launch loses where a long sequence's 256-key tiles just fill the GPU once, beside short ones (9000 tokens and 30 short, 6 heads,
+// 1081 | 1200; 4500 and 15 short 406 | 319): by tokens and number of sequences these are the same bags as others that gain.
 inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
   const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + 127) / 128;
   const double r = (double)((causal ? (tiles + 1) / 2 : tiles) * n_seq * H) / (double)((int64_t)cus * dkdv_workgroups_per_cu(d, 2));
