@@ -17,8 +17,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libknapattn.so")
 
-HIP_SOURCES = ["knap_attn_fwd.hip", "knap_attn_bwd.hip", "knap_attn_bwd_causal.hip", "knap_ulysses.hip",
-               "knap_api.hip"]
+HIP_SOURCES = ["knap_attn_fwd.hip", "knap_attn_fwd_full.hip", "knap_attn_bwd.hip", "knap_attn_bwd_causal.hip",
+               "knap_ulysses.hip", "knap_api.hip"]
 C_SOURCES = ["knap_host.c"]
 
 HIP_FLAGS = [

@@ -109,8 +109,8 @@ int fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
     if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   }
   unsigned* counters = di->queues + 8 * set;
-  e = knap::launch_fwd(q, k, v, cu_seqlens, n_seq, H, d, scale, causal, out, lse, counters,
-                                        grid, static_cast<hipStream_t>(stream));
+  e = (causal ? knap::launch_fwd_causal : knap::launch_fwd_full)(q, k, v, cu_seqlens, n_seq, H, d, scale, out, lse, counters, grid,
+                                                                 static_cast<hipStream_t>(stream));
   if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
   return KNAP_OK;
 }

@@ -67,38 +67,6 @@ struct Bwd2Cfg {
   static constexpr int TILE_ELEMS = BM * Tile<D>::LD;
 };
 
-// Readers with ONE base register each: the swizzle is an XOR on the chunk index, so the offset of
-// chunk pair cc of a row read is base ^ (32 cc) bytes-in-elements, and of (db, hi) of a transposing read
-// (base ^ (32 db + 16 hi)) + 8 hi rows.
-template <int D>
-struct RowReaderX {
-  int base;
-  __device__ __forceinline__ void init(int lane) { base = 2 * Tile<D>::off(lane & 31, 8 * (lane >> 5)); }   // bytes
-  // a copy of the base the optimizer cannot see through: what is derived from it stays in the step that
-  // uses it (an address hoisted out of the loop would need a register of its own per buffer and chunk,
-  // whereas formed next to its read the buffer's address becomes the read's immediate offset)
-  __device__ __forceinline__ int fresh() const { int b = base; asm volatile("" : "+v"(b)); return b; }
-  __device__ static __forceinline__ bf16x8 get(const __bf16* tile, int b, int cc) {
-    return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(tile) + (b ^ (32 * cc)));
-  }
-};
-template <int D>
-struct ColReaderX {
-  int base;
-  __device__ __forceinline__ void init(int lane) {
-    const int i = lane & 15, kr = i >> 2, hh = lane >> 5;
-    base = 2 * Tile<D>::off(4 * hh + kr, ((lane >> 4) & 1) * 16 + 4 * (i & 3));   // bytes
-  }
-  __device__ __forceinline__ int fresh() const { int b = base; asm volatile("" : "+v"(b)); return b; }
-  __device__ static __forceinline__ bf16x8 get(const __bf16* tile, int b, int k_base, int db) {
-    const char* p = reinterpret_cast<const char*>(tile + k_base * Tile<D>::LD);
-    // rows 8 further down: at D = 128 the swizzle flips bit 1 of the chunk position there, at D = 64 bit 2
-    // (the bit that db flips as well)
-    return join(lds_read_tr(reinterpret_cast<const __bf16*>(p + (b ^ (64 * db)))),
-                lds_read_tr(reinterpret_cast<const __bf16*>(p + ((b ^ (D == 128 ? 64 * db + 32 : 64 * (db ^ 1))) + 16 * Tile<D>::LD))));
-  }
-};
-
 // 16 times the lane's number, plus a multiple of 1024
 struct LaneWord {
   int word;

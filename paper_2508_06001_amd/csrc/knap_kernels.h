@@ -8,9 +8,11 @@
 
 namespace knap {
 
-hipError_t launch_fwd(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq,
-                      int H, int d, float scale, bool causal, void* out, float* lse, unsigned* counters,
-                      int grid, hipStream_t stream);
+// the forward without the mask (knap_attn_fwd_full.hip) and the causal one (knap_attn_fwd.hip)
+hipError_t launch_fwd_full(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq, int H, int d, float scale,
+                           void* out, float* lse, unsigned* counters, int grid, hipStream_t stream);
+hipError_t launch_fwd_causal(const void* q, const void* k, const void* v, const int32_t* cu, int n_seq, int H, int d, float scale,
+                             void* out, float* lse, unsigned* counters, int grid, hipStream_t stream);
 
 // Device address (on the current device) of the forward's work-queue counters: kQueueSets sets of 8, at zero
 // whenever no kernel uses them; nullptr on failure.

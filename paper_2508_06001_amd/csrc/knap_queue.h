@@ -175,4 +175,26 @@ struct EvenQueue {
   __device__ __forceinline__ bool last_draw(unsigned drawn) const { return (int)drawn == wide + parts - 1; }
 };
 
+// Pairs: two items of an even queue that follow each other go out as one ticket, in front of the single ones, where the kernel has a
+// cheaper form for two query tiles of a sequence and head (knap_attn_fwd_full.hip).  Which items: from the first one on, as long as
+// they are of sequences of at least kPairTiles tiles (shorter ones lose more by the longer start and end of a pair than their loop
+// gains) and the items behind them have the work of a tail of two rounds of theirs (three at d = 64, where pairs gain less: one of
+// 6000 tokens, 48 x 64, 468 -> 490 with two): the list has to end evenly.  Forward in us, all single ->
+// pairs down to a tail of one, 1.5 and 2.5 rounds: 24 heads, one of 16384 2855 -> 2634, 2709, 2766; 8 of 4096 1482 -> 1424, 1420, 1420; 6 of
+// up to 4388 567 -> 598, 602, 571; of 4267, 841 and 216 243 -> 276, 245, 247.  Counted in items and not by their work, 12000 tokens and 40 of
+// 300, 12 heads, took 879 (848 single).  From 6 tiles on instead of 12: 64 of 1024 894 -> 870 instead of 890, 32 of 2048 1583 -> 1510 instead of
+// 1536, but three heads of up to 131072 24070 -> 22290 instead of 22000, 16 of 1024 233 -> 237 instead of 232.
+constexpr int kPairTiles = 12;
+constexpr int pair_tail_rounds(int d) { return d == 64 ? 3 : 2; }
+// units of work of an item: a bag's work has to fit an int
+__device__ __forceinline__ int item_work(int tiles) { return (tiles + 7) >> 3; }
+// how many of the first of a sequence's `share` items, of `work` units each, may be paired; `behind`: the units of the queue's items
+// of shorter sequences
+__device__ __forceinline__ int pairable(int share, int tiles, int work, int behind, int tail) {
+  return tiles < kPairTiles ? 0 : max(0, min(share, share + behind / work - tail));
+}
+// the pairs of a queue whose first `paired` items may be paired and whose first `whole` are dealt out whole; a tail of those stays
+// single also where a few items behind them go out in parts (one of 5939 tokens, 24 heads, 411 -> 418 with five pairs)
+__device__ __forceinline__ int item_pairs(int paired, int whole, int tail) { return max(0, min(paired, whole - tail)) / 2; }
+
 }  // namespace knap

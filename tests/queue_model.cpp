@@ -162,6 +162,65 @@ int queue_dkdv_pairs(long long tokens, int n_seq, int H, int d, int causal, int 
   return knap::dkdv_pairs(tokens, n_seq, H, d, causal != 0, cus);
 }
 
+// the forward without the mask, whose tickets stand for pairs of items, single ones and parts (knap_attn_fwd_full.hip): out as above, with
+// the pairs of all queues in place of the items
+void queue_walk_pairs(const int* lens, int n_seq, int H, int d, int grid, int* out) {
+  const int rounds = knap::pair_tail_rounds(d);
+  std::vector<int> sorted(lens, lens + n_seq);
+  std::sort(sorted.begin(), sorted.end(), [](int a, int b) { return a > b; });
+  std::vector<int> start(n_seq + 1, 0), mine(n_seq + 1);
+  for (int r = 0; r < n_seq; ++r) start[r + 1] = start[r] + H * ((sorted[r] + 127) / 128);
+  const int n = start[n_seq];
+  std::vector<int> whole(n, 0), part((size_t)n * 2, 0);
+  std::vector<unsigned> counters(8, 0);
+  Walk w = {0, 0, 0, 0, 0, 0};
+  gridDim.x = grid;
+  const int n_q = grid % 8 == 0 ? 8 : 1;
+  for (int q = 0; q < n_q; ++q) {
+    blockIdx.x = q;
+    knap::EvenQueue<2, 1> queue;
+    queue.init(counters.data());
+    mine[0] = 0;
+    int behind = 0, paired = 0;
+    bool stop = n <= rounds * grid;
+    for (int s = 0; s < n_seq; ++s) {
+      const int items = start[s + 1] - start[s];
+      mine[s + 1] = mine[s] + queue.share(items, s);
+      behind += queue.share(items, s) * knap::item_work(items / H);
+    }
+    for (int s = 0; s < n_seq && !stop; ++s) {
+      const int share = mine[s + 1] - mine[s], tiles = (start[s + 1] - start[s]) / H, work = max(1, knap::item_work(tiles));
+      behind -= share * work;
+      const int some = knap::pairable(share, tiles, work, behind, rounds * queue.per);
+      paired = mine[s] + some;
+      stop = some < share;
+    }
+    queue.deal(mine.data(), n_seq, [&](int k) { return start[k + 1] - start[k]; });
+    const int pairs = knap::item_pairs(paired, queue.wide, rounds * queue.per), singles = queue.wide - pairs, tickets = singles + queue.parts;
+    auto global = [&](int i) {
+      const int k = knap::rank_of_item(mine.data(), n_seq, i);
+      return start[k] + queue.locate(start[k + 1] - start[k], k, i - mine[k]);
+    };
+    w.wrong += pairs < 0 || singles < pairs;
+    for (int t = 0; t < pairs; ++t) { ++whole[global(2 * t)]; ++whole[global(2 * t + 1)]; }
+    for (int t = pairs; t < singles; ++t) ++whole[global(t + pairs)];
+    for (int t = singles; t < tickets; ++t) {
+      const int p = t - singles;
+      ++part[(size_t)global(queue.item_of_part(p)) * 2 + (p & 1)];
+    }
+    w.items += pairs;
+    w.parts += queue.parts;
+    w.per = queue.per;
+    w.most = max(w.most, tickets);
+    w.draws |= tickets > queue.per;
+    // all parts: one for a workgroup, none drawn
+    w.wrong += singles == 0 && tickets > queue.per;
+  }
+  for (int i = 0; i < n; ++i) w.wrong += !((whole[i] == 1 && part[2 * i] == 0 && part[2 * i + 1] == 0) || (whole[i] == 0 && part[2 * i] == 1 && part[2 * i + 1] == 1));
+  const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
+  std::copy(values, values + 6, out);
+}
+
 // set of eager forward call `call`, and the first of the sets it clears (-1: none)
 void queue_eager_set(unsigned long long call, int* out) {
   const knap::EagerSet s = knap::eager_set(call);

@@ -39,6 +39,8 @@ def _lib():
     lib.queue_walk.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 6 + [C.POINTER(C.c_int)]
     lib.queue_walk_even.restype = None
     lib.queue_walk_even.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
+    lib.queue_walk_pairs.restype = None
+    lib.queue_walk_pairs.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 4 + [C.POINTER(C.c_int)]
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_eager_set.restype = None
     lib.queue_eager_set.argtypes = [C.c_ulonglong, C.POINTER(C.c_int)]
@@ -84,6 +86,13 @@ def walk(kernel: str, lens: Sequence[int], H: int, d: int, causal: bool, pairs: 
     out = (C.c_int * 6)()
     _lib().queue_walk((C.c_int * len(lens))(*lens), len(lens), H, tile, int(causal), split,
                       grid(kernel, d, pairs, cus), out)
+    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
+
+
+def walk_pairs(lens: Sequence[int], H: int, d: int, cus: int = CUS) -> Walk:
+    """The tickets of the forward without the mask; `items` are the pairs of query tiles, of all queues."""
+    out = (C.c_int * 6)()
+    _lib().queue_walk_pairs((C.c_int * len(lens))(*lens), len(lens), H, d, grid("fwd", d, cus=cus), out)
     return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
 
 

@@ -64,6 +64,20 @@ def test_every_item_of_both_kinds_once(causal):
     assert min(seen.values()) > 20, seen
 
 
+def test_every_item_of_the_unmasked_forward_once():
+    """Its tickets: pairs of items, single ones, parts; random bags and grids, with and without pairs, all in parts."""
+    rng = random.Random(77)
+    seen = {"pairs": 0, "no pairs": 0, "all parts": 0}
+    for _ in range(1500):
+        lens, H, d = _random_bag(rng), rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128))
+        cus = rng.choice((256, 256, 256, 304, 80, 37))
+        w = Q.walk_pairs(lens, H, d, cus)
+        assert w.wrong == 0, (lens, H, d, cus, w)
+        items = H * sum((x + 127) // 128 for x in lens)
+        seen["pairs" if w.items else "all parts" if items and w.parts == 2 * items else "no pairs"] += 1
+    assert min(seen.values()) > 100, seen
+
+
 @pytest.mark.parametrize("start", [0, (1 << 32) - 20000])
 def test_counter_sets_are_cleared_between_two_uses_far_from_either(start):
     """Eager forward calls: between two calls that draw from one set some call clears it, and calls that touch a set (draw from
