@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libknapattn.so")
 
 HIP_SOURCES = ["knap_attn_fwd.hip", "knap_attn_fwd_full.hip", "knap_attn_bwd.hip", "knap_attn_bwd_causal.hip",
-               "knap_ulysses.hip", "knap_api.hip"]
+               "knap_attn_bwd_small.hip", "knap_ulysses.hip", "knap_api.hip"]
 C_SOURCES = ["knap_host.c"]
 
 HIP_FLAGS = [
@@ -36,6 +36,8 @@ FILE_FLAGS = {
     # of 328..4533 tokens, 24 x 128: 844 us against 871); the causal dK/dV kernel is the same with it, the bidirectional one
     # 1 % slower on long sequences
     "knap_attn_bwd_causal.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
+    # ... and the causal kernel for small bags at d = 128 spills 66 values
+    "knap_attn_bwd_small.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
 }
 
 

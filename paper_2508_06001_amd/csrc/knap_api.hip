@@ -211,7 +211,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const int32_t* cu_seql
   const int dq_wg = di->dq_wg[d == 128];
   const knap::BwdArgs args = {q, k, v, out, dout, lse, cu_seqlens, n_seq, H, scale, dq, dk, dv, delta, lse2, counters};
   if (knap::bwd_joint(total_tokens, n_seq, H, d, causal, di->cus)) {
-    const hipError_t e = knap::launch_joint(args, d, causal, (int)total_tokens, di->cus, static_cast<hipStream_t>(stream), g_prof_start,
+    const hipError_t e = knap::launch_joint(args, d, causal, knap::bwd_small(total_tokens, n_seq, H, d, causal, di->cus), (int)total_tokens, di->cus, static_cast<hipStream_t>(stream), g_prof_start,
                                             g_prof_stop);
     if (e != hipSuccess) { g_last_hip_error = static_cast<int>(e); return KNAP_ERR_LAUNCH_FAILED; }
     return KNAP_OK;

@@ -23,9 +23,9 @@
 //
 // dQ items (knap_attn_dq.h): the forward kernel's structure.
 //
-// Bags that fill the GPU up to a dozen times hand out both kinds in one launch (knap_attn_joint.h), with delta from a kernel in
-// front of it; larger ones in two, dQ first, which forms delta on the way.  bwd_joint() in knap_dispatch.h chooses.  This
-// file holds the bidirectional kernels and the launches of both masks.
+// Bags that fill the GPU up to a dozen times hand out both kinds in one launch (knap_attn_joint.h; the smallest ones in items of half the
+// rows, knap_attn_bwd_small.hip), with delta from a kernel in front of it; larger ones in two, dQ first, which forms delta on the way.
+// bwd_joint() and bwd_small() in knap_dispatch.h choose.  This file holds the bidirectional kernels and the launches of both masks.
 #include "knap_attn_joint.h"
 
 namespace knap {
@@ -53,10 +53,11 @@ hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int 
   return hipSuccess;
 }
 
-hipError_t launch_joint(const BwdArgs& a, int d, bool causal, int T, int cus, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+hipError_t launch_joint(const BwdArgs& a, int d, bool causal, bool small, int T, int cus, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipError_t e = hipSuccess;
   if (ev_start && ev_stop && (e = hipEventRecord(ev_start, stream)) != hipSuccess) return e;
-  e = causal ? launch_joint_causal(a, d, T, cus, stream) : launch_joint_m<false>(a, d, T, cus, stream);
+  if ((e = launch_delta(a, d, T, stream)) != hipSuccess) return e;
+  e = small ? launch_small(a, d, causal, cus, stream) : causal ? launch_joint_causal(a, d, cus, stream) : launch_joint_m<false>(a, d, cus, stream);
   if (e != hipSuccess) return e;
   if (ev_start && ev_stop && (e = hipEventRecord(ev_stop, stream)) != hipSuccess) return e;
   return hipSuccess;

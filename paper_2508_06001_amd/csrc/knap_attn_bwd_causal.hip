@@ -11,8 +11,8 @@ hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipSt
   return launch_dkdv_m<true>(a, d, pairs, cus, stream);
 }
 
-hipError_t launch_joint_causal(const BwdArgs& a, int d, int T, int cus, hipStream_t stream) {
-  return launch_joint_m<true>(a, d, T, cus, stream);
+hipError_t launch_joint_causal(const BwdArgs& a, int d, int cus, hipStream_t stream) {
+  return launch_joint_m<true>(a, d, cus, stream);
 }
 
 }  // namespace knap

@@ -36,13 +36,6 @@ namespace knap {
 
 constexpr float kLn2 = 0.6931471805599453f;
 
-// the lane's number, formed where it is called
-__device__ __forceinline__ int lane_id() {
-  int x;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
-  return x;
-}
-
 // a wave-uniform value whose uses cannot be moved in front of this: what a form derives from it is not formed ahead of all forms
 __device__ __forceinline__ int uniform_here(int x) {
   asm volatile("" : "+s"(x));

@@ -138,14 +138,16 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
   }
 }
 
-template <bool CAUSAL>
-static hipError_t launch_joint_m(const BwdArgs& a, int d, int T, int cus, hipStream_t stream) {
+inline hipError_t launch_delta(const BwdArgs& a, int d, int T, hipStream_t stream) {
   const dim3 rows((T + 127) / 128, a.H);
   auto* delta = d == 64 ? attn_bwd_delta_kernel<64> : attn_bwd_delta_kernel<128>;
   hipLaunchKernelGGL(delta, rows, dim3(kThreads), 0, stream, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
                      a.n_seq, a.H, a.counters);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  return hipGetLastError();
+}
+
+template <bool CAUSAL>
+static hipError_t launch_joint_m(const BwdArgs& a, int d, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
   auto* joint = d == 64 ? attn_bwd_joint_kernel<64, CAUSAL> : attn_bwd_joint_kernel<128, CAUSAL>;
   hipLaunchKernelGGL(joint, dim3(cus * dkdv_workgroups_per_cu(d, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q,

@@ -220,6 +220,13 @@ __device__ __forceinline__ void store_block(__amdgpu_buffer_rsrc_t r, uint32_t o
   }
 }
 
+// the lane's number, formed where it is called
+__device__ __forceinline__ int lane_id() {
+  int x;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+  return x;
+}
+
 // Workgroup barrier for LDS traffic alone: __syncthreads() also waits for every global store in flight.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

@@ -70,6 +70,20 @@ inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal
   return !(n_seq == 1 && r > 0.8 && r <= 1.0);
 }
 
+// Whether that launch takes items of 64 rows (knap_attn_bwd_small.hip), twice as many, of half the length each, and single tiles under the
+// mask: up to as many rounds of 128-row tiles as leave a workgroup for every one of them, a quarter; under the mask, where pairs of
+// 128-row tiles leave more of the GPU idle, somewhat more.  128 rows | 64, backward in us, n the rounds.  Without the mask: one of 4776, 3 x
+// 128 (0.22), 162 | 123; one of 10784, 2 x 64 (0.22), 273 | 219; 2021 in 10, 6 x 128 (0.23), 24.0 | 21.4; one of 1500, 12 x 128 (0.28), 64 | 72;
+// one of 544, 48 x 64 (0.31), 25.9 | 28.7.  Under it: one of 4776, 3 x 128 (0.22), 176 | 104; one of 16682, 2 x 64 (0.34), 470 | 429, of 19631
+// (0.40) 547 | 560; 9960 in 3, 3 x 128 (0.46), 172 | 137; 4536 in 10, 6 x 128 (0.47), 47 | 37; one of 10019, 3 x 128 (0.46), 346 | 375; 10525 in 19, half
+// of them in one, 3 x 128 (0.56), 201 | 131; 1862 in 4, 24 x 128 (0.75), 50 | 54.  Without the mask bags of one long and many short sequences gain up to a
+// half (8352 in 14, 3 x 128, 165 | 118), and bags of like lengths of the same numbers lose up to 8 %.
+inline bool bwd_small(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
+  const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + 127) / 128;
+  const double r = (double)(tiles * n_seq * H) / (double)((int64_t)cus * dkdv_workgroups_per_cu(d, 2));
+  return r <= (!causal ? 0.25 : n_seq == 1 ? 0.375 : 0.55);
+}
+
 // Counter sets of the forward's work queues.  The forward entry points have no workspace: a launch draws from one of these sets
 // (8 counters each, at zero in the device image), which it leaves at zero.  Eager calls take the first 3 kSetsPerThird in
 // rotation.  Calls that share a set because too many were enqueued while one ran lose items and may leave the set at

@@ -147,8 +147,9 @@ struct EvenQueue {
   template <class Length>
   __device__ __forceinline__ void deal(const int* s_mine, int n_seq, Length length) {
     mine = s_mine[n_seq];
-    int last = 0;           // items of the last kind that parts stand for
-    if (mine * (KINDS - 1 + SPLIT) <= per) {
+    int last = 0;           // items of the last kind that parts stand for (SPLIT = 0: none)
+    if (SPLIT == 0) {
+    } else if (mine * (KINDS - 1 + SPLIT) <= per) {
       last = mine;
     } else {
       const int thin = KINDS * mine % per;

@@ -86,9 +86,13 @@ Walk walk_even(int grid, const std::vector<int>& start, int n_seq, int n_items) 
       const int w = global(queue.item(t));
       if (w < 0) ++r.wrong; else ++(KINDS == 2 && queue.first_kind(t) ? first : second)[w];
     }
-    for (int p = 0; p < queue.parts; ++p) {
-      const int w = global(queue.item_of_part(p));
-      if (w < 0) ++r.wrong; else ++part[(size_t)w * SPLIT + p % SPLIT];
+    if constexpr (SPLIT > 0) {
+      for (int p = 0; p < queue.parts; ++p) {
+        const int w = global(queue.item_of_part(p));
+        if (w < 0) ++r.wrong; else ++part[(size_t)w * SPLIT + p % SPLIT];
+      }
+    } else {
+      r.wrong += queue.parts != 0;
     }
     for (int i = 0; i < queue.per; ++i) {
       blockIdx.x = q + i * n_q;
@@ -152,6 +156,21 @@ void queue_walk_even(const int* lens, int n_seq, int H, int causal, int kinds, i
                             : (causal ? walk_even<4, 1>(grid, start, n_seq, n) : walk_even<2, 1>(grid, start, n_seq, n));
   const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
   std::copy(values, values + 6, out);
+}
+
+// ... and of both kinds in tiles of 64, none in parts (the backward of small bags)
+void queue_walk_small(const int* lens, int n_seq, int H, int grid, int* out) {
+  std::vector<int> sorted(lens, lens + n_seq);
+  std::sort(sorted.begin(), sorted.end(), [](int a, int b) { return a > b; });
+  std::vector<int> start(n_seq + 1, 0);
+  for (int r = 0; r < n_seq; ++r) start[r + 1] = start[r] + H * ((sorted[r] + 63) / 64);
+  const Walk w = walk_even<0, 2>(grid, start, n_seq, start[n_seq]);
+  const int values[] = {w.items, w.parts, w.per, w.most, w.draws, w.wrong};
+  std::copy(values, values + 6, out);
+}
+
+int queue_bwd_small(long long tokens, int n_seq, int H, int d, int causal, int cus) {
+  return knap::bwd_small(tokens, n_seq, H, d, causal != 0, cus);
 }
 
 int queue_bwd_joint(long long tokens, int n_seq, int H, int d, int causal, int cus) {

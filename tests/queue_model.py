@@ -41,6 +41,9 @@ def _lib():
     lib.queue_walk_even.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
     lib.queue_walk_pairs.restype = None
     lib.queue_walk_pairs.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 4 + [C.POINTER(C.c_int)]
+    lib.queue_walk_small.restype = None
+    lib.queue_walk_small.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 3 + [C.POINTER(C.c_int)]
+    lib.queue_bwd_small.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_eager_set.restype = None
     lib.queue_eager_set.argtypes = [C.c_ulonglong, C.POINTER(C.c_int)]
@@ -104,6 +107,18 @@ def bwd_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS)
 def walk_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> Walk:
     """The queues of that launch; `items` are those of one kind, `parts` those of query tiles."""
     return _walk_even(lens, H, causal, 2, grid("dkdv", d, 2, cus))
+
+
+def bwd_small(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> bool:
+    """Whether that launch takes tiles of 64 rows (walk_small) in place of 128 (walk_joint)."""
+    return bool(_lib().queue_bwd_small(sum(lens), len(lens), H, d, int(causal), cus))
+
+
+def walk_small(lens: Sequence[int], H: int, d: int, cus: int = CUS) -> Walk:
+    """The queues of the launch of both kinds of 64-row items; `items` are those of one kind."""
+    out = (C.c_int * 6)()
+    _lib().queue_walk_small((C.c_int * len(lens))(*lens), len(lens), H, grid("dkdv", d, 2, cus), out)
+    return Walk(out[0], out[1], out[2], out[3], bool(out[4]), out[5])
 
 
 def launched(lens: Sequence[int], H: int, d: int, causal: bool) -> tuple:

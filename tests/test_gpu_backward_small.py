@@ -1,0 +1,81 @@
+"""The backward of small bags, in items of 64 keys and of 64 queries (knap_attn_bwd_small.hip): parity with the fp64 oracle on bags that
+launch it, and the launch of 128-row items with every query tile in parts on bags that still take it.
+
+Bars: dq, dk, dv are sums of products of bf16-rounded factors (P and dS, relative 2^-9 each) stored in bf16: 2^-9 from either, so 2 times
+2^-9 in the 2-norm of a head where errors are independent; 4 times as the bound."""
+import numpy as np
+import pytest
+
+from knap_inputs import BagSpec
+from oracle import attention as A
+
+import queue_model as Q
+from gpu_util import GpuRun, rel_fro, say
+
+pytestmark = pytest.mark.gpu
+
+BAR = 4 * 2.0 ** -9
+
+
+def _compare(bag, causal, heads):
+    run = GpuRun(bag, causal=causal)
+    cu = [int(c) for c in run.cu]
+    worst = 0.0
+    for h in heads:
+        got = {n: np.zeros((bag.total_tokens, bag.d)) for n in ("dq", "dk", "dv")}
+        want = {n: np.zeros((bag.total_tokens, bag.d)) for n in got}
+        for s in range(len(bag.seq_lens)):
+            rows = slice(cu[s], cu[s + 1])
+            if rows.start == rows.stop:
+                continue
+            q, k, v, dout = (run.host(n, rows, h) for n in ("q", "k", "v", "dout"))
+            for n, ref in zip(("dq", "dk", "dv"), A.attn_bwd_dense(q, k, v, dout, bag.scale, causal)):
+                want[n][rows], got[n][rows] = ref, run.host(n, rows, h)
+                # no sequence is hidden behind the others' size; single rows have dq = dk = 0 up to rounding
+                if rows.stop - rows.start > 8:
+                    assert rel_fro(run.host(n, rows, h), ref) <= 2 * BAR, (n, h, s)
+        for n in got:
+            worst = max(worst, rel_fro(got[n], want[n]))
+    say(f"[small] {bag.name} d={bag.d} causal={causal}: worst rel={worst:.3e}")
+    assert worst <= BAR
+    return run
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens,H", [
+    ([1, 31, 32, 33, 63, 64, 65, 0, 95, 97, 127, 128, 129, 191, 193, 255], 2),     # edges of the 32- and 64-row blocks and steps
+    ([1537], 3), ([700, 333, 5], 4)])
+def test_small_backward(lens, H, d, causal):
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    assert Q.bwd_small(lens, H, d, causal)
+    run = _compare(BagSpec("small", lens, H=H, d=d, seed=9500 + H + d), causal, range(H))
+    # the same bits with a workspace that holds anything
+    a, x = run.attn, run.dev
+    a.workspace.fill_(0xff)
+    for t in (a.dq, a.dk, a.dv):
+        t.fill_(float("nan"))
+    a.backward(x["q"], x["k"], x["v"], x["dout"])
+    torch.cuda.synchronize()
+    for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+        assert np.array_equal(bf16_device_to_bits(got), want)
+
+
+@pytest.mark.parametrize("d,lens,H,causal", [
+    (128, [129] * 30, 4, True), (64, [129] * 30, 6, True),               # more items than workgroups: several draws
+    (128, [1, 200] * 5, 12, False), (64, [1, 129, 129, 65], 44, False)])    # sequences that the average makes look shorter
+def test_small_backward_draws(d, lens, H, causal):
+    w = Q.walk_small(lens, H, d)
+    assert Q.bwd_small(lens, H, d, causal) and w.draws and w.most > w.per
+    _compare(BagSpec("small_draws", lens, H=H, d=d, seed=9600 + H + d), causal, [0, H // 2, H - 1])
+
+
+@pytest.mark.parametrize("d,lens,H,causal", [(128, [700, 450], 14, False), (64, [700, 450], 21, False),
+                                             # empty sequences, which the host's rule counts as tiles
+                                             (128, [1537] + [0] * 40, 7, True), (64, [1537] + [0] * 40, 11, True)])
+def test_128_row_items_with_every_query_tile_in_parts(d, lens, H, causal):
+    w = Q.walk_joint(lens, H, d, causal)
+    assert Q.bwd_joint(lens, H, d, causal) and not Q.bwd_small(lens, H, d, causal)
+    assert w.parts == w.items * (4 if causal else 2) and not w.draws
+    _compare(BagSpec("joint_parts", lens, H=H, d=d, seed=9700 + H + d), causal, [0, H // 2, H - 1])

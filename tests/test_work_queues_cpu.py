@@ -78,6 +78,21 @@ def test_every_item_of_the_unmasked_forward_once():
     assert min(seen.values()) > 100, seen
 
 
+def test_every_item_of_the_small_backward_once():
+    """Tiles of 64 rows of both kinds; random bags and grids, drawn and not.  Where the rule takes it, one launch is the rule as well."""
+    rng = random.Random(99)
+    seen = {False: 0, True: 0}
+    for _ in range(1500):
+        lens, H, d = _random_bag(rng), rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128))
+        cus = rng.choice((256, 256, 256, 304, 80, 37))
+        w = Q.walk_small(lens, H, d, cus)
+        assert w.wrong == 0 and w.parts == 0, (lens, H, d, cus, w)
+        seen[w.draws] += 1
+        for causal in (False, True):
+            assert not Q.bwd_small(lens, H, d, causal, cus) or Q.bwd_joint(lens, H, d, causal, cus), (lens, H, d, causal)
+    assert min(seen.values()) > 100, seen
+
+
 @pytest.mark.parametrize("start", [0, (1 << 32) - 20000])
 def test_counter_sets_are_cleared_between_two_uses_far_from_either(start):
     """Eager forward calls: between two calls that draw from one set some call clears it, and calls that touch a set (draw from
