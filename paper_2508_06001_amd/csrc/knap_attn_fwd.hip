@@ -1,14 +1,9 @@
-// Forward kernel: out = softmax(scale q k^T) v per (sequence, head) of a packed
-// bag, with the row log-sum-exp (Sec. 3.4 / the attention listing of Sec. 3.5:
-// full bidirectional attention inside each sequence, none across sequences).
-// CAUSAL is the other mask the paper admits inside a datum (Limitations
-// paragraph): query i sees keys 0..i of its own sequence.
+// Forward kernel under the causal mask: out = softmax(scale q k^T) v per (sequence, head) of a packed bag, with the row log-sum-exp.
+// It is the other mask the paper admits inside a datum (Limitations paragraph): query i sees keys 0..i of its own sequence.
 //
-// One persistent workgroup (4 waves) takes work items (sequence, head, 128-row
-// query tile) from the longest-first schedule.  Wave w owns 32 query rows and
-// streams the sequence's keys and values through LDS in tiles of 64 rows; the
-// next tile is copied global -> LDS asynchronously (no staging registers) into
-// the other buffer while the current one is used, behind one barrier per tile.
+// One persistent workgroup (4 waves) takes work items (sequence, head, pair of 128-row query tiles) from the longest-first schedule,
+// the long tile of a pair first.  Wave w owns 32 query rows and streams the sequence's keys and values through LDS in tiles of 64 rows
+// (fwd_tile() in knap_attn_fwd_part.h, which the forward without the mask shares).
 //
 // Orientation: the scores are computed transposed, S^T = K Q^T, so that in the
 // MFMA result layout a lane holds ONE query (column l % 32) and its registers
@@ -21,18 +16,16 @@
 // stands, and the row sums that come out of it decide whether the reference has to move: only when a
 // lane's 16 probabilities sum to more than 2^8 (the first half always does: the reference starts at
 // -inf), in which case the maximum is taken (of the tile, or of the half if it is the tile's second), the accumulators
-// are rescaled and P is formed again.  So no maximum is taken per tile (a fifth of the loop's vector instructions: 4.2 -> 3.4
-// per MFMA);
-// P <= 256 all the same, and the final division by the row sum removes the reference exactly as in
-// the textbook recurrence.  The row sum is taken over the bf16-rounded P that the MFMA multiplies, so the
-// effective weights of a row sum to one exactly (a one-hot row returns its v bit for bit); the stored
+// are rescaled and P is formed again.  So no maximum is taken per tile; P <= 256 all the same, and the final division by the row sum
+// removes the reference exactly as in the textbook recurrence.  The row sum is taken over the bf16-rounded P that the MFMA multiplies, so
+// the effective weights of a row sum to one exactly (a one-hot row returns its v bit for bit); the stored
 // log-sum-exp inherits at most a 2^-8 relative change of that sum.
 //
-// What bounds it: MFMA and softmax arithmetic share the issue slots, at the clock the power limit leaves.
-// The arithmetic of a half therefore runs in the slot of the next half's MFMAs, and an item's first loads
-// go out under the previous item's epilogue.  Measured at 24 heads of 128 when both came in
-// (before -> after, us): 32 sequences of 256..648 tokens 172 -> 144, one of 4292 tokens 305 -> 283, 17 of 328..4533 tokens
-// 1104 -> 1040, one of 65536 and 200 short ones 47500 -> 46600.  Now: 136, 254, 1025 and 45500.
+// What bounds it: MFMA and softmax arithmetic share the issue slots, at the clock the power limit leaves.  Three halves of 32 keys are in
+// work at a time, and the waves whose queries precede the whole last tile leave its turn to the others.  A half's arithmetic between
+// its own two products -> this, forward in us, 24 x 128: 17 sequences of 328..4533 tokens 602 -> 583, 14 of 406..14415 3315 -> 3202, 2 of up to
+// 4173 258 -> 246, 32 of 450 110 -> 108; 6 x 128, one of 8000 141 -> 133; 12 x 64, one of 8000 144 -> 138, of 30000 1578 -> 1548, but 32 of 450
+// 30.9 -> 32.2; 80 bags 1.019 in the geometric mean.  With those waves in the last turn as well: 1.011.
 #include "knap_attn_fwd_part.h"
 
 namespace knap {
@@ -95,28 +88,33 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_causal_ker
   auto q_tile_of = [&]() {
     return sub == 0 ? (it.len + C::BM - 1) / C::BM - 1 - it.tile : it.tile;
   };
-  // asynchronous copy of tile t (keys 64 t ..) of the item; rows at or past kv_end arrive as zeros
-  auto load_tile = [&](int t, int kv_end, __bf16* dK, __bf16* dV) {
-    const int kv0 = t * C::BN;
+  // asynchronous copy of this wave's share of tile t (keys 64 t ..) of K or V; rows past the last that the query tile sees arrive as zeros
+  auto copy_rows = [&](const __bf16* __restrict__ src, int t, __bf16* dst) __attribute__((always_inline)) {
+    const int kv0 = t * C::BN, kv_end = min(it.len, (q_tile_of() + 1) * C::BM);
     const uint32_t bytes = (uint32_t)max(0, min(kv_end - kv0, C::BN)) * row_bytes;
-    const size_t off = (size_t)(it.row0 + kv0) * row_stride + (size_t)it.head * D;
-    tile_load_async<D>(dK, make_rsrc(k + off, bytes), row_bytes, C::BN, wave, lane);
-    tile_load_async<D>(dV, make_rsrc(v + off, bytes), row_bytes, C::BN, wave, lane);
+    tile_load_async<D>(dst, make_rsrc(src + (size_t)(it.row0 + kv0) * row_stride + (size_t)it.head * D, bytes), row_bytes, C::BN, wave, lane);
   };
   const uint32_t q_off = (uint32_t)(wave * 32 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
-  // what an item needs before its first product: tile 0 and the query rows (rows past the end read as zero)
-  auto load_first = [&]() {
+  // what a query tile needs before its first product, the keys of tile 0 and the query rows (rows past the end read as zero), and
+  // behind it what its first turn of the loop reads: the values of tile 0 and the keys of tile 1
+  auto load_first = [&]() __attribute__((always_inline)) {
     const int q0 = q_tile_of() * C::BM;
-    load_tile(0, min(it.len, q0 + C::BM), sK0, sV0);
+    copy_rows(k, 0, sK0);
     const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
                               (uint32_t)min(it.len - q0, C::BM) * row_bytes);
 #pragma unroll
     for (int cc = 0; cc < C::KC; ++cc) qf[cc] = __builtin_bit_cast(bf16x8, buffer_load16(rq, q_off + 32u * cc));
+    KNAP_SCHED_FENCE();
+    copy_rows(v, 0, sV0);
+    copy_rows(k, 1, sK1);
+    KNAP_SCHED_FENCE();
   };
+  constexpr int COPIES = C::BN * D / 2048;      // copies of a wave's share of a tile
+  const FwdLds lds = {sK0, sK1, sV0, sV1};
   if (ticket < queue.wide) {
   it = take(ticket);
   load_first();
-  wait_async_loads();
+  wait_vm<2 * COPIES>();
   lds_barrier();
 
   for (;;) {
@@ -127,114 +125,29 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_causal_ker
     // keys this query tile sees at all
     const int kv_end = min(L, q0 + C::BM);
     const int n_tiles = (kv_end + C::BN - 1) / C::BN;
-    // the last pair of tiles of the item's second query tile
-    const int t_draw = queue.draws && !(sub == 0 && it.tile != q_tile) ? (n_tiles - 1) & ~1 : -1;
-
+    // the next ticket is drawn in the last turn of the item's second query tile
+    const bool draws = queue.draws && !(sub == 0 && it.tile != q_tile);
+    // From tile 2 q_tile on some key of this item's queries is masked: after a query (which covers the ragged end for the rows of the
+    // sequence).
     f32x16 o[C::DB];
-#pragma unroll
-    for (int db = 0; db < C::DB; ++db) o[db] = zero16();
-    float m_ref = -INFINITY;   // exponent reference (raw score units)
-    float mc = -INFINITY;      // m_ref * c
-    float l_run = 0.f;         // this lane's share of the row sum (its 32 of the 64 keys per tile)
+    float m_ref, l_run;
+    fwd_tile<D, true>(lds, qf, k_rows, v_cols, c, n_tiles, min(n_tiles, (q0 + 32 * wave + 31) / C::BN + 1), 2 * q_tile, q_row + 1, hh,
+                [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(k, t, dst); },
+                [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(v, t, dst); },
+                [&] { if (draws && tid == 0) next_ticket = atomicAdd(queue.ctr, 1u); }, o, m_ref, l_run);
 
-    // the first tile in which some key of this item's queries is masked: after a query (which covers the ragged end for the
-    // rows of the sequence)
-    const int first_masked = 2 * q_tile;
-    const int kv_lim = q_row + 1;
-
-    // One tile: 64 keys as two halves of 32.  A wave whose 32 queries all precede the tile's first key has
-    // nothing to do in it.
-    auto process_tile = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
-      load_tile(t + 1, kv_end, nK, nV);
-      const bool masked = t >= first_masked;
-      if (t * C::BN <= q0 + 32 * wave + 31) {
-
-      bf16x8 ak0[C::KC], ak1[C::KC];
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) ak0[cc] = k_rows.get(tK, 0, cc);
-      KNAP_SCHED_FENCE();
-
-      f32x16 s0 = zero16(), s1 = zero16();
-      // slot 1: S^T of keys 0..31 | K fragments of keys 32..63
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) s0 = mfma32(ak0[cc], qf[cc], s0);
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) ak1[cc] = k_rows.get(tK, 32, cc);
-#pragma unroll
-      for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); }
-      KNAP_SCHED_FENCE();
-
-      if (masked) mask_half(s0, kv_lim - t * C::BN, hh);
-      KNAP_SCHED_FENCE();
-      // slot 2: S^T of keys 32..63 | P^T of keys 0..31, V^T fragments of keys 0..15
-      bf16x8 vt0[2][C::DB], vt1[2][C::DB];
-      bf16x8 pb0[2], pb1[2];
-      float l0 = l_run;
-#pragma unroll
-      for (int cc = 0; cc < C::KC; ++cc) s1 = mfma32(ak1[cc], qf[cc], s1);
-      half_exps(s0, c, mc, pb0, l0);
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) vt0[0][db] = v_cols.get(tV, 0, db);
-#pragma unroll
-      for (int i = 0; i < C::KC; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 1); KNAP_SGB(KNAP_SG_VALU, 48 / C::KC); }
-      KNAP_SCHED_FENCE();
-      half_settle<C::DB>(s0, c, [&] { return fmaxf(half_max(s0, C::BN, hh), half_max(s1, kv_lim - t * C::BN - 32, hh)); }, pb0, l0, m_ref, mc, l_run, o);
-      if (masked) mask_half(s1, kv_lim - t * C::BN - 32, hh);
-      KNAP_SCHED_FENCE();
-
-      // slot 3: O^T += V^T P^T over keys 0..31 | P^T of keys 32..63, V^T fragments of keys 16..47
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) vt0[1][db] = v_cols.get(tV, 16, db);
-#pragma unroll
-      for (int ck = 0; ck < 2; ++ck)
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db) o[db] = mfma32(vt0[ck][db], pb0[ck], o[db]);
-      float l1 = l_run;
-      half_exps(s1, c, mc, pb1, l1);
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) vt1[0][db] = v_cols.get(tV, 32, db);
-#pragma unroll
-      for (int i = 0; i < 2 * C::DB; ++i) { KNAP_SGB(KNAP_SG_DS_READ, 2); KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_VALU, 24 / C::DB); }
-      KNAP_SCHED_FENCE();
-      half_settle<C::DB>(s1, c, [&] { return half_max(s1, C::BN, hh); }, pb1, l1, m_ref, mc, l_run, o);
-      KNAP_SCHED_FENCE();
-
-      // slot 4: O^T += V^T P^T over keys 32..63 | V^T fragments of keys 48..63
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) vt1[1][db] = v_cols.get(tV, 48, db);
-#pragma unroll
-      for (int ck = 0; ck < 2; ++ck)
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db) o[db] = mfma32(vt1[ck][db], pb1[ck], o[db]);
-#pragma unroll
-      for (int i = 0; i < C::DB; ++i) { KNAP_SGB(KNAP_SG_DS_READ, 2); KNAP_SGB(KNAP_SG_MFMA, 1); }
-      KNAP_SCHED_FENCE();
-      }
-      wait_async_loads();
-      __syncthreads();     // next tile visible; this tile no longer read
-    };
-
-    for (int t = 0; t < n_tiles; t += 2) {
-      if (t == t_draw && tid == 0) next_ticket = atomicAdd(queue.ctr, 1u);
-      process_tile(t, sK0, sV0, sK1, sV1);
-      if (t + 1 < n_tiles) process_tile(t + 1, sK1, sV1, sK0, sV0);
-    }
-
-    // The next item's first loads go out before this one's results are stored, so that they travel under
-    // the epilogue; both tile buffers are free (the last tile ended with a barrier).
+    // The next item's first loads go out before this one's results are stored, so that they travel under the epilogue.
     const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D,
                               (uint32_t)min(L - q0, C::BM) * row_bytes);
     const auto rl = make_rsrc(lse + (size_t)it.head * T + it.row0 + q0, (uint32_t)min(L - q0, C::BM) * 4u);
     bool more = true;
+    if (draws && tid == 0) s_ticket = drawn_ticket(queue, next_ticket);   // every wave read the old one many barriers ago
+    lds_barrier();          // nobody reads a tile any longer
     if (sub == 0 && it.tile != q_tile) {   // not the middle tile of an odd count
       sub = 1;
     } else if (!queue.draws) {
       more = false;
     } else {
-      if (tid == 0) {
-        s_ticket = drawn_ticket(queue, next_ticket);   // every wave read the old one many barriers ago
-      }
-      lds_barrier();
       ticket = __builtin_amdgcn_readfirstlane(s_ticket);
       more = ticket < queue.wide;
       if (more) it = take(ticket);
@@ -251,8 +164,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_causal_ker
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) store_block(ro, q_off + 64u * db, o[db], inv);
     if (!more) break;
-    // the loads have landed: all but the 2 DB stores of the output, which are younger (in-order completion)
-    wait_vm<2 * C::DB>();
+    // the keys and the query rows have landed: all but the copies behind them and the stores, which are younger (in-order completion)
+    wait_vm<2 * COPIES + 1 + 2 * C::DB>();
     lds_barrier();
   }
   }
@@ -262,7 +175,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_causal_ker
   // the length 145 us, alone 67).
   if (queue.parts > 0) lds_barrier();     // every wave has the ticket before the next one is put down
   const FwdPtrs g = {q, k, v, out, lse, T, H, scale};
-  const FwdLds lds = {sK0, sK1, sV0, sV1};
   for (int part = ticket - queue.wide; part >= 0 && part < queue.parts;) {
     it = take(queue.item_of_part(part));
     const int q_tiles = (it.len + C::BM - 1) / C::BM;

@@ -438,11 +438,7 @@ pairs_of_items:
   }
   }
 
-  // Single items: 128 queries, 32 per wave.  Three halves of 32 keys that follow each other are in work at a time, in one slot of the
-  // pipeline: the scores of the last one, the probabilities of the middle one, the product with the values of the first one.  No
-  // MFMA of a slot waits for its arithmetic, nor the other way round.  Against a loop in which a half's arithmetic stood between its
-  // two products, us: 32 of 256..648 tokens 138 -> 133, one of 4292 259 -> 247, 20 of 1536 610 -> 571, 8 of 1024 119 -> 109, 64 of 450
-  // 263 -> 252 (24 x 128), the same bits.
+  // Single items: 128 queries, 32 per wave (fwd_tile).
   if (single < 0 && ticket >= pairs && ticket < singles && whole < 0) single = ticket + pairs;
   if (single >= 0) {
     lds_barrier();            // every wave has the ticket; nobody reads a tile any longer
@@ -489,152 +485,9 @@ pairs_of_items:
       // the next ticket is drawn in the last turn of the loop
       auto draw = [&] { if (draws && other < 0 && tid == 0) next_ticket = atomicAdd(queue.ctr, 1u); };
       f32x16 o[DB];
-#pragma unroll
-      for (int db = 0; db < DB; ++db) o[db] = zero16();
-      float m_ref = -INFINITY;   // exponent reference (raw score units)
-      float mc = -INFINITY;      // m_ref * c
-      float l_run = 0.f;         // this lane's share of the row sum (its 32 of the 64 keys per tile)
-      bf16x8 ak[KC];
-      // One slot: the scores sn of a half (QK: its keys in `ak`), the probabilities pn of the half before (of scores s), the product of
-      // the one before that (PV: its probabilities pb, its values at tV).  Cut into as many groups as it has MFMAs, fences between
-      // them, so that the order below is the order issued; `behind(i)` goes into the groups of the second product.
-      auto slot = [&](auto qk_tag, auto pv_tag, auto lead_tag, const f32x16& s, f32x16& sn, const bf16x8 (&pb)[2], bf16x8 (&pn)[2],
-                      const __bf16* tV, float& l, auto behind) __attribute__((always_inline)) {
-        constexpr bool QK = decltype(qk_tag)::value, PV = decltype(pv_tag)::value;
-        constexpr int LEAD = decltype(lead_tag)::value;          // probabilities in front of the first MFMA
-        constexpr int GROUPS = (QK ? KC : 0) + (PV ? 2 * DB : 0), PER = (16 + GROUPS - 1) / GROUPS;
-        float p[16];
-        uint32_t w[2][4];
-        auto form = [&](int r) __attribute__((always_inline)) {          // probability r, and the pair that is complete
-          if (r < 16) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mc));
-          if (r >= 3 && (r & 1)) {
-            const int j = (r - 3) >> 1;      // pair j: registers 2 j and 2 j + 1
-            bf16x2 x;
-            x[0] = (__bf16)p[2 * j];
-            x[1] = (__bf16)p[2 * j + 1];
-            l = __builtin_amdgcn_fdot2_f32_bf16(x, ones, l, false);
-            w[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, x);
-          }
-        };
-#pragma unroll
-        for (int r = 0; r < LEAD; ++r) form(r);
-        KNAP_SCHED_FENCE();
-        bf16x8 vt[2][DB];
-        if constexpr (PV && !QK) {
-#pragma unroll
-          for (int i = 0; i < 2 * DB; ++i) vt[i / DB][i % DB] = v_cols.get(tV, 16 * (i / DB), i % DB);
-          KNAP_SCHED_FENCE();
-        }
-        int r = LEAD;
-        if constexpr (QK) {
-#pragma unroll
-          for (int i = 0; i < KC; ++i) {
-            sn = mfma32(ak[i], qs[i], i == 0 ? zero16() : sn);
-            if constexpr (PV) vt[i / DB][i % DB] = v_cols.get(tV, 16 * (i / DB), i % DB);
-#pragma unroll
-            for (int e = 0; e < PER; ++e) form(r++);
-            KNAP_SCHED_FENCE();
-          }
-        }
-        if constexpr (PV) {
-#pragma unroll
-          for (int i = 0; i < 2 * DB; ++i) {
-            o[i % DB] = mfma32(vt[i / DB][i % DB], pb[i / DB], o[i % DB]);
-            behind(i);
-#pragma unroll
-            for (int e = 0; e < PER; ++e) { if (r < 18) form(r); ++r; }
-            KNAP_SCHED_FENCE();
-          }
-        }
-        for (; r < 18; ++r) form(r);
-#pragma unroll
-        for (int ck = 0; ck < 2; ++ck) {
-          u32x4 x;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = w[ck][e];
-          pn[ck] = __builtin_bit_cast(bf16x8, x);
-        }
-      };
-      constexpr std::true_type yes{};
-      constexpr std::false_type no{};
-      constexpr std::integral_constant<int, 0> at_once{};
-      constexpr std::integral_constant<int, 4> some{};
-      f32x16 s0, s1;            // scores of a tile's first and second half
-      bf16x8 pb0[2], pb1[2];    // their probabilities
-      auto keys_of = [&](const __bf16* tK, int row) __attribute__((always_inline)) {
-#pragma unroll
-        for (int cc = 0; cc < KC; ++cc) ak[cc] = k_rows.get(tK, row, cc);
-      };
-      auto nothing = [](int) {};
-      auto mask_first = [&](int t) __attribute__((always_inline)) {
-        if (t >= first_masked) mask_half(s0, L - t * C::BN, hh);
-        KNAP_SCHED_FENCE();
-      };
-      auto settle_first = [&](int t, float l) __attribute__((always_inline)) {
-        half_settle<DB>(s0, c, [&] { return fmaxf(half_max(s0, C::BN, hh), half_max(s1, L - t * C::BN - 32, hh)); }, pb0, l, m_ref, mc, l_run, o);
-        KNAP_SCHED_FENCE();
-      };
-      auto mask_second = [&](int t) __attribute__((always_inline)) {
-        if (t >= first_masked) mask_half(s1, L - t * C::BN - 32, hh);
-        KNAP_SCHED_FENCE();
-      };
-      auto settle_second = [&](float l) __attribute__((always_inline)) {
-        half_settle<DB>(s1, c, [&] { return half_max(s1, C::BN, hh); }, pb1, l, m_ref, mc, l_run, o);
-        KNAP_SCHED_FENCE();
-      };
-      // One turn: the second half of tile t and the first of tile t + 1 go through the softmax.  Behind its barrier the keys of tile
-      // t + 1 and the values of tile t are there, and nobody reads the keys of tile t or the values before it any longer.
-      auto turn = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) __attribute__((always_inline)) {
-        wait_async_loads();
-        lds_barrier();
-        if (t == n_tiles - 2) draw();
-        keys_of(tK, 0);
-        copy_rows(k, t + 2, nK);
-        copy_rows(v, t + 1, nV);
-        mask_second(t);
-        float l = l_run;
-        slot(yes, yes, some, s1, s0, pb0, pb1, tV, l, [&](int i) __attribute__((always_inline)) { if (i < KC) ak[i] = k_rows.get(tK, 32, i); });
-        settle_second(l);
-        mask_first(t + 1);
-        l = l_run;
-        slot(yes, yes, at_once, s0, s1, pb1, pb0, tV + 32 * Tile<D>::LD, l, nothing);
-        settle_first(t + 1, l);
-      };
-      keys_of(sK0, 0);
-#pragma unroll
-      for (int cc = 0; cc < KC; ++cc) s0 = mfma32(ak[cc], qs[cc], cc == 0 ? zero16() : s0);
-      keys_of(sK0, 32);
-      KNAP_SCHED_FENCE();
-      if (n_tiles == 1) draw();
-      {
-        mask_first(0);
-        float l = l_run;
-        slot(yes, no, at_once, s0, s1, pb1, pb0, sV0, l, nothing);
-        settle_first(0, l);
-      }
-      for (int t = 0; t < n_tiles - 1; t += 2) {
-        turn(t, sK1, sV0, sK0, sV1);
-        if (t + 2 < n_tiles) turn(t + 1, sK0, sV1, sK1, sV0);
-      }
-      wait_async_loads();
-      lds_barrier();
-      {       // the last tile's second half
-        const __bf16* tV = (n_tiles & 1) ? sV0 : sV1;
-        mask_second(n_tiles - 1);
-        float l = l_run;
-        slot(no, yes, at_once, s1, s0, pb0, pb1, tV, l, nothing);
-        settle_second(l);
-        bf16x8 vt[2][DB];
-#pragma unroll
-        for (int ck = 0; ck < 2; ++ck)
-#pragma unroll
-          for (int db = 0; db < DB; ++db) vt[ck][db] = v_cols.get(tV, 32 + 16 * ck, db);
-#pragma unroll
-        for (int ck = 0; ck < 2; ++ck)
-#pragma unroll
-          for (int db = 0; db < DB; ++db) o[db] = mfma32(vt[ck][db], pb1[ck], o[db]);
-        KNAP_SCHED_FENCE();
-      }
+      float m_ref, l_run;
+      fwd_tile<D, false>(lds, qs, k_rows, v_cols, c, n_tiles, n_tiles, first_masked, L, hh, [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(k, t, dst); },
+                  [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(v, t, dst); }, draw, o, m_ref, l_run);
       const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D, (uint32_t)min(L - q0, 128) * row_bytes);
       const auto rl = make_rsrc(lse + (size_t)it.head * T + it.row0 + q0, (uint32_t)min(L - q0, 128) * 4u);
       if (draws && other < 0 && tid == 0) s_ticket = drawn_next(next_ticket);     // every wave read the old one many barriers ago

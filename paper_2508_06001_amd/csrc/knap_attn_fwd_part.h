@@ -1,8 +1,10 @@
-// Pieces of the forward that its kernels share: the softmax of half a tile (32 keys), and the narrow items.
+// Pieces of the forward that its kernels share: the softmax of half a tile (32 keys), the query tiles of 128 rows, and the narrow items.
 #pragma once
 
 #include "knap_device.h"
 #include "knap_kernels.h"
+
+#include <type_traits>
 
 namespace knap {
 
@@ -79,6 +81,181 @@ __device__ __forceinline__ void half_settle(const f32x16& s, float c, Maximum ma
     if (m_new == -INFINITY) mc = -INFINITY;   // scores of -inf alone set no reference: the next half has to settle too
   }
   l_run = l_new;
+}
+
+// The loop over the keys of a query tile of 128 rows, 32 per wave.  Three halves of 32 keys that follow each other are in work at a time, in
+// one slot of the pipeline: the scores of the last one, the probabilities of the middle one, the product with the values of the first one.
+// No MFMA of a slot waits for its arithmetic, nor the other way round.  Against a loop in which a half's arithmetic stood between its two
+// products, without the mask, us: 32 of 256..648 tokens 138 -> 133, one of 4292 259 -> 247, 20 of 1536 610 -> 571, 8 of 1024 119 -> 109, 64 of 450
+// 263 -> 252 (24 x 128), the same bits.  Results: o, its reference and this lane's share of the row sum (its 32 of the 64
+// keys per tile).  kv_lim: the first key that this lane's query does not see, in tiles from first_masked on.  copy_k(t, to) and copy_v
+// copy this wave's share of tile t; n_own: the tiles that this wave's queries see (wave-uniform; under the mask one less than n_tiles for
+// half of the waves, which leave the last turn to the others).  The keys of tile 0 have landed, the values of tile 0 and the keys of tile 1 are on their way.
+// draw() is called in the last turn.  A barrier has to stand behind it in front of whatever fills the tiles.
+template <int D, bool CAUSAL, class CopyK, class CopyV, class Draw>
+__device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D / 16], const RowReader<D>& k_rows, const ColReader<D>& v_cols, float c,
+                                         int n_tiles, int n_own, int first_masked, int kv_lim, int hh, CopyK copy_k, CopyV copy_v, Draw draw,
+                                         f32x16 (&o)[D / 32], float& m_ref, float& l_run) {
+  using C = FwdCfg<D>;
+  constexpr int KC = C::KC, DB = C::DB;
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = zero16();
+  m_ref = -INFINITY;         // exponent reference (raw score units)
+  float mc = -INFINITY;      // m_ref * c
+  l_run = 0.f;
+  bf16x2 ones;
+  ones[0] = (__bf16)1.0f;
+  ones[1] = (__bf16)1.0f;
+  bf16x8 ak[KC];
+  // One slot: the scores sn of a half (QK: its keys in `ak`), the probabilities pn of the half before (of scores s), the product of
+  // the one before that (PV: its probabilities pb, its values at tV).  Cut into as many groups as it has MFMAs, fences between
+  // them, so that the order below is the order issued; `behind(i)` goes into the groups of the second product.
+  auto slot = [&](auto qk_tag, auto pv_tag, auto lead_tag, const f32x16& s, f32x16& sn, const bf16x8 (&pb)[2], bf16x8 (&pn)[2],
+                  const __bf16* tV, float& l, auto behind) __attribute__((always_inline)) {
+    constexpr bool QK = decltype(qk_tag)::value, PV = decltype(pv_tag)::value;
+    constexpr int LEAD = decltype(lead_tag)::value;          // probabilities in front of the first MFMA
+    constexpr int GROUPS = (QK ? KC : 0) + (PV ? 2 * DB : 0), PER = (16 + GROUPS - 1) / GROUPS;
+    float p[16];
+    uint32_t w[2][4];
+    auto form = [&](int r) __attribute__((always_inline)) {          // probability r, and the pair that is complete
+      if (r < 16) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mc));
+      if (r >= 3 && (r & 1)) {
+        const int j = (r - 3) >> 1;      // pair j: registers 2 j and 2 j + 1
+        bf16x2 x;
+        x[0] = (__bf16)p[2 * j];
+        x[1] = (__bf16)p[2 * j + 1];
+        l = __builtin_amdgcn_fdot2_f32_bf16(x, ones, l, false);
+        w[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, x);
+      }
+    };
+#pragma unroll
+    for (int r = 0; r < LEAD; ++r) form(r);
+    KNAP_SCHED_FENCE();
+    bf16x8 vt[2][DB];
+    if constexpr (PV && !QK) {
+#pragma unroll
+      for (int i = 0; i < 2 * DB; ++i) vt[i / DB][i % DB] = v_cols.get(tV, 16 * (i / DB), i % DB);
+      KNAP_SCHED_FENCE();
+    }
+    int r = LEAD;
+    if constexpr (QK) {
+#pragma unroll
+      for (int i = 0; i < KC; ++i) {
+        sn = mfma32(ak[i], qs[i], i == 0 ? zero16() : sn);
+        if constexpr (PV) vt[i / DB][i % DB] = v_cols.get(tV, 16 * (i / DB), i % DB);
+#pragma unroll
+        for (int e = 0; e < PER; ++e) form(r++);
+        KNAP_SCHED_FENCE();
+      }
+    }
+    if constexpr (PV) {
+#pragma unroll
+      for (int i = 0; i < 2 * DB; ++i) {
+        o[i % DB] = mfma32(vt[i / DB][i % DB], pb[i / DB], o[i % DB]);
+        behind(i);
+#pragma unroll
+        for (int e = 0; e < PER; ++e) { if (r < 18) form(r); ++r; }
+        KNAP_SCHED_FENCE();
+      }
+    }
+    for (; r < 18; ++r) form(r);
+#pragma unroll
+    for (int ck = 0; ck < 2; ++ck) {
+      u32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = w[ck][e];
+      pn[ck] = __builtin_bit_cast(bf16x8, x);
+    }
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  constexpr std::integral_constant<int, 0> at_once{};
+  constexpr std::integral_constant<int, 4> some{};
+  f32x16 s0, s1;            // scores of a tile's first and second half
+  bf16x8 pb0[2], pb1[2];    // their probabilities
+  auto keys_of = [&](const __bf16* tK, int row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int cc = 0; cc < KC; ++cc) ak[cc] = k_rows.get(tK, row, cc);
+  };
+  auto nothing = [](int) {};
+  auto mask_first = [&](int t) __attribute__((always_inline)) {
+    if (t >= first_masked) mask_half(s0, kv_lim - t * C::BN, hh);
+    KNAP_SCHED_FENCE();
+  };
+  auto settle_first = [&](int t, float l) __attribute__((always_inline)) {
+    half_settle<DB>(s0, c, [&] { return fmaxf(half_max(s0, C::BN, hh), half_max(s1, kv_lim - t * C::BN - 32, hh)); }, pb0, l, m_ref, mc, l_run, o);
+    KNAP_SCHED_FENCE();
+  };
+  auto mask_second = [&](int t) __attribute__((always_inline)) {
+    if (t >= first_masked) mask_half(s1, kv_lim - t * C::BN - 32, hh);
+    KNAP_SCHED_FENCE();
+  };
+  auto settle_second = [&](float l) __attribute__((always_inline)) {
+    half_settle<DB>(s1, c, [&] { return half_max(s1, C::BN, hh); }, pb1, l, m_ref, mc, l_run, o);
+    KNAP_SCHED_FENCE();
+  };
+  // One turn: the second half of tile t and the first of tile t + 1 go through the softmax.  Behind its barrier the keys of tile
+  // t + 1 and the values of tile t are there, and nobody reads the keys of tile t or the values before it any longer.
+  auto turn = [&](int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) __attribute__((always_inline)) {
+    wait_async_loads();
+    lds_barrier();
+    if (t == n_tiles - 2) draw();
+    keys_of(tK, 0);
+    copy_k(t + 2, nK);
+    copy_v(t + 1, nV);
+    mask_second(t);
+    float l = l_run;
+    slot(yes, yes, some, s1, s0, pb0, pb1, tV, l, [&](int i) __attribute__((always_inline)) { if (i < KC) ak[i] = k_rows.get(tK, 32, i); });
+    settle_second(l);
+    mask_first(t + 1);
+    l = l_run;
+    slot(yes, yes, at_once, s0, s1, pb1, pb0, tV + 32 * Tile<D>::LD, l, nothing);
+    settle_first(t + 1, l);
+  };
+  keys_of(lds.k0, 0);
+#pragma unroll
+  for (int cc = 0; cc < KC; ++cc) s0 = mfma32(ak[cc], qs[cc], cc == 0 ? zero16() : s0);
+  keys_of(lds.k0, 32);
+  KNAP_SCHED_FENCE();
+  if (n_tiles == 1) draw();
+  {
+    mask_first(0);
+    float l = l_run;
+    slot(yes, no, at_once, s0, s1, pb1, pb0, lds.v0, l, nothing);
+    settle_first(0, l);
+  }
+  for (int t = 0; t < n_own - 1; t += 2) {
+    turn(t, lds.k1, lds.v0, lds.k0, lds.v1);
+    if (t + 2 < n_own) turn(t + 1, lds.k0, lds.v1, lds.k1, lds.v0);
+  }
+  wait_async_loads();
+  lds_barrier();
+  const bool early = CAUSAL && n_own < n_tiles;
+  if (early) {              // the others' last turn: nothing but its copy
+    draw();
+    copy_v(n_own, (n_own & 1) ? lds.v1 : lds.v0);
+  }
+  {       // the last tile's second half
+    const __bf16* tV = (n_own & 1) ? lds.v0 : lds.v1;
+    mask_second(n_own - 1);
+    float l = l_run;
+    slot(no, yes, at_once, s1, s0, pb0, pb1, tV, l, nothing);
+    settle_second(l);
+    bf16x8 vt[2][DB];
+#pragma unroll
+    for (int ck = 0; ck < 2; ++ck)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) vt[ck][db] = v_cols.get(tV, 32 + 16 * ck, db);
+#pragma unroll
+    for (int ck = 0; ck < 2; ++ck)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) o[db] = mfma32(vt[ck][db], pb1[ck], o[db]);
+    KNAP_SCHED_FENCE();
+  }
+  if (early) {
+    wait_async_loads();
+    lds_barrier();
+  }
 }
 
 // 64 query rows of an item's sequence and head, from q0 on.  Waves w and w + 2 share 32 of them, one taking the first 32 keys of
