@@ -344,6 +344,10 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
       second_product(tQ, cb, 1, da[1], [&](int) {});
     };
 
+    // CAUSAL: a pair whose keys all come after a tile's queries (in the last two, four or six steps, the pairs behind the first) leaves the
+    // SIMDs to the other waves.  Backward, us, with the halves of tiles that dq_tile leaves out likewise: 32 sequences of 450 tokens, 24 x
+    // 128, 315 -> 309, 48 x 64, 334 -> 324; 17 of 328..4533 1902 -> 1886, 2038 -> 2013; 63 bags 1.008 in the geometric mean.
+    const int n_own = CAUSAL ? n_tiles - 2 * pair : n_tiles;
     // Each role runs its own copy of the loop over the steps: with the roles as branches inside one
     // loop the accumulators would be merged at every step's join, and the register allocator then keeps
     // two sets.  Every wave still executes the same sequence of copies, waits and barriers.
@@ -351,9 +355,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
     do {                                                                                      \
       issue_tile((t) + 1, sQ##nxt, sdO##nxt, sLse##nxt, sDelta##nxt);                  \
       if constexpr (ROLE == 0) {                                                              \
-        if ((t) < n_tiles) dv_step((t), sQ##cur, sdO##cur, sLse##cur);                        \
+        if ((t) < n_own) dv_step((t), sQ##cur, sdO##cur, sLse##cur);                          \
       } else {                                                                                \
-        if ((t) >= 1) dk_step((t) - 1, sQ##prev, sdO##prev, sDelta##prev);                    \
+        if ((t) >= 1 && (!CAUSAL || (t) <= n_own)) dk_step((t) - 1, sQ##prev, sdO##prev, sDelta##prev); \
       }                                                                                       \
       step_sync();                                                                            \
     } while (0)

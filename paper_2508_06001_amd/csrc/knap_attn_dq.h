@@ -146,7 +146,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     // the q and dO fragments and the dQ accumulator; the second wave of the SIMD fills the gaps).
     // Within a half the LDS reads are streamed a few MFMAs ahead of their use.
     // MODE 2: the tile crosses the causal diagonal; keys after this lane's query get dS = 0, and a wave
-    // whose 32 queries all precede the tile's first key has nothing to do in it.
+    // whose 32 queries all precede a half's first key has nothing to do in it.
     // MODE 1: the ragged last tile; the scores of keys past the end of the sequence start (and stay) at
     // -inf, so P = 0 and dS = 0 there.  Their K and V rows arrive as zeros: left at score 0, P would be
     // exp2(-LSE2), which overflows for a query whose scores are all far below zero, and the product of
@@ -155,9 +155,9 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
       constexpr int MODE = decltype(mode_tag)::value;
       constexpr bool DIAG = MODE == 2;
       load_tile(t + 1, nK, nV);
-      if (!(DIAG && t * C::BN > q0 + 32 * wave + 31)) {
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
+        if (DIAG && t * C::BN + 32 * half > q0 + 32 * wave + 31) break;
         f32x16 s = zero16(), dp = SEEDED ? dp_start : zero16();
         if constexpr (MODE == 1) {
           const int first_past = L - t * C::BN - 32 * half - 4 * hh;   // counted from this half's first key
@@ -197,7 +197,6 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
         for (int i = 0; i < C::DB; ++i) { KNAP_SGB(KNAP_SG_MFMA, 1); KNAP_SGB(KNAP_SG_DS_READ, 2); }
         KNAP_SGB(KNAP_SG_MFMA, C::DB);
         KNAP_SCHED_FENCE();
-      }
       }
       wait_async_loads();
       __syncthreads();     // next tile visible; this tile no longer read
