@@ -344,10 +344,11 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
       second_product(tQ, cb, 1, da[1], [&](int) {});
     };
 
-    // CAUSAL: a pair whose keys all come after a tile's queries (in the last two, four or six steps, the pairs behind the first) leaves the
-    // SIMDs to the other waves.  Backward, us, with the halves of tiles that dq_tile leaves out likewise: 32 sequences of 450 tokens, 24 x
-    // 128, 315 -> 309, 48 x 64, 334 -> 324; 17 of 328..4533 1902 -> 1886, 2038 -> 2013; 63 bags 1.008 in the geometric mean.
-    const int n_own = CAUSAL ? n_tiles - 2 * pair : n_tiles;
+    // Steps that a pair has part in: none where the sequence ends in front of its keys, and under the mask none of those whose queries all
+    // come before its keys (the last two, four or six, for the pairs behind the first); it leaves the SIMDs to the other waves.  Backward,
+    // us: 100 sequences of 290 tokens, 24 x 128, 658 -> 642, 32 of 256..648 400 -> 395; under the mask, with the halves of tiles that dq_tile leaves out
+    // likewise, 32 of 450 315 -> 309, 48 x 64, 334 -> 324, 17 of 328..4533 1902 -> 1886, 2038 -> 2013.
+    const int n_own = 64 * pair >= L - kv0 ? 0 : CAUSAL ? n_tiles - 2 * pair : n_tiles;
     // Each role runs its own copy of the loop over the steps: with the roles as branches inside one
     // loop the accumulators would be merged at every step's join, and the register allocator then keeps
     // two sets.  Every wave still executes the same sequence of copies, waits and barriers.
@@ -357,7 +358,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdPtrs& g, const DkdvLds& lds, 
       if constexpr (ROLE == 0) {                                                              \
         if ((t) < n_own) dv_step((t), sQ##cur, sdO##cur, sLse##cur);                          \
       } else {                                                                                \
-        if ((t) >= 1 && (!CAUSAL || (t) <= n_own)) dk_step((t) - 1, sQ##prev, sdO##prev, sDelta##prev); \
+        if ((t) >= 1 && (t) <= n_own) dk_step((t) - 1, sQ##prev, sdO##prev, sDelta##prev); \
       }                                                                                       \
       step_sync();                                                                            \
     } while (0)

@@ -89,8 +89,9 @@ __device__ __forceinline__ void half_settle(const f32x16& s, float c, Maximum ma
 // products, without the mask, us: 32 of 256..648 tokens 138 -> 133, one of 4292 259 -> 247, 20 of 1536 610 -> 571, 8 of 1024 119 -> 109, 64 of 450
 // 263 -> 252 (24 x 128), the same bits.  Results: o, its reference and this lane's share of the row sum (its 32 of the 64
 // keys per tile).  kv_lim: the first key that this lane's query does not see, in tiles from first_masked on.  copy_k(t, to) and copy_v
-// copy this wave's share of tile t; n_own: the tiles that this wave's queries see (wave-uniform; under the mask one less than n_tiles for
-// half of the waves, which leave the last turn to the others).  The keys of tile 0 have landed, the values of tile 0 and the keys of tile 1 are on their way.
+// copy this wave's share of tile t; n_own: the tiles that this wave's queries see (wave-uniform): under the mask one less than n_tiles for
+// half of the waves, which leave the last turn to the others, and none for a wave whose rows lie past the end of the sequence, which leaves
+// its SIMD to other workgroups (forward in us, 24 x 128: 100 of 290 tokens 216 -> 207, 32 of 256..648 130.5 -> 127, causal 102 -> 99).  The keys of tile 0 have landed, the values of tile 0 and the keys of tile 1 are on their way.
 // draw() is called in the last turn.  A barrier has to stand behind it in front of whatever fills the tiles.
 template <int D, bool CAUSAL, class CopyK, class CopyV, class Draw>
 __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D / 16], const RowReader<D>& k_rows, const ColReader<D>& v_cols, float c,
@@ -103,6 +104,17 @@ __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D
   m_ref = -INFINITY;         // exponent reference (raw score units)
   float mc = -INFINITY;      // m_ref * c
   l_run = 0.f;
+  if (n_own == 0) {         // no rows: nothing but this wave's copies
+    for (int t = 0; t < n_tiles - 1; ++t) {
+      wait_async_loads();
+      lds_barrier();
+      copy_k(t + 2, (t & 1) ? lds.k1 : lds.k0);
+      copy_v(t + 1, (t & 1) ? lds.v0 : lds.v1);
+    }
+    wait_async_loads();
+    lds_barrier();
+    return;
+  }
   bf16x2 ones;
   ones[0] = (__bf16)1.0f;
   ones[1] = (__bf16)1.0f;
