@@ -150,7 +150,9 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
     // MODE 1: the ragged last tile; the scores of keys past the end of the sequence start (and stay) at
     // -inf, so P = 0 and dS = 0 there.  Their K and V rows arrive as zeros: left at score 0, P would be
     // exp2(-LSE2), which overflows for a query whose scores are all far below zero, and the product of
-    // that dS with the zero K row would be NaN.
+    // that dS with the zero K row would be NaN.  A second half without keys is left out, in the kernel of query tiles alone (64 sequences of
+    // 450 tokens, 48 x 64, backward 827 -> 820 us, 32 of 24 x 128 404 -> 400; in the launch of both kinds it costs registers,
+    // and one of 16384, 6 x 128, 0.9 %).
     auto process_tile = [&](auto mode_tag, int t, const __bf16* tK, const __bf16* tV, __bf16* nK, __bf16* nV) {
       constexpr int MODE = decltype(mode_tag)::value;
       constexpr bool DIAG = MODE == 2;
@@ -158,6 +160,7 @@ __device__ __forceinline__ void dq_tile(const BwdPtrs& g, const DqLds& lds, cons
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         if (DIAG && t * C::BN + 32 * half > q0 + 32 * wave + 31) break;
+        if (MODE == 1 && DELTA && t * C::BN + 32 * half >= L) break;
         f32x16 s = zero16(), dp = SEEDED ? dp_start : zero16();
         if constexpr (MODE == 1) {
           const int first_past = L - t * C::BN - 32 * half - 4 * hh;   // counted from this half's first key

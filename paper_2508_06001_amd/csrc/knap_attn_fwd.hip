@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_causal_ker
     f32x16 o[C::DB];
     float m_ref, l_run;
     fwd_tile<D, true>(lds, qf, k_rows, v_cols, c, n_tiles,
-                q0 + 32 * wave < L ? min(n_tiles, (q0 + 32 * wave + 31) / C::BN + 1) : 0, 2 * q_tile, q_row + 1, hh,
+                q0 + 32 * wave < L ? min(n_tiles, (q0 + 32 * wave + 31) / C::BN + 1) : 0, (wave & 1) != 0, 2 * q_tile, q_row + 1, hh,
                 [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(k, t, dst); },
                 [&](int t, __bf16* dst) __attribute__((always_inline)) { copy_rows(v, t, dst); },
                 [&] { if (draws && tid == 0) next_ticket = atomicAdd(queue.ctr, 1u); }, o, m_ref, l_run);

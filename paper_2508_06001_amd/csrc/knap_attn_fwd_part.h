@@ -87,15 +87,20 @@ __device__ __forceinline__ void half_settle(const f32x16& s, float c, Maximum ma
 // one slot of the pipeline: the scores of the last one, the probabilities of the middle one, the product with the values of the first one.
 // No MFMA of a slot waits for its arithmetic, nor the other way round.  Against a loop in which a half's arithmetic stood between its two
 // products, without the mask, us: 32 of 256..648 tokens 138 -> 133, one of 4292 259 -> 247, 20 of 1536 610 -> 571, 8 of 1024 119 -> 109, 64 of 450
-// 263 -> 252 (24 x 128), the same bits.  Results: o, its reference and this lane's share of the row sum (its 32 of the 64
-// keys per tile).  kv_lim: the first key that this lane's query does not see, in tiles from first_masked on.  copy_k(t, to) and copy_v
-// copy this wave's share of tile t; n_own: the tiles that this wave's queries see (wave-uniform): under the mask one less than n_tiles for
-// half of the waves, which leave the last turn to the others, and none for a wave whose rows lie past the end of the sequence, which leaves
-// its SIMD to other workgroups (forward in us, 24 x 128: 100 of 290 tokens 216 -> 207, 32 of 256..648 130.5 -> 127, causal 102 -> 99).  The keys of tile 0 have landed, the values of tile 0 and the keys of tile 1 are on their way.
-// draw() is called in the last turn.  A barrier has to stand behind it in front of whatever fills the tiles.
+// 263 -> 252 (24 x 128), the same bits.
+//
+// Results: o, its reference and this lane's share of the row sum (its 32 of the 64 keys per tile).  kv_lim: the first key that this
+// lane's query does not see, in tiles from first_masked on.  copy_k(t, to) and copy_v copy this wave's share of tile t; the keys of tile 0
+// have landed, the values of tile 0 and the keys of tile 1 are on their way.  draw() is called in the last turn.  A barrier has to stand
+// behind it in front of whatever fills the tiles.
+//
+// n_own: the tiles that this wave's queries see (wave-uniform): under the mask one less than n_tiles for half of the waves, which leave
+// the last turn to the others, and none for a wave whose rows lie past the end of the sequence, which leaves its SIMD to other
+// workgroups (forward in us, 24 x 128: 100 of 290 tokens 216 -> 207, 32 of 256..648 130.5 -> 127, causal 102 -> 99).  last_half: whether
+// they see keys of the second half of the last of these (left out where not: 64 of 450, 48 x 64, 276 -> 271, causal 211 -> 207).
 template <int D, bool CAUSAL, class CopyK, class CopyV, class Draw>
 __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D / 16], const RowReader<D>& k_rows, const ColReader<D>& v_cols, float c,
-                                         int n_tiles, int n_own, int first_masked, int kv_lim, int hh, CopyK copy_k, CopyV copy_v, Draw draw,
+                                         int n_tiles, int n_own, bool last_half, int first_masked, int kv_lim, int hh, CopyK copy_k, CopyV copy_v, Draw draw,
                                          f32x16 (&o)[D / 32], float& m_ref, float& l_run) {
   using C = FwdCfg<D>;
   constexpr int KC = C::KC, DB = C::DB;
@@ -247,21 +252,25 @@ __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D
     draw();
     copy_v(n_own, (n_own & 1) ? lds.v1 : lds.v0);
   }
-  {       // the last tile's second half
-    const __bf16* tV = (n_own & 1) ? lds.v0 : lds.v1;
+  const __bf16* tV = (n_own & 1) ? lds.v0 : lds.v1;
+  if (last_half) {
     mask_second(n_own - 1);
     float l = l_run;
     slot(no, yes, at_once, s1, s0, pb0, pb1, tV, l, nothing);
     settle_second(l);
+  }
+  {       // the product of the last half with keys
+    const bf16x8 (&pb)[2] = last_half ? pb1 : pb0;
+    const int row = last_half ? 32 : 0;
     bf16x8 vt[2][DB];
 #pragma unroll
     for (int ck = 0; ck < 2; ++ck)
 #pragma unroll
-      for (int db = 0; db < DB; ++db) vt[ck][db] = v_cols.get(tV, 32 + 16 * ck, db);
+      for (int db = 0; db < DB; ++db) vt[ck][db] = v_cols.get(tV + row * Tile<D>::LD, 16 * ck, db);
 #pragma unroll
     for (int ck = 0; ck < 2; ++ck)
 #pragma unroll
-      for (int db = 0; db < DB; ++db) o[db] = mfma32(vt[ck][db], pb1[ck], o[db]);
+      for (int db = 0; db < DB; ++db) o[db] = mfma32(vt[ck][db], pb[ck], o[db]);
     KNAP_SCHED_FENCE();
   }
   if (early) {
