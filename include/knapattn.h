@@ -58,8 +58,9 @@ extern "C" {
  * in another order and against another softmax reference.  It follows from
  * the lengths and H alone, and may hold for some heads of a sequence only.
  *
- * Supported: d in {64, 128}; 0 <= n_seq <= KNAP_MAX_SEQS; H >= 1; scale positive
- * and finite; T < 2^31.
+ * Supported: d in {64, 128}; 0 <= n_seq <= KNAP_MAX_SEQS; H >= 1, H * d < 2^24 in
+ * the forward and 2^23 in the backward (the kernels count the bytes of 128 and of 256
+ * rows in 32 bits; not checked); scale positive and finite; T < 2^31.
  * n_seq == 0 succeeds and enqueues nothing.  With n_seq > 0 every pointer must be
  * non-null even if all sequences are empty (T = 0): the host cannot see T.
  * ------------------------------------------------------------------------ */

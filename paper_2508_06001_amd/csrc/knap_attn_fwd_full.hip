@@ -168,6 +168,9 @@ pairs_of_items:
   const int H_pairs = uniform_here(H), wave = uniform_here(wave_id);
   const size_t row_stride = (size_t)H_pairs * D;
   const uint32_t row_bytes = (uint32_t)(row_stride * sizeof(__bf16));
+  // This wave's 64 rows lie in the first or the second of the two tiles.  Descriptors of q and out cover one tile each, as those of
+  // the other forms: 256 rows of 65536 heads of 128 are 2^32 bytes.
+  const int own_tile = 128 * (wave >> 1), own_row = 64 * (wave & 1);
   RowReaderX<D> rows;
   ColReaderX<D> cols;
   const int ln = lane_id();
@@ -196,10 +199,10 @@ pairs_of_items:
   auto load_wide = [&]() __attribute__((always_inline)) {
     load_rows(k, 0, sK0);
     load_rows(v, 0, sV0);
-    const int q0 = it.tile * 128;
+    const int q0 = it.tile * 128 + own_tile;
     const int ln = lane_id(), l32 = ln & 31, hh = ln >> 5;
-    const uint32_t q_off = (uint32_t)(wave * 64 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
-    const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D, (uint32_t)min(it.len - q0, 128 * QB) * row_bytes);
+    const uint32_t q_off = (uint32_t)(own_row + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+    const auto rq = make_rsrc(q + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D, (uint32_t)min(it.len - q0, 128) * row_bytes);
 #pragma unroll
     for (int b = 0; b < QB; ++b)
 #pragma unroll
@@ -407,7 +410,7 @@ pairs_of_items:
       if (draws) ticket = __builtin_amdgcn_readfirstlane(s_ticket);
       break;
     }
-    const auto ro = make_rsrc(out + (size_t)(it.row0 + q0) * row_stride + (size_t)it.head * D, (uint32_t)min(L - q0, 128 * QB) * row_bytes);
+    const auto ro = make_rsrc(out + (size_t)(it.row0 + q0 + own_tile) * row_stride + (size_t)it.head * D, (uint32_t)min(L - q0 - own_tile, 128) * row_bytes);
     const auto rl = make_rsrc(lse + (size_t)it.head * T + it.row0 + q0, (uint32_t)min(L - q0, 128 * QB) * 4u);
     // the next item's first loads go out before this one's results are stored, so that they travel under the epilogue
     bool more = draws;
@@ -428,7 +431,7 @@ pairs_of_items:
     const int ln = lane_id(), l32 = ln & 31, hh = ln >> 5;
 #pragma unroll
     for (int b = 0; b < QB; ++b) {
-      const uint32_t q_off = (uint32_t)(wave * 64 + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
+      const uint32_t q_off = (uint32_t)(own_row + l32) * row_bytes + (uint32_t)(8 * hh) * 2u;
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, mc[b] * kLn2 + __logf(l[b])), rl, hh == 0 ? (wave * 64 + 32 * b + l32) * 4 : 4 * 128 * QB, 0, 0);
 #pragma unroll
       for (int db = 0; db < C::DB; ++db) store_block(ro, q_off + (uint32_t)(32 * b) * row_bytes + 64u * db, o[b][db], inv[b]);

@@ -59,3 +59,31 @@ def test_pairs_with_keys_far_above_the_first_64(d, power):
         big = tensors["k"][first:first + 3, ::2]
         big[(big & 0x7f80) != 0] += np.uint16(power << 7)
     _compare(GpuRun(bag, tensors=tensors, backward=False), d, False, 3e-3)
+
+
+@pytest.mark.parametrize("d,H", [(128, 65536), (64, 131072)])
+def test_pairs_at_rows_of_16_mb(d, H):
+    """256 rows of q or out are 2^32 bytes, the first size that a 32-bit byte count does not hold.  One tensor for q, k and v (24 GB);
+    a scale of 1 / d, so that a row's weights are spread over its keys and not on itself.  Bar: as in _compare, and 1e-3 for lse."""
+    import torch
+    import paper_2508_06001_amd as K
+    L, scale = 1450, 1.0 / d
+    assert Q.walk_pairs([L], H, d).items > 0
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GB of GPU memory")
+    say(f"[pairs] 16 MB rows: d={d} H={H}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9300 + d)
+    x = torch.empty((L, H, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    attn = K.VarlenAttention([0, L], H, d, scale)
+    attn.out.fill_(float("nan"))
+    attn.forward(x, x, x)
+    torch.cuda.synchronize()
+    for h in (0, 1, H // 2 + 1, H - 1):
+        v = x[:, h].double().cpu().numpy()
+        O, LSE = A.attn_fwd_dense(v, v, v, scale)
+        err = np.abs(attn.out[:, h].double().cpu().numpy() - O) / (2.0 ** -9 * (2 * np.abs(v).max() + np.abs(O)))
+        assert err.max() <= 1.0 and np.abs(attn.lse[h].cpu().numpy() - LSE).max() <= 1e-3, (h, err.max())
+    assert all(bool(torch.isfinite(rows).all()) for rows in attn.out.split(64))
+    del attn, x
+    torch.cuda.empty_cache()
