@@ -48,7 +48,7 @@ struct FwdFullCfg : FwdCfg<D> {
   static constexpr int AHEAD = D == 64 ? 2 : 3;          // K operands requested ahead of their MFMAs
   static constexpr int ROWS_PER_INSTR = 512 / D;         // rows that one instruction copies, and ...
   static constexpr int COPIES = FwdCfg<D>::BN / (4 * ROWS_PER_INSTR);     // ... those of a wave for its share of a tile of K or V
-  // of a lane's 32 probabilities of a half, of its two queries, against the reference.  Without the second term (2048) the error of out
+  // of a lane's 32 probabilities of a half, 16 of either of its two queries, against the reference.  Without the second term (2048) the error of out
   // grew by up to 5 % on the bags above, at 512 (d = 128) by up to 1.7 %; forward of 16 x 4096 of them, 48 x 64, us: 256 3584, 512 3408
   static constexpr float kLargeSum = D == 64 ? 512.f : 256.f;
 };
@@ -318,7 +318,12 @@ pairs_of_items:
         if constexpr (C::DB == 4) exp_slice(1, db >> 1, db & 1);
         else { exp_slice(1, db, 0); exp_slice(1, db, 1); }
       });
-      const bool large = __builtin_amdgcn_ballot_w64(!(l[0] + l[1] - before <= C::kLargeSum)) != 0;
+      // l[0] + l[1] - before, the increase, plus 2^-16 of what was there: from 2^16 kLargeSum on every half counts as large, before one
+      // row's sum hides the other's increase in its rounding
+      const bool large = __builtin_amdgcn_ballot_w64(!(__builtin_fmaf(before, 0x1p-16f - 1.0f, l[0] + l[1]) <= C::kLargeSum)) != 0;
+      // (8 bytes of code where a subtraction has 4; with the 4 of this behind it the loop goes on 8 bytes further and loses nothing:
+      // 65536 tokens and 200 short, 24 x 128, us: 41250 with a subtraction, 41540 without this, 41330; 32 of 2048 1481, 1489, 1481)
+      asm volatile("s_nop 0");
       second_product(1, [&](int db) __attribute__((always_inline)) {
         if (nextK) {
           constexpr int PER = (AHEAD + C::DB - 1) / C::DB;

@@ -2,6 +2,8 @@
 
 The bag: sequences of 17 and 14 query tiles, odd and even, so that some pairs fall apart at the end of a head (their tiles are then
 taken singly), with 33 and 36 rows in the last tile, and short ones that are never paired."""
+import math
+
 import numpy as np
 import pytest
 
@@ -87,3 +89,64 @@ def test_pairs_at_rows_of_16_mb(d, H):
     assert all(bool(torch.isfinite(rows).all()) for rows in attn.out.split(64))
     del attn, x
     torch.cuda.empty_cache()
+
+
+# Inputs of known probabilities: keys of zeros but for a few with one entry, so that against the reference (the maximum of the first 64 keys,
+# 0) a key's probability is 1 or 2^x.  One sequence of so many heads that most of its query tiles are paired.
+L_ONE, HEADS_ONE = 1700, {128: 256, 64: 512}
+# A probability of 2^x with x from here is 2^16 (1 + 0.56 .. 0.96 2^-8), which bf16 takes down to 2^16: alone, that is an error of 2.2e-3 to
+# 3.7e-3 of lse, where such keys dominate the row.  With the second term 2^-17 of P is left, 7.6e-6 of lse; fp32 exponents of up to
+# 64 and the logarithm of their sum take the rest of the bar.
+X_DOWN = (16.0032, 16.0054)
+LSE_BAR = 5e-5
+
+
+def _entries(d, low, high):
+    """Entries of a query and a key, exact in bf16, and the exponent x in [low, high] of their probability."""
+    for i in range(128, 256):
+        for j in range(128, 256):
+            for e in range(-4, 5):
+                a, b = i / 16.0, j / 128.0 * 2.0 ** e
+                if low <= a * b * d ** -0.5 / math.log(2.0) <= high:
+                    return a, b, a * b * d ** -0.5 / math.log(2.0)
+    raise AssertionError((d, low, high))
+
+
+def _lse_of_one_sequence(d, fill):
+    """lse (H, L) of the sequence behind fill(q, k), in float64."""
+    import torch
+    import paper_2508_06001_amd as K
+    H = HEADS_ONE[d]
+    w = Q.walk_pairs([L_ONE], H, d)
+    assert 2 * w.items > 7 * H          # of 14 H query tiles
+    q, k, v = (torch.zeros((L_ONE, H, d), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    fill(q, k)
+    out, lse = K.VarlenAttention([0, L_ONE], H, d, d ** -0.5).forward(q, k, v)
+    assert bool((out == 0).all())
+    return lse.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("huge_first", [True, False])
+@pytest.mark.parametrize("d", [64, 128])
+def test_second_term_of_a_row_beside_one_of_a_huge_sum(d, huge_first):
+    """A lane holds two rows, 32 apart.  Those of one block have a key of 2^60, beside which the other block's three keys of 2^16 are nothing;
+    they take their second term all the same."""
+    a, b, x = _entries(d, *X_DOWN)
+    a0, b0, x0 = _entries(d, 59.5, 60.5)
+    rows = np.arange(L_ONE) % 64 < 32
+    huge = rows if huge_first else ~rows
+
+    def fill(q, k):
+        import torch
+        at = torch.from_numpy(huge).to("cuda")
+        q[at, :, 0] = a0
+        q[~at, :, 1] = a
+        k[100, :, 0] = b0
+        k[900:903, :, 1] = b
+
+    lse = _lse_of_one_sequence(d, fill)
+    want = np.where(huge, math.log(L_ONE - 1 + 2.0 ** x0), math.log(L_ONE - 3 + 3 * 2.0 ** x))
+    assert math.log(L_ONE - 3 + 3 * 2.0 ** x) - math.log(L_ONE - 3 + 3 * 2.0 ** 16) > 20 * LSE_BAR      # without the second term
+    err = float(np.abs(lse - want).max())
+    say(f"[pairs] d={d} beside a huge sum: lse error={err:.2e}")
+    assert err <= LSE_BAR
