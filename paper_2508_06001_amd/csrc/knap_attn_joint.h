@@ -10,66 +10,6 @@
 
 namespace knap {
 
-// -delta and the LSE in base 2 of 128 rows of one head; bound by reading out and dout once (31464 tokens,
-// 24 x 128: 67 us, 5.8 TB/s; 79 before).  The D / 8 lanes of a row hold 8 columns each, so that a load takes whole rows, and add up
-// over the lanes.  With 32 bytes of 32 rows to a load, as the dQ kernel takes its rows, backward in us:
-// 4 sequences of up to 311 tokens, 2 x 64, 11.5 against 11.0; 4 of 400, 24 x 128, 55.2 against 53.9; 17 of 328..4533 3228 against 3219.  out
-// is not read again, and past the caches where it is large (32 of 1024, 12 x 64, 378 -> 374; 40 of 600, 24 x 128, 762 -> 753; but
-// 4 of 400 54.2 -> 54.9).  It also clears the counters of the queues of the launch behind it, which therefore may hold
-// anything (a caller's workspace) and need no launch of their own.
-constexpr size_t kOutPastCaches = 20u << 20;        // elements
-
-template <int D>
-__global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
-    const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ lse2, const int32_t* __restrict__ cu, int n_seq, int H,
-    unsigned* __restrict__ counters) {
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0u;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t0 = blockIdx.x * 128, head = blockIdx.y, T = cu[n_seq];
-  if (t0 >= T) return;
-  const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
-  const size_t at = ((size_t)t0 * H + head) * D;
-  const uint32_t bytes = (uint32_t)min(T - t0, 128) * row_bytes;
-  const auto ro = make_rsrc(out + at, bytes);
-  const auto rd = make_rsrc(dout + at, bytes);
-  constexpr int LANES = D / 8, ROWS = 64 / LANES, N = 32 / ROWS;      // lanes of a row, rows of a load, loads of a wave
-  bf16x8 of[N], dof[N];
-  const uint32_t off = (uint32_t)(wave * 32 + lane / LANES) * row_bytes + (uint32_t)(lane % LANES) * 16u;
-  if ((size_t)T * H * D > kOutPastCaches) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      of[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ro, (int)(off + (uint32_t)(i * ROWS) * row_bytes), 0, 2 /* nt */));
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) of[i] = __builtin_bit_cast(bf16x8, buffer_load16(ro, off + (uint32_t)(i * ROWS) * row_bytes));
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) dof[i] = __builtin_bit_cast(bf16x8, buffer_load16(rd, off + (uint32_t)(i * ROWS) * row_bytes));
-  KNAP_SCHED_FENCE();
-  float mine = 0.f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    float x = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x = __builtin_fmaf((float)dof[i][e], (float)of[i][e], x);
-    auto add = [&](auto ctrl) {
-      x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-    };
-    add(std::integral_constant<int, 0xb1>{});         // quad_perm 1, 0, 3, 2
-    add(std::integral_constant<int, 0x4e>{});         // quad_perm 2, 3, 0, 1
-    add(std::integral_constant<int, 0x141>{});        // row_half_mirror: the other four of eight
-    if constexpr (D == 128) add(std::integral_constant<int, 0x140>{});        // row_mirror: the other eight of sixteen
-    mine = lane % LANES == i ? x : mine;              // row ROWS i + lane / LANES of the wave's 32, kept by lane i of its row
-  }
-  const int t = t0 + wave * 32 + ROWS * (lane % LANES) + lane / LANES;
-  if (lane % LANES < N && t < T) {
-    const size_t row_at = (size_t)head * T + t;
-    delta[row_at] = -mine;
-    lse2[row_at] = lse[row_at] * kLog2e;
-  }
-}
-
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
@@ -161,14 +101,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kern
     ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows
   }
-}
-
-inline hipError_t launch_delta(const BwdArgs& a, int d, int T, hipStream_t stream) {
-  const dim3 rows((T + 127) / 128, a.H);
-  auto* delta = d == 64 ? attn_bwd_delta_kernel<64> : attn_bwd_delta_kernel<128>;
-  hipLaunchKernelGGL(delta, rows, dim3(kThreads), 0, stream, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
-                     a.n_seq, a.H, a.counters);
-  return hipGetLastError();
 }
 
 template <bool CAUSAL>
