@@ -64,15 +64,46 @@ hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int 
 // anything (a caller's workspace) and need no launch of their own.
 constexpr size_t kOutPastCaches = 20u << 20;        // elements
 
+// One workgroup beside those with rows: which items the launch behind this one takes (small_pays()).
+template <int D>
+__device__ __forceinline__ void decide_small(const int32_t* __restrict__ cu, int n_seq, int H, unsigned* __restrict__ counters, int slots, bool causal) {
+  __shared__ int s_tiles[kThreads / 64], s_longest[kThreads / 64];
+  int tiles = 0, longest = 0;
+  for (int i = threadIdx.x; i < n_seq; i += kThreads) {
+    const int n = (cu[i + 1] - cu[i] + 63) / 64;
+    tiles += n;
+    longest = max(longest, n);
+  }
+  tiles = wave_scan(tiles);
+  longest = wave_max(longest);
+  if ((threadIdx.x & 63) == 63) {
+    s_tiles[threadIdx.x >> 6] = tiles;
+    s_longest[threadIdx.x >> 6] = longest;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    tiles = longest = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+      tiles += s_tiles[w];
+      longest = max(longest, s_longest[w]);
+    }
+    counters[kSmallPays] = small_pays(tiles, longest, H, slots, D, causal) ? 1u : 0u;
+  }
+}
+
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
     const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ lse2, const int32_t* __restrict__ cu, int n_seq, int H,
-    unsigned* __restrict__ counters) {
+    unsigned* __restrict__ counters, int slots, bool causal) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int t0 = blockIdx.x * 128, head = blockIdx.y, T = cu[n_seq];
-  if (t0 >= T) return;
+  if (t0 >= T) {
+    if (slots > 0 && head == 0 && blockIdx.x == gridDim.x - 1) decide_small<D>(cu, n_seq, H, counters, slots, causal);
+    return;
+  }
   const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
   const size_t at = ((size_t)t0 * H + head) * D;
   const uint32_t bytes = (uint32_t)min(T - t0, 128) * row_bytes;
@@ -115,19 +146,21 @@ __global__ __launch_bounds__(kThreads) void attn_bwd_delta_kernel(
   }
 }
 
-static hipError_t launch_delta(const BwdArgs& a, int d, int T, hipStream_t stream) {
-  const dim3 rows((T + 127) / 128, a.H);
+// slots: of the workgroups of a launch behind it that asks for the decision on its items, else 0
+static hipError_t launch_delta(const BwdArgs& a, int d, int T, int slots, bool causal, hipStream_t stream) {
+  const dim3 rows((T + 127) / 128 + (slots > 0 ? 1 : 0), a.H);
   auto* delta = d == 64 ? attn_bwd_delta_kernel<64> : attn_bwd_delta_kernel<128>;
   hipLaunchKernelGGL(delta, rows, dim3(kThreads), 0, stream, (const __bf16*)a.out, (const __bf16*)a.dout, a.lse, a.delta, a.lse2, a.cu,
-                     a.n_seq, a.H, a.counters);
+                     a.n_seq, a.H, a.counters, slots, causal);
   return hipGetLastError();
 }
 
 hipError_t launch_joint(const BwdArgs& a, int d, bool causal, bool small, int T, int cus, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   hipError_t e = hipSuccess;
   if (ev_start && ev_stop && (e = hipEventRecord(ev_start, stream)) != hipSuccess) return e;
-  if ((e = launch_delta(a, d, T, stream)) != hipSuccess) return e;
-  e = small ? launch_small(a, d, causal, cus, stream) : causal ? launch_joint_causal(a, d, cus, stream) : launch_joint_m<false>(a, d, cus, stream);
+  const bool sure = !small || small_sure(T, a.n_seq, a.H, d, causal, cus);
+  if ((e = launch_delta(a, d, T, sure ? 0 : cus * dkdv_workgroups_per_cu(d, 2), causal, stream)) != hipSuccess) return e;
+  e = small ? launch_small(a, d, causal, sure, cus, stream) : causal ? launch_joint_causal(a, d, cus, stream) : launch_joint_m<false>(a, d, cus, stream);
   if (e != hipSuccess) return e;
   if (ev_start && ev_stop && (e = hipEventRecord(ev_stop, stream)) != hipSuccess) return e;
   return hipSuccess;

@@ -1,10 +1,9 @@
 // Backward of bags whose tiles of 128 rows would leave most of the GPU idle, either mask: both kinds of items in one launch, as in
 // knap_attn_joint.h, but of 64 rows each, so that there are twice as many and each walks half as far in time.  What bounds such a bag is
 // its longest item, one workgroup alone on a CU: a 128-key item takes a step of 32 queries after the other, 1.0 to 1.2 us each, and no part of it
-// could go to an idle CU.  Under the mask the items are single tiles, the dearest first, and not pairs of equal cost.  bwd_small() in
-// knap_dispatch.h chooses and has both sides measured.
-#include "knap_attn_dkdv.h"
-#include "knap_attn_dq.h"
+// could go to an idle CU.  Under the mask the items are single tiles, the dearest first, and not pairs of equal cost.  bwd_small() and
+// small_pays() in knap_dispatch.h choose and have both sides measured.
+#include "knap_attn_joint.h"
 
 namespace knap {
 
@@ -203,29 +202,29 @@ __device__ __forceinline__ void dkdv_part(const BwdPtrs& g, const DqLds& lds, fl
   if (half == 0) finish(dk); else finish(dv);
 }
 
-template <int D, bool CAUSAL>
+// SURE: the host knows that items of 64 rows pay (small_sure()).  Else the kernel in front has decided, by the lengths (small_pays()), and where
+// they do not the items are those of knap_attn_joint.h.
+template <int D, bool CAUSAL, bool SURE>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
     float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
     __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
   constexpr int BM = 64;                           // rows of an item of either kind
-  extern __shared__ int s_dyn[];
-  int* s_order = s_dyn;
-  int* s_start = s_dyn + n_seq;
-  constexpr int TILE = DqCfg<D>::TILE_ELEMS;
-  __shared__ __attribute__((aligned(1024))) __bf16 sA0[TILE];
-  __shared__ __attribute__((aligned(1024))) __bf16 sA1[TILE];
-  __shared__ __attribute__((aligned(1024))) __bf16 sA2[TILE];
-  __shared__ __attribute__((aligned(1024))) __bf16 sA3[TILE];
-  __shared__ __attribute__((aligned(256))) float sLse0[64], sDelta0[64], sLse1[64], sDelta1[64], sSink[64];
-  __shared__ int s_ticket;
-
-  const int T = cu[n_seq];
-  build_schedule<BM, kThreads, false>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sA0[0]));
+  KNAP_JOINT_LDS(D, all);
+  int *const s_order = all.order, *const s_start = all.start;
+  const unsigned pays = SURE ? 1u : counters[kSmallPays];      // (arrives with the lengths)
+  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, cu[n_seq], H, scale};
+  build_schedule_of(cu, n_seq, [&](int len) {
+    const int wide = items_per_head<CAUSAL>((len + 127) / 128), tiles = (len + BM - 1) / BM;
+    return (SURE || pays ? tiles : wide) * H;
+  }, s_order, s_start, reinterpret_cast<int*>(sA0));
+  if (!SURE && __builtin_amdgcn_readfirstlane(pays) == 0) {
+    joint_items<D, CAUSAL>(g, all, cu, n_seq, H, counters);
+    return;
+  }
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, T, H, scale};
   const DqLds lds = {sA0, sA1, sA2, sA3};
   float* const scalars[2][2] = {{sLse0, sDelta0}, {sLse1, sDelta1}};
 
@@ -259,18 +258,19 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kern
   }
 }
 
-template <int D, bool CAUSAL>
-static hipError_t launch_small_t(const BwdArgs& a, int cus, hipStream_t stream) {
+template <int D>
+static hipError_t launch_small_d(const BwdArgs& a, bool causal, bool sure, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
-  hipLaunchKernelGGL((attn_bwd_small_kernel<D, CAUSAL>), dim3(cus * dkdv_workgroups_per_cu(D, 2)), dim3(kThreads), dyn, stream,
-                     (const __bf16*)a.q, (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H,
-                     a.scale, (__bf16*)a.dq, (__bf16*)a.dk, (__bf16*)a.dv, a.counters);
+  auto* kernel = causal ? (sure ? attn_bwd_small_kernel<D, true, true> : attn_bwd_small_kernel<D, true, false>)
+                        : (sure ? attn_bwd_small_kernel<D, false, true> : attn_bwd_small_kernel<D, false, false>);
+  hipLaunchKernelGGL(kernel, dim3(cus * dkdv_workgroups_per_cu(D, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k,
+                     (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale, (__bf16*)a.dq, (__bf16*)a.dk,
+                     (__bf16*)a.dv, a.counters);
   return hipGetLastError();
 }
 
-hipError_t launch_small(const BwdArgs& a, int d, bool causal, int cus, hipStream_t stream) {
-  if (d == 64) return causal ? launch_small_t<64, true>(a, cus, stream) : launch_small_t<64, false>(a, cus, stream);
-  return causal ? launch_small_t<128, true>(a, cus, stream) : launch_small_t<128, false>(a, cus, stream);
+hipError_t launch_small(const BwdArgs& a, int d, bool causal, bool sure, int cus, hipStream_t stream) {
+  return d == 64 ? launch_small_d<64>(a, causal, sure, cus, stream) : launch_small_d<128>(a, causal, sure, cus, stream);
 }
 
 }  // namespace knap

@@ -337,9 +337,21 @@ __device__ __forceinline__ int wave_scan(int x) {
   return x;
 }
 
-template <int TILE, int NT = kThreads, bool PAIRED = false>
-__device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, int n_seq, int H,
-                                              int* s_order, int* s_start, int* s_part /* NT ints */) {
+// largest of the lanes up to this one, of numbers from 0 on
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
+// items(len): of a sequence of that length, all heads
+template <int NT = kThreads, class Items>
+__device__ __forceinline__ int build_schedule_of(const int32_t* __restrict__ cu, int n_seq, Items items_of, int* s_order, int* s_start,
+                                                 int* s_part /* NT ints */) {
   constexpr int kThreads = NT;   // threads of the calling workgroup
   const int tid = threadIdx.x;
   // Up to 64 sequences: one wave, one load of the boundaries, no barrier but the last.  What bounds it is latency, which
@@ -352,7 +364,7 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
       for (int j = 0; j < n_seq; ++j) rank += __builtin_amdgcn_readlane(len, j) > len - (j < tid ? 1 : 0) ? 1 : 0;
       if (tid < n_seq) {
         s_order[rank] = tid;
-        s_start[rank] = items_per_head<PAIRED>((len + TILE - 1) / TILE) * H;
+        s_start[rank] = items_of(len);
       }
       const int items = tid < n_seq ? s_start[tid] : 0;
       const int sum = wave_scan(items);
@@ -381,7 +393,7 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
   int local = 0;
   for (int r = lo; r < hi; ++r) {
     const int s = s_order[r];
-    local += items_per_head<PAIRED>((cu[s + 1] - cu[s] + TILE - 1) / TILE) * H;
+    local += items_of(cu[s + 1] - cu[s]);
   }
   s_part[tid] = local;
   __syncthreads();
@@ -395,11 +407,16 @@ __device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, in
   for (int r = lo; r < hi; ++r) {
     const int s = s_order[r];
     s_start[r] = run;
-    run += items_per_head<PAIRED>((cu[s + 1] - cu[s] + TILE - 1) / TILE) * H;
+    run += items_of(cu[s + 1] - cu[s]);
   }
   if (tid == kThreads - 1) s_start[n_seq] = s_part[kThreads - 1];
   __syncthreads();
   return s_start[n_seq];
+}
+
+template <int TILE, int NT = kThreads, bool PAIRED = false>
+__device__ __forceinline__ int build_schedule(const int32_t* __restrict__ cu, int n_seq, int H, int* s_order, int* s_start, int* s_part) {
+  return build_schedule_of<NT>(cu, n_seq, [&](int len) { return items_per_head<PAIRED>((len + TILE - 1) / TILE) * H; }, s_order, s_start, s_part);
 }
 
 // s_start turned into an even queue's table: its items of the sequences of lower rank, for every rank.  By one wave; a barrier

@@ -77,11 +77,43 @@ inline bool bwd_joint(int64_t total_tokens, int n_seq, int H, int d, bool causal
 // one of 544, 48 x 64 (0.31), 25.9 | 28.7.  Under it: one of 4776, 3 x 128 (0.22), 176 | 104; one of 16682, 2 x 64 (0.34), 470 | 429, of 19631
 // (0.40) 547 | 560; 9960 in 3, 3 x 128 (0.46), 172 | 137; 4536 in 10, 6 x 128 (0.47), 47 | 37; one of 10019, 3 x 128 (0.46), 346 | 375; 10525 in 19, half
 // of them in one, 3 x 128 (0.56), 201 | 131; 1862 in 4, 24 x 128 (0.75), 50 | 54.  Without the mask bags of one long and many short sequences gain up to a
-// half (8352 in 14, 3 x 128, 165 | 118), and bags of like lengths of the same numbers lose up to 8 %.
+// half (8352 in 14, 3 x 128, 165 | 118), and bags of like lengths of the same numbers lose up to 8 %.  Bags of other lengths than the average's lose
+// by it: small_pays() takes those back.
 inline bool bwd_small(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
   const int64_t tiles = ((total_tokens + n_seq - 1) / n_seq + 127) / 128;
   const double r = (double)(tiles * n_seq * H) / (double)((int64_t)cus * dkdv_workgroups_per_cu(d, 2));
   return r <= (!causal ? 0.25 : n_seq == 1 ? 0.375 : 0.55);
+}
+
+// Whether items of 64 rows pay after all: decided in front of that launch on the device, which knows the lengths.  tiles: of 64 rows, of
+// all sequences of a head; longest: those of the longest.  Where not, the launch takes items of 128 rows.  Backward in us, 128 rows | 64, n
+// the workgroups' worth of 64-row items of both kinds; 554 bags without the mask and 652 under it.
+//  * Without the mask: where each item has a workgroup.  Sequences of 1 and 200 tokens in turn, 3 x 128: 34 (n = 1.0) 23.7 | 21.1, 40 (1.17) 25.3 |
+//    26.9; 92, 2 x 64 (1.2), 20.3 | 25.9.
+//  * Under it items of half the average length fill in behind the long ones, so that more than one worth pays, but not
+//    - of one long sequence, alone or beside a few short ones, where the longer walks count and not the starts: one of 7864, 3 x 128 (1.44), 285 |
+//      273, 9175 and 1 (1.7) 320 | 338; 24576 and 1, 2 x 64 (2.0), 725 | 911; but 18432 and 20 of 300 (2.0) 533 | 516;
+//    - of sequences up to 128 tokens, each one item of 128 rows, from one worth on until those need a second round as well: 32 of 128, 6 x
+//      128 (1.5), 23.6 | 27.7, 46 (2.16) 36.2 | 35.2; 24 of 96, 12 x 64 (1.5), 16.4 | 23.9; 46 of 64, 6 x 128 (1.08), 29.5 | 24.5;
+//    - at d = 64, where a 128-row item of two tiles is short as well, up to 192 tokens, and up to 256 from one and a half on: 24 of 160, 6 x 64
+//      (1.12), 18.9 | 20.8; 24 of 256 (1.5) 26.5 | 26.4, 35 (2.19) 28.4 | 33.9; but 23 of 320 (1.8) 31.2 | 29.8, and 32 of 192, 6 x 128 (1.12), 28.3 | 24.0.
+constexpr bool small_pays(int tiles, int longest, int H, int slots, int d, bool causal) {
+  const int64_t both = 2 * (int64_t)tiles * H, n = slots;
+  if (!causal) return both <= n;
+  if (longest > 128 && 4 * (int64_t)longest >= 3 * (int64_t)tiles) return 5 * both <= 8 * n;
+  if (longest == 2) return 10 * both <= 11 * n || (d == 128 && both > 2 * n);
+  if (d == 64 && longest == 3) return 10 * both <= 11 * n;
+  if (d == 64 && longest == 4) return 50 * both <= 76 * n;
+  return true;
+}
+
+// Whether that is so whatever the lengths are (L tokens have at most (L + 63) / 64 tiles, and the longest sequence the average): such bags
+// take a kernel without the other form, whose prologue and code are shorter: half a us of 10 to 60 (134 bags, 2.7 %).
+inline bool small_sure(int64_t total_tokens, int n_seq, int H, int d, bool causal, int cus) {
+  const int64_t slots = (int64_t)cus * dkdv_workgroups_per_cu(d, 2), most = 2 * ((total_tokens + 63 * (int64_t)n_seq) / 64) * H;
+  if (!causal) return most <= slots;
+  if (10 * most <= 11 * slots) return true;
+  return total_tokens > (d == 128 ? 128 : 256) * (int64_t)n_seq && (total_tokens <= 8192 || 5 * most <= 8 * slots);
 }
 
 // Counter sets of the forward's work queues.  The forward entry points have no workspace: a launch draws from one of these sets

@@ -34,9 +34,10 @@ hipError_t launch_bwd(const BwdArgs& a, int d, bool causal, int dkdv_pairs, int 
                       hipEvent_t ev_start, hipEvent_t ev_stop);
 // both kinds of items in one launch, T tokens, behind the kernel that forms delta: tiles of 128 rows (knap_attn_joint.h) or, `small`, of 64
 // (knap_attn_bwd_small.hip)
+constexpr int kSmallPays = 8;      // behind the counters of the launch's queues: whether items of 64 rows pay, where that is decided on the device
 hipError_t launch_joint(const BwdArgs& a, int d, bool causal, bool small, int T, int cus, hipStream_t stream, hipEvent_t ev_start,
                         hipEvent_t ev_stop);
-hipError_t launch_small(const BwdArgs& a, int d, bool causal, int cus, hipStream_t stream);
+hipError_t launch_small(const BwdArgs& a, int d, bool causal, bool sure, int cus, hipStream_t stream);
 hipError_t launch_joint_causal(const BwdArgs& a, int d, int cus, hipStream_t stream);
 hipError_t launch_dq_causal(const BwdArgs& a, int d, int cus, int wg_per_cu, hipStream_t stream);
 hipError_t launch_dkdv_causal(const BwdArgs& a, int d, int pairs, int cus, hipStream_t stream);

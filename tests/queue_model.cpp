@@ -173,6 +173,20 @@ int queue_bwd_small(long long tokens, int n_seq, int H, int d, int causal, int c
   return knap::bwd_small(tokens, n_seq, H, d, causal != 0, cus);
 }
 
+// What the host knows about the items of 64 rows of that launch (2: taken whatever the lengths are, 1: the device decides), and the
+// device's decision.
+void queue_small_items(const int* lens, int n_seq, int H, int d, int causal, int cus, int* out) {
+  long long tokens = 0;
+  int tiles = 0, longest = 0;
+  for (int s = 0; s < n_seq; ++s) {
+    tokens += lens[s];
+    tiles += (lens[s] + 63) / 64;
+    longest = max(longest, (lens[s] + 63) / 64);
+  }
+  out[0] = !knap::bwd_small(tokens, n_seq, H, d, causal != 0, cus) ? 0 : knap::small_sure(tokens, n_seq, H, d, causal != 0, cus) ? 2 : 1;
+  out[1] = knap::small_pays(tiles, longest, H, cus * knap::dkdv_workgroups_per_cu(d, 2), d, causal != 0);
+}
+
 int queue_bwd_joint(long long tokens, int n_seq, int H, int d, int causal, int cus) {
   return knap::bwd_joint(tokens, n_seq, H, d, causal != 0, cus);
 }

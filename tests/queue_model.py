@@ -44,6 +44,8 @@ def _lib():
     lib.queue_walk_small.restype = None
     lib.queue_walk_small.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 3 + [C.POINTER(C.c_int)]
     lib.queue_bwd_small.argtypes = [C.c_longlong] + [C.c_int] * 5
+    lib.queue_small_items.restype = None
+    lib.queue_small_items.argtypes = [C.POINTER(C.c_int)] + [C.c_int] * 5 + [C.POINTER(C.c_int)]
     lib.queue_bwd_joint.argtypes = [C.c_longlong] + [C.c_int] * 5
     lib.queue_eager_set.restype = None
     lib.queue_eager_set.argtypes = [C.c_ulonglong, C.POINTER(C.c_int)]
@@ -110,8 +112,19 @@ def walk_joint(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS
 
 
 def bwd_small(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> bool:
-    """Whether that launch takes tiles of 64 rows (walk_small) in place of 128 (walk_joint)."""
+    """Whether that launch is the one that can take tiles of 64 rows (walk_small) in place of 128 (walk_joint); see small_items()."""
     return bool(_lib().queue_bwd_small(sum(lens), len(lens), H, d, int(causal), cus))
+
+
+class SmallItems(NamedTuple):
+    host: int        # 0: the host takes tiles of 128 rows, 1: it leaves it to the device, 2: tiles of 64 rows whatever the lengths are
+    pays: bool       # the device's decision
+
+
+def small_items(lens: Sequence[int], H: int, d: int, causal: bool, cus: int = CUS) -> SmallItems:
+    out = (C.c_int * 2)()
+    _lib().queue_small_items((C.c_int * len(lens))(*lens), len(lens), H, d, int(causal), cus, out)
+    return SmallItems(out[0], bool(out[1]))
 
 
 def walk_small(lens: Sequence[int], H: int, d: int, cus: int = CUS) -> Walk:

@@ -63,12 +63,46 @@ def test_small_backward(lens, H, d, causal):
 
 
 @pytest.mark.parametrize("d,lens,H,causal", [
-    (128, [129] * 30, 4, True), (64, [129] * 30, 6, True),               # more items than workgroups: several draws
+    (128, [129] * 30, 4, True), (64, [129] * 30, 6, True),               # more items than workgroups: several draws; the last three take 128 rows
     (128, [1, 200] * 5, 12, False), (64, [1, 129, 129, 65], 44, False)])    # sequences that the average makes look shorter
 def test_small_backward_draws(d, lens, H, causal):
     w = Q.walk_small(lens, H, d)
     assert Q.bwd_small(lens, H, d, causal) and w.draws and w.most > w.per
     _compare(BagSpec("small_draws", lens, H=H, d=d, seed=9600 + H + d), causal, [0, H // 2, H - 1])
+
+
+@pytest.mark.parametrize("d,lens,H,causal", [(128, [160] * 22, 6, True), (64, [320] * 20, 6, True), (64, [700, 333, 5, 64], 24, True)])
+def test_small_backward_draws_where_items_of_64_rows_pay(d, lens, H, causal):
+    w = Q.walk_small(lens, H, d)
+    s = Q.small_items(lens, H, d, causal)
+    assert s.host > 0 and s.pays and w.draws and w.most > w.per
+    _compare(BagSpec("small_draws", lens, H=H, d=d, seed=9650 + H + d), causal, [0, H // 2, H - 1])
+
+
+@pytest.mark.parametrize("d,lens,H,causal,pays", [
+    (128, [1, 200] * 20, 3, False, False), (64, [1, 200] * 40, 2, False, False), (128, [128] * 40, 3, False, True),
+    (64, [128] * 96, 2, False, True),
+    (128, [64] * 30 + [1, 0], 6, True, True), (128, [9176, 1], 3, True, False), (128, [96] * 70, 3, True, False), (128, [128] * 93, 3, True, True),
+    (64, [20644, 0, 0], 2, True, False), (64, [160] * 105, 2, True, False), (64, [64] * 34 + [1], 12, True, True),
+    (64, [0, 8] * 200 + [320] * 4, 1, True, True)])
+def test_small_backward_of_bags_whose_lengths_decide(d, lens, H, causal, pays):
+    """The kernel in front of the launch writes the decision behind the launch's counters, 256 bytes from the workspace's end: up to 64
+    sequences, more, and more than a workgroup has threads; empty ones."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    s = Q.small_items(lens, H, d, causal)
+    assert s.host == 1 and s.pays == pays
+    run = _compare(BagSpec("small_decided", lens, H=H, d=d, seed=9900 + H + d), causal, sorted({0, H // 2, H - 1}))
+    a, x = run.attn, run.dev
+    for fill in (0xff, 0):
+        a.workspace.fill_(fill)
+        for t in (a.dq, a.dk, a.dv):
+            t.fill_(float("nan"))
+        a.backward(x["q"], x["k"], x["v"], x["dout"])
+        torch.cuda.synchronize()
+        assert int(a.workspace[-256:].view(torch.int32)[8]) == pays
+        for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+            assert np.array_equal(bf16_device_to_bits(got), want)
 
 
 @pytest.mark.parametrize("d,lens,H,causal", [(128, [700, 450], 14, False), (64, [700, 450], 21, False),

@@ -93,6 +93,41 @@ def test_every_item_of_the_small_backward_once():
     assert min(seen.values()) > 100, seen
 
 
+def test_small_items_are_left_to_the_device_where_the_lengths_decide():
+    """Where the host takes tiles of 64 rows by itself the device would for any lengths of that sum and number; random bags near the
+    limits of every rule."""
+    rng = random.Random(123)
+    seen = {0: 0, 1: 0, 2: 0, "not": 0}
+    for _ in range(6000):
+        H, d, causal = rng.choice((1, 2, 3, 6, 12, 24, 48)), rng.choice((64, 128)), rng.random() < 0.6
+        cus = rng.choice((256, 256, 304, 80, 37))
+        room = max(1, int(rng.uniform(0.1, 0.6) * cus * (3 if d == 64 else 2) / H))        # tiles of 128 rows
+        top = rng.choice((64, 128, 192, 256, 320, 600, 128 * room))
+        lens = []
+        while sum((x + 127) // 128 for x in lens) < room and len(lens) < 2048:
+            lens.append(rng.choice((0, 1, top, rng.randint(1, top))))
+        if sum(lens) == 0:
+            continue
+        s = Q.small_items(lens, H, d, causal, cus)
+        assert s.host < 2 or s.pays, (lens, H, d, causal, cus)
+        assert bool(s.host) == Q.bwd_small(lens, H, d, causal, cus)
+        seen[s.host] += 1
+        seen["not"] += s.host == 1 and not s.pays
+    assert min(seen.values()) > 100, seen
+
+
+@pytest.mark.parametrize("lens,H,d,causal,pays", [
+    ([10019], 3, 128, True, None), ([10019, 1], 3, 128, True, False), ([20644, 0, 0], 2, 64, True, False),    # one long sequence, alone or not
+    ([5262] + [300] * 17, 3, 128, True, True),
+    ([1, 200] * 20, 3, 128, False, False), ([1, 200] * 7, 12, 64, False, False), ([1, 200] * 17, 3, 128, False, True),
+    ([128] * 40, 6, 128, True, False), ([128] * 46, 6, 128, True, True), ([64] * 46, 6, 128, True, True), ([96] * 24, 12, 64, True, False),
+    ([160] * 35, 6, 64, True, False), ([256] * 24, 6, 64, True, True), ([256] * 35, 6, 64, True, False), ([320] * 23, 6, 64, True, True)])
+def test_small_items_of_bags_measured_both_ways(lens, H, d, causal, pays):
+    """pays: None where the host does not ask."""
+    s = Q.small_items(lens, H, d, causal)
+    assert s.host == (0 if pays is None else s.host) and (pays is None or (s.host in ((1, 2) if pays else (1,)) and s.pays == pays)), s
+
+
 @pytest.mark.parametrize("start", [0, (1 << 32) - 20000])
 def test_counter_sets_are_cleared_between_two_uses_far_from_either(start):
     """Eager forward calls: between two calls that draw from one set some call clears it, and calls that touch a set (draw from
