@@ -61,11 +61,14 @@ __device__ __forceinline__ void half_exps(const f32x16& s, float c, float mc, bf
 // on the first half, where it is -inf and the sum inf or NaN): up to the maximum, with what is accumulated rescaled
 // and the half's probabilities formed again.  The first half of a tile takes the maximum of the whole tile, so that
 // the largest probability of an item's first 64 keys is exactly 1 and carries no rounding error (taken over 32
-// keys, the error of lse against 64 bits grew by up to 6 %, that of out by up to 1.7 %).
-template <int DB, class Maximum>
+// keys, the error of lse against 64 bits grew by up to 6 %, that of out by up to 1.7 %).  That it moves is rare behind the first keys: what it takes
+// stands out of the loops' way (APART), but not under the mask.  Forward in us, with the start of fwd_tile: 6 sequences of 1536, 2 x 64, 19.7 -> 18.5, 1944,
+// 12 x 64, 23.9 -> 22.7, 30 of 290, 3 x 128, 18.8 -> 18.1, 6 x 128 26.4 -> 27.1; 146 bags 1.009; under the mask 32 of 450, 12 x 128, 53.9 -> 57.9.
+template <bool APART, int DB, class Maximum>
 __device__ __forceinline__ void half_settle(const f32x16& s, float c, Maximum maximum, bf16x8 (&pb)[2], float l_new, float& m_ref, float& mc,
                                             float& l_run, f32x16 (&o)[DB]) {
-  if (__builtin_amdgcn_ballot_w64(!(l_new - l_run <= kMaxHalfSum)) != 0) {
+  const bool moves = __builtin_amdgcn_ballot_w64(!(l_new - l_run <= kMaxHalfSum)) != 0;
+  if (APART ? __builtin_expect(moves, 0) : moves) {
     const float m_loc = maximum();
     const float m_new = fmaxf(m_ref, fmaxf(m_loc, xor32(m_loc)));
     const float alpha = m_new == m_ref ? 1.f : fast_exp2((m_ref - m_new) * c);
@@ -200,7 +203,7 @@ __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D
     KNAP_SCHED_FENCE();
   };
   auto settle_first = [&](int t, float l) __attribute__((always_inline)) {
-    half_settle<DB>(s0, c, [&] { return fmaxf(half_max(s0, C::BN, hh), half_max(s1, kv_lim - t * C::BN - 32, hh)); }, pb0, l, m_ref, mc, l_run, o);
+    half_settle<!CAUSAL, DB>(s0, c, [&] { return fmaxf(half_max(s0, C::BN, hh), half_max(s1, kv_lim - t * C::BN - 32, hh)); }, pb0, l, m_ref, mc, l_run, o);
     KNAP_SCHED_FENCE();
   };
   auto mask_second = [&](int t) __attribute__((always_inline)) {
@@ -208,7 +211,7 @@ __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D
     KNAP_SCHED_FENCE();
   };
   auto settle_second = [&](float l) __attribute__((always_inline)) {
-    half_settle<DB>(s1, c, [&] { return half_max(s1, C::BN, hh); }, pb1, l, m_ref, mc, l_run, o);
+    half_settle<!CAUSAL, DB>(s1, c, [&] { return half_max(s1, C::BN, hh); }, pb1, l, m_ref, mc, l_run, o);
     KNAP_SCHED_FENCE();
   };
   // One turn: the second half of tile t and the first of tile t + 1 go through the softmax.  Behind its barrier the keys of tile
@@ -237,9 +240,22 @@ __device__ __forceinline__ void fwd_tile(const FwdLds& lds, const bf16x8 (&qs)[D
   if (n_tiles == 1) draw();
   {
     mask_first(0);
-    float l = l_run;
-    slot(yes, no, at_once, s0, s1, pb1, pb0, lds.v0, l, nothing);
-    settle_first(0, l);
+    if constexpr (CAUSAL) {
+      float l = l_run;
+      slot(yes, no, at_once, s0, s1, pb1, pb0, lds.v0, l, nothing);
+      settle_first(0, l);
+    } else {
+      // What the settling comes to here, without the probabilities against no reference: 30 of 600, 24 x 128, 185 -> 181 us.  Under the mask it loses
+      // more than it gains: 32 of 450, 24 x 128, 104.6 -> 101, but 16 of 512 52.9 -> 58.3; at d = 64 5 % on 130 to 192 tokens, 3 % gained on 193 to 256.
+#pragma unroll
+      for (int cc = 0; cc < KC; ++cc) s1 = mfma32(ak[cc], qs[cc], cc == 0 ? zero16() : s1);
+      const float m = fmaxf(half_max(s0, C::BN, hh), half_max(s1, kv_lim - 32, hh));
+      m_ref = fmaxf(m, xor32(m));
+      mc = m_ref == -INFINITY ? 0.f : m_ref * c;
+      half_exps(s0, c, mc, pb0, l_run);
+      if (m_ref == -INFINITY) mc = -INFINITY;
+      KNAP_SCHED_FENCE();
+    }
   }
   for (int t = 0; t < n_own - 1; t += 2) {
     turn(t, lds.k1, lds.v0, lds.k0, lds.v1);
@@ -340,7 +356,7 @@ __device__ __forceinline__ void fwd_part(const FwdPtrs& g, const FwdLds& lds, co
       bf16x8 pb[2];
       float l_new = l_run;
       half_exps(s, c, mc, pb, l_new);
-      half_settle<C::DB>(s, c, [&] { return half_max(s, C::BN, hh); }, pb, l_new, m_ref, mc, l_run, o);
+      half_settle<!CAUSAL, C::DB>(s, c, [&] { return half_max(s, C::BN, hh); }, pb, l_new, m_ref, mc, l_run, o);
 #pragma unroll
       for (int ck = 0; ck < 2; ++ck)
 #pragma unroll
@@ -349,8 +365,9 @@ __device__ __forceinline__ void fwd_part(const FwdPtrs& g, const FwdLds& lds, co
     wait_async_loads();
     lds_barrier();
   };
-  // The loop starts on a multiple of 32 bytes whatever stands in front of it (d = 64: six instructions on).  2280 tokens, 2 x
-  // 64, 19.1 us; at 12 past one 19.6, at 24 past 19.25.  At d = 128, and under the mask, the same anywhere.
+  // The code here starts two instructions past a multiple of 32 bytes whatever stands in front of it.  Of 16 places, forward in us: 6
+  // sequences of 1536 tokens, 2 x 64, 18.2 to 18.6 two and three past one, 19.1 to 19.6 elsewhere, 1944, 12 x 64, 22.6 to 22.9 and 23.4 to 23.8;
+  // 2280, 2 x 64, 19.1 to 19.3 anywhere; d = 128 within 0.7 %; under the mask 1500, 12 x 64, 16.0 here (15.8 to 16.6), 5000, 2 x 64, 36.7 (35.4 to 37.0).
   asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0");
   for (int t = 0; t < n_tiles; t += 2) {
     half_tile(t, lds.k0, lds.v0, lds.k1, lds.v1);
