@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_full_kerne
   __syncthreads();
   deal_even<128, false>(queue, cu, n_seq, s_order, s_start);
   // tickets: pairs of items that follow each other, single ones, parts
-  const int pairs = __builtin_amdgcn_readfirstlane(item_pairs(s_paired, queue.wide, TAIL_ROUNDS * queue.per));
+  const int pairs = __builtin_amdgcn_readfirstlane(item_pairs(s_paired, queue.wide, TAIL_ROUNDS * queue.per, least_pairs(D, queue.per)));
   const int singles = queue.wide - pairs;         // tickets before the parts
   const int tickets = singles + queue.parts;
   const bool draws = tickets > queue.per;

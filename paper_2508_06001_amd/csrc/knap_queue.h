@@ -187,6 +187,10 @@ struct EvenQueue {
 // 1536, but three heads of up to 131072 24070 -> 22290 instead of 22000, 16 of 1024 233 -> 237 instead of 232.
 constexpr int kPairTiles = 12;
 constexpr int pair_tail_rounds(int d) { return d == 64 ? 3 : 2; }
+// ... and fewer than these are none.  At d = 64 a few pairs gain nothing, and the list ends less evenly behind them: 6000 tokens and 10 of 250, 48 x
+// 64 (7 pairs for 96 workgroups), 465 without pairs, 476 with, and 460; 20 such bags 1.008.  At d = 128 a few are better than none: 6000 and 20 of 250, 24 x
+// 128, 431 with, 437 without (and 424 without any before there were pairs).
+constexpr int least_pairs(int d, int per) { return d == 64 ? (per + 3) / 4 : 0; }
 // units of work of an item: a bag's work has to fit an int
 __device__ __forceinline__ int item_work(int tiles) { return (tiles + 7) >> 3; }
 // how many of the first of a sequence's `share` items, of `work` units each, may be paired; `behind`: the units of the queue's items
@@ -196,6 +200,9 @@ __device__ __forceinline__ int pairable(int share, int tiles, int work, int behi
 }
 // the pairs of a queue whose first `paired` items may be paired and whose first `whole` are dealt out whole; a tail of those stays
 // single also where a few items behind them go out in parts (one of 5939 tokens, 24 heads, 411 -> 418 with five pairs)
-__device__ __forceinline__ int item_pairs(int paired, int whole, int tail) { return max(0, min(paired, whole - tail)) / 2; }
+__device__ __forceinline__ int item_pairs(int paired, int whole, int tail, int least) {
+  const int pairs = max(0, min(paired, whole - tail)) / 2;
+  return pairs < least ? 0 : pairs;
+}
 
 }  // namespace knap

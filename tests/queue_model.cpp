@@ -229,7 +229,7 @@ void queue_walk_pairs(const int* lens, int n_seq, int H, int d, int grid, int* o
       stop = some < share;
     }
     queue.deal(mine.data(), n_seq, [&](int k) { return start[k + 1] - start[k]; });
-    const int pairs = knap::item_pairs(paired, queue.wide, rounds * queue.per), singles = queue.wide - pairs, tickets = singles + queue.parts;
+    const int pairs = knap::item_pairs(paired, queue.wide, rounds * queue.per, knap::least_pairs(d, queue.per)), singles = queue.wide - pairs, tickets = singles + queue.parts;
     auto global = [&](int i) {
       const int k = knap::rank_of_item(mine.data(), n_seq, i);
       return start[k] + queue.locate(start[k + 1] - start[k], k, i - mine[k]);

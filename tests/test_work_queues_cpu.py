@@ -78,6 +78,11 @@ def test_every_item_of_the_unmasked_forward_once():
     assert min(seen.values()) > 100, seen
 
 
+@pytest.mark.parametrize("lens,H,d,pairs", [([6000] + [250] * 10, 48, 64, False), ([6000] + [250] * 20, 24, 128, True), ([10000], 48, 64, True)])
+def test_a_few_pairs_are_none_at_d_64(lens, H, d, pairs):
+    assert (Q.walk_pairs(lens, H, d).items > 0) == pairs
+
+
 def test_every_item_of_the_small_backward_once():
     """Tiles of 64 rows of both kinds; random bags and grids, drawn and not.  Where the rule takes it, one launch is the rule as well."""
     rng = random.Random(99)
