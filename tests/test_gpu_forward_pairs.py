@@ -18,18 +18,20 @@ pytestmark = pytest.mark.gpu
 LENS = [2081, 130, 1700, 64, 1]
 # more than two and three rounds of 128-row items
 HEADS = {128: 48, 64: 104}
+# lse on N(0, 1) inputs: a sum of probabilities of relative error 2^-9 each is off by at most as much, and the fp32 rest
+LSE_MOST = 2.0 ** -9 + 1e-4
 
 
-def _compare(run, d, strict, lse_tol):
+def _compare(run, d, strict, lse_tol, sequences=None, heads=None):
     """First, middle and last heads.  strict: 1e-2, on N(0, 1) inputs.  Else the bound of rows that few keys dominate: every
     probability carries a relative error of up to 2^-9, sum_i w_i e_i (v_i - out), and the stored result another 2^-9 of itself:
     2^-9 (2 max|v| + |ref|).  lse relative to its own size where scores are large (fp32 scores of hundreds)."""
     worst = worst_lse = 0.0
     cu = [int(c) for c in run.cu]
     H = run.bag.H
-    for s in range(len(LENS)):
+    for s in range(len(cu) - 1) if sequences is None else sequences:
         rows = slice(cu[s], cu[s + 1])
-        for h in (0, 1, 2, H // 8, H // 2, H - 1):
+        for h in (0, 1, 2, H // 8, H // 2, H - 1) if heads is None else heads:
             q, k, v = (run.host(n, rows, h) for n in ("q", "k", "v"))
             O, LSE = A.attn_fwd_dense(q, k, v, run.bag.scale)
             bar = 1e-2 if strict else 2.0 ** -9 * (2 * np.abs(v).max() + np.abs(O))
@@ -47,7 +49,26 @@ def _bag(d, seed):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_pairs_of_query_tiles(d):
-    _compare(GpuRun(_bag(d, 9100), backward=False), d, d == 128, 1e-3 if d == 128 else 3e-3)
+    _compare(GpuRun(_bag(d, 9100), backward=False), d, True, 1e-3 if d == 128 else LSE_MOST)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("length", [2048, 1984, 2012, 1660])
+def test_pairs_at_the_ends_of_the_loop_over_the_keys(d, length):
+    """The last tile whole, in either buffer (32 and 31 tiles; the ticket is then drawn in the loop), or ragged behind an odd number of whole
+    ones (31 and 25)."""
+    lens = [length, 130, length, 64]
+    w = Q.walk_pairs(lens, HEADS[d], d)
+    assert w.items > 100 and w.draws
+    _compare(GpuRun(BagSpec("pair_ends", lens, H=HEADS[d], d=d, seed=9400 + d + length), backward=False), d, True, LSE_MOST)
+
+
+@pytest.mark.parametrize("d,H", [(128, 4), (64, 8)])
+def test_pairs_of_more_sequences_than_a_wave_has_lanes(d, H):
+    """How many items are paired is counted by one wave, 64 sequences at a time."""
+    lens = [1409 + (37 * i) % 192 for i in range(90)]
+    assert min(lens) == 1409 and Q.walk_pairs(lens, H, d).items > 8 * 50
+    _compare(GpuRun(BagSpec("many_pairs", lens, H=H, d=d, seed=9500 + d), backward=False), d, True, LSE_MOST, range(0, 90, 11), [0, H - 1])
 
 
 @pytest.mark.parametrize("power", [3, 8])
@@ -150,3 +171,69 @@ def test_second_term_of_a_row_beside_one_of_a_huge_sum(d, huge_first):
     err = float(np.abs(lse - want).max())
     say(f"[pairs] d={d} beside a huge sum: lse error={err:.2e}")
     assert err <= LSE_BAR
+
+
+@pytest.mark.parametrize("keys", [(900, 901, 902), (930, 951, 959), (1665, 1670, 1695), (1696, 1698, 1699), (910, 940, 1690)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_second_term_where_three_keys_dominate(d, keys):
+    """In the first half of a tile, in the second, in either half of the ragged last tile (1664 to 1699), in several.  Rounded once their
+    probabilities put lse off by more than 20 times the bar."""
+    a, b, x = _entries(d, *X_DOWN)
+
+    def fill(q, k):
+        q[:, :, 1] = a
+        k[list(keys), :, 1] = b
+
+    want = math.log(L_ONE - 3 + 3 * 2.0 ** x)
+    assert want - math.log(L_ONE - 3 + 3 * 2.0 ** 16) > 20 * LSE_BAR
+    err = float(np.abs(_lse_of_one_sequence(d, fill) - want).max())
+    say(f"[pairs] d={d} keys {keys}: lse error={err:.2e}")
+    assert err <= LSE_BAR
+
+
+def _one_sequence(d, change):
+    """The sequence of known pairs with N(0, 1) inputs behind change(q, k, v): inputs and results of three heads in float64."""
+    import torch
+    import paper_2508_06001_amd as K
+    H = HEADS_ONE[d]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9700 + d)
+    q, k, v = (torch.empty((L_ONE, H, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(3))
+    change(q, k, v)
+    out, lse = K.VarlenAttention([0, L_ONE], H, d, d ** -0.5).forward(q, k, v)
+    for h in (0, H // 2, H - 1):
+        yield tuple(x[:, h].double().cpu().numpy() for x in (q, k, v, out)) + (lse[h].double().cpu().numpy(),)
+
+
+@pytest.mark.parametrize("n", [32, 63, 64, 96, 200])
+@pytest.mark.parametrize("d", [64, 128])
+def test_pairs_behind_keys_of_minus_infinity(d, n):
+    """The first n keys have scores of -inf: from 64 on the pair has no reference, and its rows are done again in parts.  Bars as in
+    _compare, strict."""
+    def change(q, k, v):
+        q[:, :, 0] = 1.0
+        k[:n, :, 0] = -math.inf
+
+    for q, k, v, out, lse in _one_sequence(d, change):
+        O, LSE = A.attn_fwd_dense(q, k[n:], v[n:], d ** -0.5)
+        assert np.abs(out - O).max() <= 1e-2 and np.abs(lse - LSE).max() <= LSE_MOST
+
+
+@pytest.mark.parametrize("what,value", [("q", math.nan), ("k", math.nan), ("v", math.nan), ("v", math.inf), ("k", math.inf)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_pairs_with_infinities_and_nan(d, what, value):
+    """One entry, behind the first 64 keys.  Rows whose fp64 result is finite are as without it (k = +inf: where q's entry is negative the
+    score is -inf), the others not finite; a NaN or an infinity in q or v stays in its row or column."""
+    def change(q, k, v):
+        {"q": q, "k": k, "v": v}[what][700, :, 3] = value
+
+    for q, k, v, out, lse in _one_sequence(d, change):
+        with np.errstate(all="ignore"):
+            O, LSE = A.attn_fwd_dense(q, k, v, d ** -0.5)
+        finite = np.isfinite(O)
+        assert 0 < int((~finite).sum()) and (what == "k" and value != math.inf or finite.any())
+        assert not np.isfinite(out[~finite]).any()
+        assert not finite.any() or np.abs(out[finite] - O[finite]).max() <= 1e-2
+        rows = np.isfinite(LSE)
+        assert not rows.any() or np.abs(lse[rows] - LSE[rows]).max() <= LSE_MOST
+        assert not np.isfinite(lse[~rows]).any()
