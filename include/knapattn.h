@@ -53,10 +53,17 @@ extern "C" {
  *
  * Reproducibility.  The same calls on the same bag give the same bits every
  * time.  Between bags a sequence's results (out, lse and the three gradients)
- * may differ within their rounding errors: where a bag has few work items, or
- * few in its last round, the kernels cut them in two, and such an item's sums run
- * in another order and against another softmax reference.  It follows from
- * the lengths and H alone, and may hold for some heads of a sequence only.
+ * may differ within their rounding errors, because the kernels have several
+ * forms, whose sums run in another order and against another softmax reference:
+ * of 64 rows where a bag has few work items or few in its last round, of 128, and
+ * of 256 in the forward without the mask where it has many.  Which rows of a
+ * sequence and head take which form follows from all lengths of the bag and H
+ * alone.  A row's last bits may also depend on the values of other rows of its
+ * sequence and head: rows of one wave move their softmax reference or take a
+ * second term of their probabilities together, and 256 rows of which one leaves
+ * the range (a score more than about 69 above those of the first 64 keys,
+ * infinities, NaN) are done again in the form of 64.  No result depends on the
+ * values of other sequences or heads.
  *
  * Supported: d in {64, 128}; 0 <= n_seq <= KNAP_MAX_SEQS; H >= 1, H * d < 2^24 in
  * the forward and 2^23 in the backward (the kernels count the bytes of 128 and of 256

@@ -11,7 +11,7 @@ namespace knap {
 // queries (w >> 1): the walk over the sequence has half as many steps as that of a 128-key tile, and no wave waits for another's
 // probabilities.  What bounds it is the latency of a step (a CU has one workgroup, a SIMD one wave): two chains of MFMAs, the
 // exponentials, the other products, the barrier.  LDS operands are requested two MFMA groups ahead in fenced groups, so that nothing is
-// spilled (with the order left to the compiler 46 values were, reloaded in every step behind the tile copies: one of 1300 tokens, 3 x 128, backward
+// spilled in the loops (one value of the causal kernel at d = 128 outside of them; with the order left to the compiler 46 were, reloaded in every step behind the tile copies: one of 1300 tokens, 3 x 128, backward
 // 51 us, 48 with 128-key items, 32 so).  The two halves of the queries are added through LDS at the end.  `ending` is called
 // in front of the stores.
 template <int D, bool CAUSAL, class Ending>
@@ -168,7 +168,7 @@ __device__ __forceinline__ void dkdv_part(const BwdPtrs& g, const DqLds& lds, fl
   }
 
   ending();
-  // The waves of the same keys trade halves: those of the first queries finish dK, those of the second dV.  A wave's 4 D bytes per
+  // The waves of the same keys trade halves: those of the first queries finish dK, those of the second dV.  A wave's 2 D bytes per
   // lane fill one of the four tile buffers.
   float* const mine = reinterpret_cast<float*>(half == 0 ? (kb == 0 ? sQ0 : sQ1) : (kb == 0 ? sdO0 : sdO1));
   const float* const other = reinterpret_cast<const float*>(half == 0 ? (kb == 0 ? sdO0 : sdO1) : (kb == 0 ? sQ0 : sQ1));

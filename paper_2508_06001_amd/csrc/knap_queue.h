@@ -178,13 +178,14 @@ struct EvenQueue {
 
 // Pairs: two items of an even queue that follow each other go out as one ticket, in front of the single ones, where the kernel has a
 // cheaper form for two query tiles of a sequence and head (knap_attn_fwd_full.hip).  Which items: from the first one on, as long as
-// they are of sequences of at least kPairTiles tiles (shorter ones lose more by the longer start and end of a pair than their loop
+// they are of sequences of at least kPairTiles tiles (shorter ones lose about as much by the longer start and end of a pair as their loop
 // gains) and the items behind them have the work of a tail of two rounds of theirs (three at d = 64, where pairs gain less: one of
 // 6000 tokens, 48 x 64, 468 -> 490 with two): the list has to end evenly.  Forward in us, all single ->
 // pairs down to a tail of one, 1.5 and 2.5 rounds: 24 heads, one of 16384 2855 -> 2634, 2709, 2766; 8 of 4096 1482 -> 1424, 1420, 1420; 6 of
 // up to 4388 567 -> 598, 602, 571; of 4267, 841 and 216 243 -> 276, 245, 247.  Counted in items and not by their work, 12000 tokens and 40 of
-// 300, 12 heads, took 879 (848 single).  From 6 tiles on instead of 12: 64 of 1024 894 -> 870 instead of 890, 32 of 2048 1583 -> 1510 instead of
-// 1536, but three heads of up to 131072 24070 -> 22290 instead of 22000, 16 of 1024 233 -> 237 instead of 232.
+// 300, 12 heads, took 879 (848 single).  The limit decides on sequences of up to 1408 tokens alone.  From 6 | 8 | 12 tiles on, 24 x 128: 64 of 1024 tokens 848 |
+// 858 | 862, 16 of 1024 219 | 220 | 224, 32 of 900 394 | 394 | 380, 64 of 800 620 | 617 | 605; 48 x 64: 64 of 1024 940 | 943 | 973, 24 of 1400 642 | 647 | 664,
+// 32 of 900 429 | 427 | 424; from 8 against from 12, 48 bags of 600 to 1500 tokens, 1.002 at d = 128 (0.96 to 1.04), 1.008 at d = 64.
 constexpr int kPairTiles = 12;
 constexpr int pair_tail_rounds(int d) { return d == 64 ? 3 : 2; }
 // ... and fewer than these are none.  At d = 64 a few pairs gain nothing, and the list ends less evenly behind them: 6000 tokens and 10 of 250, 48 x
