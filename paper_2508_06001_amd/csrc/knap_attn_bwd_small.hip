@@ -202,31 +202,15 @@ __device__ __forceinline__ void dkdv_part(const BwdPtrs& g, const DqLds& lds, fl
   if (half == 0) finish(dk); else finish(dv);
 }
 
-// SURE: the host knows that items of 64 rows pay (small_sure()).  Else the kernel in front has decided, by the lengths (small_pays()), and where
-// they do not the items are those of knap_attn_joint.h.
-template <int D, bool CAUSAL, bool SURE>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kernel(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-    float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
-    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
+template <int D, bool CAUSAL>
+__device__ __forceinline__ void small_items(const BwdPtrs g, const SmallLds<D> s, const int32_t* __restrict__ cu, int n_seq, int H,
+                                            const int* s_order, int* s_start, unsigned* __restrict__ counters) {
   constexpr int BM = 64;                           // rows of an item of either kind
-  KNAP_JOINT_LDS(D, all);
-  int *const s_order = all.order, *const s_start = all.start;
-  const unsigned pays = SURE ? 1u : counters[kSmallPays];      // (arrives with the lengths)
-  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, cu[n_seq], H, scale};
-  build_schedule_of(cu, n_seq, [&](int len) {
-    const int wide = items_per_head<CAUSAL>((len + 127) / 128), tiles = (len + BM - 1) / BM;
-    return (SURE || pays ? tiles : wide) * H;
-  }, s_order, s_start, reinterpret_cast<int*>(sA0));
-  if (!SURE && __builtin_amdgcn_readfirstlane(pays) == 0) {
-    joint_items<D, CAUSAL>(g, all, cu, n_seq, H, counters);
-    return;
-  }
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const DqLds lds = {sA0, sA1, sA2, sA3};
-  float* const scalars[2][2] = {{sLse0, sDelta0}, {sLse1, sDelta1}};
+  const DqLds lds = {s.a0, s.a1, s.a2, s.a3};
+  float* const scalars[2][2] = {{s.lse0, s.delta0}, {s.lse1, s.delta1}};
 
   EvenQueue<0, 2> queue;          // key items, then query items, all of them whole
   queue.init(counters);
@@ -244,7 +228,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kern
     int ln = lane;
     asm volatile("" : "+v"(ln));      // what follows from the lane is formed per item, not kept through the other kind's
     if (keys) {
-      dkdv_part<D, CAUSAL>(g, lds, scalars, sSink, x, tile * BM, ln, wave, draw);
+      dkdv_part<D, CAUSAL>(g, lds, scalars, s.sink, x, tile * BM, ln, wave, draw);
     } else {
       DqLane<D> me;
       me.init(ln, wave);
@@ -252,17 +236,40 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kern
       dq_part<D, CAUSAL, false>(g, lds, me, x, (CAUSAL ? tiles - 1 - tile : tile) * BM, [] {}, draw);
     }
     if (!queue.draws) return;
-    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);
+    if (tid == 0) *s.ticket = queue.later_ticket(next_ticket);
     lds_barrier();                    // (and the partial sums are no longer read)
-    ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+    ticket = __builtin_amdgcn_readfirstlane(*s.ticket);
   }
+}
+
+// Items of 64 rows whatever the lengths are: the host knows that they pay (small_sure()).
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_small_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
+    float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
+    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
+  extern __shared__ int s_dyn[];
+  int* s_order = s_dyn;
+  int* s_start = s_dyn + n_seq;
+  constexpr int TILE = DqCfg<D>::TILE_ELEMS;
+  __shared__ __attribute__((aligned(1024))) __bf16 sA0[TILE];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA1[TILE];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA2[TILE];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA3[TILE];
+  __shared__ __attribute__((aligned(256))) float sLse0[64], sDelta0[64], sLse1[64], sDelta1[64], sSink[64];
+  __shared__ int s_ticket;
+  const int T = cu[n_seq];
+  build_schedule<64, kThreads, false>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sA0[0]));
+  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, T, H, scale};
+  const SmallLds<D> lds = {sA0, sA1, sA2, sA3, sLse0, sDelta0, sLse1, sDelta1, sSink, &s_ticket};
+  small_items<D, CAUSAL>(g, lds, cu, n_seq, H, s_order, s_start, counters);
 }
 
 template <int D>
 static hipError_t launch_small_d(const BwdArgs& a, bool causal, bool sure, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
-  auto* kernel = causal ? (sure ? attn_bwd_small_kernel<D, true, true> : attn_bwd_small_kernel<D, true, false>)
-                        : (sure ? attn_bwd_small_kernel<D, false, true> : attn_bwd_small_kernel<D, false, false>);
+  auto* kernel = causal ? (sure ? attn_bwd_small_kernel<D, true> : attn_bwd_joint_kernel<D, true, true>)
+                        : (sure ? attn_bwd_small_kernel<D, false> : attn_bwd_joint_kernel<D, false, true>);
   hipLaunchKernelGGL(kernel, dim3(cus * dkdv_workgroups_per_cu(D, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q, (const __bf16*)a.k,
                      (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale, (__bf16*)a.dq, (__bf16*)a.dk,
                      (__bf16*)a.dv, a.counters);

@@ -10,45 +10,67 @@
 
 namespace knap {
 
-// LDS of the launch.  Four arrays that hold a K or V tile each for one kind, and a tile of Q and of dO (or the P of the pairs) for the
-// other: whatever is copied into while another is read is an array of its own, so that the reads are known not to depend on it.
+// What items of 64 rows need of the LDS
 template <int D>
-struct JointLds {
-  static constexpr int HALF = Bwd2Cfg<D, 2>::TILE_ELEMS, P_ELEMS = 2 * DkdvLane<D, 2>::P_PAIR / (int)sizeof(__bf16);
-  static_assert(DqCfg<D>::TILE_ELEMS == 2 * HALF && P_ELEMS >= 2 * HALF, "the arrays serve both kinds");
-  __bf16 *a0, *a1, *a2, *a3;       // 2 HALF each, P_ELEMS the last
-  float *lse0, *delta0, *lse1, *delta1, *lse2, *delta2, *sink;      // 64 each
+struct SmallLds {
+  __bf16 *a0, *a1, *a2, *a3;                       // a tile of 64 rows each
+  float *lse0, *delta0, *lse1, *delta1, *sink;     // 64 each
   int* ticket;
-  int *order, *start;              // of the schedule, n_seq and n_seq + 1
 };
 
-#define KNAP_JOINT_LDS(D, lds)                                                                                                   \
-  extern __shared__ int s_dyn[];                                                                                                 \
-  __shared__ __attribute__((aligned(1024))) __bf16 sA0[2 * JointLds<D>::HALF];                                                   \
-  __shared__ __attribute__((aligned(1024))) __bf16 sA1[2 * JointLds<D>::HALF];                                                   \
-  __shared__ __attribute__((aligned(1024))) __bf16 sA2[2 * JointLds<D>::HALF];                                                   \
-  __shared__ __attribute__((aligned(1024))) __bf16 sA3[JointLds<D>::P_ELEMS];                                                    \
-  __shared__ __attribute__((aligned(256))) float sLse0[64], sDelta0[64], sLse1[64], sDelta1[64], sLse2[64], sDelta2[64], sSink[64]; \
-  __shared__ int s_ticket;                                                                                                       \
-  const JointLds<D> lds = {sA0, sA1, sA2, sA3, sLse0, sDelta0, sLse1, sDelta1, sLse2, sDelta2, sSink, &s_ticket, s_dyn, s_dyn + n_seq}
-
-// all items of a launch, tiles of 128 rows, behind their schedule
+// All items of a launch in tiles of 64 rows, behind their schedule (knap_attn_bwd_small.hip)
 template <int D, bool CAUSAL>
-__device__ __forceinline__ void joint_items(const BwdPtrs& g, const JointLds<D>& lds, const int32_t* __restrict__ cu, int n_seq, int H,
-                                            unsigned* __restrict__ counters) {
+__device__ __forceinline__ void small_items(const BwdPtrs g, const SmallLds<D> s, const int32_t* __restrict__ cu, int n_seq, int H,
+                                            const int* s_order, int* s_start, unsigned* __restrict__ counters);
+
+// EITHER: the kernel in front has decided, by the lengths, whether the items are of 64 rows (small_pays()).
+template <int D, bool CAUSAL, bool EITHER>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
+    float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
+    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
   using KV = Bwd2Cfg<D, 2>;
   constexpr int BM = 128;                          // rows of a tile of either kind
   static_assert(KV::BN == BM && DqCfg<D>::BM == BM, "one schedule serves both");
-  constexpr int HALF = JointLds<D>::HALF;
-  int *const s_order = lds.order, *const s_start = lds.start;
+  extern __shared__ int s_dyn[];
+  int* s_order = s_dyn;
+  int* s_start = s_dyn + n_seq;
+  // Four arrays that hold a K or V tile each for one kind, and a tile of Q and of dO (or the P of the pairs) for the other:
+  // whatever is copied into while another is read is an array of its own, so that the reads are known not to depend on it.
+  constexpr int HALF = KV::TILE_ELEMS, P_ELEMS = 2 * DkdvLane<D, 2>::P_PAIR / (int)sizeof(__bf16);
+  static_assert(DqCfg<D>::TILE_ELEMS == 2 * HALF && P_ELEMS >= 2 * HALF, "the arrays serve both kinds");
+  __shared__ __attribute__((aligned(1024))) __bf16 sA0[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA1[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA2[2 * HALF];
+  __shared__ __attribute__((aligned(1024))) __bf16 sA3[P_ELEMS];
+  __shared__ __attribute__((aligned(256))) float sLse0[64], sDelta0[64], sLse1[64], sDelta1[64], sLse2[64], sDelta2[64], sSink[64];
+  __shared__ int s_ticket;
+
+  const int T = cu[n_seq];
+  if constexpr (EITHER) {
+    const unsigned pays = counters[kSmallPays];    // (arrives with the lengths)
+    build_schedule_of(cu, n_seq, [&](int len) {
+      const int wide = items_per_head<CAUSAL>((len + BM - 1) / BM), tiles = (len + 63) / 64;
+      return (pays ? tiles : wide) * H;
+    }, s_order, s_start, reinterpret_cast<int*>(&sA0[0]));
+    if (__builtin_amdgcn_readfirstlane(pays)) {
+      const BwdPtrs all = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, T, H, scale};
+      const SmallLds<D> lds = {sA0, sA1, sA2, sA3, sLse0, sDelta0, sLse1, sDelta1, sSink, &s_ticket};
+      small_items<D, CAUSAL>(all, lds, cu, n_seq, H, s_order, s_start, counters);
+      return;
+    }
+  } else {
+    build_schedule<BM, kThreads, CAUSAL>(cu, n_seq, H, s_order, s_start, reinterpret_cast<int*>(&sA0[0]));
+  }
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int role = (wave >> 1) ^ ((int)(blockIdx.x * dkdv_workgroups_per_cu(D, 2) / gridDim.x) & 1);
   const uint32_t row_bytes = (uint32_t)((size_t)H * D * sizeof(__bf16));
-  const DkdvLds kv_lds = {lds.a0, lds.a0 + HALF, lds.a1, lds.a1 + HALF, lds.a2, lds.a2 + HALF, lds.lse0, lds.delta0, lds.lse1, lds.delta1,
-                          lds.lse2, lds.delta2, lds.sink, reinterpret_cast<u32x4*>(lds.a3)};
-  const DqLds q_lds = {lds.a0, lds.a1, lds.a2, lds.a3};
+  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, T, H, scale};
+  const DkdvLds kv_lds = {sA0, sA0 + HALF, sA1, sA1 + HALF, sA2, sA2 + HALF, sLse0, sDelta0, sLse1, sDelta1, sLse2, sDelta2, sSink,
+                          reinterpret_cast<u32x4*>(sA3)};
+  const DqLds q_lds = {sA0, sA1, sA2, sA3};
 
   // the first kind are the key tiles (the dearer ones), the second the query tiles
   constexpr int SPLIT = CAUSAL ? 4 : 2;     // narrow items (64 queries) of a query tile, or of a pair of them
@@ -102,28 +124,17 @@ __device__ __forceinline__ void joint_items(const BwdPtrs& g, const JointLds<D>&
       }
     }
     if (!queue.draws) return;
-    if (tid == 0) *lds.ticket = queue.later_ticket(next_ticket);
+    if (tid == 0) s_ticket = queue.later_ticket(next_ticket);
     lds_barrier();                    // (and the partial sums of a narrow tile are no longer read)
-    ticket = __builtin_amdgcn_readfirstlane(*lds.ticket);
+    ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket >= queue.wide) lds_barrier();        // every wave has the ticket before the next one is put down: a part may have no rows
   }
-}
-
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_bwd_joint_kernel(
-    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, const __bf16* __restrict__ dout,
-    float* __restrict__ lse2, float* __restrict__ delta, const int32_t* __restrict__ cu, int n_seq, int H, float scale,
-    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, unsigned* __restrict__ counters) {
-  KNAP_JOINT_LDS(D, lds);
-  const BwdPtrs g = {q, k, v, nullptr, dout, nullptr, lse2, delta, dq, dk, dv, cu[n_seq], H, scale};
-  build_schedule<128, kThreads, CAUSAL>(cu, n_seq, H, lds.order, lds.start, reinterpret_cast<int*>(sA0));
-  joint_items<D, CAUSAL>(g, lds, cu, n_seq, H, counters);
 }
 
 template <bool CAUSAL>
 static hipError_t launch_joint_m(const BwdArgs& a, int d, int cus, hipStream_t stream) {
   const size_t dyn = (size_t)(2 * a.n_seq + 1) * sizeof(int);
-  auto* joint = d == 64 ? attn_bwd_joint_kernel<64, CAUSAL> : attn_bwd_joint_kernel<128, CAUSAL>;
+  auto* joint = d == 64 ? attn_bwd_joint_kernel<64, CAUSAL, false> : attn_bwd_joint_kernel<128, CAUSAL, false>;
   hipLaunchKernelGGL(joint, dim3(cus * dkdv_workgroups_per_cu(d, 2)), dim3(kThreads), dyn, stream, (const __bf16*)a.q,
                      (const __bf16*)a.k, (const __bf16*)a.v, (const __bf16*)a.dout, a.lse2, a.delta, a.cu, a.n_seq, a.H, a.scale,
                      (__bf16*)a.dq, (__bf16*)a.dk, (__bf16*)a.dv, a.counters);
