@@ -87,7 +87,7 @@ inline bool bwd_small(int64_t total_tokens, int n_seq, int H, int d, bool causal
 
 // Whether items of 64 rows pay after all: decided in front of that launch on the device, which knows the lengths.  tiles: of 64 rows, of
 // all sequences of a head; longest: those of the longest.  Where not, the launch takes items of 128 rows.  Backward in us, 128 rows | 64, n
-// the workgroups' worth of 64-row items of both kinds; 554 bags without the mask and 652 under it.
+// the workgroups' worth of 64-row items of both kinds; 583 bags without the mask and 623 under it.
 //  * Without the mask: where each item has a workgroup.  Sequences of 1 and 200 tokens in turn, 3 x 128: 34 (n = 1.0) 23.7 | 21.1, 40 (1.17) 25.3 |
 //    26.9; 92, 2 x 64 (1.2), 20.3 | 25.9.
 //  * Under it items of half the average length fill in behind the long ones, so that more than one worth pays, but not

@@ -113,3 +113,33 @@ def test_128_row_items_with_every_query_tile_in_parts(d, lens, H, causal):
     assert Q.bwd_joint(lens, H, d, causal) and not Q.bwd_small(lens, H, d, causal)
     assert w.parts == w.items * (4 if causal else 2) and not w.draws
     _compare(BagSpec("joint_parts", lens, H=H, d=d, seed=9700 + H + d), causal, [0, H // 2, H - 1])
+
+
+def test_captured_small_backward_decides_at_every_replay():
+    """Two bags of the same tokens and number of sequences, one of which takes items of 128 rows: a captured call follows the lengths that
+    stand in cu_seqlens when it is replayed."""
+    import torch
+    from paper_2508_06001_amd.runtime import bf16_device_to_bits
+    H, d, bags = 3, 128, ([96] * 70, [64] * 69 + [96 * 70 - 64 * 69])
+    for lens, pays in zip(bags, (False, True)):
+        s = Q.small_items(lens, H, d, True)
+        assert s.host == 1 and s.pays == pays
+    runs = [GpuRun(BagSpec("small_captured", lens, H=H, d=d, seed=9990), causal=True) for lens in bags]
+    a, x = runs[0].attn, runs[0].dev
+    # the first one's buffers are those of the captured call
+    given = [{"cu": r.attn.cu.clone(), "out": r.attn.out.clone(), "lse": r.attn.lse.clone(), **{n: r.dev[n].clone() for n in x}} for r in runs]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        a.backward(x["q"], x["k"], x["v"], x["dout"])
+    for i in (0, 1, 1, 0, 1):
+        run = runs[i]
+        for n, t in (("cu", a.cu), ("out", a.out), ("lse", a.lse), *x.items()):
+            t.copy_(given[i][n])
+        for t in (a.dq, a.dk, a.dv):
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(a.workspace[-256:].view(torch.int32)[8]) == i
+        for got, want in zip((a.dq, a.dk, a.dv), (run.dq_bits, run.dk_bits, run.dv_bits)):
+            assert np.array_equal(bf16_device_to_bits(got), want), i

@@ -272,6 +272,7 @@ def _graph_nodes(graph) -> int:
 @pytest.mark.parametrize("causal,d,lens,H,nodes", [
     (False, 64, [37, 128, 200, 311], 2, 2), (True, 128, [300], 3, 2),                          # one launch, nothing drawn
     (False, 128, [700, 90, 1300], 48, 2), (True, 64, [1290, 333, 64, 700], 90, 2),             # one launch, items drawn
+    (True, 128, [96] * 70, 3, 2), (False, 64, [128] * 96, 2, 2),                               # one launch, the lengths decide on its items
     (False, 128, [1 + i % 9 for i in range(640)], 4, 3), (True, 64, [1 + i % 9 for i in range(900)], 4, 3)])   # two launches
 def test_captured_backward_whatever_the_workspace_holds(causal, d, lens, H, nodes):
     """A captured backward draws from counters in its workspace: replays reproduce the eager gradients bit for bit whatever
